@@ -139,12 +139,12 @@ double raw_sincos(float x, bool is_cos) {
     uint32_t ub;
     std::memcpy(&ub, &ax, 4);
     const gp::crm::SinCosK K = gp::crm::sincos_k(is_cos);
-    return ax < 0x1p+20f ? gp::crm::sincos_small(ax, gp::crm::kSinCosTab, K)
+    return ax < gp::crm::kSinCosLarge ? gp::crm::sincos_small(ax, gp::crm::kSinCosTab, K)
                          : gp::crm::sincos_large(ub, is_cos, gp::crm::kSinCosTab, K);
 }
 double raw_sin(float x) { return raw_sincos(x, false); }
 double raw_cos(float x) { return raw_sincos(x, true); }
-double raw_log(float x) { return gp::crm::log_double(x, gp::crm::kLogTab, gp::crm::log_k()); }
+double raw_log(float x) { return gp::crm::log_double(gp::crm::fbits(x), gp::crm::kLogTab, gp::crm::log_k()); }
 
 }  // namespace
 

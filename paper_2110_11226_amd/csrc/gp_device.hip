@@ -175,12 +175,12 @@ __device__ __forceinline__ MathTabs global_tabs() { return MathTabs{crm::kSinCos
 
 // The kernel-resident copies (one per block, filled before its first use).
 struct MathTabsLds {
-    crm::LogEntry lg[128];       // (at offset 0: its entries' address is the index alone)
-    crm::SinCosEntry sc[128];    // (at 2 KB: the offset merges into the index's mask)
+    crm::LogEntry lg[256];       // (at offset 0: its entries' address is the index alone)
+    crm::SinCosEntry sc[256];    // (at 4 KB: the offset is the read's immediate)
 };
 __device__ __forceinline__ MathTabs stage_tabs(MathTabsLds& lds) {
-    for (int i = threadIdx.x; i < 128; i += blockDim.x) lds.sc[i] = crm::kSinCosTab[i];
-    for (int i = threadIdx.x; i < 128; i += blockDim.x) lds.lg[i] = crm::kLogTab[i];
+    for (int i = threadIdx.x; i < 256; i += blockDim.x) lds.sc[i] = crm::kSinCosTab[i];
+    for (int i = threadIdx.x; i < 256; i += blockDim.x) lds.lg[i] = crm::kLogTab[i];
     __syncthreads();
     return MathTabs{lds.sc, lds.lg};
 }
@@ -197,53 +197,21 @@ __device__ __forceinline__ float op_log(float a, const MathTabs& mt, const crm::
     return fabsf(a) > GP_PROTECT_EPS ? l : 0.0f;
 }
 
-// The same on the R rows of a lane, with one branch, rarely taken, for the
-// exception-table lookups of all the rows instead of one per row: fewer
-// scalar instructions, but the rows' results and inputs are held together.
-// The evaluation kernel goes row by row (the extra registers cost it an
-// occupancy step); the adjoint kernel, with registers to spare at its
-// occupancy, takes this form.
-template <int R>
-__device__ __forceinline__ void log_rows(float (&t)[R], const MathTabs& mt) {
-    const crm::LogK K = crm::log_k();   // (once for the R rows)
-    float f[R];
-    bool near[R];
-    bool any = false;
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const double y = crm::log_double(fabsf(t[j]), mt.lg, K);   // (finite for inf and NaN)
-        f[j] = static_cast<float>(y);
-        near[j] = crm::near_boundary(y);
-        any |= near[j];
-    }
-    if (any) {
-#pragma unroll
-        for (int j = 0; j < R; ++j)
-            if (near[j]) f[j] = crm::exception(crm::kLogExc, crm::kLogExcN, crm::fbits(fabsf(t[j])), f[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const float a = fabsf(t[j]);
-        const float l = a <= 0x1.fffffep+127f ? f[j] : a;   // +inf (and NaN) unchanged
-        t[j] = a > GP_PROTECT_EPS ? l : 0.0f;
-    }
-}
-
 // sqrt|a|, correctly rounded: in double from the hardware reciprocal square
-// root y (relative error e below 2^-22) by two Newton steps on s = d y with
-// h = y / 2 held fixed (the error goes e -> 1.5 e^2 -> about 1.5 e^3), then
-// rounded to float.  A float's square root lies at least 2^-51 (relative)
+// root y (relative error below 2^-22): s = d y, e = 1 - s y, and
+// sqrt d = s (1 - e)^(-1/2) = s + s e (1/2 + 3/8 e + O(e^2)), where the e^3
+// left out is below 2^-61 and the rounding of s enters e, so that the result
+// is within 2^-52.  A float's square root lies at least 2^-51 (relative)
 // from every float rounding boundary (a - m^2 is a nonzero multiple of the
-// least bit of m^2 for a midpoint m), so the double result, within 2^-53,
-// rounds as the exact one does.  Zeros and infinity are passed through (the
+// least bit of m^2 for a midpoint m), so the double result rounds to float
+// as the exact one does.  Zeros and infinity are passed through (the
 // steps would give NaN there); NaN stays NaN.
 __device__ __forceinline__ float op_sqrt(float a) {
     const double d = static_cast<double>(fabsf(a));
     const double y = __builtin_amdgcn_rsq(d);
-    const double h = 0.5 * y;
-    double s = d * y;
-    s = fma(fma(-s, s, d), h, s);
-    s = fma(fma(-s, s, d), h, s);
+    const double s0 = d * y;
+    const double e = fma(-s0, y, 1.0);
+    const double s = fma(s0 * e, fma(e, crm::kreg(0.375), 0.5), s0);
     // class mask: +0 (bit 6) or +inf (bit 9)
     return __builtin_amdgcn_class(d, 0x240) ? fabsf(a) : static_cast<float>(s);
 }
@@ -253,7 +221,7 @@ __device__ __forceinline__ float op_inv(float a) {
 
 // t = sin t (is_cos false) or cos t on the R rows of a lane: the common
 // path on every row, then one branch, rarely taken, for the rows with
-// |t| >= 2^20, inf or NaN
+// |t| >= 2^24, inf or NaN
 template <int R>
 __device__ __forceinline__ void sincos_rows(bool is_cos, float (&t)[R], const MathTabs& mt) {
     const crm::SinCosK K = crm::sincos_k(is_cos);   // (once for the R rows)
@@ -261,7 +229,7 @@ __device__ __forceinline__ void sincos_rows(bool is_cos, float (&t)[R], const Ma
     bool rare = false;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        f[j] = crm::sincos_common(t[j], is_cos, mt.sc, K);
+        f[j] = crm::sincos_common(t[j], mt.sc, K);
         rare |= crm::sincos_rare_input(t[j]);
     }
     if (rare) {
@@ -365,8 +333,7 @@ __device__ __forceinline__ void apply_binary(uint32_t fn, float (&a)[R], const f
 
 // t = f(t) for the unary function index fn (NEG, LOG, SQRT, SIN, COS, TAN
 // first, then the wider set)
-// (LOG_ROWS: the protected log by log_rows rather than row by row)
-template <int R, bool LOG_ROWS = false>
+template <int R>
 __device__ __forceinline__ void apply_unary(uint32_t fn, float (&t)[R], const MathTabs& mt) {
     if (fn >= 6) {
         apply_unary_wide<R>(fn, t);
@@ -375,13 +342,9 @@ __device__ __forceinline__ void apply_unary(uint32_t fn, float (&t)[R], const Ma
 #pragma unroll
             for (int j = 0; j < R; ++j) t[j] = -t[j];
         } else if (fn == 1) {
-            if constexpr (LOG_ROWS) {
-                log_rows<R>(t, mt);
-            } else {
-                const crm::LogK K = crm::log_k();   // (once for the R rows)
+            const crm::LogK K = crm::log_k();   // (once for the R rows)
 #pragma unroll
-                for (int j = 0; j < R; ++j) t[j] = op_log(t[j], mt, K);
-            }
+            for (int j = 0; j < R; ++j) t[j] = op_log(t[j], mt, K);
         } else {
 #pragma unroll
             for (int j = 0; j < R; ++j) t[j] = op_sqrt(t[j]);
@@ -1278,11 +1241,21 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const double* __restrict__ 
 // sin cos a, cos -sin a, tan 1 + tan^2 a, neg -1.
 // ---------------------------------------------------------------------------
 constexpr int kGradLds = 16;            // constants per program summed in a fixed order
-// per-wavefront tape held in LDS: 12 KB, 15 KB at 4 rows per lane (two
-// waves per SIMD there, so eight per CU still fit in LDS beside the 4 KB of
-// function tables each holds)
+// Four wavefronts a block share one LDS copy of the function tables (8 KB); they
+// work independently of each other.  Per-wavefront tape held in LDS: 12 KB,
+// 15 KB at 4 rows per lane (two waves per SIMD there, so eight per CU still
+// fit in LDS)
+constexpr int kAdjWaves = 4;
 template <int R>
 constexpr int tape_lds_bytes() { return R == 4 ? 15360 : 12288; }
+
+// Orders a wavefront's own LDS writes before its later LDS reads (its LDS
+// operations complete in order; this only keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // tape entries an instruction records (0, 1 or 2)
 __device__ __forceinline__ int tape_entries(uint32_t cls, uint32_t fn) {
@@ -1300,7 +1273,41 @@ constexpr int64_t adjoint_wave_floats(int64_t tape_entries_max) {
     return (2 * kStackLds + beyond) * R * kWave;
 }
 
-// derivative of unary function fn (1..5: log, sqrt, sin, cos, tan; 6..13:
+// t = sin t (is_cos false) or cos t and dv = the derivative at the input, on
+// the R rows of a lane.  With theta the table's angle, sin and cos are both
+// sin(theta + r) = S cos r + C sin r, whose derivative C cos r - S sin r takes
+// two more operations on the same reduction, table entry and polynomials (a
+// library cos or sin at the input cost about thirty).
+template <int R>
+__device__ __forceinline__ void sincos_rows_derivative(bool is_cos, float (&t)[R], float (&dv)[R],
+                                                       const MathTabs& mt) {
+    const crm::SinCosK K = crm::sincos_k(is_cos);
+    float f[R];
+    bool rare = false;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const crm::SinCosArg a = crm::sincos_reduce(static_cast<double>(t[j]), K);
+        const crm::SinCosEntry& e = crm::sincos_entry(mt.sc, a.off);
+        double sr, cr;
+        crm::sincos_poly(a.r, K, &sr, &cr);
+        f[j] = static_cast<float>(fma(e.c, sr, e.s * cr));
+        dv[j] = static_cast<float>(fma(-e.s, sr, e.c * cr));
+        rare |= crm::sincos_rare_input(t[j]);
+    }
+    if (rare) {
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            if (crm::sincos_rare_input(t[j])) {
+                f[j] = crm::sincos_rare(t[j], is_cos, mt.sc, K);
+                const float g = crm::sincos_rare(t[j], !is_cos, mt.sc, K);
+                dv[j] = is_cos ? -g : g;
+            }
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) t[j] = f[j];
+}
+
+// derivative of unary function fn (1, 2, 5: log, sqrt, tan; 6..13:
 // abs, exp, inv, sq, cube, tanh, atan, cbrt) at input x, whose result is y.
 // Reciprocals here (and in the quotient's partials) come from the hardware
 // reciprocal, within 1 ulp: a partial's own rounding, well inside the
@@ -1315,8 +1322,6 @@ __device__ __forceinline__ void unary_derivative(uint32_t fn, const float (&x)[R
         switch (fn) {
         case 1: dv[j] = fabsf(x[j]) > GP_PROTECT_EPS ? __builtin_amdgcn_rcpf(x[j]) : 0.0f; break;
         case 2: dv[j] = x[j] == 0.0f ? 0.0f : copysignf(__builtin_amdgcn_rcpf(2.0f * y[j]), x[j]); break;
-        case 3: dv[j] = cosf(x[j]); break;
-        case 4: dv[j] = -sinf(x[j]); break;
         case 5: dv[j] = 1.0f + y[j] * y[j]; break;
         case 6: dv[j] = x[j] > 0.0f ? 1.0f : (x[j] < 0.0f ? -1.0f : 0.0f); break;
         case 7: dv[j] = y[j]; break;
@@ -1331,7 +1336,7 @@ __device__ __forceinline__ void unary_derivative(uint32_t fn, const float (&x)[R
 }
 
 template <int R, int FREG, int METRIC>
-__global__ __launch_bounds__(kWave) void k_adjoint(PopView pop, CodeView cv, DataView d, Sched s,
+__global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint(PopView pop, CodeView cv, DataView d, Sched s,
                                                     const double* __restrict__ stats,
                                                     const double* __restrict__ wsum,
                                                     const float* __restrict__ gscale,
@@ -1342,19 +1347,20 @@ __global__ __launch_bounds__(kWave) void k_adjoint(PopView pop, CodeView cv, Dat
                                                     int64_t wave_floats) {
     constexpr int FA = FREG > 0 ? FREG : 1;
     constexpr int kTapeLds = tape_lds_bytes<R>() / (R * kWave * 4);
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int64_t N = d.N;
     const int64_t ld = d.ld;
     const float* __restrict__ X = d.X;
-    __shared__ float ltape[kTapeLds * R * kWave];
-    __shared__ double gw[kGradLds];
-    float* __restrict__ wmem = gmem + static_cast<int64_t>(blockIdx.x) * wave_floats;
+    __shared__ float ltape_all[kAdjWaves][kTapeLds * R * kWave];
+    __shared__ double gw_all[kAdjWaves][kGradLds];
+    float* ltape = ltape_all[wid];
+    double* gw = gw_all[wid];
+    float* __restrict__ wmem = gmem + (static_cast<int64_t>(blockIdx.x) * kAdjWaves + wid) * wave_floats;
     float* __restrict__ ovf = wmem;                                 // value stack beyond registers
     float* __restrict__ aovf = wmem + kStackLds * R * kWave;        // adjoint stack beyond registers
     float* __restrict__ gtape = wmem + 2 * kStackLds * R * kWave;   // tape entries beyond LDS
     const double W = *wsum;
-    // (the function tables' LDS copy takes the 4 KB the tape gives up at
-    // four rows per lane: eight wavefronts per CU still fit)
     __shared__ MathTabsLds tabs_lds;
     const MathTabs mt = stage_tabs(tabs_lds);
 
@@ -1419,7 +1425,7 @@ __global__ __launch_bounds__(kWave) void k_adjoint(PopView pop, CodeView cv, Dat
         (void)sm0; (void)sm5;
         const int nlds = min(nconst, kGradLds);
         if (lane < nlds) gw[lane] = 0.0;
-        __syncthreads();
+        wave_lds_sync();
         double lacc = 0.0;
         // a program without constants needs only its loss, and only when asked
         const int64_t r_end = (nconst == 0 && !part) ? r0 : r1;
@@ -1467,12 +1473,19 @@ __global__ __launch_bounds__(kWave) void k_adjoint(PopView pop, CodeView cv, Dat
                     float x[R];
 #pragma unroll
                     for (int j = 0; j < R; ++j) x[j] = t[j];
-                    apply_unary<R, true>(fn, t, mt);
-                    if (fn != 0 && act) {
+                    if (act && (fn == 3 || fn == 4)) {
                         float dv[R];
-                        unary_derivative<R>(fn, x, t, dv);
+                        sincos_rows_derivative<R>(fn == 4, t, dv, mt);
                         tape_put(ntape, dv);
                         ++ntape;
+                    } else {
+                        apply_unary<R>(fn, t, mt);
+                        if (fn != 0 && act) {
+                            float dv[R];
+                            unary_derivative<R>(fn, x, t, dv);
+                            tape_put(ntape, dv);
+                            ++ntape;
+                        }
                     }
                 } else if (cls == kBin) {
                     if (dp < kStackRegs) {
@@ -1562,12 +1575,19 @@ __global__ __launch_bounds__(kWave) void k_adjoint(PopView pop, CodeView cv, Dat
                     float x[R];
 #pragma unroll
                     for (int j = 0; j < R; ++j) x[j] = t[j];
-                    apply_unary<R, true>(u, t, mt);
-                    if (u != 0 && act) {
+                    if (act && (u == 3 || u == 4)) {
                         float dv[R];
-                        unary_derivative<R>(u, x, t, dv);
+                        sincos_rows_derivative<R>(u == 4, t, dv, mt);
                         tape_put(ntape, dv);
                         ++ntape;
+                    } else {
+                        apply_unary<R>(u, t, mt);
+                        if (u != 0 && act) {
+                            float dv[R];
+                            unary_derivative<R>(u, x, t, dv);
+                            tape_put(ntape, dv);
+                            ++ntape;
+                        }
                     }
                 }
             }
@@ -1738,13 +1758,13 @@ __global__ __launch_bounds__(kWave) void k_adjoint(PopView pop, CodeView cv, Dat
             }
         }
         // ---------------- per-item results ----------------
-        __syncthreads();
+        wave_lds_sync();
         if (lane < nlds) gpart[(cbase + lane) * s.n_chunks + c] = gw[lane];
         if (part) {
             lacc = wave_sum(lacc);
             if (lane == 0) part[static_cast<int64_t>(p) * s.n_chunks + c] = lacc;
         }
-        __syncthreads();
+        wave_lds_sync();
     }
 }
 
@@ -4184,20 +4204,21 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
     const int freg = (g_forced && g_forced_cfg.freg == 0) ? 0 : freg_fit;
     auto occ = [](const void* k) {
         int n = 0;
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kWave, 0);
+        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kAdjWaves * kWave, 0);
         return n;
     };
     double* lossp = needs_forward ? nullptr : sc->part;
     auto go = [&](auto kernel, int64_t wave_floats) -> gp_status {
         int per_cu = 0;
-        GP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kWave, 0));
+        GP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kAdjWaves * kWave, 0));
         per_cu = std::max(per_cu, 1);
-        int64_t blocks = std::min<int64_t>(static_cast<int64_t>(per_cu) * sc->n_cu, sch.n_items);
+        int64_t blocks = std::min<int64_t>(static_cast<int64_t>(per_cu) * sc->n_cu,
+                                           (sch.n_items + kAdjWaves - 1) / kAdjWaves);
         blocks = std::max<int64_t>(blocks, 1);
         gp_status r2 = grow(reinterpret_cast<void**>(&sc->tape), &sc->tape_cap,
-                            static_cast<size_t>(blocks) * static_cast<size_t>(wave_floats), sizeof(float));
+                            static_cast<size_t>(blocks) * kAdjWaves * static_cast<size_t>(wave_floats), sizeof(float));
         if (r2 != GP_OK) return r2;
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kWave), 0, st, pv, cvw, dv, sch,
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kAdjWaves * kWave), 0, st, pv, cvw, dv, sch,
                            needs_forward ? sc->stats : nullptr, wsum, grad_fitness, lossp, sc->gpart, sc->gextra,
                            sc->tape, wave_floats);
         GP_HIP(hipGetLastError());
