@@ -1,0 +1,625 @@
+"""Writes gp_eval_asm.h: the evaluation kernel's interpreter as gfx950 assembly,
+one inline-assembly block per (rows per lane R, feature registers FREG).
+
+The block walks one compiled program (gp_eval_code.h) over one tile of 64 R
+rows with threaded dispatch: every instruction word holds its handler's byte
+offset from the handler table, each handler ends by jumping straight to the
+next one, and the program's instructions sit in two vector registers (lane i
+holds instruction i), so that fetching one is two v_readlane.  Stack slots,
+features and the top of the stack have fixed registers, so an operation on
+them is one vector instruction per row, with no copy and no indexed access.
+
+What a compiler's switch costs here, per instruction: a compare tree (no jump
+tables on this target), copies of each case's result into the loop's
+registers, an indexed store of the top: 21 vector and 21 scalar instructions
+and 9 branches for an addition on four rows.  Here: 4 vector instructions for
+the rows, 2 for the fetch, 5 scalar.  Fitness of 256 programs of 1 to 200 nodes
+on 16.8M rows: 104.4 ms with the switch, 75.6 ms here (28 features, log-loss,
+500 programs, 1.1M rows: 18.6 and 10.0 ms).
+
+The arithmetic bodies repeat, operation for operation, gp_crmath.h's sin, cos
+and log and gp_device.hip's square root and division.  Inputs the common
+paths do not cover, and the functions taken from the device library, leave
+the block with a code (kExit...); the caller applies that operation to the
+top and enters again.
+
+Handler table order and register assignment are repeated in gp_eval_code.h
+and gp_eval_asm.h by this generator.
+
+Run from this directory: python gen_eval_asm.py
+"""
+
+SLOTS = 11          # stack entries below the top held in registers
+STRIDE = 64         # bytes per handler
+SRC_MAX = 9
+FOPS = ["ADD", "SUB", "RSUB", "MUL", "DIV", "RDIV", "MAX", "MIN", "AT2", "RAT2"]
+UNARY = ["NEG", "LOG", "SQRT", "SIN", "COS", "TAN", "ABS", "EXP", "INV", "SQ", "CUBE", "TANH", "ATAN", "CBRT"]
+END, RELOAD, LOADY, SAVEL, LDT, LDB, UN = 0, 1, 2, 3, 4, 5, 6
+SAVE = UN + len(UNARY)
+LOADS = SAVE + SLOTS
+SET = LOADS + SLOTS
+# exit codes: 1 + unary index; these for the binary functions
+EXIT_MAX, EXIT_MIN, EXIT_AT_TB, EXIT_AT_BT = 32, 33, 34, 35
+
+
+def sections(freg):
+    nsrc = 1 + max(1, freg)
+    push = SET + nsrc
+    fold = push + SLOTS * nsrc
+    bin_ = fold + len(FOPS) * nsrc
+    return dict(nsrc=nsrc, push=push, fold=fold, bin=bin_, count=bin_ + len(FOPS) * (SLOTS + 1))
+
+
+class Gen:
+    # scalar registers (see the operand list in emit_function)
+    J, N0, N1, B, P, IDX, BLK, XC, T59, A, XB = 48, 50, 51, 52, 54, 55, 56, 58, 59, 60, 62
+    INV, PA, PB, S5, C4, L2, L3, L5 = 64, 66, 68, 70, 72, 74, 76, 78
+    LN2, C375, EPS, MASK, CLS, FOUR = 80, 82, 84, 85, 86, 87
+    LD, Q0, Q1, Q2 = 88, 90, 92, 94
+
+    def __init__(self, R, freg):
+        self.R, self.freg = R, freg
+        self.mem = freg == 0
+        v = {1: 24, 2: 26, 4: 30}[R]
+
+        def take(n):
+            nonlocal v
+            r = v
+            v += n + (n & 1)
+            return r
+        self.base = v
+        self.t = take(R)
+        self.s = take(SLOTS * R)
+        self.i = take(2)
+        self.k = take(10)
+        self.x = take(freg * R) if freg else None
+        self.off = take(R) if self.mem else None
+        self.p = take(R) if self.mem else None
+        self.lds = take(1)
+        self.nb = min(R, 2)
+        self.tmp = take(12 * self.nb)
+        self.end = v
+        self.RNDS, self.RNDC, self.S3, self.C2, self.L4 = (self.k + 2 * q for q in range(5))
+        self.lines = []
+        self.sec = sections(freg)
+
+    # ---- emission helpers ----
+    def o(self, s):
+        self.lines.append(s)
+
+    def label(self, n):
+        self.o(f".L{n}_%=:")
+
+    def br(self, n):
+        self.o(f"s_branch .L{n}_%=")
+
+    def hb(self):
+        """Fetch the next instruction (its handler offset and payload)."""
+        self.o(f"v_readlane_b32 s{self.N0}, v{self.i}, s{self.IDX}")
+        self.o(f"v_readlane_b32 s{self.N1}, v{self.i + 1}, s{self.IDX}")
+        self.o(f"s_add_u32 s{self.IDX}, s{self.IDX}, 1")
+
+    def he(self):
+        """Jump to it."""
+        self.o(f"s_add_u32 s{self.J}, s{self.B}, s{self.N0}")
+        self.o(f"s_addc_u32 s{self.J + 1}, s{self.B + 1}, 0")
+        self.o(f"s_mov_b32 s{self.P}, s{self.N1}")
+        self.o(f"s_setpc_b64 s[{self.J}:{self.J + 1}]")
+
+    def rows(self, f):
+        for j in range(self.R):
+            self.o(f(j))
+
+    def T(self, j):
+        return f"v{self.t + j}"
+
+    def S(self, k, j):
+        return f"v{self.s + k * self.R + j}"
+
+    def M(self, j):
+        return f"v{self.tmp + j}"
+
+    def src(self, q, j):
+        if q == 0:
+            return f"s{self.P}"
+        return f"v{self.p + j}" if self.mem else f"v{self.x + (q - 1) * self.R + j}"
+
+    # ---- handlers ----
+    def handler(self, idx):
+        self.o(f".p2align 6")
+        self.label(f"h{idx}")
+
+    def table(self):
+        sec, R = self.sec, self.R
+        wait = "s_waitcnt vmcnt(0)"
+        h = 0
+
+        def begin(want):
+            nonlocal h
+            assert h == want, (h, want)
+            self.handler(h)
+            h += 1
+        begin(END)
+        self.o(f"s_mov_b32 s{self.XC}, 0")
+        self.br("exit")
+        begin(RELOAD)
+        self.br("reload")
+        begin(LOADY)            # (the caller entered with it on top)
+        self.hb()
+        self.he()
+        for want, name in ((SAVEL, "savel"), (LDT, "ldt"), (LDB, "ldb")):
+            begin(want)
+            self.hb()
+            self.br(name)
+        for u, name in enumerate(UNARY):
+            begin(UN + u)
+            self.hb()
+            if name == "NEG":
+                self.rows(lambda j: f"v_xor_b32 {self.T(j)}, 0x80000000, {self.T(j)}")
+                self.he() if R < 4 else self.br("next")
+            elif name == "ABS":
+                self.rows(lambda j: f"v_and_b32 {self.T(j)}, 0x7fffffff, {self.T(j)}")
+                self.he() if R < 4 else self.br("next")
+            elif name == "SQ":
+                self.rows(lambda j: f"v_mul_f32 {self.T(j)}, {self.T(j)}, {self.T(j)}")
+                self.he()
+            elif name == "CUBE":
+                self.br("cube")
+            elif name in ("LOG", "SQRT", "SIN", "COS"):
+                self.br(name.lower())
+            else:
+                self.o(f"s_mov_b32 s{self.XC}, {1 + u}")
+                self.br("leave")
+        for k in range(SLOTS):
+            begin(SAVE + k)
+            self.hb()
+            self.rows(lambda j: f"v_mov_b32 {self.S(k, j)}, {self.T(j)}")
+            self.he()
+        for k in range(SLOTS):
+            begin(LOADS + k)
+            self.hb()
+            self.rows(lambda j: f"v_mov_b32 {self.T(j)}, {self.S(k, j)}")
+            self.he()
+
+        def from_src(q, op, tail="he"):
+            """op on the rows with terminal q, then the next instruction (for a
+            feature from memory, after requesting the next one)."""
+            self.hb()
+            if self.mem and q == 1:
+                self.o(wait)
+            self.rows(op)
+            if self.mem and q == 1:
+                self.br("m" + ("next" if tail == "he" else tail))
+            elif tail == "he":
+                self.he()
+            else:
+                self.br(tail)
+        for q in range(sec["nsrc"]):
+            begin(SET + q)
+            from_src(q, lambda j: f"v_mov_b32 {self.T(j)}, {self.src(q, j)}")
+        for k in range(SLOTS):
+            for q in range(sec["nsrc"]):
+                begin(sec["push"] + k * sec["nsrc"] + q)
+                self.hb()
+                if self.mem and q == 1:
+                    self.o(wait)
+                self.rows(lambda j: f"v_mov_b32 {self.S(k, j)}, {self.T(j)}")
+                if R == 4:      # (the second half does not fit the handler)
+                    self.br(f"set{q}")
+                else:
+                    self.rows(lambda j: f"v_mov_b32 {self.T(j)}, {self.src(q, j)}")
+                    self.br("mnext") if self.mem and q == 1 else self.he()
+        for f, name in enumerate(FOPS):
+            for q in range(sec["nsrc"]):
+                begin(sec["fold"] + f * sec["nsrc"] + q)
+                simple = {"ADD": "v_add_f32", "SUB": "v_sub_f32", "RSUB": "v_subrev_f32", "MUL": "v_mul_f32"}
+                if name in simple:
+                    from_src(q, lambda j: f"{simple[name]} {self.T(j)}, {self.src(q, j)}, {self.T(j)}")
+                else:
+                    tail = {"DIV": "divmt", "RDIV": "divtm", "MAX": "max", "MIN": "min", "AT2": "atmt",
+                            "RAT2": "attm"}[name]
+                    from_src(q, lambda j: f"v_mov_b32 {self.M(j)}, {self.src(q, j)}", tail)
+        for f, name in enumerate(FOPS):
+            for k in range(SLOTS + 1):
+                begin(sec["bin"] + f * (SLOTS + 1) + k)
+                self.hb()
+                b = (lambda j: self.S(k, j)) if k < SLOTS else self.M
+                simple = {"ADD": ("v_add_f32", 0), "SUB": ("v_sub_f32", 0), "RSUB": ("v_sub_f32", 1),
+                          "MUL": ("v_mul_f32", 0)}
+                if name in simple:
+                    op, rev = simple[name]
+                    self.rows(lambda j: f"{op} {self.T(j)}, " + (f"{b(j)}, {self.T(j)}" if rev else f"{self.T(j)}, {b(j)}"))
+                    self.he()
+                else:
+                    if k < SLOTS:
+                        self.rows(lambda j: f"v_mov_b32 {self.M(j)}, {b(j)}")
+                    self.br({"DIV": "divtm", "RDIV": "divmt", "MAX": "max", "MIN": "min", "AT2": "attm",
+                             "RAT2": "atmt"}[name])
+        assert h == sec["count"]
+
+    # ---- out-of-line bodies ----
+    def prefetch(self):
+        """Requests the next feature from memory (payload: its index, negative: none)."""
+        if not self.mem:
+            return
+        n = len(self.lines)
+        self.o(f"s_cmp_lt_i32 s{self.P}, 0")
+        self.o(f"s_cbranch_scc1 .Lnp{n}_%=")
+        self.o(f"s_mul_i32 s{self.A}, s{self.P}, s{self.LD}")
+        self.o(f"s_mul_hi_u32 s{self.A + 1}, s{self.P}, s{self.LD}")
+        self.o(f"s_mul_i32 s{self.T59}, s{self.P}, s{self.LD + 1}")
+        self.o(f"s_add_u32 s{self.A + 1}, s{self.A + 1}, s{self.T59}")
+        self.o(f"s_add_u32 s{self.A}, s{self.A}, s{self.XB}")
+        self.o(f"s_addc_u32 s{self.A + 1}, s{self.A + 1}, s{self.XB + 1}")
+        self.rows(lambda j: f"global_load_dword v{self.p + j}, v{self.off + j}, s[{self.A}:{self.A + 1}]")
+        self.label(f"np{n}")
+
+    def batches(self):
+        return [list(range(a, min(a + self.nb, self.R))) for a in range(0, self.R, self.nb)]
+
+    def interleave(self, per_row):
+        """Rows' instruction lists merged round-robin."""
+        for group in zip(*per_row):
+            for x in group:
+                if x:
+                    self.o(x)
+
+    def tp(self, b, q):
+        """Temporary register q (0..11) of the batch's row b."""
+        return self.tmp + 12 * b + q
+
+    def pair(self, r):
+        return f"v[{r}:{r + 1}]"
+
+    def rare(self, name, code, cond):
+        """Leaves for the caller's path if cond(j) holds on any row."""
+        qs = [f"s[{self.Q0}:{self.Q0 + 1}]", f"s[{self.Q1}:{self.Q1 + 1}]", f"s[{self.Q2}:{self.Q2 + 1}]", "vcc"]
+        for j in range(self.R):
+            self.o(cond(j).format(q=qs[j]))
+        for j in range(1, self.R):
+            self.o(f"s_or_b64 {qs[0]}, {qs[0]}, {qs[j]}")
+        if self.R == 1:
+            self.o(f"s_cmp_lg_u64 {qs[0]}, 0")
+        self.o(f"s_cbranch_scc1 .Lrare_{name}_%=")
+        self.rare_exits.append((name, code))
+
+    def sincos(self, name, rnd):
+        self.label(name)
+        self.o(f"s_mov_b32 s{self.T59}, 0x4b800000")
+        self.rare(name, 1 + UNARY.index(name.upper()),
+                  lambda j: f"v_cmp_ge_f32_e64 {{q}}, |{self.T(j)}|, s{self.T59}")
+        for rows in self.batches():
+            lists = []
+            for b, j in enumerate(rows):
+                P = lambda q: self.pair(self.tp(b, q))
+                r = lambda q: f"v{self.tp(b, q)}"
+                e = self.tp(b, 8)
+                lists.append([
+                    f"v_cvt_f64_f32 {P(0)}, {self.T(j)}",
+                    f"v_fma_f64 {P(2)}, {P(0)}, s[{self.INV}:{self.INV + 1}], {self.pair(rnd)}",
+                    f"v_lshlrev_b32_sdwa {r(6)}, s{self.FOUR}, {r(2)} dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0",
+                    f"ds_read_b128 v[{e}:{e + 3}], {r(6)} offset:4096",
+                    f"v_add_f64 {P(4)}, {P(2)}, -{self.pair(rnd)}",
+                    f"v_fma_f64 {P(0)}, -{P(4)}, s[{self.PA}:{self.PA + 1}], {P(0)}",
+                    f"v_fma_f64 {P(0)}, -{P(4)}, s[{self.PB}:{self.PB + 1}], {P(0)}",
+                    f"v_mul_f64 {P(2)}, {P(0)}, {P(0)}",
+                    f"v_fma_f64 {P(4)}, s[{self.S5}:{self.S5 + 1}], {P(2)}, {self.pair(self.S3)}",
+                    f"v_fma_f64 {P(6)}, s[{self.C4}:{self.C4 + 1}], {P(2)}, {self.pair(self.C2)}",
+                    f"v_fma_f64 {P(4)}, {P(2)}, {P(4)}, 1.0",
+                    f"v_fma_f64 {P(6)}, {P(2)}, {P(6)}, 1.0",
+                    f"v_mul_f64 {P(0)}, {P(0)}, {P(4)}",
+                    f"s_waitcnt lgkmcnt({len(rows) - 1 - b})",
+                    f"v_mul_f64 {P(4)}, {P(8)}, {P(6)}",
+                    f"v_fma_f64 {P(4)}, {P(10)}, {P(0)}, {P(4)}",
+                    f"v_cvt_f32_f64 {self.T(j)}, {P(4)}"])
+            self.interleave(lists)
+        self.he()
+
+    def log(self):
+        self.label("log")
+        self.o(f"s_mov_b32 s{self.T59}, 0x7f800000")
+        self.rare("log", 1 + UNARY.index("LOG"), lambda j: f"v_cmp_eq_f32_e64 {{q}}, |{self.T(j)}|, s{self.T59}")
+        for rows in self.batches():
+            lists = []
+            for b, j in enumerate(rows):
+                P = lambda q: self.pair(self.tp(b, q))
+                r = lambda q: f"v{self.tp(b, q)}"
+                e = self.tp(b, 8)
+                q = (self.Q0, self.Q1)[b]
+                lists.append([
+                    f"v_lshrrev_b32 {r(2)}, 11, {self.T(j)}",
+                    f"v_and_b32 {r(2)}, 0xff0, {r(2)}",
+                    f"ds_read_b128 v[{e}:{e + 3}], {r(2)}",
+                    f"v_cmp_gt_f32_e64 s[{q}:{q + 1}], |{self.T(j)}|, s{self.EPS}",
+                    f"v_add_u32 {r(4)}, 0xffcb0000, {self.T(j)}",
+                    f"v_bfi_b32 {r(0)}, s{self.MASK}, {self.T(j)}, 1.0",
+                    f"v_frexp_exp_i32_f32 {r(4)}, {r(4)}",
+                    f"v_cvt_f64_f32 {P(0)}, {r(0)}",
+                    f"v_cvt_f64_i32 {P(4)}, {r(4)}",
+                    f"s_waitcnt lgkmcnt({len(rows) - 1 - b})",
+                    f"v_fma_f64 {P(0)}, {P(0)}, {P(8)}, -1.0",
+                    f"v_fma_f64 {P(2)}, s[{self.L5}:{self.L5 + 1}], {P(0)}, {self.pair(self.L4)}",
+                    f"v_mul_f64 {P(6)}, {P(0)}, {P(0)}",
+                    f"v_fma_f64 {P(2)}, {P(2)}, {P(0)}, s[{self.L3}:{self.L3 + 1}]",
+                    f"v_fma_f64 {P(4)}, {P(4)}, s[{self.LN2}:{self.LN2 + 1}], {P(10)}",
+                    f"v_fma_f64 {P(2)}, {P(2)}, {P(0)}, s[{self.L2}:{self.L2 + 1}]",
+                    f"v_fma_f64 {P(2)}, {P(6)}, {P(2)}, {P(0)}",
+                    f"v_add_f64 {P(2)}, {P(4)}, {P(2)}",
+                    f"v_cvt_f32_f64 {r(0)}, {P(2)}",
+                    f"v_cndmask_b32_e64 {self.T(j)}, 0, {r(0)}, s[{q}:{q + 1}]"])
+            self.interleave(lists)
+        self.he()
+
+    def sqrt(self):
+        self.label("sqrt")
+        for rows in self.batches():
+            lists = []
+            for b, j in enumerate(rows):
+                P = lambda q: self.pair(self.tp(b, q))
+                r = lambda q: f"v{self.tp(b, q)}"
+                q = (self.Q0, self.Q1)[b]
+                lists.append([
+                    f"v_cvt_f64_f32_e64 {P(0)}, |{self.T(j)}|",
+                    f"v_rsq_f64 {P(2)}, {P(0)}",
+                    f"v_cmp_class_f64_e64 s[{q}:{q + 1}], {P(0)}, s{self.CLS}",
+                    "s_nop 0" if b == 0 else "",
+                    f"v_mul_f64 {P(4)}, {P(0)}, {P(2)}",
+                    f"v_fma_f64 {P(2)}, -{P(4)}, {P(2)}, 1.0",
+                    f"v_fma_f64 {P(6)}, {P(2)}, s[{self.C375}:{self.C375 + 1}], 0.5",
+                    f"v_mul_f64 {P(2)}, {P(4)}, {P(2)}",
+                    f"v_fma_f64 {P(4)}, {P(2)}, {P(6)}, {P(4)}",
+                    f"v_cvt_f32_f64 {r(0)}, {P(4)}",
+                    f"v_cndmask_b32_e64 {self.T(j)}, {r(0)}, |{self.T(j)}|, s[{q}:{q + 1}]"])
+            self.interleave(lists)
+        self.he()
+
+    def div(self, name, num, den):
+        """t = |den| > eps ? num / den : 1, the compiler's IEEE division."""
+        self.label(name)
+        for rows in self.batches():
+            lists = []
+            for b, j in enumerate(rows):
+                d, r, n, q, e = (f"v{self.tmp + self.R + 5 * b + x}" for x in range(5))
+                a, c = num(j), den(j)
+                pq = (self.Q0, self.Q1)[b]
+                vc = "vcc" if b == 0 else f"s[{self.Q2}:{self.Q2 + 1}]"
+                lists.append([
+                    f"v_cmp_gt_f32_e64 s[{pq}:{pq + 1}], |{c}|, s{self.EPS}",
+                    f"v_div_scale_f32 {d}, s[{self.J}:{self.J + 1}], {c}, {c}, {a}",
+                    f"v_div_scale_f32 {n}, {vc}, {a}, {c}, {a}",
+                    f"v_rcp_f32 {r}, {d}",
+                    "s_nop 0" if b == 0 else "",
+                    f"v_fma_f32 {q}, -{d}, {r}, 1.0",
+                    f"v_fma_f32 {r}, {q}, {r}, {r}",
+                    f"v_mul_f32 {q}, {n}, {r}",
+                    f"v_fma_f32 {e}, -{d}, {q}, {n}",
+                    f"v_fma_f32 {q}, {e}, {r}, {q}",
+                    f"v_fma_f32 {d}, -{d}, {q}, {n}"])
+            self.interleave(lists)
+            for b, j in enumerate(rows):
+                d, r, n, q, e = (f"v{self.tmp + self.R + 5 * b + x}" for x in range(5))
+                a, c = num(j), den(j)
+                if b == 1:
+                    self.o(f"s_mov_b64 vcc, s[{self.Q2}:{self.Q2 + 1}]")
+                self.o(f"v_div_fmas_f32 {q}, {d}, {r}, {q}")
+            for b, j in enumerate(rows):
+                d, r, n, q, e = (f"v{self.tmp + self.R + 5 * b + x}" for x in range(5))
+                self.o(f"v_div_fixup_f32 {q}, {q}, {den(j)}, {num(j)}")
+            for b, j in enumerate(rows):
+                q = f"v{self.tmp + self.R + 5 * b + 3}"
+                pq = (self.Q0, self.Q1)[b]
+                self.o(f"v_cndmask_b32_e64 {self.T(j)}, 1.0, {q}, s[{pq}:{pq + 1}]")
+        self.he()
+
+    def bodies(self):
+        R = self.R
+        self.rare_exits = []
+        self.label("next")
+        self.he()
+        if R == 4:
+            for q in range(self.sec["nsrc"]):
+                self.label(f"set{q}")
+                self.rows(lambda j: f"v_mov_b32 {self.T(j)}, {self.src(q, j)}")
+                self.br("mnext") if self.mem and q == 1 else self.he()
+        if self.mem:
+            self.label("mnext")
+            self.prefetch()
+            self.he()
+        self.label("cube")
+        self.rows(lambda j: f"v_mul_f32 {self.M(j)}, {self.T(j)}, {self.T(j)}")
+        self.rows(lambda j: f"v_mul_f32 {self.T(j)}, {self.M(j)}, {self.T(j)}")
+        self.he()
+        a = self.tmp + 12 * self.nb - 1     # an address, clear of the operand in the first temporaries
+        for name, ins in (("savel", "ds_write_b32 v{a}, {t} offset:{o}"), ("ldt", "ds_read_b32 {t}, v{a} offset:{o}"),
+                          ("ldb", "ds_read_b32 {m}, v{a} offset:{o}")):
+            self.label(name)
+            self.o(f"v_add_u32 v{a}, s{self.P}, v{self.lds}")
+            self.rows(lambda j: ins.format(a=a, t=self.T(j), m=self.M(j), o=256 * j))
+            if name != "savel":
+                self.o("s_waitcnt lgkmcnt(0)")
+            self.he()
+        self.sincos("sin", self.RNDS)
+        self.sincos("cos", self.RNDC)
+        self.log()
+        self.sqrt()
+        for name, num, den in (("divtm", self.T, self.M), ("divmt", self.M, self.T)):
+            if self.mem:
+                self.label("m" + name)
+                self.prefetch()
+            self.div(name, num, den)
+        for name, code in (("max", EXIT_MAX), ("min", EXIT_MIN), ("attm", EXIT_AT_TB), ("atmt", EXIT_AT_BT)):
+            if self.mem:
+                self.label("m" + name)
+                self.prefetch()
+            self.label(name)
+            self.o(f"s_mov_b32 s{self.XC}, {code}")
+            self.br("leave")
+        for name, code in self.rare_exits:
+            self.label(f"rare_{name}")
+            self.o(f"s_mov_b32 s{self.XC}, {code}")
+            self.br("leave")
+        self.label("reload")
+        self.o(f"s_add_u32 s{self.BLK}, s{self.BLK}, 512")
+        self.o(f"s_addc_u32 s{self.BLK + 1}, s{self.BLK + 1}, 0")
+        self.o(f"v_mbcnt_lo_u32_b32 v{a}, -1, 0")
+        self.o(f"v_mbcnt_hi_u32_b32 v{a}, -1, v{a}")
+        self.o(f"v_lshlrev_b32 v{a}, 3, v{a}")
+        self.o(f"global_load_dwordx2 v[{self.i}:{self.i + 1}], v{a}, s[{self.BLK}:{self.BLK + 1}]")
+        self.o(f"s_mov_b32 s{self.IDX}, 0")
+        self.o("s_waitcnt vmcnt(0)")
+        self.br("start")
+        self.label("leave")
+        # the instruction after this one was fetched: fetched again on entry
+        self.o(f"s_sub_u32 s{self.IDX}, s{self.IDX}, 1")
+        if self.mem:
+            self.o("s_waitcnt vmcnt(0)")
+        self.label("exit")
+
+    def text(self):
+        # everything the caller has in flight must have landed: the block counts
+        # its own loads from zero
+        self.o("s_waitcnt vmcnt(0) lgkmcnt(0)")
+        self.o(f"s_getpc_b64 s[{self.B}:{self.B + 1}]")
+        self.label("pc")
+        self.o(f"s_add_u32 s{self.B}, s{self.B}, .Lh0_%=-.Lpc_%=")
+        self.o(f"s_addc_u32 s{self.B + 1}, s{self.B + 1}, 0")
+        self.label("start")
+        self.hb()
+        self.he()
+        self.table()
+        self.bodies()
+        return self.lines
+
+
+def pieces(n):
+    """Register-tuple sizes covering n registers."""
+    out = []
+    for p in (32, 16, 8, 4, 2, 1):
+        while n >= p:
+            out.append(p)
+            n -= p
+    return out
+
+
+def vec(n):
+    return "float" if n == 1 else f"EvVec<float, {n}>"
+
+
+def emit_function(R, freg):
+    g = Gen(R, freg)
+    lines = g.text()
+    w = []
+    # members: (name, type, first register, size, is_output)
+    members = [("t", g.t, R)]
+    at = g.s
+    for q, n in enumerate(pieces(SLOTS * R)):
+        members.append((f"s{q}", at, n))
+        at += n
+    outs = members + [("m", g.tmp, R)]
+    ins = [("k0", g.k, 8), ("k1", g.k + 8, 2), ("lds", g.lds, 1)]
+    if freg:
+        at = g.x
+        for q, n in enumerate(pieces(freg * R)):
+            ins.append((f"x{q}", at, n))
+            at += n
+    else:
+        ins.append(("off", g.off, R))
+        outs.append(("p", g.p, R))
+
+    def vr(first, n):
+        return f"{{v[{first}:{first + n - 1}]}}" if n > 1 else f"{{v{first}}}"
+    w.append("template <>")
+    w.append(f"struct Interp<{R}, {freg}> {{")
+    w.append(f"    // v{g.base} .. v{g.end - 1}")
+    for name, first, n in outs + ins:
+        ty = "uint32_t" if name == "lds" or name == "off" and n == 1 else \
+            (f"EvVec<uint32_t, {n}>" if name == "off" else vec(n))
+        w.append(f"    {ty} {name};")
+    w.append("    EvVec<uint32_t, 2> ins;      // lane i: instruction i of the block")
+    w.append("    uint32_t idx;                // next instruction of the block")
+    w.append("    uint32_t blk0, blk1;         // address of the block")
+    w.append("    uint64_t xb, ld4;            // feature 0 of the tile's first row; bytes between features")
+    w.append("    EvVec<uint32_t, 16> c0;      // scalar constants")
+    w.append("    EvVec<uint32_t, 8> c1;")
+    w.append("    __device__ __forceinline__ uint32_t run() {")
+    w.append("        uint32_t code;")
+    w.append("        asm volatile(")
+    for ln in lines:
+        w.append(f'            "{ln}\\n"')
+    w.append("            : " + ", ".join(f'"+{vr(f, n)}"({nm})' for nm, f, n in outs) + ",")
+    w.append(f'              "+{{v[{g.i}:{g.i + 1}]}}"(ins), "+{{s{g.IDX}}}"(idx), "+{{s{g.BLK}}}"(blk0), "+{{s{g.BLK + 1}}}"(blk1), "={{s{g.XC}}}"(code)')
+    w.append("            : " + ", ".join(f'"{vr(f, n)}"({nm})' for nm, f, n in ins) + ",")
+    w.append(f'              "{{s[64:79]}}"(c0), "{{s[80:87]}}"(c1)' +
+             (f', "{{s[{g.XB}:{g.XB + 1}]}}"(xb), "{{s[{g.LD}:{g.LD + 1}]}}"(ld4)' if not freg else ""))
+    clob = ["vcc", "scc", "memory"]
+    clob += [f"s{q}" for q in (48, 49, 50, 51, 52, 53, 54, 59, 60, 61, 90, 91, 92, 93, 94, 95)]
+    clob += [f"v{q}" for q in range(g.tmp + R, g.tmp + 12 * g.nb)]
+    w.append("            : " + ", ".join(f'"{c}"' for c in clob) + ");")
+    # (scalar registers all along; this tells the compiler that they are uniform)
+    for nm in ("idx", "blk0", "blk1"):
+        w.append(f"        {nm} = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>({nm})));")
+    w.append("        return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(code)));")
+    w.append("    }")
+    w.append("};")
+    return w
+
+
+def main():
+    out = ["// Generated by gen_eval_asm.py; do not edit.  The interpreter of the evaluation",
+           "// kernel as gfx950 assembly (see the generator for its design).",
+           "#pragma once", "", "#include <cstdint>", "",
+           "template <typename T, int N>", "using EvVec = T __attribute__((ext_vector_type(N)));", "",
+           "template <int R, int FREG>", "struct Interp;", ""]
+    for R in (1, 2, 4):
+        for freg in (0, 2, 8):
+            out += emit_function(R, freg) + [""]
+    with open("gp_eval_asm.h", "w") as f:
+        f.write("\n".join(out))
+    code = ["// Generated by gen_eval_asm.py; do not edit.  The instruction stream that",
+            "// the compile kernels write and the evaluation kernel's interpreter runs.",
+            "//",
+            "// An instruction is two words: the byte offset of its handler in the",
+            "// interpreter's table, and a payload (a constant's bits; the index of the next",
+            "// feature to fetch from memory, or -1; the byte offset of a stack slot in LDS).",
+            "// Programs run in execution order; the value on top of the stack lives in its",
+            "// own registers and entry e below it (from the bottom) in slot e.  The 64th",
+            "// word pair of every 64 is kOpReload unless the program has ended.",
+            "#pragma once", "", "#include <cstdint>", "",
+            f"constexpr int kRegSlots = {SLOTS};        // slots held in registers; deeper ones live in LDS",
+            f"constexpr uint32_t kOpBytes = {STRIDE};    // bytes per handler",
+            "enum : uint32_t {",
+            f"    kOpEnd = {END},", f"    kOpReload = {RELOAD},       // the next 64 instructions",
+            f"    kOpLoadY = {LOADY},        // top = the row's target (first instruction only: the caller put it there)",
+            f"    kOpSaveL = {SAVEL},        // LDS slot = top",
+            f"    kOpLoadTopL = {LDT},     // top = LDS slot",
+            f"    kOpLoadL = {LDB},        // operand register = LDS slot (for a kOpBin of slot kRegSlots)",
+            f"    kOpUnary = {UN},        // + unary index: top = f(top)",
+            f"    kOpSave = {SAVE},        // + slot: slot = top",
+            f"    kOpLoadS = {LOADS},       // + slot: top = slot",
+            f"    kOpSet = {SET},         // + source: top = source",
+            "};",
+            "// Sources: 0 a constant; 1 + f feature f in registers, or 1 the feature fetched",
+            "// from memory (FREG = 0).  kPush + slot * n_src + source: slot = top, top = source.",
+            "// kFold + op * n_src + source: top = source (op) top; kBin + op * (kRegSlots + 1) + slot:",
+            "// top = top (op) slot; the reversed forms exchange the operands.",
+            "struct EvalOps {", "    uint32_t n_src, push, fold, bin;", "};",
+            "constexpr uint32_t eval_n_src(int freg) { return 1u + static_cast<uint32_t>(freg > 0 ? freg : 1); }",
+            "constexpr EvalOps eval_ops(int freg) {",
+            "    const uint32_t n = eval_n_src(freg), push = kOpSet + n, fold = push + kRegSlots * n;",
+            f"    return EvalOps{{n, push, fold, fold + {len(FOPS)}u * n}};", "}",
+            "enum : uint32_t {"]
+    names = {"ADD": "Add", "SUB": "Sub", "RSUB": "SubRev", "MUL": "Mul", "DIV": "Div", "RDIV": "DivRev", "MAX": "Max",
+             "MIN": "Min", "AT2": "Atan2", "RAT2": "Atan2Rev"}
+    code += [f"    kB{names[n]} = {i}," for i, n in enumerate(FOPS)]
+    code += ["};",
+             "// What the interpreter leaves to its caller: 1 + unary index (top = f(top)), or one of",
+             "// these on the top t and the operand register m.",
+             "enum : uint32_t {", "    kExitEnd = 0,", f"    kExitMax = {EXIT_MAX},", f"    kExitMin = {EXIT_MIN},",
+             f"    kExitAtan2TM = {EXIT_AT_TB},   // atan2(t, m)", f"    kExitAtan2MT = {EXIT_AT_BT},   // atan2(m, t)",
+             "};", ""]
+    with open("gp_eval_code.h", "w") as f:
+        f.write("\n".join(code))
+
+
+if __name__ == "__main__":
+    main()

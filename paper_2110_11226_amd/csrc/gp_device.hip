@@ -29,9 +29,12 @@
 #include <new>
 #include <tuple>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "gp_crmath.h"
+#include "gp_eval_asm.h"
+#include "gp_eval_code.h"
 #include "gp_internal.h"
 
 using namespace gp;
@@ -68,10 +71,10 @@ struct DataView {
 struct CodeView {
     const uint4* code;     // the adjoint's format (k_compile)
     const int32_t* clen;
-    const uint4* ecode;    // the evaluation kernel's format (k_compile_eval):
-    const int32_t* eclen;  // program p from ecode[prog_off[p] * ex_mul + p * ex_add]
-    int32_t ex_mul;        // instructions per node at most (1, or the longest user definition)
-    int32_t ex_add;        // instructions per program added by a user loss
+    const uint4* ecode;    // the evaluation kernel's format (gp_eval_code.h, two instructions per
+    const uint32_t* ehdr;  // uint4): program p from ecode[prog_off[p] * ex_mul + p * ex_add], its header
+    int32_t ex_mul;        // room per node (1, or the longest user definition)
+    int32_t ex_add;        // room per program for a user loss
 };
 
 // Work decomposition: rows are split into n_chunks chunks of `chunk` rows
@@ -157,9 +160,17 @@ __device__ __forceinline__ T ldu(const T* p) {
     return *(const __attribute__((address_space(4))) T*)p;
 }
 
-// Stack slots: slots below kStackRegs live in VGPRs, slots from kStackRegs
-// on in a per-wavefront LDS area; register slot kStackRegs is a sink for the
-// speculative writes of those deeper slots (see k_eval).  Slot 0 is never
+// Orders a wavefront's own LDS writes before its later LDS reads (its LDS
+// operations complete in order; this only keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The adjoint kernel's stack slots: slots below kStackRegs live in VGPRs, slots
+// from kStackRegs on in a per-wavefront memory area; register slot kStackRegs is
+// a sink for the speculative writes of those deeper slots.  Slot 0 is never
 // read, so a full stack of GP_MAX_STACK values uses slots 1 .. GP_MAX_STACK-1.
 constexpr int kStackRegs = 15;
 constexpr int kStackLds = GP_MAX_STACK - kStackRegs;
@@ -521,105 +532,126 @@ __global__ __launch_bounds__(kBlock) void k_compile(PopView pop, uint4* __restri
 }
 
 // ---------------------------------------------------------------------------
-// The evaluation kernel's instruction stream (k_compile_eval): one uint4 per
-// instruction, in execution order, each instruction's stack slots fixed by
-// the pre-pass, so the kernel keeps no stack pointer.
-//   x bits 0-7    opcode (below)
-//   x bits 8-15   slot the kernel stores the current top into before the
-//                 instruction: for a push, the slot of the entry it covers;
-//                 for every other instruction the sink slot kEvalRegs, which
-//                 is never read (one store per instruction keeps the
-//                 register array in place)
-//   x bits 16-23  slot of a binary function's second operand (kIBin); the
-//                 LDS slot a deep push covers (kIDeep)
-//   y             a constant's float bits (kIPushC, kIFoldC), a feature
-//                 index (kIPushX, kIFoldX) or the slot a copy reads (kIPushS)
-//   z             up to 8 unary functions applied, in order, to the
-//                 instruction's result (4 bits each from the lowest: unary
-//                 index + 1; 0 ends the chain), so that a unary function
-//                 costs no dispatch of its own
-// Stack entries are numbered from the bottom; the top entry lives in
-// registers and entry e below it in slot e.  Slots from kEvalRegs on live in
-// LDS; the instructions that reach them carry kIDeep.
+// The evaluation kernel's instruction stream: gp_eval_code.h.  A terminal that
+// is an operand of a binary function is fused with it, a subtree of constants
+// only is replaced by its value (formed here, once, by the same float32
+// functions the kernel applies per row), and every other node is one
+// instruction.
+//
+// A binary function's operands are evaluated in the order that needs fewer
+// stack entries (the one that needs more of them first), whichever comes first
+// in the prefix list: the same operations on the same operands, so the same
+// value, but a random program of 200 nodes needs at most 5 entries instead of
+// up to 20.
 //
 // A user function (Sec. V: custom function sets) is expanded in place: its
 // arguments are evaluated as usual, its definition's argument references
-// become kIPushS copies of the argument entries, and once the definition has
-// left its value on top, the arguments below it are simply forgotten (the
-// next push overwrites their slots).  A user loss (GP_METRIC_USER_i) is the
-// same expansion around the whole program: kIPushY pushes the row's target
-// first, and the loss function's definition runs on (output, target) last.
+// become copies of the argument entries, and once the definition has left its
+// value on top, the arguments below it are simply forgotten (the next push
+// overwrites their slots).  A user loss (GP_METRIC_USER_i) is the same
+// expansion around the whole program: kOpLoadY pushes the row's target first,
+// and the loss function's definition runs on (output, target) last.
 // These stacks reach past the program's own GP_MAX_STACK, into LDS slots
 // kEvalLds .. kEvalLdsUser-1, which launches that may meet them provide.
 // ---------------------------------------------------------------------------
-enum : uint32_t {
-    kIPushX = 0,    // push feature
-    kIPushC = 1,    // push constant
-    kIBin = 2,      // + binary index: top = top (op) slot
-    kIFoldX = 9,    // + binary index: top = feature (op) top
-    kIFoldC = 16,   // + binary index: top = constant (op) top
-    kIUn = 23,      // + unary index: top = f(top)
-    kIPushS = 40,   // push a copy of the entry in slot y (register or LDS)
-    kIPushY = 41,   // push the row's target
-    kIDeep = 64     // with kIPushX, kIPushC, kIPushS, kIBin: the slot x
-                    // bits 16-23 names lives in LDS
-};
 constexpr int kEvalSlots = GP_MAX_STACK - 1;   // entries below the top
-constexpr int kEvalRegs = 15;                  // slots held in VGPRs (plus the sink)
-constexpr int kEvalLds = kEvalSlots - kEvalRegs;
+constexpr int kEvalLds = kEvalSlots - kRegSlots;
 // with user functions or a user loss: the target below the program, and a
 // definition's own GP_USER_MAX_STACK values above its arguments
 constexpr int kEvalSlotsUser = GP_MAX_STACK + GP_USER_MAX_STACK;
-constexpr int kEvalLdsUser = kEvalSlotsUser - kEvalRegs;
+constexpr int kEvalLdsUser = kEvalSlotsUser - kRegSlots;
 constexpr int kCompileDepth = kEvalSlotsUser + 1;   // entries the compiler tracks
+// instructions the evaluation kernel may fetch past a program's end (whole
+// blocks of 64), in 16-byte units
+constexpr int64_t kCodePad = 32;
 
-__device__ __forceinline__ uint32_t ins_x(uint32_t op, uint32_t wslot, uint32_t rslot) {
-    return op | (wslot << 8) | (rslot << 16);
+// A program's header word: bit 31, it has more than one block of 64
+// instructions; bit 30, it reads features from memory, the first of which is
+// the one in the low bits (kOpReload and the fetch chain of gp_eval_code.h).
+constexpr uint32_t kHdrBlocks = 1u << 31, kHdrFetch = 1u << 30, kHdrFeature = (1u << 24) - 1u;
+
+// Word pair of instruction q: every 64th is a kOpReload.
+__device__ __forceinline__ int64_t code_pos(int64_t q) { return q + q / 63; }
+
+// How the operations of a program map to handlers for one configuration of
+// the evaluation kernel.
+struct Emit {
+    EvalOps ops;
+    int32_t R;
+    int32_t mem;        // features come from memory
+    __device__ uint32_t handler(uint32_t id) const { return id * kOpBytes; }
+    __device__ uint32_t source(bool is_c, uint32_t arg) const { return is_c ? 0u : (mem ? 1u : 1u + arg); }
+    __device__ uint32_t set(uint32_t src) const { return handler(kOpSet + src); }
+    __device__ uint32_t push(uint32_t slot, uint32_t src) const { return handler(ops.push + slot * ops.n_src + src); }
+    __device__ uint32_t fold(uint32_t op, uint32_t src) const { return handler(ops.fold + op * ops.n_src + src); }
+    __device__ uint32_t bin(uint32_t op, uint32_t slot) const {
+        return handler(ops.bin + op * (kRegSlots + 1) + slot);
+    }
+    __device__ uint32_t lds(uint32_t slot) const { return (slot - kRegSlots) * static_cast<uint32_t>(R * kWave * 4); }
+};
+
+// The interpreter's operation for binary function index fn (ADD, SUB, MUL,
+// DIV, MAX, MIN, ATAN2) with its operands as given, or exchanged.
+__device__ __forceinline__ uint32_t bin_op(uint32_t fn, bool rev) {
+    switch (fn) {
+    case 0: return kBAdd;
+    case 1: return rev ? kBSubRev : kBSub;
+    case 2: return kBMul;
+    case 3: return rev ? kBDivRev : kBDiv;
+    case 4: return kBMax;
+    case 5: return kBMin;
+    default: return rev ? kBAtan2Rev : kBAtan2;
+    }
 }
 
-// k_compile_eval: one lane per program; the same right-to-left scan as
-// k_compile, emitting the stream above.  A terminal that is a binary
-// function's first operand is fused with it; a unary function is chained
-// onto the instruction before it; a subtree of constants only is evaluated
-// here, once, by the same float32 functions the kernel applies per row, and
-// replaced by one push of its value.  User functions are expanded from
-// `ud`; loss_fn >= 0 wraps the program in the user loss (GP_OP_USER2 +
-// loss_fn) of (output, target).
-__global__ __launch_bounds__(kBlock) void k_compile_eval(PopView pop, uint4* __restrict__ code,
-                                                          int32_t* __restrict__ clen, UserDefs ud,
-                                                          int32_t loss_fn, int32_t ex_mul, int32_t ex_add) {
-    __shared__ uint32_t shadow[kCompileDepth][kBlock];   // start | const-only << 31
-    __shared__ float shadow_v[kCompileDepth][kBlock];    // value of a const-only entry
-    const int32_t p = static_cast<int32_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (p >= pop.P) return;
-    const int64_t off = pop.prog_off[p];
-    const int32_t L = pop.len[p];
-    const uint32_t* pn = pop.nodes + off;
-    const float* pc = pop.consts + pop.const_off[p];
-    uint4* out = code + off * ex_mul + static_cast<int64_t>(p) * ex_add;
-    uint32_t* sh = &shadow[0][threadIdx.x];   // entry h at sh[h * kBlock]
-    float* shv = &shadow_v[0][threadIdx.x];
+// One program by one lane, in the prefix list's own right-to-left order: for
+// programs with user functions or a user loss, and for those too long or too
+// deep for the wavefront-parallel path below.
+__device__ __forceinline__ void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, uint2* out,
+                                                uint32_t* hdr, const Emit& em, const UserDefs& ud, int32_t loss_fn,
+                                                uint32_t* sh, float* shv) {
     int h = 0;                                // entries on the stack
-    int32_t k = 0;                            // instructions emitted
-    int chain = 0;                            // unary functions chained on out[k-1]
-    const uint32_t sink = static_cast<uint32_t>(kEvalRegs);
+    int64_t k = 0;                            // instructions emitted
+    int64_t last_fetch = -1;                  // the latest feature fetch (its payload names the next)
+    uint32_t head = 0u;
     auto clampe = [](int e) { return min(max(e, 0), kCompileDepth - 1); };
-    // a push of constant v as entry e
-    auto push_c = [&](int e, float v) {
-        const uint32_t slot = static_cast<uint32_t>(max(e - 1, 0));
-        return slot >= sink ? make_uint4(ins_x(kIPushC | kIDeep, sink, slot), __float_as_uint(v), 0u, 0u)
-                            : make_uint4(ins_x(kIPushC, slot, 0u), __float_as_uint(v), 0u, 0u);
+    auto emit = [&](uint32_t handler, uint32_t payload) {
+        out[code_pos(k)] = make_uint2(handler, payload);
+        ++k;
     };
-    // a push of the value of entry src as entry e
+    // an instruction whose handler consumes the fetched feature arg
+    auto fetch = [&](uint32_t handler, uint32_t arg) {
+        if (last_fetch >= 0) out[code_pos(last_fetch)].y = arg;
+        else head |= kHdrFetch | (arg & kHdrFeature);
+        last_fetch = k;
+        emit(handler, 0xffffffffu);
+    };
+    // a terminal as entry e
+    auto push = [&](int e, bool is_c, uint32_t arg, float v) {
+        const uint32_t src = em.source(is_c, arg);
+        uint32_t handler;
+        if (e < 1) {
+            handler = em.set(src);
+        } else if (e - 1 < kRegSlots) {
+            handler = em.push(static_cast<uint32_t>(e - 1), src);
+        } else {
+            emit(em.handler(kOpSaveL), em.lds(static_cast<uint32_t>(e - 1)));
+            handler = em.set(src);
+        }
+        if (is_c) emit(handler, __float_as_uint(v));
+        else if (em.mem) fetch(handler, arg);
+        else emit(handler, 0u);
+    };
+    // a copy of entry src as entry e
     auto push_s = [&](int e, int src) {
-        const uint32_t slot = static_cast<uint32_t>(max(e - 1, 0));
-        const uint32_t rs = static_cast<uint32_t>(clampe(src));
-        return slot >= sink ? make_uint4(ins_x(kIPushS | kIDeep, sink, slot), rs, 0u, 0u)
-                            : make_uint4(ins_x(kIPushS, slot, 0u), rs, 0u, 0u);
-    };
-    auto emit = [&](uint4 ins) {
-        out[k++] = ins;
-        chain = 0;
+        if (e >= 1) {
+            if (e - 1 < kRegSlots) emit(em.handler(kOpSave + static_cast<uint32_t>(e - 1)), 0u);
+            else emit(em.handler(kOpSaveL), em.lds(static_cast<uint32_t>(e - 1)));
+        }
+        if (src == e - 1) return;             // the entry just covered
+        const uint32_t s = static_cast<uint32_t>(clampe(src));
+        if (s < static_cast<uint32_t>(kRegSlots)) emit(em.handler(kOpLoadS + s), 0u);
+        else emit(em.handler(kOpLoadTopL), em.lds(s));
     };
     // The item source: the program right to left; while a user function is
     // expanded, its definition right to left.  (i: next program position;
@@ -630,7 +662,7 @@ __global__ __launch_bounds__(kBlock) void k_compile_eval(PopView pop, uint4* __r
     bool loss_pending = loss_fn >= 0;
     if (loss_pending) {
         // entry 0: the target, under the program's value
-        emit(make_uint4(ins_x(kIPushY, 0u, 0u), 0u, 0u, 0u));
+        emit(em.handler(kOpLoadY), 0u);
         sh[0] = 0u;
         h = 1;
     }
@@ -641,8 +673,9 @@ __global__ __launch_bounds__(kBlock) void k_compile_eval(PopView pop, uint4* __r
             if (di < 0) {
                 // end of the expansion: the value replaces the arguments
                 const int base = max(call_h - call_ar, 0);
-                sh[clampe(base) * kBlock] = sh[clampe(base) * kBlock] & 0x7fffffffu;   // the deepest argument's start
+                sh[clampe(base)] = sh[clampe(base)] & 0x7fffffffu;   // the deepest argument's start
                 h = base + 1;
+                // the value is in the top's registers, as entry `base`
                 uf = -1;
                 continue;
             }
@@ -674,8 +707,8 @@ __global__ __launch_bounds__(kBlock) void k_compile_eval(PopView pop, uint4* __r
         if (in_def && op == GP_OP_VAR) {
             // argument `arg` of the function: entry call_h - 1 - arg
             const int e = clampe(h);
-            emit(push_s(e, call_h - 1 - static_cast<int>(arg)));
-            sh[e * kBlock] = static_cast<uint32_t>(k - 1);
+            sh[e] = static_cast<uint32_t>(k);
+            push_s(e, call_h - 1 - static_cast<int>(arg));
             ++h;
             --di;
             continue;
@@ -694,55 +727,46 @@ __global__ __launch_bounds__(kBlock) void k_compile_eval(PopView pop, uint4* __r
         const int ar = arity(op);
         const int top = clampe(h - 1);
         if (ar == 1) {
-            if (h >= 1 && (sh[top * kBlock] >> 31)) {
+            if (h >= 1 && (sh[top] >> 31)) {
                 // a unary function of a constant: its push (the last
                 // instruction) takes the value
-                float t[1] = {shv[top * kBlock]};
+                float t[1] = {shv[top]};
                 apply_unary<1>(unary_index(op), t, global_tabs());
-                shv[top * kBlock] = t[0];
-                if (k >= 1) out[k - 1].y = __float_as_uint(t[0]);
-            } else if (k >= 1 && chain < 8) {
-                out[k - 1].z |= (unary_index(op) + 1u) << (4 * chain);
-                ++chain;
+                shv[top] = t[0];
+                if (k >= 1) out[code_pos(k - 1)].y = __float_as_uint(t[0]);
             } else {
-                emit(make_uint4(ins_x(kIUn + unary_index(op), sink, 0u), 0u, 0u, 0u));
+                emit(em.handler(kOpUnary + unary_index(op)), 0u);
             }
             advance(1);
             continue;
         }
         if (ar == 0) {
-            const uint32_t is_c = op == GP_OP_CONST ? 1u : 0u;
+            const bool is_c = op == GP_OP_CONST;
             if (pos >= 1 && pos != last && is_builtin_binary(prev) && h >= 1) {
                 // first operand of the binary function before it; the top is the second
                 const uint32_t fn = binary_index(prev);
-                const uint32_t e2 = sh[top * kBlock];
+                const uint32_t e2 = sh[top];
                 if (is_c && (e2 >> 31)) {
                     float a[1] = {cval};
-                    const float b[1] = {shv[top * kBlock]};
+                    const float b[1] = {shv[top]};
                     apply_binary<1>(fn, a, b);
-                    k = static_cast<int32_t>(e2 & 0x7fffffffu);   // drop the operand's instructions
-                    emit(push_c(top, a[0]));
-                    sh[top * kBlock] = static_cast<uint32_t>(k - 1) | (1u << 31);
-                    shv[top * kBlock] = a[0];
+                    k = static_cast<int64_t>(e2 & 0x7fffffffu);   // drop the operand's instructions
+                    push(top, true, 0u, a[0]);
+                    shv[top] = a[0];
                 } else {
-                    emit(is_c ? make_uint4(ins_x(kIFoldC + fn, sink, 0u), __float_as_uint(cval), 0u, 0u)
-                              : make_uint4(ins_x(kIFoldX + fn, sink, 0u), arg, 0u, 0u));
-                    sh[top * kBlock] = e2 & 0x7fffffffu;
+                    const uint32_t handler = em.fold(bin_op(fn, false), em.source(is_c, arg));
+                    if (is_c) emit(handler, __float_as_uint(cval));
+                    else if (em.mem) fetch(handler, arg);
+                    else emit(handler, 0u);
+                    sh[top] = e2 & 0x7fffffffu;
                 }
                 advance(2);
                 continue;
             }
             const int e = clampe(h);
-            if (is_c) {
-                emit(push_c(e, cval));
-                sh[e * kBlock] = static_cast<uint32_t>(k - 1) | (1u << 31);
-                shv[e * kBlock] = cval;
-            } else {
-                const uint32_t slot = static_cast<uint32_t>(max(e - 1, 0));
-                emit(slot >= sink ? make_uint4(ins_x(kIPushX | kIDeep, sink, slot), arg, 0u, 0u)
-                                  : make_uint4(ins_x(kIPushX, slot, 0u), arg, 0u, 0u));
-                sh[e * kBlock] = static_cast<uint32_t>(k - 1);
-            }
+            sh[e] = static_cast<uint32_t>(k) | (is_c ? 1u << 31 : 0u);
+            shv[e] = cval;
+            push(e, is_c, arg, cval);
             ++h;
             advance(1);
             continue;
@@ -750,25 +774,312 @@ __global__ __launch_bounds__(kBlock) void k_compile_eval(PopView pop, uint4* __r
         // binary, operands not fused: the first is the top (entry h-1), the
         // second the entry below it (slot h-2)
         const int e1 = clampe(h - 1), e2 = clampe(h - 2);
-        const uint32_t first = sh[e1 * kBlock], second = sh[e2 * kBlock];
+        const uint32_t first = sh[e1], second = sh[e2];
         const uint32_t fn = binary_index(op);
         if ((first >> 31) && (second >> 31)) {
-            float a[1] = {shv[e1 * kBlock]};
-            const float b[1] = {shv[e2 * kBlock]};
+            float a[1] = {shv[e1]};
+            const float b[1] = {shv[e2]};
             apply_binary<1>(fn, a, b);
-            k = static_cast<int32_t>(second & 0x7fffffffu);
-            emit(push_c(e2, a[0]));
-            sh[e2 * kBlock] = static_cast<uint32_t>(k - 1) | (1u << 31);
-            shv[e2 * kBlock] = a[0];
+            k = static_cast<int64_t>(second & 0x7fffffffu);
+            push(e2, true, 0u, a[0]);
+            shv[e2] = a[0];
         } else {
-            const uint32_t slot = static_cast<uint32_t>(e2);
-            emit(make_uint4(ins_x(kIBin + fn | (slot >= sink ? kIDeep : 0u), sink, slot), 0u, 0u, 0u));
-            sh[e2 * kBlock] = second & 0x7fffffffu;
+            uint32_t slot = static_cast<uint32_t>(e2);
+            if (slot >= static_cast<uint32_t>(kRegSlots)) {
+                emit(em.handler(kOpLoadL), em.lds(slot));
+                slot = kRegSlots;
+            }
+            emit(em.bin(bin_op(fn, false), slot), 0u);
+            sh[e2] = second & 0x7fffffffu;
         }
         h = max(h - 1, 0);
         advance(1);
     }
-    clen[p] = k;
+    emit(em.handler(kOpEnd), 0u);
+    for (int64_t b = 63; b < code_pos(k - 1); b += 64) out[b] = make_uint2(em.handler(kOpReload), 0u);
+    if (code_pos(k - 1) >= 64) head |= kHdrBlocks;
+    *hdr = head;
+}
+
+// A wavefront's program in the parallel path, one entry per node, at most
+// kParNodes (13 KB: twelve wavefronts per CU).
+constexpr int kParNodes = 1024;
+struct ParNodes {
+    float val[kParNodes];        // value of a constant subtree; later, an instruction's feature
+    uint16_t sec[kParNodes];     // second operand of a binary function
+    uint16_t cnt[kParNodes];     // instructions of the subtree
+    uint16_t start[kParNodes];   // its first instruction
+    uint8_t op[kParNodes];
+    uint8_t ent[kParNodes];      // stack entries the subtree needs; kLeaf, kConst
+    uint8_t lev[kParNodes];      // entries below it when it is evaluated
+};
+constexpr uint8_t kEntMask = 31, kLeaf = 64, kConst = 128;
+
+// k_compile_eval: one wavefront per program.
+//   1. From the right, blocks of 64 nodes: the stack height after each node of
+//      the right-to-left scan (a suffix sum of 1 - arity).  A binary function's
+//      first operand is the node after it; its second is the nearest node to
+//      its right with its own height (the entry below its first operand came
+//      about there), found among the block's nodes by one ballot per height
+//      and beyond it from the leftmost node so far of each height, which lane
+//      `height` holds.
+//   2. From the leaves up, each block's nodes as their operands are done: the
+//      entries and instructions each subtree takes, and constant subtrees'
+//      values.
+//   3. From the root down: each evaluated subtree's first instruction and the
+//      entries below it.
+//   4. Every node writes its instruction.
+// A lane per program, scanning it node by node (as before), took 64 to 500 us:
+// every step waited for memory, and 64 programs took each other's branches,
+// the functions of constant subtrees among them.  A wavefront per program
+// takes about as many steps as the program is deep.
+__global__ __launch_bounds__(kBlock) void k_compile_eval(PopView pop, uint4* __restrict__ code,
+                                                          uint32_t* __restrict__ hdr, UserDefs ud, int32_t loss_fn,
+                                                          int32_t ex_mul, int32_t ex_add, Emit em, int32_t seq_only) {
+    __shared__ ParNodes nodes_all[kBlock / kWave];
+    __shared__ uint32_t seq_sh[kBlock / kWave][kCompileDepth];
+    __shared__ float seq_shv[kBlock / kWave][kCompileDepth];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int32_t p = static_cast<int32_t>(blockIdx.x) * (kBlock / kWave) + wid;
+    if (p >= pop.P) return;
+    const int64_t off = pop.prog_off[p];
+    const int32_t L = pop.len[p];
+    const uint32_t* pn = pop.nodes + off;
+    const float* pc = pop.consts + pop.const_off[p];
+    uint2* out = reinterpret_cast<uint2*>(code + off * ex_mul + static_cast<int64_t>(p) * ex_add);
+    ParNodes& nd = nodes_all[wid];
+    bool sequential = seq_only || L > kParNodes;
+    if (!sequential) {
+        const int nb = (L + kWave - 1) / kWave;
+        // ---- 1. heights and second operands ----
+        int carry = 0;                 // height to the right of the block
+        int lastpos = 0;               // lane h: the leftmost node so far of height h
+        for (int b = nb - 1; b >= 0; --b) {
+            const int i = b * kWave + lane;
+            const bool valid = i < L;
+            const uint32_t op = valid ? (pn[i] & 0xffu) : 0u;
+            const int ar = arity(op);
+            int hs = valid ? 1 - ar : 0;
+            for (int d = 1; d < kWave; d <<= 1) {
+                const int o = __shfl_down(hs, d, kWave);
+                if (lane + d < kWave) hs += o;
+            }
+            const int H = min(max(hs + carry, 0), 31);
+            uint64_t same = 0, mine = 0;
+            for (int hv = 1; hv <= GP_MAX_STACK; ++hv) {
+                const uint64_t m = __ballot(valid && H == hv);
+                if (H == hv) same = m;
+                if (lane == hv) mine = m;
+            }
+            const uint64_t right = lane < 63 ? same >> (lane + 1) : 0;
+            const int beyond = __shfl(lastpos, H, kWave);
+            const int sec = right ? i + 1 + __builtin_ctzll(right) : beyond;
+            if (mine) lastpos = b * kWave + __builtin_ctzll(mine);
+            carry = __builtin_amdgcn_readfirstlane(hs + carry);
+            if (valid) {
+                nd.op[i] = static_cast<uint8_t>(op);
+                nd.sec[i] = static_cast<uint16_t>(min(max(sec, 0), L - 1));   // (the clamp only guards a malformed program)
+                nd.start[i] = 0xffffu;
+            }
+        }
+        wave_lds_sync();
+        // ---- 2. entries, instructions, constants ----
+        for (int b = nb - 1; b >= 0; --b) {
+            const int i = b * kWave + lane;
+            const bool valid = i < L;
+            const uint32_t op = valid ? nd.op[i] : 0u;
+            const int ar = arity(op);
+            const int c1 = min(i + 1, L - 1), c2 = valid && ar == 2 ? nd.sec[i] : c1;
+            bool done = !valid;
+            // an operand outside the block is done
+            const uint64_t need = (ar >= 1 && c1 < (b + 1) * kWave ? 1ull << (c1 & 63) : 0ull) |
+                                  (ar == 2 && c2 < (b + 1) * kWave ? 1ull << (c2 & 63) : 0ull);
+            for (int round = 0; round <= kWave; ++round) {
+                const uint64_t ready = __ballot(done);
+                if (ready == ~0ull) break;
+                if (!done && (need & ~ready) == 0) {
+                    uint32_t ent = 1, cnt = 1;
+                    float v = 0.0f;
+                    if (ar == 0) {
+                        ent |= op == GP_OP_CONST ? kConst : kLeaf;
+                        if (op == GP_OP_CONST) v = pc[pn[i] >> 8];
+                    } else if (ar == 1) {
+                        const uint32_t e = nd.ent[c1];
+                        if (e & kConst) {
+                            float t[1] = {nd.val[c1]};
+                            apply_unary<1>(unary_index(op), t, global_tabs());
+                            v = t[0];
+                            ent = 1 | kConst;
+                        } else {
+                            ent = max(e & kEntMask, 1u);
+                            cnt = nd.cnt[c1] + 1u;
+                        }
+                    } else {
+                        const uint32_t ea = nd.ent[c1], eb = nd.ent[c2];
+                        if ((ea & kConst) && (eb & kConst)) {
+                            float a[1] = {nd.val[c1]};
+                            const float bb[1] = {nd.val[c2]};
+                            apply_binary<1>(binary_index(op), a, bb);
+                            v = a[0];
+                            ent = 1 | kConst;
+                        } else if (ea & (kLeaf | kConst)) {
+                            ent = eb & kEntMask;
+                            cnt = nd.cnt[c2] + 1u;
+                        } else if (eb & (kLeaf | kConst)) {
+                            ent = ea & kEntMask;
+                            cnt = nd.cnt[c1] + 1u;
+                        } else {
+                            const uint32_t na = ea & kEntMask, nb2 = eb & kEntMask;
+                            ent = na == nb2 ? na + 1u : max(na, nb2);
+                            cnt = nd.cnt[c1] + nd.cnt[c2] + 1u;
+                        }
+                    }
+                    nd.ent[i] = static_cast<uint8_t>(ent);
+                    nd.cnt[i] = static_cast<uint16_t>(cnt);
+                    nd.val[i] = v;
+                    done = true;
+                }
+                wave_lds_sync();
+            }
+        }
+        sequential = (nd.ent[0] & kEntMask) > kRegSlots + 1;
+    }
+    if (sequential) {
+        if (lane == 0)
+            compile_sequential(pn, pc, L, out, hdr + p, em, ud, loss_fn, seq_sh[wid], seq_shv[wid]);
+        return;
+    }
+    // ---- 3. and 4. places and instructions ----
+    const int nb = (L + kWave - 1) / kWave;
+    const int total = nd.cnt[0];
+    if (lane == 0) {
+        nd.start[0] = 0;
+        nd.lev[0] = 0;
+    }
+    wave_lds_sync();
+    for (int b = 0; b < nb; ++b) {
+        const int i = b * kWave + lane;
+        const bool valid = i < L;
+        const uint32_t op = valid ? nd.op[i] : 0u;
+        const int ar = arity(op);
+        const int c1 = min(i + 1, L - 1), c2 = valid && ar == 2 ? nd.sec[i] : c1;
+        const uint32_t ea = nd.ent[c1], eb = nd.ent[c2];
+        const bool ta = ea & (kLeaf | kConst), tb = eb & (kLeaf | kConst);
+        const bool is_c = valid && (nd.ent[min(i, L - 1)] & kConst);
+        bool done = !valid;
+        uint32_t start = 0xffffu, lev = 0;
+        // a node whose place is known gives its evaluated operands theirs; a
+        // round without a new one ends the block (the others belong to
+        // constant subtrees or are fused)
+        for (int round = 0; round <= kWave; ++round) {
+            bool fresh = false;
+            if (!done) {
+                start = nd.start[i];
+                if (start != 0xffffu) {
+                    lev = nd.lev[i];
+                    done = fresh = true;
+                    if (ar == 1 && !is_c) {
+                        nd.start[c1] = static_cast<uint16_t>(start);
+                        nd.lev[c1] = static_cast<uint8_t>(lev);
+                    } else if (ar == 2 && !is_c) {
+                        // the operand evaluated first, and (if neither is a
+                        // terminal) the one evaluated above it
+                        const bool a_first = ta ? false : (tb ? true : (ea & kEntMask) > (eb & kEntMask));
+                        const int f = a_first ? c1 : c2, s = a_first ? c2 : c1;
+                        nd.lev[f] = static_cast<uint8_t>(lev);
+                        nd.start[f] = static_cast<uint16_t>(start);
+                        if (!ta && !tb) {
+                            nd.lev[s] = static_cast<uint8_t>(lev + 1);
+                            nd.start[s] = static_cast<uint16_t>(start + nd.cnt[f]);
+                        }
+                    }
+                }
+            }
+            wave_lds_sync();
+            if (__ballot(fresh) == 0) break;
+        }
+    }
+    // features by instruction (-1: none) replace the constants' values, which
+    // each lane reads before any is overwritten
+    for (int b = 0; b < nb; ++b) {
+        const int i = b * kWave + lane;
+        const bool valid = i < L;
+        const int ii = min(i, L - 1);
+        const uint32_t start = valid ? nd.start[ii] : 0xffffu;
+        if (start == 0xffffu) continue;
+        const uint32_t op = nd.op[ii], lev = nd.lev[ii], me = nd.ent[ii];
+        const int ar = arity(op);
+        const int64_t pos = code_pos(start + nd.cnt[ii] - 1);
+        uint32_t handler, payload = 0u;
+        if (me & (kLeaf | kConst)) {
+            const bool is_c = me & kConst;
+            const uint32_t arg = is_c ? 0u : pn[ii] >> 8;
+            const uint32_t src = em.source(is_c, arg);
+            handler = lev == 0 ? em.set(src) : em.push(lev - 1, src);
+            payload = is_c ? __float_as_uint(nd.val[ii]) : arg;
+        } else if (ar == 1) {
+            handler = em.handler(kOpUnary + unary_index(op));
+        } else {
+            const int c1 = ii + 1, c2 = nd.sec[ii];
+            const uint32_t ea = nd.ent[c1], eb = nd.ent[c2];
+            const bool ta = ea & (kLeaf | kConst), tb = eb & (kLeaf | kConst);
+            const uint32_t fn = binary_index(op);
+            if (ta || tb) {
+                // terminal (op) top, or top (op) terminal
+                const int c = ta ? c1 : c2;
+                const bool is_c = (ta ? ea : eb) & kConst;
+                const uint32_t arg = is_c ? 0u : pn[c] >> 8;
+                handler = em.fold(bin_op(fn, !ta), em.source(is_c, arg));
+                payload = is_c ? __float_as_uint(nd.val[c]) : arg;
+            } else {
+                // the second operand evaluated first, the first on top of it; or exchanged
+                const bool a_first = (ea & kEntMask) > (eb & kEntMask);
+                handler = em.bin(bin_op(fn, a_first), lev);
+            }
+        }
+        out[pos] = make_uint2(handler, payload);
+    }
+    const int64_t end = code_pos(total);
+    if (lane == 0) out[end] = make_uint2(em.handler(kOpEnd), 0u);
+    for (int64_t r = 63 + 64 * static_cast<int64_t>(lane); r < end; r += 64 * kWave)
+        out[r] = make_uint2(em.handler(kOpReload), 0u);
+    uint32_t head = end >= 64 ? kHdrBlocks : 0u;
+    if (em.mem) {
+        // the fetch chain: each instruction that consumes a feature names the
+        // next one's, found from the last instruction back
+        wave_lds_sync();
+        uint32_t* feat = reinterpret_cast<uint32_t*>(nd.val);
+        for (int q = lane; q < total; q += kWave) feat[q] = 0xffffffffu;
+        wave_lds_sync();
+        for (int b = 0; b < nb; ++b) {
+            const int i = b * kWave + lane;
+            if (i >= L || nd.start[i] == 0xffffu) continue;
+            const uint32_t op = nd.op[i], me = nd.ent[i];
+            const int q = nd.start[i] + nd.cnt[i] - 1;
+            if (me & kLeaf) {
+                feat[q] = pn[i] >> 8;
+            } else if (!(me & kConst) && arity(op) == 2) {
+                const int c1 = i + 1, c2 = nd.sec[i];
+                const uint32_t ea = nd.ent[c1], eb = nd.ent[c2];
+                if (ea & kLeaf) feat[q] = pn[c1] >> 8;
+                else if (!(ea & kConst) && (eb & kLeaf)) feat[q] = pn[c2] >> 8;
+            }
+        }
+        wave_lds_sync();
+        uint32_t next = 0xffffffffu;
+        for (int q0 = (total - 1) & ~63; q0 >= 0; q0 -= kWave) {
+            const int q = q0 + lane;
+            const uint32_t f = q < total ? feat[q] : 0xffffffffu;
+            const uint64_t m = __ballot(f != 0xffffffffu);
+            const uint64_t right = lane < 63 ? m >> (lane + 1) : 0;
+            const uint32_t fr = __shfl(f, right ? lane + 1 + __builtin_ctzll(right) : lane, kWave);
+            if (f != 0xffffffffu) out[code_pos(q)].y = right ? fr : next;
+            if (m) next = __shfl(f, __builtin_ctzll(m), kWave);
+        }
+        if (next != 0xffffffffu) head |= kHdrFetch | (next & kHdrFeature);
+    }
+    if (lane == 0) hdr[p] = head;
 }
 
 // ---------------------------------------------------------------------------
@@ -786,34 +1097,39 @@ __global__ void k_zero_u32(uint32_t* __restrict__ p) { p[0] = 0u; }
 
 // ---------------------------------------------------------------------------
 // k_prepare: order programs by length (longest first) and reset the work
-// counter.  One block; counting sort over min(len, kBins-1).
+// counter.  One block; counting sort over min(len, kBins-1), one bin per
+// thread in the scan.
 // ---------------------------------------------------------------------------
 constexpr int kBins = 1024;
 
-__global__ __launch_bounds__(1024) void k_prepare(const int32_t* __restrict__ len, int32_t P,
+__global__ __launch_bounds__(kBins) void k_prepare(const int32_t* __restrict__ len, int32_t P,
                                                    int32_t* __restrict__ order,
                                                    uint32_t* __restrict__ counter) {
     __shared__ int32_t start[kBins];
-    const int tid = threadIdx.x;
-    for (int b = tid; b < kBins; b += blockDim.x) start[b] = 0;
+    __shared__ int32_t wtot[kBins / kWave];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid >> 6;
+    start[tid] = 0;
+    if (tid < kQueues) counter[tid * kQueueStride] = 0u;
     __syncthreads();
     // key: kBins-1 - min(len, kBins-1), so longer programs come first
-    for (int p = tid; p < P; p += blockDim.x) {
+    for (int p = tid; p < P; p += kBins) {
         const int key = kBins - 1 - min(max(len[p], 0), kBins - 1);
         atomicAdd(&start[key], 1);
     }
     __syncthreads();
-    if (tid == 0) {
-        int32_t run = 0;
-        for (int b = 0; b < kBins; ++b) {
-            const int32_t c = start[b];
-            start[b] = run;
-            run += c;
-        }
-        for (int q = 0; q < kQueues; ++q) counter[q * kQueueStride] = 0u;
+    const int32_t c = start[tid];
+    int32_t v = c;
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int32_t o = __shfl_up(v, d, kWave);
+        if (lane >= d) v += o;
     }
+    if (lane == kWave - 1) wtot[wid] = v;
     __syncthreads();
-    for (int p = tid; p < P; p += blockDim.x) {
+    int32_t before = 0;
+    for (int q = 0; q < kBins / kWave; ++q) before += q < wid ? wtot[q] : 0;
+    start[tid] = before + v - c;
+    __syncthreads();
+    for (int p = tid; p < P; p += kBins) {
         const int key = kBins - 1 - min(max(len[p], 0), kBins - 1);
         order[atomicAdd(&start[key], 1)] = p;
     }
@@ -863,7 +1179,9 @@ __global__ __launch_bounds__(kBlock) void k_ystats(DataView d, int64_t chunk, in
 //   MODE 1: accumulate the metric's float64 row sums per (program, chunk)
 //           into part[(p * n_chunks + c) * KK + k]     (gp_fitness)
 // R rows per lane; FREG > 0 keeps the tile's F <= FREG feature values in
-// registers, FREG == 0 reads a feature from memory at each terminal.
+// registers, FREG == 0 fetches each feature from memory where the program
+// uses it, one use ahead.  The program itself runs in the interpreter of
+// gp_eval_asm.h.
 // ---------------------------------------------------------------------------
 template <int METRIC>
 struct MetricTraits {
@@ -871,30 +1189,96 @@ struct MetricTraits {
     static constexpr int KK = (METRIC == GP_METRIC_PEARSON) ? 4 : 1;  // doubles per partial
 };
 
-// Row-slot helpers of the evaluation kernel: the R per-row copies of a
-// register array are separate plain locals (GP_ARRAYS), indexed by a
-// wave-uniform slot.
 #define GP_ROWS(stmt)                  \
     _Pragma("unroll") for (int j = 0; j < R; ++j) { stmt; }
 
+// Element j of an interpreter register group (a vector, or one value).
+template <typename V>
+__device__ __forceinline__ auto ev_get(const V& v, int j) {
+    if constexpr (std::is_arithmetic_v<V>) return v;
+    else return v[j];
+}
+template <typename V, typename T>
+__device__ __forceinline__ void ev_set(V& v, int j, T x) {
+    if constexpr (std::is_arithmetic_v<V>) v = x;
+    else v[j] = x;
+}
+// One row of an operation the interpreter leaves to its caller (one row at a
+// time: the function library's temporaries for all the rows at once would
+// take the kernel past an occupancy step).
+__device__ __forceinline__ float leave_row(uint32_t code, float t0, float m0, const unsigned char* lds) {
+    const MathTabsLds& tabs = *reinterpret_cast<const MathTabsLds*>(lds);
+    const MathTabs mt{tabs.sc, tabs.lg};
+    float t[1] = {t0};
+    float m[1] = {m0};
+    if (code < kExitMax) {
+        apply_unary<1>(code - 1u, t, mt);
+    } else if (code == kExitMax) {
+        apply_binary_wide<1>(4, t, m);
+    } else if (code == kExitMin) {
+        apply_binary_wide<1>(5, t, m);
+    } else if (code == kExitAtan2TM) {
+        apply_binary_wide<1>(6, t, m);
+    } else {
+        apply_binary_wide<1>(6, m, t);
+        t[0] = m[0];
+    }
+    return t[0];
+}
+
+// LDS: the function tables (at offset 0, where the interpreter expects them),
+// then s.lds_slots * R * 64 stack words per wavefront (dynamic, sized at launch:
+// kEvalLds slots, or kEvalLdsUser when user functions may be expanded).
+// Wavefronts per SIMD asked of the compiler: what the interpreter's own
+// registers leave room for.
+constexpr int eval_waves(int R, int freg) {
+    return R == 1 ? (freg == 8 ? 6 : 7) : R == 2 ? (freg == 8 ? 4 : 5) : (freg == 8 ? 3 : 4);
+}
+
 template <int R, int FREG, int MODE, int METRIC>
-__global__ __launch_bounds__(kBlock) void k_eval(PopView pop, CodeView cv, DataView d, Sched s,
+__global__ __launch_bounds__(kBlock, eval_waves(R, FREG)) void k_eval(PopView pop, CodeView cv, DataView d, Sched s,
                                                   float* __restrict__ out,
                                                   double* __restrict__ part) {
     constexpr int K = MetricTraits<METRIC>::K;
     constexpr int KK = MetricTraits<METRIC>::KK;
-    constexpr int FA = FREG > 0 ? FREG : 1;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t N = d.N;
     const int64_t ld = d.ld;
     const float* __restrict__ X = d.X;
-    // stack slots beyond the registers: s.lds_slots * R * 64 floats per
-    // wavefront of the block (dynamic LDS, sized at launch: kEvalLds, or
-    // kEvalLdsUser when user functions may be expanded)
-    extern __shared__ float ovf_all[];
-    float* ovf = ovf_all + (threadIdx.x >> 6) * (s.lds_slots * R * kWave) + lane;
-    __shared__ MathTabsLds tabs_lds;
-    const MathTabs mt = stage_tabs(tabs_lds);
+    extern __shared__ __align__(16) unsigned char lds_all[];
+    stage_tabs(*reinterpret_cast<MathTabsLds*>(lds_all));
+
+    Interp<R, FREG> in;
+    in.c0 = EvVec<uint32_t, 16>{};
+    {
+        const double c[8] = {crm::kInvPi128, crm::kPi128a, crm::kPi128b, crm::kS5, crm::kC4, crm::kL2, crm::kL3, crm::kL5};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint64_t u = crm::dbits(c[q]);
+            in.c0[2 * q] = static_cast<uint32_t>(u);
+            in.c0[2 * q + 1] = static_cast<uint32_t>(u >> 32);
+        }
+        const uint64_t ln2 = crm::dbits(crm::kLn2), c375 = crm::dbits(0.375);
+        in.c1 = EvVec<uint32_t, 8>{static_cast<uint32_t>(ln2), static_cast<uint32_t>(ln2 >> 32),
+                                   static_cast<uint32_t>(c375), static_cast<uint32_t>(c375 >> 32),
+                                   crm::fbits(GP_PROTECT_EPS), 0x7fffffu, 0x240u, 4u};
+        const double k[5] = {crm::kRound, crm::kRoundCos, crm::kS3, crm::kC2, crm::kL4};
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            const uint64_t u = crm::dbits(k[q]);
+            const float lo = crm::bitsf(static_cast<uint32_t>(u)), hi = crm::bitsf(static_cast<uint32_t>(u >> 32));
+            if (q < 4) {
+                in.k0[2 * q] = lo;
+                in.k0[2 * q + 1] = hi;
+            } else {
+                in.k1[0] = lo;
+                in.k1[1] = hi;
+            }
+        }
+    }
+    in.lds = static_cast<uint32_t>(sizeof(MathTabsLds)) +
+             (threadIdx.x >> 6) * static_cast<uint32_t>(s.lds_slots * R * kWave * 4) + lane * 4u;
+    if constexpr (FREG == 0) in.ld4 = static_cast<uint64_t>(ld) * 4u;
 
     // Work items: one queue per XCD.  Queue x holds the chunks c with
     // c % kQueues == x, chunk-major, each chunk's programs in LPT order
@@ -904,216 +1288,152 @@ __global__ __launch_bounds__(kBlock) void k_eval(PopView pop, CodeView cv, DataV
     // has run dry takes items from the next ones, and leaves once all are
     // dry.  A claim takes s.batch consecutive items.
     const int q0 = static_cast<int>(blockIdx.x % kQueues);
+    const uint32_t P = static_cast<uint32_t>(pop.P);
     for (int qi = 0; qi < kQueues;) {
         const int qx = (q0 + qi) % kQueues;
-        const int64_t q_items = (static_cast<int64_t>(s.n_chunks) - qx + kQueues - 1) / kQueues * pop.P;
+        // (items stay below 2^31: n_items is at most 2^30)
+        const uint32_t q_items = (static_cast<uint32_t>(s.n_chunks) - qx + kQueues - 1) / kQueues * P;
         uint32_t it32 = 0;
         if (lane == 0) it32 = atomicAdd(s.counter + qx * kQueueStride, static_cast<uint32_t>(s.batch));
-        const int64_t it0 = static_cast<int64_t>(
-            static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(it32))));
+        const uint32_t it0 = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(it32)));
         if (it0 >= q_items) {   // this queue is dry: the next one
             ++qi;
             continue;
         }
-        const int64_t it1 = min(it0 + static_cast<int64_t>(s.batch), q_items);
-        for (int64_t it = it0; it < it1; ++it) {
-        const int32_t cq = static_cast<int32_t>(it / pop.P);
-        const int32_t k = static_cast<int32_t>(it - static_cast<int64_t>(cq) * pop.P);
-        const int32_t c = cq * kQueues + qx;
-        const int32_t p = ldu(s.order + k);
-        const int64_t off = ldu(pop.prog_off + p);
-        const int32_t CL = ldu(cv.eclen + p);
-        const uint4* __restrict__ pcode = cv.ecode + off * cv.ex_mul + static_cast<int64_t>(p) * cv.ex_add;
-        const int64_t r0 = static_cast<int64_t>(c) * s.chunk;
-        const int64_t r1 = min(r0 + s.chunk, N);
-
-        double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
-        double shift = 0.0, yshift = 0.0;
-        if constexpr (METRIC == GP_METRIC_PEARSON) yshift = static_cast<double>(d.y[r0]);
-        bool first_tile = true;
-
-        for (int64_t base = r0; base < r1; base += kWave * R) {
-            int64_t row[R];
-            bool valid[R];
-#pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const int64_t r = base + j * kWave + lane;
-                valid[j] = r < r1;
-                row[j] = valid[j] ? r : r1 - 1;
+        const uint32_t it1 = min(it0 + static_cast<uint32_t>(s.batch), q_items);
+        uint32_t cq = it0 / P, k = it0 - cq * P;
+        for (uint32_t it = it0; it < it1; ++it) {
+            const int32_t c = static_cast<int32_t>(cq) * kQueues + qx;
+            const int32_t p = ldu(s.order + k);
+            if (++k == P) {
+                k = 0;
+                ++cq;
             }
-            // feature tile in registers (one array per row slot)
-            GP_ARRAYS(xa, FA);
-            if constexpr (FREG > 0) {
+            const int64_t off = ldu(pop.prog_off + p);
+            const uint32_t head = ldu(cv.ehdr + p);
+            const uint4* __restrict__ pcode = cv.ecode + off * cv.ex_mul + static_cast<int64_t>(p) * cv.ex_add;
+            in.ins = reinterpret_cast<const EvVec<uint32_t, 2>*>(pcode)[lane];
+            const int64_t r0 = static_cast<int64_t>(c) * s.chunk;
+            const int64_t r1 = min(r0 + s.chunk, N);
+
+            double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
+            double shift = 0.0, yshift = 0.0;
+            if constexpr (METRIC == GP_METRIC_PEARSON) yshift = static_cast<double>(d.y[r0]);
+            bool first_tile = true;
+
+            for (int64_t base = r0; base < r1; base += kWave * R) {
+                // byte offset of row j * 64 + lane; rows past the chunk's end
+                // repeat its last one
+                const int left = static_cast<int>(min<int64_t>(r1 - base, kWave * R));
+                auto row_off = [left](int ln, int j) {
+                    return static_cast<uint32_t>(min(j * kWave + ln, left - 1)) * 4u;
+                };
+                auto at = [](const float* col, uint32_t o) {
+                    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(col) + o);
+                };
+                if constexpr (FREG > 0) {
 #pragma unroll
-                for (int f = 0; f < FREG; ++f) {
-                    if (f < d.F) {
-                        xa0[f] = X[f * ld + row[0]];
-                        if constexpr (R > 1) xa1[f] = X[f * ld + row[1]];
-                        if constexpr (R > 2) xa2[f] = X[f * ld + row[2]];
-                        if constexpr (R > 3) xa3[f] = X[f * ld + row[3]];
+                    for (int f = 0; f < FREG; ++f)
+                        if (f < d.F) {
+                            const float* __restrict__ col = X + f * ld + base;
+                            GP_ROWS(in.x0[f * R + j] = at(col, row_off(lane, j)));
+                        }
+                } else {
+                    in.xb = reinterpret_cast<uint64_t>(X + base);
+                    GP_ROWS(ev_set(in.off, j, row_off(lane, j)));
+                    if (head & kHdrFetch) {
+                        const float* __restrict__ col = X + static_cast<int64_t>(head & kHdrFeature) * ld + base;
+                        GP_ROWS(ev_set(in.p, j, at(col, row_off(lane, j))));
                     }
                 }
-            }
+                if constexpr (METRIC == GP_METRIC_USER_0) GP_ROWS(ev_set(in.t, j, at(d.y + base, row_off(lane, j))));
+                const uint64_t blk = reinterpret_cast<uint64_t>(pcode);
+                in.blk0 = static_cast<uint32_t>(blk);
+                in.blk1 = static_cast<uint32_t>(blk >> 32);
+                if ((head & kHdrBlocks) && !first_tile) in.ins = reinterpret_cast<const EvVec<uint32_t, 2>*>(pcode)[lane];
+                in.idx = 0;
+                uint32_t code;
+                while ((code = in.run()) != kExitEnd)
+                    GP_ROWS(ev_set(in.t, j, leave_row(code, ev_get(in.t, j), ev_get(in.m, j), lds_all)));
+                float t[R];
+                GP_ROWS(t[j] = ev_get(in.t, j));
+                // (row offsets and targets are formed here again rather than held
+                // across the program: their registers would cost an occupancy step)
+                int ln = lane;
+                asm volatile("" : "+v"(ln));
+                bool valid[R];
+                GP_ROWS(valid[j] = j * kWave + ln < left);
 
-            // ---- the stack machine (Sec. III-A order, compiled by k_compile_eval) ----
-            // t[] is the top entry; entry e below it is slot e (VGPRs below
-            // kEvalRegs, LDS from there on).  Each instruction first stores the
-            // top into its store slot (the sink unless it pushes), so the
-            // register array has one indexed write per instruction and is
-            // never copied; every case then updates t[] in place.  The next
-            // instruction is fetched one ahead by a vector load (in order
-            // with the others, so its wait covers only the older loads; a
-            // scalar load is waited for with every other one) and made
-            // scalar where it is used.
-            float t[R];
-            GP_ROWS(t[j] = 0.0f);
-            GP_ARRAYS(st, kEvalRegs + 1);
-            uint4 nxt = pcode[0];
-            for (int q = 0; q < CL; ++q) {
-                const uint4 cur = nxt;
-                nxt = pcode[q + 1];
-                const uint32_t cx = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(cur.x)));
-                const uint32_t cy = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(cur.y)));
-                const uint32_t cz = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(cur.z)));
-                const uint32_t op = cx & 0xffu;
-                const uint32_t wslot = (cx >> 8) & 0xffu;
-                const uint32_t rslot = cx >> 16;
-                GP_PUT(st, wslot, t);
-                float v[R];   // a terminal's value
-                // the feature cy (for kIPushX / kIFoldX)
-#define GP_FEATURE()                                                          \
-    do {                                                                      \
-        if constexpr (FREG > 0) {                                             \
-            v[0] = xa0[cy];                                                   \
-            if constexpr (R > 1) v[1] = xa1[cy];                              \
-            if constexpr (R > 2) v[2] = xa2[cy];                              \
-            if constexpr (R > 3) v[3] = xa3[cy];                              \
-        } else {                                                              \
-            const float* __restrict__ col = X + static_cast<int64_t>(cy) * ld; \
-            GP_ROWS(v[j] = col[row[j]]);                                      \
-        }                                                                     \
-    } while (0)
-#define GP_BIN_CASES(BASE, LOAD)                                                        \
-    case (BASE) + 0: { LOAD; GP_ROWS(t[j] = A0 + B0); } break;                          \
-    case (BASE) + 1: { LOAD; GP_ROWS(t[j] = A0 - B0); } break;                          \
-    case (BASE) + 2: { LOAD; GP_ROWS(t[j] = A0 * B0); } break;                          \
-    case (BASE) + 3: { LOAD; GP_ROWS(t[j] = op_div(A0, B0)); } break;                   \
-    case (BASE) + 4: case (BASE) + 5: case (BASE) + 6: {                                    \
-        LOAD; float a_[R], b_[R]; GP_ROWS(a_[j] = A0; b_[j] = B0);                    \
-        apply_binary_wide<R>(op - (BASE), a_, b_); GP_ROWS(t[j] = a_[j]);             \
-    } break;
-                switch (op) {
-                case kIPushX: GP_FEATURE(); GP_ROWS(t[j] = v[j]); break;
-                case kIPushC: {
-                    const float cval = __uint_as_float(cy);
-                    GP_ROWS(t[j] = cval);
-                } break;
-                case kIPushX | kIDeep: {
-                    GP_FEATURE();
-                    GP_ROWS(ovf[((rslot - kEvalRegs) * R + j) * kWave] = t[j]);
-                    GP_ROWS(t[j] = v[j]);
-                } break;
-                case kIPushC | kIDeep: {
-                    const float cval = __uint_as_float(cy);
-                    GP_ROWS(ovf[((rslot - kEvalRegs) * R + j) * kWave] = t[j]);
-                    GP_ROWS(t[j] = cval);
-                } break;
-                case kIPushS:
-                case kIPushS | kIDeep: {
-                    // (the covered entry is stored first: a copy of the
-                    // entry just covered reads it back)
-                    if (op & kIDeep) GP_ROWS(ovf[((rslot - kEvalRegs) * R + j) * kWave] = t[j]);
-                    if (cy < static_cast<uint32_t>(kEvalRegs)) {
-                        GP_GET(st, cy, v);
+                if constexpr (MODE == 0) {
+                    float* __restrict__ o = out + static_cast<int64_t>(p) * N + base;
+#pragma unroll
+                    for (int j = 0; j < R; ++j)
+                        if (valid[j]) o[j * kWave + ln] = t[j];
+                } else {
+                    float yv4[R], wv4[R];
+                    GP_ROWS(yv4[j] = at(d.y + base, row_off(ln, j)));
+                    if (d.w) {
+                        GP_ROWS(wv4[j] = at(d.w + base, row_off(ln, j)));
                     } else {
-                        GP_ROWS(v[j] = ovf[((cy - kEvalRegs) * R + j) * kWave]);
+                        GP_ROWS(wv4[j] = 1.0f);
                     }
-                    GP_ROWS(t[j] = v[j]);
-                } break;
-                case kIPushY: GP_ROWS(t[j] = d.y[row[j]]); break;
-#define A0 t[j]
-#define B0 v[j]
-                GP_BIN_CASES(kIBin, GP_GET(st, rslot, v))
-                GP_BIN_CASES(kIBin | kIDeep, GP_ROWS(v[j] = ovf[((rslot - kEvalRegs) * R + j) * kWave]))
-#undef A0
-#undef B0
-#define A0 v[j]
-#define B0 t[j]
-                GP_BIN_CASES(kIFoldX, GP_FEATURE())
-                GP_BIN_CASES(kIFoldC, const float cval = __uint_as_float(cy); GP_ROWS(v[j] = cval))
-#undef A0
-#undef B0
-                default: apply_unary<R>(op - kIUn, t, mt); break;
-                }
-                // the unary functions chained on this instruction
-                for (uint32_t ch = cz; ch != 0u; ch >>= 4) apply_unary<R>((ch & 15u) - 1u, t, mt);
-#undef GP_BIN_CASES
-#undef GP_FEATURE
-            }
-
-            if constexpr (MODE == 0) {
-                float* __restrict__ o = out + static_cast<int64_t>(p) * N;
+                    if constexpr (METRIC == GP_METRIC_PEARSON) {
+                        if (first_tile) shift = static_cast<double>(__shfl(t[0], 0, kWave));
+                    }
 #pragma unroll
-                for (int j = 0; j < R; ++j)
-                    if (valid[j]) o[row[j]] = t[j];
-            } else {
-                if constexpr (METRIC == GP_METRIC_PEARSON) {
-                    if (first_tile) shift = static_cast<double>(__shfl(t[0], 0, kWave));
+                    for (int j = 0; j < R; ++j) {
+                        const float yv = yv4[j];
+                        const double wv = static_cast<double>(wv4[j]);
+                        if constexpr (METRIC == GP_METRIC_MSE || METRIC == GP_METRIC_RMSE) {
+                            const double e = static_cast<double>(t[j]) - static_cast<double>(yv);
+                            const double l = e * e;
+                            const double term = wv * l;
+                            acc0 += valid[j] ? term : 0.0;
+                        } else if constexpr (METRIC == GP_METRIC_MAE) {
+                            const double e = static_cast<double>(t[j]) - static_cast<double>(yv);
+                            const double term = wv * fabs(e);
+                            acc0 += valid[j] ? term : 0.0;
+                        } else if constexpr (METRIC == GP_METRIC_USER_0) {
+                            // a user loss: the stream already ends in the row loss
+                            (void)yv;
+                            const double term = wv * static_cast<double>(t[j]);
+                            acc0 += valid[j] ? term : 0.0;
+                        } else if constexpr (METRIC == GP_METRIC_LOGLOSS) {
+                            const float z = t[j];
+                            const float t1 = fmaxf(z, 0.0f);
+                            const float t2 = yv * z;
+                            const float t3 = t1 - t2;
+                            const float t5 = log1pf(expf(-fabsf(z)));
+                            const double term = wv * static_cast<double>(t3 + t5);
+                            acc0 += valid[j] ? term : 0.0;
+                        } else {  // PEARSON: shifted first and second moments
+                            const double a = static_cast<double>(t[j]) - shift;
+                            const double bb = static_cast<double>(yv) - yshift;
+                            const double wa = wv * a;
+                            acc0 += valid[j] ? wa : 0.0;
+                            acc1 += valid[j] ? wa * a : 0.0;
+                            acc2 += valid[j] ? wa * bb : 0.0;
+                        }
+                    }
                 }
                 first_tile = false;
-#pragma unroll
-                for (int j = 0; j < R; ++j) {
-                    const float yv = d.y[row[j]];
-                    const double wv = d.w ? static_cast<double>(d.w[row[j]]) : 1.0;
-                    if constexpr (METRIC == GP_METRIC_MSE || METRIC == GP_METRIC_RMSE) {
-                        const double e = static_cast<double>(t[j]) - static_cast<double>(yv);
-                        const double l = e * e;
-                        const double term = wv * l;
-                        acc0 += valid[j] ? term : 0.0;
-                    } else if constexpr (METRIC == GP_METRIC_MAE) {
-                        const double e = static_cast<double>(t[j]) - static_cast<double>(yv);
-                        const double term = wv * fabs(e);
-                        acc0 += valid[j] ? term : 0.0;
-                    } else if constexpr (METRIC == GP_METRIC_USER_0) {
-                        // a user loss: the stream already ends in the row loss
-                        (void)yv;
-                        const double term = wv * static_cast<double>(t[j]);
-                        acc0 += valid[j] ? term : 0.0;
-                    } else if constexpr (METRIC == GP_METRIC_LOGLOSS) {
-                        const float z = t[j];
-                        const float t1 = fmaxf(z, 0.0f);
-                        const float t2 = yv * z;
-                        const float t3 = t1 - t2;
-                        const float t5 = log1pf(expf(-fabsf(z)));
-                        const double term = wv * static_cast<double>(t3 + t5);
-                        acc0 += valid[j] ? term : 0.0;
-                    } else {  // PEARSON: shifted first and second moments
-                        const double a = static_cast<double>(t[j]) - shift;
-                        const double bb = static_cast<double>(yv) - yshift;
-                        const double wa = wv * a;
-                        acc0 += valid[j] ? wa : 0.0;
-                        acc1 += valid[j] ? wa * a : 0.0;
-                        acc2 += valid[j] ? wa * bb : 0.0;
+            }
+            if constexpr (MODE == 1) {
+                acc0 = wave_sum(acc0);
+                if constexpr (K > 1) {
+                    acc1 = wave_sum(acc1);
+                    acc2 = wave_sum(acc2);
+                }
+                if (lane == 0) {
+                    double* dst = part + (static_cast<int64_t>(p) * s.n_chunks + c) * KK;
+                    dst[0] = acc0;
+                    if constexpr (K > 1) {
+                        dst[1] = acc1;
+                        dst[2] = acc2;
+                        dst[3] = shift;
                     }
                 }
             }
-        }
-        if constexpr (MODE == 1) {
-            acc0 = wave_sum(acc0);
-            if constexpr (K > 1) {
-                acc1 = wave_sum(acc1);
-                acc2 = wave_sum(acc2);
-            }
-            if (lane == 0) {
-                double* dst = part + (static_cast<int64_t>(p) * s.n_chunks + c) * KK;
-                dst[0] = acc0;
-                if constexpr (K > 1) {
-                    dst[1] = acc1;
-                    dst[2] = acc2;
-                    dst[3] = shift;
-                }
-            }
-        }
         }
     }
 }
@@ -1248,14 +1568,6 @@ constexpr int kGradLds = 16;            // constants per program summed in a fix
 constexpr int kAdjWaves = 4;
 template <int R>
 constexpr int tape_lds_bytes() { return R == 4 ? 15360 : 12288; }
-
-// Orders a wavefront's own LDS writes before its later LDS reads (its LDS
-// operations complete in order; this only keeps the compiler from moving them).
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // tape entries an instruction records (0, 1 or 2)
 __device__ __forceinline__ int tape_entries(uint32_t cls, uint32_t fn) {
@@ -2326,8 +2638,8 @@ struct DeviceScratch {
     size_t clen_cap = 0;
     uint4* ecode = nullptr;      // the evaluation kernel's instruction stream
     size_t ecode_cap = 0;
-    int32_t* eclen = nullptr;
-    size_t eclen_cap = 0;
+    uint32_t* ehdr = nullptr;    // its programs' headers
+    size_t ehdr_cap = 0;
     double* stats = nullptr;     // per-program statistics (kStats doubles each)
     size_t stats_cap = 0;
     double* gpart = nullptr;     // gradient partials
@@ -2411,7 +2723,7 @@ gp_status scratch_init(DeviceScratch& s, int dev) {
 }
 
 bool scratch_empty(const DeviceScratch& s) {
-    return !s.counter && !s.order && !s.part && !s.ystat && !s.code && !s.clen && !s.ecode && !s.eclen &&
+    return !s.counter && !s.order && !s.part && !s.ystat && !s.code && !s.clen && !s.ecode && !s.ehdr &&
            !s.stats && !s.gpart &&
            !s.gextra && !s.tape && !s.fit_tmp && !s.sp_k0 && !s.sp_k1 && !s.sp_v0 && !s.sp_v1 &&
            !s.sp_rs && !s.sp_cnt && !s.sp_r2y && !s.sp_nan && !s.sp_ty;
@@ -2421,7 +2733,7 @@ bool scratch_empty(const DeviceScratch& s) {
 void scratch_free(DeviceScratch& s) {
     for (void* q : {s.counter, static_cast<void*>(s.order), static_cast<void*>(s.part),
                     static_cast<void*>(s.ystat), static_cast<void*>(s.code), static_cast<void*>(s.clen),
-                    static_cast<void*>(s.ecode), static_cast<void*>(s.eclen),
+                    static_cast<void*>(s.ecode), static_cast<void*>(s.ehdr),
                     static_cast<void*>(s.stats), static_cast<void*>(s.gpart), static_cast<void*>(s.gextra),
                     static_cast<void*>(s.tape), static_cast<void*>(s.fit_tmp),
                     static_cast<void*>(s.sp_k0), static_cast<void*>(s.sp_k1), static_cast<void*>(s.sp_v0),
@@ -2569,7 +2881,7 @@ gp_status launch_eval_m(const LaunchCfg& cfg, int n_cu, const PopView& pv, const
                         const DataView& dv, const Sched& s, float* out, double* part, hipStream_t st,
                         int64_t node_rows, const Timing& tm) {
     const int block = cfg.wpb * kWave;
-    const size_t lds = static_cast<size_t>(cfg.wpb) * s.lds_slots * cfg.R * kWave * sizeof(float);
+    const size_t lds = sizeof(MathTabsLds) + static_cast<size_t>(cfg.wpb) * s.lds_slots * cfg.R * kWave * sizeof(float);
     auto go = [&](auto kernel) -> gp_status {
         int per_cu = 0;
         GP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, lds));
@@ -2680,11 +2992,14 @@ gp_status reserve(DeviceScratch* sc, int32_t P, int64_t total_nodes, int64_t n_c
         rc = need(&sc->clen, &sc->clen_cap, P, sizeof(int32_t));
         if (rc != GP_OK) return rc;
     }
-    // (+1: the evaluation kernel fetches one instruction past a program's end)
+    // (the evaluation kernel fetches whole blocks of instructions, past a
+    // program's end; in a fixed scratch other buffers follow)
     rc = need(&sc->ecode, &sc->ecode_cap,
-              static_cast<size_t>(total_nodes) * ex_mul + static_cast<size_t>(P) * ex_add + 1, sizeof(uint4));
+              static_cast<size_t>(total_nodes) * ex_mul + static_cast<size_t>(P) * ex_add +
+                  static_cast<size_t>(sc->fixed ? 1 : kCodePad),
+              sizeof(uint4));
     if (rc != GP_OK) return rc;
-    rc = need(&sc->eclen, &sc->eclen_cap, P, sizeof(int32_t));
+    rc = need(&sc->ehdr, &sc->ehdr_cap, P, sizeof(uint32_t));
     if (rc != GP_OK) return rc;
     if (mode == 1) {
         const size_t kk = metric == GP_METRIC_PEARSON ? 4 : 1;
@@ -2735,13 +3050,15 @@ gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_data
     const int32_t batch = static_cast<int32_t>(std::min<int64_t>(8, std::max<int64_t>(1, n_items / claims)));
     *sch = Sched{chunk, static_cast<int32_t>(n_chunks), n_items, sc->order, static_cast<uint32_t*>(sc->counter),
                  batch, xp.lds_slots};
-    hipLaunchKernelGGL(k_prepare, dim3(1), dim3(1024), 0, st, pop->len, pop->n_programs, sc->order,
+    hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kBins), 0, st, pop->len, pop->n_programs, sc->order,
                        static_cast<uint32_t*>(sc->counter));
     GP_HIP(hipGetLastError());
     const dim3 cgrid((pop->n_programs + kBlock - 1) / kBlock);
     if (!adjoint || both) {
-        hipLaunchKernelGGL(k_compile_eval, cgrid, dim3(kBlock), 0, st, *pv, sc->ecode, sc->eclen, xp.defs,
-                           xp.loss_fn, xp.mul, xp.add);
+        const dim3 egrid((pop->n_programs + kBlock / kWave - 1) / (kBlock / kWave));
+        const Emit em{eval_ops(cfg->freg), cfg->R, cfg->freg == 0};
+        hipLaunchKernelGGL(k_compile_eval, egrid, dim3(kBlock), 0, st, *pv, sc->ecode, sc->ehdr, xp.defs,
+                           xp.loss_fn, xp.mul, xp.add, em, xp.lds_slots == kEvalLdsUser);
         GP_HIP(hipGetLastError());
     }
     if (adjoint) {
@@ -2749,7 +3066,7 @@ gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_data
         GP_HIP(hipGetLastError());
     }
     *cvw = CodeView{adjoint ? sc->code : nullptr, adjoint ? sc->clen : nullptr,
-                    (!adjoint || both) ? sc->ecode : nullptr, (!adjoint || both) ? sc->eclen : nullptr, xp.mul,
+                    (!adjoint || both) ? sc->ecode : nullptr, (!adjoint || both) ? sc->ehdr : nullptr, xp.mul,
                     xp.add};
     return GP_OK;
 }
@@ -2836,10 +3153,12 @@ gp_status noalloc_carve(unsigned char* base, DeviceScratch* sc, int32_t P, int64
     sc->counter = take(kCounterBytes);
     sc->order = reinterpret_cast<int32_t*>(take(static_cast<size_t>(P) * sizeof(int32_t)));
     sc->order_cap = static_cast<size_t>(P);
-    sc->eclen = reinterpret_cast<int32_t*>(take(static_cast<size_t>(P) * sizeof(int32_t)));
-    sc->eclen_cap = static_cast<size_t>(P);
+    sc->ehdr = reinterpret_cast<uint32_t*>(take(static_cast<size_t>(P) * sizeof(uint32_t)));
+    sc->ehdr_cap = static_cast<size_t>(P);
     sc->ecode = reinterpret_cast<uint4*>(take(n_code * sizeof(uint4)));
     sc->ecode_cap = n_code;
+    // (whole blocks of instructions are fetched, up to 504 bytes past the
+    // stream's end: the two buffers after it, at least 256 bytes each, cover that)
     sc->part = reinterpret_cast<double*>(take(n_part * sizeof(double)));
     sc->part_cap = n_part;
     sc->ystat = reinterpret_cast<double*>(take(n_ystat * sizeof(double)));
@@ -4190,7 +4509,7 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
                                sc->ystat, sch.n_chunks, P, data->n_rows, has_w, fit, sc->stats);
         GP_HIP(hipGetLastError());
         // the forward pass consumed the work counter: reset it (and reorder)
-        hipLaunchKernelGGL(k_prepare, dim3(1), dim3(1024), 0, st, pop->len, P, sc->order,
+        hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kBins), 0, st, pop->len, P, sc->order,
                            static_cast<uint32_t*>(sc->counter));
         GP_HIP(hipGetLastError());
     }
