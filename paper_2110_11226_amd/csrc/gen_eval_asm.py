@@ -55,7 +55,7 @@ class Gen:
     J, N0, N1, B, P, IDX, BLK, XC, T59, A, XB = 48, 50, 51, 52, 54, 55, 56, 58, 59, 60, 62
     INV, PA, PB, S5, C4, L2, L3, L5 = 64, 66, 68, 70, 72, 74, 76, 78
     LN2, C375, EPS, MASK, CLS, FOUR = 80, 82, 84, 85, 86, 87
-    LD, Q0, Q1, Q2 = 88, 90, 92, 94
+    LD, Q0, Q1, Q2, LDS = 88, 90, 92, 94, 47
 
     def __init__(self, R, freg):
         self.R, self.freg = R, freg
@@ -75,7 +75,6 @@ class Gen:
         self.x = take(freg * R) if freg else None
         self.off = take(R) if self.mem else None
         self.p = take(R) if self.mem else None
-        self.lds = take(1)
         self.nb = min(R, 2)
         self.tmp = take(12 * self.nb)
         self.end = v
@@ -253,6 +252,11 @@ class Gen:
         self.o(f"s_addc_u32 s{self.A + 1}, s{self.A + 1}, s{self.XB + 1}")
         self.rows(lambda j: f"global_load_dword v{self.p + j}, v{self.off + j}, s[{self.A}:{self.A + 1}]")
         self.label(f"np{n}")
+
+    def lane(self, a):
+        """This lane's index into v[a]."""
+        self.o(f"v_mbcnt_lo_u32_b32 v{a}, -1, 0")
+        self.o(f"v_mbcnt_hi_u32_b32 v{a}, -1, v{a}")
 
     def batches(self):
         return [list(range(a, min(a + self.nb, self.R))) for a in range(0, self.R, self.nb)]
@@ -433,7 +437,9 @@ class Gen:
         for name, ins in (("savel", "ds_write_b32 v{a}, {t} offset:{o}"), ("ldt", "ds_read_b32 {t}, v{a} offset:{o}"),
                           ("ldb", "ds_read_b32 {m}, v{a} offset:{o}")):
             self.label(name)
-            self.o(f"v_add_u32 v{a}, s{self.P}, v{self.lds}")
+            self.lane(a)
+            self.o(f"s_add_u32 s{self.T59}, s{self.P}, s{self.LDS}")
+            self.o(f"v_lshl_add_u32 v{a}, v{a}, 2, s{self.T59}")
             self.rows(lambda j: ins.format(a=a, t=self.T(j), m=self.M(j), o=256 * j))
             if name != "savel":
                 self.o("s_waitcnt lgkmcnt(0)")
@@ -461,8 +467,7 @@ class Gen:
         self.label("reload")
         self.o(f"s_add_u32 s{self.BLK}, s{self.BLK}, 512")
         self.o(f"s_addc_u32 s{self.BLK + 1}, s{self.BLK + 1}, 0")
-        self.o(f"v_mbcnt_lo_u32_b32 v{a}, -1, 0")
-        self.o(f"v_mbcnt_hi_u32_b32 v{a}, -1, v{a}")
+        self.lane(a)
         self.o(f"v_lshlrev_b32 v{a}, 3, v{a}")
         self.o(f"global_load_dwordx2 v[{self.i}:{self.i + 1}], v{a}, s[{self.BLK}:{self.BLK + 1}]")
         self.o(f"s_mov_b32 s{self.IDX}, 0")
@@ -516,7 +521,7 @@ def emit_function(R, freg):
         members.append((f"s{q}", at, n))
         at += n
     outs = members + [("m", g.tmp, R)]
-    ins = [("k0", g.k, 8), ("k1", g.k + 8, 2), ("lds", g.lds, 1)]
+    ins = [("k0", g.k, 8), ("k1", g.k + 8, 2)]
     if freg:
         at = g.x
         for q, n in enumerate(pieces(freg * R)):
@@ -532,12 +537,13 @@ def emit_function(R, freg):
     w.append(f"struct Interp<{R}, {freg}> {{")
     w.append(f"    // v{g.base} .. v{g.end - 1}")
     for name, first, n in outs + ins:
-        ty = "uint32_t" if name == "lds" or name == "off" and n == 1 else \
+        ty = "uint32_t" if name == "off" and n == 1 else \
             (f"EvVec<uint32_t, {n}>" if name == "off" else vec(n))
         w.append(f"    {ty} {name};")
     w.append("    EvVec<uint32_t, 2> ins;      // lane i: instruction i of the block")
     w.append("    uint32_t idx;                // next instruction of the block")
     w.append("    uint32_t blk0, blk1;         // address of the block")
+    w.append("    uint32_t lds;                // LDS address of the wavefront's stack slots")
     w.append("    uint64_t xb, ld4;            // feature 0 of the tile's first row; bytes between features")
     w.append("    EvVec<uint32_t, 16> c0;      // scalar constants")
     w.append("    EvVec<uint32_t, 8> c1;")
@@ -549,7 +555,7 @@ def emit_function(R, freg):
     w.append("            : " + ", ".join(f'"+{vr(f, n)}"({nm})' for nm, f, n in outs) + ",")
     w.append(f'              "+{{v[{g.i}:{g.i + 1}]}}"(ins), "+{{s{g.IDX}}}"(idx), "+{{s{g.BLK}}}"(blk0), "+{{s{g.BLK + 1}}}"(blk1), "={{s{g.XC}}}"(code)')
     w.append("            : " + ", ".join(f'"{vr(f, n)}"({nm})' for nm, f, n in ins) + ",")
-    w.append(f'              "{{s[64:79]}}"(c0), "{{s[80:87]}}"(c1)' +
+    w.append(f'              "{{s[64:79]}}"(c0), "{{s[80:87]}}"(c1), "{{s{g.LDS}}}"(lds)' +
              (f', "{{s[{g.XB}:{g.XB + 1}]}}"(xb), "{{s[{g.LD}:{g.LD + 1}]}}"(ld4)' if not freg else ""))
     clob = ["vcc", "scc", "memory"]
     clob += [f"s{q}" for q in (48, 49, 50, 51, 52, 53, 54, 59, 60, 61, 90, 91, 92, 93, 94, 95)]

@@ -94,8 +94,10 @@ struct Sched {
     int64_t n_items;
     const int32_t* order;
     uint32_t* counter;
-    int32_t batch;     // work items claimed per atomic by the evaluation kernel
+    int32_t batch;     // work items per claim
     int32_t lds_slots; // stack slots per row in LDS (kEvalLds or kEvalLdsUser)
+    int32_t blocks;    // the launch's blocks, and wavefronts per block
+    int32_t wpb;
 };
 
 // ---------------------------------------------------------------------------
@@ -158,6 +160,83 @@ GP_HD uint32_t enc(uint32_t cls, uint32_t fn, uint32_t is_const, uint32_t arg) {
 template <typename T>
 __device__ __forceinline__ T ldu(const T* p) {
     return *(const __attribute__((address_space(4))) T*)p;
+}
+
+// A wavefront's claims of work items, `batch` consecutive items each.  One
+// queue per XCD: queue x holds the chunks c with c % kQueues == x, chunk-major,
+// each chunk's programs in LPT order (longest first), so that a chunk's rows
+// are read into one L2 while every program walks them.  Blocks are dealt to
+// the XCDs in turn, so a block starts on queue blockIdx.x % kQueues.
+// Every wavefront's first claim is its own by position, and the counters
+// count only the claims after those: a job of at most one claim per wavefront
+// touches no counter (with every claim an atomic, 4,096 rows x 256 programs
+// spent 150 of its 180 us on 70 thousand of them, most from wavefronts finding
+// all eight queues dry one after the other).  A wavefront whose queue has run
+// dry reads all the counters at once to find one that has not.
+struct Claims {
+    uint32_t* counter;
+    uint32_t P, n_chunks, batch, blocks, wpb;
+    uint32_t index;                    // this wavefront among its queue's
+    int q0, q;
+    bool first;
+    __device__ Claims(const Sched& s, uint32_t programs, uint32_t wid)
+        : counter(s.counter), P(programs), n_chunks(static_cast<uint32_t>(s.n_chunks)),
+          batch(static_cast<uint32_t>(s.batch)), blocks(static_cast<uint32_t>(s.blocks)),
+          wpb(static_cast<uint32_t>(s.wpb)), index(blockIdx.x / kQueues * static_cast<uint32_t>(s.wpb) + wid), q0(static_cast<int>(blockIdx.x % kQueues)), q(q0),
+          first(true) {}
+    // (items stay below 2^31: n_items is at most 2^30)
+    __device__ uint32_t items(uint32_t x) const { return (n_chunks - x + kQueues - 1) / kQueues * P; }
+    // items covered by the first claims of queue x's wavefronts
+    __device__ uint32_t given(uint32_t x) const {
+        return (blocks - x + kQueues - 1) / kQueues * wpb * batch;
+    }
+    // The next claim: queue *qx, items [*it0, *it1).  False once all are dry.
+    __device__ bool next(int lane, int* qx, uint32_t* it0, uint32_t* it1) {
+        if (first) {
+            first = false;
+            const uint32_t n = items(static_cast<uint32_t>(q)), i = index * batch;
+            if (i < n) {
+                *qx = q;
+                *it0 = i;
+                *it1 = min(i + batch, n);
+                return true;
+            }
+        }
+        for (;;) {
+            const uint32_t n = items(static_cast<uint32_t>(q)), g = given(static_cast<uint32_t>(q));
+            if (g < n) {
+                uint32_t c = 0;
+                if (lane == 0) c = atomicAdd(counter + q * kQueueStride, batch);
+                const uint32_t i = g + static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(c)));
+                if (i < n) {
+                    *qx = q;
+                    *it0 = i;
+                    *it1 = min(i + batch, n);
+                    return true;
+                }
+            }
+            // dry: the next queue, from q0 on, that still has items
+            // (formed from the lane here: hoisted, it would hold registers
+            // throughout the caller's loops)
+            bool left = false;
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            if (ln < kQueues) {
+                const uint32_t x = static_cast<uint32_t>((q0 + ln) % kQueues);
+                const uint32_t nx = items(x), gx = given(x);
+                left = gx < nx && gx + __hip_atomic_load(counter + x * kQueueStride, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT) < nx;
+            }
+            const uint64_t m = __ballot(left);
+            if (m == 0) return false;
+            q = (q0 + __builtin_ctzll(m)) % kQueues;
+        }
+    }
+};
+
+// A wave-uniform value the compiler cannot see is one.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
 }
 
 // Orders a wavefront's own LDS writes before its later LDS reads (its LDS
@@ -1276,31 +1355,18 @@ __global__ __launch_bounds__(kBlock, eval_waves(R, FREG)) void k_eval(PopView po
             }
         }
     }
-    in.lds = static_cast<uint32_t>(sizeof(MathTabsLds)) +
-             (threadIdx.x >> 6) * static_cast<uint32_t>(s.lds_slots * R * kWave * 4) + lane * 4u;
+    const uint32_t wid = uniform(threadIdx.x >> 6);
+    in.lds = static_cast<uint32_t>(sizeof(MathTabsLds)) + wid * static_cast<uint32_t>(s.lds_slots * R * kWave * 4);
     if constexpr (FREG == 0) in.ld4 = static_cast<uint64_t>(ld) * 4u;
 
-    // Work items: one queue per XCD.  Queue x holds the chunks c with
-    // c % kQueues == x, chunk-major, each chunk's programs in LPT order
-    // (longest first), so that a chunk's rows are read into one L2 while
-    // every program walks them.  Blocks are dealt to the XCDs in turn, so
-    // a block starts on queue blockIdx.x % kQueues; a wavefront whose queue
-    // has run dry takes items from the next ones, and leaves once all are
-    // dry.  A claim takes s.batch consecutive items.
-    const int q0 = static_cast<int>(blockIdx.x % kQueues);
     const uint32_t P = static_cast<uint32_t>(pop.P);
-    for (int qi = 0; qi < kQueues;) {
-        const int qx = (q0 + qi) % kQueues;
-        // (items stay below 2^31: n_items is at most 2^30)
-        const uint32_t q_items = (static_cast<uint32_t>(s.n_chunks) - qx + kQueues - 1) / kQueues * P;
-        uint32_t it32 = 0;
-        if (lane == 0) it32 = atomicAdd(s.counter + qx * kQueueStride, static_cast<uint32_t>(s.batch));
-        const uint32_t it0 = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(it32)));
-        if (it0 >= q_items) {   // this queue is dry: the next one
-            ++qi;
-            continue;
-        }
-        const uint32_t it1 = min(it0 + static_cast<uint32_t>(s.batch), q_items);
+    Claims claims(s, P, wid);
+    int qx;
+    uint32_t it0, it1;
+    while (claims.next(lane, &qx, &it0, &it1)) {
+        it0 = uniform(it0);
+        it1 = uniform(it1);
+        qx = static_cast<int>(uniform(static_cast<uint32_t>(qx)));
         uint32_t cq = it0 / P, k = it0 - cq * P;
         for (uint32_t it = it0; it < it1; ++it) {
             const int32_t c = static_cast<int32_t>(cq) * kQueues + qx;
@@ -1317,8 +1383,8 @@ __global__ __launch_bounds__(kBlock, eval_waves(R, FREG)) void k_eval(PopView po
             const int64_t r1 = min(r0 + s.chunk, N);
 
             double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
-            double shift = 0.0, yshift = 0.0;
-            if constexpr (METRIC == GP_METRIC_PEARSON) yshift = static_cast<double>(d.y[r0]);
+            float shift = 0.0f, yshift = 0.0f;     // (scalar registers)
+            if constexpr (METRIC == GP_METRIC_PEARSON) yshift = ldu(d.y + r0);
             bool first_tile = true;
 
             for (int64_t base = r0; base < r1; base += kWave * R) {
@@ -1378,7 +1444,7 @@ __global__ __launch_bounds__(kBlock, eval_waves(R, FREG)) void k_eval(PopView po
                         GP_ROWS(wv4[j] = 1.0f);
                     }
                     if constexpr (METRIC == GP_METRIC_PEARSON) {
-                        if (first_tile) shift = static_cast<double>(__shfl(t[0], 0, kWave));
+                        if (first_tile) shift = __uint_as_float(uniform(__float_as_uint(t[0])));
                     }
 #pragma unroll
                     for (int j = 0; j < R; ++j) {
@@ -1407,8 +1473,8 @@ __global__ __launch_bounds__(kBlock, eval_waves(R, FREG)) void k_eval(PopView po
                             const double term = wv * static_cast<double>(t3 + t5);
                             acc0 += valid[j] ? term : 0.0;
                         } else {  // PEARSON: shifted first and second moments
-                            const double a = static_cast<double>(t[j]) - shift;
-                            const double bb = static_cast<double>(yv) - yshift;
+                            const double a = static_cast<double>(t[j]) - static_cast<double>(shift);
+                            const double bb = static_cast<double>(yv) - static_cast<double>(yshift);
                             const double wa = wv * a;
                             acc0 += valid[j] ? wa : 0.0;
                             acc1 += valid[j] ? wa * a : 0.0;
@@ -1430,7 +1496,7 @@ __global__ __launch_bounds__(kBlock, eval_waves(R, FREG)) void k_eval(PopView po
                     if constexpr (K > 1) {
                         dst[1] = acc1;
                         dst[2] = acc2;
-                        dst[3] = shift;
+                        dst[3] = static_cast<double>(shift);
                     }
                 }
             }
@@ -1697,27 +1763,14 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint(PopView pop, Code
     };
 
     // work items: the evaluation kernel's per-XCD queues, one item per claim
-    const int q0 = static_cast<int>(blockIdx.x % kQueues);
-    int qi = 0;
-    for (;;) {
-        int64_t it = -1;
-        int qx = q0;
-        while (qi < kQueues) {
-            qx = (q0 + qi) % kQueues;
-            const int64_t q_items = (static_cast<int64_t>(s.n_chunks) - qx + kQueues - 1) / kQueues * pop.P;
-            uint32_t it32 = 0;
-            if (lane == 0) it32 = atomicAdd(s.counter + qx * kQueueStride, 1u);
-            const int64_t cand = static_cast<int64_t>(
-                static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(it32), 0)));
-            if (cand < q_items) {
-                it = cand;
-                break;
-            }
-            ++qi;   // this queue is dry
-        }
-        if (it < 0) break;   // every queue is dry
-        const int32_t cq = static_cast<int32_t>(it / pop.P);
-        const int32_t k = static_cast<int32_t>(it - static_cast<int64_t>(cq) * pop.P);
+    Claims claims(s, static_cast<uint32_t>(pop.P), static_cast<uint32_t>(wid));
+    int qx;
+    uint32_t it, it_end;
+    while (claims.next(lane, &qx, &it, &it_end)) {
+        it = uniform(it);
+        qx = static_cast<int>(uniform(static_cast<uint32_t>(qx)));
+        const int32_t cq = static_cast<int32_t>(it / static_cast<uint32_t>(pop.P));
+        const int32_t k = static_cast<int32_t>(it) - cq * pop.P;
         const int32_t c = cq * kQueues + qx;
         const int32_t p = ldu(s.order + k);
         const int64_t off = ldu(pop.prog_off + p);
@@ -2838,25 +2891,40 @@ std::map<TuneKey, TuneVal> g_tuned;
 
 LaunchCfg heuristic_cfg(int F, int64_t N, int32_t P, int n_cu) {
     LaunchCfg c;
-    c.R = 4;
+    // four rows per lane amortise an instruction's fetch and jump best (1M rows
+    // x 1,000 programs: 3.3 ms, 3.9 with two, 5.1 with one), and at 256
+    // programs x 4,096 rows too (26 us against 28 and 32); fewer only where
+    // the rows do not fill them
+    c.R = N > 2 * kWave ? 4 : N > kWave ? 2 : 1;
     c.wpb = 4;
-    // features in registers only for F <= 2: eight of them cost a wavefront of
-    // occupancy at 4 rows per lane, which measures slower than reading them
+    // features in registers only for F <= 2: eight of them cost a wavefront per
+    // SIMD at 4 rows per lane, which fetching them one use ahead does not
+    // (equal for the nine-function set, 3.5 ms against 4.0 for all 21)
     c.freg = F <= 2 ? 2 : 0;
-    // a small job (fewer single-tile items than 8 per SIMD at 4 rows per
-    // lane) takes one row per lane: four times the items, each a quarter as
-    // long, so that the chip fills
-    const int64_t tiles4 = (N + kWave * 4 - 1) / (kWave * 4);
-    if (tiles4 * static_cast<int64_t>(P) < static_cast<int64_t>(n_cu) * 4 * 8) c.R = 1;
     const int64_t tile_rows = static_cast<int64_t>(kWave) * c.R;
     const int64_t n_tiles = (N + tile_rows - 1) / tile_rows;
-    // aim for >= 32 work items per resident wavefront, chunks of <= 64 tiles
-    const int64_t target_items = static_cast<int64_t>(n_cu) * 16 * 32;
+    // about 10 items per resident wavefront, of at most 16 tiles: longer items
+    // leave the last ones alone (1M x 1,000: 3.26 ms at 16 tiles, 3.36 at 32,
+    // 3.65 at 64), shorter ones pay each item's claim and start (65,536 rows x
+    // 1,024 short programs: 246 us at 8 tiles, 281 at 4, 428 at 2)
+    const int64_t target_items = static_cast<int64_t>(n_cu) * 16 * 10;
     int64_t want_chunks = std::max<int64_t>(1, (target_items + P - 1) / std::max<int32_t>(P, 1));
     want_chunks = std::min(want_chunks, n_tiles);
     int64_t tiles = (n_tiles + want_chunks - 1) / want_chunks;
-    tiles = std::min<int64_t>(std::max<int64_t>(tiles, 1), 64);
-    c.tiles = static_cast<int>(tiles);
+    tiles = std::min<int64_t>(std::max<int64_t>(tiles, 1), 16);
+    // the chunks are dealt to the XCDs' queues in turn: of the sizes from half
+    // to a quarter more, the one that leaves the least of a last round empty,
+    // the nearest of those (65,536 rows x 1,024: 37 chunks 287 us, 32 chunks 246)
+    auto waste = [&](int64_t t) {
+        const int64_t nc = (n_tiles + t - 1) / t;
+        return static_cast<double>((nc + kQueues - 1) / kQueues * kQueues) / static_cast<double>(nc);
+    };
+    int64_t best = tiles;
+    for (int64_t t = std::max<int64_t>(1, tiles / 2); t <= std::min<int64_t>(16, tiles + tiles / 4); ++t)
+        if (waste(t) < waste(best) - 0.005 ||
+            (waste(t) < waste(best) + 0.005 && std::abs(t - tiles) < std::abs(best - tiles)))
+            best = t;
+    c.tiles = static_cast<int>(best);
     return c;
 }
 
@@ -2899,7 +2967,10 @@ gp_status launch_eval_m(const LaunchCfg& cfg, int n_cu, const PopView& pv, const
         }
         if (tm.launched) *tm.launched = reinterpret_cast<const void*>(kernel);
         if (tm.stamp) hipLaunchKernelGGL(k_stamp, dim3(1), dim3(kWave), 0, st, tm.stamp);
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(block), lds, st, pv, cv, dv, s, out,
+        Sched sl = s;
+        sl.blocks = static_cast<int32_t>(blocks);
+        sl.wpb = cfg.wpb;
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(block), lds, st, pv, cv, dv, sl, out,
                            part);
         GP_HIP(hipGetLastError());
         if (tm.stamp) {
@@ -3043,13 +3114,16 @@ gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_data
     const ExpandPlan xp = expand_plan(mode, metric);
     rc = reserve(sc, pop->n_programs, pop->total_nodes, n_chunks, mode, metric, adjoint, xp.mul, xp.add);
     if (rc != GP_OK) return rc;
-    // items claimed per atomic: enough that a launch issues about 32 claims
-    // per resident wavefront (16 per CU), at most 8
+    // items per claim: single ones up to 64 a resident wavefront (16 per CU).
+    // A claim costs its queue about 25 ns, but consecutive items are programs of
+    // like length, and a wavefront that claims several of the longest holds up
+    // the rest (1M rows x 1,000 programs, 62 items a wavefront: 3.26 ms with
+    // single claims, 3.9 with seven items each)
     const int64_t n_items = n_chunks * pop->n_programs;
     const int64_t claims = static_cast<int64_t>(sc->n_cu) * 16 * 32;
     const int32_t batch = static_cast<int32_t>(std::min<int64_t>(8, std::max<int64_t>(1, n_items / claims)));
     *sch = Sched{chunk, static_cast<int32_t>(n_chunks), n_items, sc->order, static_cast<uint32_t*>(sc->counter),
-                 batch, xp.lds_slots};
+                 batch, xp.lds_slots, 0, 0};
     hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kBins), 0, st, pop->len, pop->n_programs, sc->order,
                        static_cast<uint32_t*>(sc->counter));
     GP_HIP(hipGetLastError());
@@ -4537,7 +4611,11 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
         gp_status r2 = grow(reinterpret_cast<void**>(&sc->tape), &sc->tape_cap,
                             static_cast<size_t>(blocks) * kAdjWaves * static_cast<size_t>(wave_floats), sizeof(float));
         if (r2 != GP_OK) return r2;
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kAdjWaves * kWave), 0, st, pv, cvw, dv, sch,
+        Sched sl = sch;
+        sl.batch = 1;
+        sl.blocks = static_cast<int32_t>(blocks);
+        sl.wpb = kAdjWaves;
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kAdjWaves * kWave), 0, st, pv, cvw, dv, sl,
                            needs_forward ? sc->stats : nullptr, wsum, grad_fitness, lossp, sc->gpart, sc->gextra,
                            sc->tape, wave_floats);
         GP_HIP(hipGetLastError());

@@ -143,3 +143,34 @@ def test_inputs_left_to_the_caller(gp):
         progs += [([N(6)] * n + [N(u), N(oracle.VAR, 0)], []) for u in un]
         progs += [([N(u)] + [N(6)] * n + [N(oracle.VAR, 0)], []) for u in un]
     check(gp, progs, x)
+
+
+@pytest.mark.parametrize("P,n,cfg", [(1, 100_003, (1, 2, 1, 4)), (5000, 70, (1, 2, 1, 1)), (9, 4357, (4, 2, 1, 4)),
+                                     (700, 20_011, (1, 2, 1, 4)), (3000, 2100, (1, 2, 1, 2)), (8, 2049, (4, 2, 64, 4))])
+def test_work_claims(gp, P, n, cfg):
+    """Fewer items than wavefronts, one chunk in one queue, more items than first
+    claims cover, several items a claim: every item done once."""
+    import torch
+    host = gp.build_population(P, 2, "rhh", min_depth=1, max_depth=3, seed=P)
+    X = rows(2, n, P)
+    y = np.random.default_rng(1).normal(size=n).astype(np.float32)
+    gp.set_launch_config(cfg)
+    try:
+        pop, data = gp.DevicePopulation(host, n_features=2), gp.DeviceDataset(X, y)
+        out = gp.evaluate(pop, data)
+        fit = [gp.fitness(pop, data, "mse").clone() for _ in range(2)]
+        torch.cuda.synchronize()
+    finally:
+        gp.set_launch_config(None)
+    op = oracle.Population(host.nodes, host.prog_off, host.consts, host.const_off, host.length)
+    ref = oracle.evaluate_f32(op, X, n_threads=NT)
+    got = out.cpu().numpy()
+    same = (got.view(np.uint32) == ref.view(np.uint32)) | (np.isnan(got) & np.isnan(ref))
+    assert same.all()
+    assert torch.equal(fit[0], fit[1])
+    with np.errstate(over="ignore", invalid="ignore"):
+        want = ((ref.astype(np.float64) - y) ** 2).mean(axis=1).astype(np.float32)
+    g = fit[0].cpu().numpy()
+    fin = np.isfinite(want)
+    assert np.array_equal(np.isfinite(g), fin)
+    assert np.allclose(g[fin], want[fin], rtol=1e-6, atol=0)
