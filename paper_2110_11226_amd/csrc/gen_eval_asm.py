@@ -1,5 +1,7 @@
 """Writes gp_eval_asm.h: the evaluation kernel's interpreter as gfx950 assembly,
-one inline-assembly block per (rows per lane R, feature registers FREG).
+one inline-assembly block per (rows per lane R, feature registers FREG), and the
+adjoint's, one per R (AdjGen: the same instructions, those that record and apply
+partial derivatives, and those that sum a constant's).
 
 The block walks one compiled program (gp_eval_code.h) over one tile of 64 R
 rows with threaded dispatch: every instruction word holds its handler's byte
@@ -287,10 +289,12 @@ class Gen:
         self.o(f"s_cbranch_scc1 .Lrare_{name}_%=")
         self.rare_exits.append((name, code))
 
-    def sincos(self, name, rnd):
-        self.label(name)
+    def sincos(self, name, rnd, deriv=None):
+        """t = sin t or cos t; with `deriv`, its label, u = the derivative too."""
+        self.label(deriv or name)
         self.o(f"s_mov_b32 s{self.T59}, 0x4b800000")
-        self.rare(name, 1 + UNARY.index(name.upper()),
+        u = UNARY.index(name.upper())
+        self.rare(deriv or name, EXIT_ADJ_UN + u if deriv else 1 + u,
                   lambda j: f"v_cmp_ge_f32_e64 {{q}}, |{self.T(j)}|, s{self.T59}")
         for rows in self.batches():
             lists = []
@@ -314,8 +318,11 @@ class Gen:
                     f"v_mul_f64 {P(0)}, {P(0)}, {P(4)}",
                     f"s_waitcnt lgkmcnt({len(rows) - 1 - b})",
                     f"v_mul_f64 {P(4)}, {P(8)}, {P(6)}",
+                    f"v_mul_f64 {P(6)}, {P(10)}, {P(6)}" if deriv else "",
                     f"v_fma_f64 {P(4)}, {P(10)}, {P(0)}, {P(4)}",
-                    f"v_cvt_f32_f64 {self.T(j)}, {P(4)}"])
+                    f"v_fma_f64 {P(6)}, -{P(8)}, {P(0)}, {P(6)}" if deriv else "",
+                    f"v_cvt_f32_f64 {self.T(j)}, {P(4)}",
+                    f"v_cvt_f32_f64 {self.U(j)}, {P(6)}" if deriv else ""])
             self.interleave(lists)
         self.he()
 
@@ -570,6 +577,286 @@ def emit_function(R, freg):
     return w
 
 
+# ---------------------------------------------------------------------------
+# The adjoint kernel's interpreter: the same table, then the instructions of
+# reverse mode.  The forward part of a program records partial derivatives on
+# a tape whose first TAPE entries are registers (written and read by handlers
+# of their own: no address, no latency), the next TAPE_LDS lie in LDS and the
+# rest in a per-wavefront memory area.  The reverse part carries the adjoint
+# in the top's registers; slots hold the adjoints still to be carried back.
+# ---------------------------------------------------------------------------
+TAPE = 26
+TAPE_LDS = 16
+ACC = 8             # constants whose adjoints are summed in registers
+ADJ_TAPE = ["PUTT", "PUTM", "PUTU", "GMUL", "MMUL"]
+ADJ_ONE = ["SETMC", "SETMF", "MOVMT", "NEGMT", "MOVUT", "DINVM", "DINVT", "DNEGT", "DNEGM", "DSQRT", "SIND", "COSD", "CADDX"]
+ADJ_BIN = ["MAXT", "MAXM", "MINT", "MINM", "ATTM", "ATMT"]
+EXIT_ADJ_UN, EXIT_ADJ_BIN, EXIT_CADD = 64, 96, 112
+
+
+def adj_sections():
+    base = sections(0)["count"]
+    sec = {}
+    at = base
+    for name, n in ([(t, TAPE) for t in ADJ_TAPE] + [(t + "L", 1) for t in ADJ_TAPE] + [(t + "G", 1) for t in ADJ_TAPE] +
+                    [("LOADM", SLOTS), ("SAVEM", SLOTS)] + [(t, 1) for t in ADJ_ONE] + [("CADD", ACC)] +
+                    [("UNX", len(UNARY)), ("BINX", len(ADJ_BIN))]):
+        sec[name] = at
+        at += n
+    sec["count"] = at
+    return sec
+
+
+class AdjGen(Gen):
+    VM, GB = 36, 44     # row masks (R pairs); the wavefront's memory area
+
+    def __init__(self, R):
+        super().__init__(R, 0)
+        v = self.end
+
+        def take(n):
+            nonlocal v
+            r = v
+            v += n + (n & 1)
+            return r
+        self.u = take(R)
+        self.acc = take(2 * ACC)
+        self.tape = take(TAPE * R)
+        self.end = v
+        self.adj = adj_sections()
+
+    def U(self, j):
+        return f"v{self.u + j}"
+
+    def E(self, e, j):
+        return f"v{self.tape + e * self.R + j}"
+
+    def table(self):
+        super().table()
+        h = self.sec["count"]
+        a = self.adj
+
+        def begin(want):
+            nonlocal h
+            assert h == want, (h, want)
+            self.handler(h)
+            self.hb()
+            h += 1
+        on = {"PUTT": lambda j, e: f"v_mov_b32 {e}, {self.T(j)}", "PUTM": lambda j, e: f"v_mov_b32 {e}, {self.M(j)}",
+              "PUTU": lambda j, e: f"v_mov_b32 {e}, {self.U(j)}",
+              "GMUL": lambda j, e: f"v_mul_f32 {self.T(j)}, {self.T(j)}, {e}",
+              "MMUL": lambda j, e: f"v_mul_f32 {self.M(j)}, {self.T(j)}, {e}"}
+        for name in ADJ_TAPE:
+            for e in range(TAPE):
+                begin(a[name] + e)
+                self.rows(lambda j: on[name](j, self.E(e, j)))
+                self.he()
+        for tier in "LG":
+            for name in ADJ_TAPE:
+                begin(a[name + tier])
+                self.br(name.lower() + tier.lower())
+        for k in range(SLOTS):
+            begin(a["LOADM"] + k)
+            self.rows(lambda j: f"v_mov_b32 {self.M(j)}, {self.S(k, j)}")
+            self.he()
+        for k in range(SLOTS):
+            begin(a["SAVEM"] + k)
+            self.rows(lambda j: f"v_mov_b32 {self.S(k, j)}, {self.M(j)}")
+            self.he()
+        for name in ADJ_ONE:
+            begin(a[name])
+            if name == "SETMC":
+                self.rows(lambda j: f"v_mov_b32 {self.M(j)}, s{self.P}")
+                self.he()
+            elif name == "SETMF":
+                self.o("s_waitcnt vmcnt(0)")
+                self.rows(lambda j: f"v_mov_b32 {self.M(j)}, v{self.p + j}")
+                self.br("mnext")
+            elif name == "MOVMT":
+                self.rows(lambda j: f"v_mov_b32 {self.M(j)}, {self.T(j)}")
+                self.he()
+            elif name == "MOVUT":
+                self.rows(lambda j: f"v_mov_b32 {self.U(j)}, {self.T(j)}")
+                self.he()
+            elif name == "CADDX":
+                self.o(f"s_mov_b32 s{self.XC}, {EXIT_CADD}")
+                self.br("leave")
+            else:
+                self.br(name.lower())
+        for k in range(ACC):
+            begin(a["CADD"] + k)
+            self.br(f"cadd{k}")
+        for u in range(len(UNARY)):
+            begin(a["UNX"] + u)
+            self.o(f"s_mov_b32 s{self.XC}, {EXIT_ADJ_UN + u}")
+            self.br("leave")
+        for q in range(len(ADJ_BIN)):
+            begin(a["BINX"] + q)
+            self.o(f"s_mov_b32 s{self.XC}, {EXIT_ADJ_BIN + q}")
+            self.br("leave")
+        assert h == a["count"]
+
+    def recip(self, name, x):
+        """u = |x| > eps ? 1 / x (hardware reciprocal) : 0."""
+        self.label(name)
+        n = self.tmp + self.R
+        q = (self.Q0, self.Q1, self.Q2)
+        for rows in [list(range(b, min(b + 3, self.R))) for b in range(0, self.R, 3)]:
+            for i, j in enumerate(rows):
+                self.o(f"v_cmp_gt_f32_e64 s[{q[i]}:{q[i] + 1}], |{x(j)}|, s{self.EPS}")
+            for i, j in enumerate(rows):
+                self.o(f"v_rcp_f32 v{n + i}, {x(j)}")
+            self.o("s_nop 0")
+            for i, j in enumerate(rows):
+                self.o(f"v_cndmask_b32_e64 {self.U(j)}, 0, v{n + i}, s[{q[i]}:{q[i] + 1}]")
+        self.he()
+
+    def bodies(self):
+        R, a = self.R, self.tmp + 12 * self.nb - 1
+        n = self.tmp + R                    # temporaries beside the operand register
+        leave = len(self.lines)
+        super().bodies()
+        # (the shared tail, from "reload" on, goes last)
+        cut = next(i for i in range(leave, len(self.lines)) if self.lines[i].startswith(".Lreload_"))
+        tail = self.lines[cut:]
+        del self.lines[cut:]
+        self.rare_exits = []
+        self.label("negmt")
+        self.rows(lambda j: f"v_xor_b32 {self.M(j)}, 0x80000000, {self.T(j)}")
+        self.he()
+        self.recip("dinvm", self.M)
+        self.recip("dinvt", self.T)
+        # u = u == 0 ? 0 : -x u u (a protected quotient has u = 0)
+        for name, x in (("dnegt", self.T), ("dnegm", self.M)):
+            self.label(name)
+            for j in range(R):
+                self.o(f"v_cmp_neq_f32_e64 vcc, 0, {self.U(j)}")
+                self.o(f"v_mul_f32_e64 v{n}, -{x(j)}, {self.U(j)}")
+                self.o(f"v_mul_f32 v{n}, v{n}, {self.U(j)}")
+                self.o("s_nop 0")
+                self.o(f"v_cndmask_b32_e32 {self.U(j)}, 0, v{n}, vcc")
+            self.he()
+        # u (the input x) and the top y = sqrt|x|: u = x == 0 ? 0 : copysign(1 / 2y, x)
+        self.label("dsqrt")
+        self.o(f"s_mov_b32 s{self.T59}, 0x7fffffff")
+        for j in range(R):
+            self.o(f"v_add_f32 v{n}, {self.T(j)}, {self.T(j)}")
+            self.o(f"v_rcp_f32 v{n}, v{n}")
+            self.o(f"v_cmp_neq_f32_e64 vcc, 0, {self.U(j)}")
+            self.o(f"s_nop 0")
+            self.o(f"v_bfi_b32 v{n}, s{self.T59}, v{n}, {self.U(j)}")
+            self.o(f"v_cndmask_b32_e32 {self.U(j)}, 0, v{n}, vcc")
+        self.he()
+        self.sincos("sin", self.RNDS, "sind")
+        self.sincos("cos", self.RNDC, "cosd")
+        for k in range(ACC):
+            self.label(f"cadd{k}")
+            s0 = self.tmp + self.R + (self.R & 1)
+            A = self.pair(self.acc + 2 * k)
+            for j in range(R):
+                self.o(f"v_cndmask_b32_e64 v{s0 + 4}, 0, {self.M(j)}, s[{self.VM + 2 * j}:{self.VM + 2 * j + 1}]")
+                d = self.pair(s0 + (0 if j == 0 else 2))
+                self.o(f"v_cvt_f64_f32 {d}, v{s0 + 4}")
+                if j:
+                    self.o(f"v_add_f64 {self.pair(s0)}, {self.pair(s0)}, {d}")
+            self.o(f"v_add_f64 {A}, {A}, {self.pair(s0)}")
+            self.he()
+        regs = {"putt": self.T, "putm": self.M, "putu": self.U}
+        for name in ADJ_TAPE:
+            name = name.lower()
+            self.label(name + "l")
+            self.lane(a)
+            self.o(f"s_add_u32 s{self.T59}, s{self.P}, s{self.LDS}")
+            self.o(f"v_lshl_add_u32 v{a}, v{a}, 2, s{self.T59}")
+            self.tape_op(name, regs, n, lambda j, r: f"ds_write_b32 v{a}, {r} offset:{256 * j}",
+                         lambda j, r: f"ds_read_b32 {r}, v{a} offset:{256 * j}", "lgkmcnt(0)")
+            self.label(name + "g")
+            self.lane(a)
+            self.o(f"v_lshlrev_b32 v{a}, 2, v{a}")
+            self.o(f"s_add_u32 s{self.A}, s{self.GB}, s{self.P}")
+            self.o(f"s_addc_u32 s{self.A + 1}, s{self.GB + 1}, 0")
+            # (a read waits for the writes before it; a write's data stays put
+            # until the wait at the next fetch, exit or read: the tape's
+            # sources are only overwritten through the same registers in order)
+            self.tape_op(name, regs, n,
+                         lambda j, r: f"global_store_dword v{a}, {r}, s[{self.A}:{self.A + 1}] offset:{256 * j}",
+                         lambda j, r: f"global_load_dword {r}, v{a}, s[{self.A}:{self.A + 1}] offset:{256 * j}",
+                         "vmcnt(0)")
+        for name, code in self.rare_exits:
+            self.label(f"rare_{name}")
+            self.o(f"s_mov_b32 s{self.XC}, {code}")
+            self.br("leave")
+        self.lines += tail
+
+    def tape_op(self, name, regs, n, store, load, wait):
+        if name in regs:
+            self.rows(lambda j: store(j, regs[name](j)))
+        else:
+            if "vmcnt" in wait:
+                self.o("s_waitcnt vmcnt(0)")
+            self.rows(lambda j: load(j, f"v{n + j}"))
+            self.o(f"s_waitcnt {wait}")
+            self.rows(lambda j: f"v_mul_f32 {self.T(j) if name == 'gmul' else self.M(j)}, {self.T(j)}, v{n + j}")
+        self.he()
+
+
+def emit_adjoint(R):
+    g = AdjGen(R)
+    lines = g.text()
+    w = []
+    outs = []
+
+    def group(name, first, n):
+        at = first
+        for q, m in enumerate(pieces(n)):
+            outs.append((f"{name}{q}", at, m))
+            at += m
+    outs.append(("t", g.t, R))
+    group("s", g.s, SLOTS * R)
+    outs.append(("m", g.tmp, R))
+    outs.append(("p", g.p, R))
+    outs.append(("u", g.u, R))
+    outs.append(("acc", g.acc, 2 * ACC))
+    group("e", g.tape, TAPE * R)
+    ins = [("k0", g.k, 8), ("k1", g.k + 8, 2), ("off", g.off, R)]
+
+    def vr(first, n):
+        return f"{{v[{first}:{first + n - 1}]}}" if n > 1 else f"{{v{first}}}"
+    w.append("template <>")
+    w.append(f"struct InterpAdjoint<{R}> {{")
+    w.append(f"    // v{g.base} .. v{g.end - 1}")
+    for name, first, n in outs + ins:
+        ty = ("uint32_t" if n == 1 else f"EvVec<uint32_t, {n}>") if name == "off" else vec(n)
+        w.append(f"    {ty} {name};")
+    w.append("    EvVec<uint32_t, 2> ins;")
+    w.append("    uint32_t idx, blk0, blk1, lds;")
+    w.append("    uint32_t payload;            // of the instruction that left")
+    w.append("    uint64_t xb, ld4, area;      // area: the wavefront's tape memory")
+    w.append(f"    uint64_t mask[{R}];            // rows that count")
+    w.append("    EvVec<uint32_t, 16> c0;")
+    w.append("    EvVec<uint32_t, 8> c1;")
+    w.append("    __device__ __forceinline__ uint32_t run() {")
+    w.append("        uint32_t code;")
+    w.append("        asm volatile(")
+    for ln in lines:
+        w.append(f'            "{ln}\\n"')
+    w.append("            : " + ", ".join(f'"+{vr(f, n)}"({nm})' for nm, f, n in outs) + ",")
+    w.append(f'              "+{{v[{g.i}:{g.i + 1}]}}"(ins), "+{{s{g.IDX}}}"(idx), "+{{s{g.BLK}}}"(blk0), "+{{s{g.BLK + 1}}}"(blk1), "={{s{g.XC}}}"(code), "={{s{g.P}}}"(payload)')
+    w.append("            : " + ", ".join(f'"{vr(f, n)}"({nm})' for nm, f, n in ins) + ",")
+    masks = ", ".join(f'"{{s[{g.VM + 2 * j}:{g.VM + 2 * j + 1}]}}"(mask[{j}])' for j in range(R))
+    w.append(f'              "{{s[64:79]}}"(c0), "{{s[80:87]}}"(c1), "{{s{g.LDS}}}"(lds), "{{s[{g.XB}:{g.XB + 1}]}}"(xb), "{{s[{g.LD}:{g.LD + 1}]}}"(ld4), "{{s[{g.GB}:{g.GB + 1}]}}"(area), {masks}')
+    clob = ["vcc", "scc", "memory"]
+    clob += [f"s{q}" for q in (48, 49, 50, 51, 52, 53, 59, 60, 61, 90, 91, 92, 93, 94, 95)]
+    clob += [f"v{q}" for q in range(g.tmp + R, g.tmp + 12 * g.nb)]
+    w.append("            : " + ", ".join(f'"{c}"' for c in clob) + ");")
+    for nm in ("idx", "blk0", "blk1", "payload"):
+        w.append(f"        {nm} = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>({nm})));")
+    w.append("        return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(code)));")
+    w.append("    }")
+    w.append("};")
+    return w
+
+
 def main():
     out = ["// Generated by gen_eval_asm.py; do not edit.  The interpreter of the evaluation",
            "// kernel as gfx950 assembly (see the generator for its design).",
@@ -579,6 +866,9 @@ def main():
     for R in (1, 2, 4):
         for freg in (0, 2, 8):
             out += emit_function(R, freg) + [""]
+    out += ["// The adjoint kernel's: the same, then reverse mode.", "template <int R>", "struct InterpAdjoint;", ""]
+    for R in (1, 2, 4):
+        out += emit_adjoint(R) + [""]
     with open("gp_eval_asm.h", "w") as f:
         f.write("\n".join(out))
     code = ["// Generated by gen_eval_asm.py; do not edit.  The instruction stream that",
@@ -623,6 +913,32 @@ def main():
              "enum : uint32_t {", "    kExitEnd = 0,", f"    kExitMax = {EXIT_MAX},", f"    kExitMin = {EXIT_MIN},",
              f"    kExitAtan2TM = {EXIT_AT_TB},   // atan2(t, m)", f"    kExitAtan2MT = {EXIT_AT_BT},   // atan2(m, t)",
              "};", ""]
+    names = {"PUTT": "PutT", "PUTM": "PutM", "PUTU": "PutU", "GMUL": "GMul", "MMUL": "MMul", "LOADM": "LoadM",
+             "SAVEM": "SaveM", "SETMC": "SetMC", "SETMF": "SetMF", "MOVMT": "MovMT", "NEGMT": "NegMT", "MOVUT": "MovUT",
+             "DINVM": "DInvM", "DINVT": "DInvT", "DNEGT": "DNegT", "DNEGM": "DNegM", "DSQRT": "DSqrt", "SIND": "SinD",
+             "COSD": "CosD", "CADDX": "CAddX", "CADD": "CAdd", "UNX": "UnX", "BINX": "BinX"}
+    code += ["// The adjoint kernel's instructions, after the table above (FREG = 0).  t is the",
+             "// top (in the reverse part the adjoint), m the operand register, u a third.",
+             "// kAPutT/M/U + entry: tape entry = t / m / u; kAGMul + entry: t *= entry; kAMMul +",
+             "// entry: m = t * entry.  Entries from kTapeRegs on use the ...L forms (LDS, the",
+             "// payload a byte offset), from kTapeRegs + kTapeLds on the ...G forms (memory).",
+             "// kALoadM / kASaveM + slot: m = slot / slot = m.  kASetMC, kASetMF: m = constant, fetched",
+             "// feature.  kAMovMT m = t, kANegMT m = -t, kAMovUT u = t.  kADInvM/T: u = protected",
+             "// reciprocal of m / t; kADNegT/M: u = -t u u / -m u u; kADSqrt: u = d sqrt (u the input,",
+             "// t the root); kASinD, kACosD: t = f(t), u = f'(t).  kACAdd + slot: the constant's adjoint",
+             "// += m over the rows that count; kACAddX: the same by the caller (payload: slot).",
+             "// kAUnX + unary index: t = f(t), u = f'(t) by the caller; kABinX + kind: by the caller,",
+             "// t = f of t and m, u = its derivative by t, m = by m (kinds: max and min with t, then",
+             "// with m as the first operand, atan2(t, m), atan2(m, t)).",
+             f"constexpr int kTapeRegs = {TAPE}, kTapeLds = {TAPE_LDS}, kAccRegs = {ACC};", "enum : uint32_t {"]
+    sec = adj_sections()
+    for k, v in sec.items():
+        if k == "count":
+            continue
+        base = k[:-1] if k[:-1] in ADJ_TAPE and k[-1] in "LG" else None
+        code.append(f"    kA{names[base] + k[-1] if base else names[k]} = {v},")
+    code += [f"    kAdjointOps = {sec['count']},", f"    kExitAdjUnary = {EXIT_ADJ_UN},", f"    kExitAdjBinary = {EXIT_ADJ_BIN},",
+             f"    kExitCAdd = {EXIT_CADD},", "};", ""]
     with open("gp_eval_code.h", "w") as f:
         f.write("\n".join(code))
 

@@ -1162,6 +1162,475 @@ __global__ __launch_bounds__(kBlock) void k_compile_eval(PopView pop, uint4* __r
 }
 
 // ---------------------------------------------------------------------------
+// k_compile_adjoint: one wavefront per program of at most kParNodes nodes, as
+// k_compile_eval: the forward instructions of the adjoint kernel (every
+// constant stays, active operations record their partial derivatives), kOpEnd,
+// the reverse instructions, kOpEnd.
+// ---------------------------------------------------------------------------
+struct AdjNodes {
+    uint16_t sec[kParNodes];      // second operand of a binary function
+    uint16_t cnt[kParNodes], rcnt[kParNodes], tcnt[kParNodes], fcnt[kParNodes];
+                                  // forward and reverse instructions, tape entries, feature
+                                  // fetches of the subtree
+    uint16_t start[kParNodes], rstart[kParNodes], tstart[kParNodes], fstart[kParNodes];
+                                  // where they begin
+    uint8_t op[kParNodes], ent[kParNodes], lev[kParNodes];
+    uint32_t feat[kParNodes / 2 + 1];   // the features in the order they are fetched
+};
+constexpr int kAdjCompileWaves = 2;
+constexpr uint8_t kActiveEnt = 32;      // ent bit: the subtree holds a constant
+constexpr int64_t kAdjCodePerNode = 8;  // uint4 (two instructions each) of code per node
+
+// What a binary function does with its operands: which is fused (kOpFold...)
+// or evaluated first, and in which order the function takes them.
+struct BinShape {
+    bool fold;      // one operand is a terminal, fused; else both are evaluated
+    bool a_first;   // the first operand is the one evaluated first (fold: the one evaluated)
+};
+__device__ __forceinline__ BinShape bin_shape(uint32_t ea, uint32_t eb) {
+    const bool ta = ea & kLeaf, tb = eb & kLeaf;
+    return BinShape{ta || tb, ta ? false : (tb ? true : (ea & kEntMask) > (eb & kEntMask))};
+}
+
+// The instructions of one node itself, given to fw (forward) and rv (reverse):
+// called to count them and again to write them, so the two agree.  For a
+// function of one argument or a fold, E is the evaluated operand and T the
+// fused terminal; else F is evaluated first (its value in slot `lev`), S on
+// top of it.  Tape entry e of the node is tape(e).
+template <typename Fw, typename Rv>
+__device__ __forceinline__ void adjoint_ops(uint32_t op, bool act, uint32_t lev, bool leaf_const, uint32_t slot_c,
+                                            float cval, uint32_t ea, uint32_t eb, const Emit& em, Fw&& fw, Rv&& rv) {
+    auto id = [](uint32_t i) { return i * kOpBytes; };
+    const int ar = arity(op);
+    enum { kPlain = 0, kFetch = 1, kTape = 2 };      // what a payload names
+    auto cadd = [&](uint32_t slot) __attribute__((always_inline)) {
+        if (slot < static_cast<uint32_t>(kAccRegs)) rv(id(kACAdd + slot), 0u, kPlain);
+        else rv(id(kACAddX), slot, kPlain);
+    };
+    if (ar == 0) {
+        const uint32_t src = em.source(op == GP_OP_CONST, 0u);
+        fw(lev == 0 ? em.set(src) : em.push(lev - 1, src), __float_as_uint(cval), op == GP_OP_CONST ? kPlain : kFetch);
+        if (op == GP_OP_CONST) {
+            rv(id(kAMovMT), 0u, kPlain);
+            cadd(slot_c);
+        }
+        return;
+    }
+    if (ar == 1) {
+        const uint32_t u = unary_index(op);
+        if (!act) {
+            fw(id(kOpUnary + u), 0u, kPlain);
+        } else if (u == 0) {
+            fw(id(kOpUnary + u), 0u, kPlain);
+            rv(id(kOpUnary + u), 0u, kPlain);
+        } else {
+            if (u == 1) {
+                fw(id(kADInvT), 0u, kPlain);
+                fw(id(kAPutU), 0u, kTape);
+                fw(id(kOpUnary + u), 0u, kPlain);
+            } else if (u == 2) {
+                fw(id(kAMovUT), 0u, kPlain);
+                fw(id(kOpUnary + u), 0u, kPlain);
+                fw(id(kADSqrt), 0u, kPlain);
+                fw(id(kAPutU), 0u, kTape);
+            } else {
+                fw(id(u == 3 ? kASinD : u == 4 ? kACosD : kAUnX + u), 0u, kPlain);
+                fw(id(kAPutU), 0u, kTape);
+            }
+            rv(id(kAGMul), 0u, kTape);
+        }
+        return;
+    }
+    const BinShape sh = bin_shape(ea, eb);
+    const uint32_t fn = binary_index(op);
+    if (sh.fold) {
+        const bool t_is_a = !sh.a_first;
+        const bool tc = leaf_const, e_act = (t_is_a ? eb : ea) & kActiveEnt;
+        const uint32_t src = em.source(tc, 0u), cb = __float_as_uint(cval);
+        if (!act || fn < 2 || (fn == 2 && tc)) {
+            if (act && fn == 2) fw(id(kAPutT), 0u, kTape);
+            fw(em.fold(bin_op(fn, !t_is_a), src), cb, tc ? kPlain : kFetch);
+            if (!act) return;
+            if (fn < 2) {
+                // T - E carries -g to E; E - T carries -g to T
+                if (tc) {
+                    rv(id(fn == 1 && !t_is_a ? kANegMT : kAMovMT), 0u, kPlain);
+                    cadd(slot_c);
+                }
+                if (e_act && fn == 1 && t_is_a) rv(id(kOpUnary + 0), 0u, kPlain);
+            } else {
+                rv(id(kAMMul), 0u, kTape);
+                cadd(slot_c);
+                if (e_act) rv(em.fold(kBMul, 0u), cb, kPlain);
+            }
+            return;
+        }
+        // the terminal as the operand register; entry 0 belongs to E (if
+        // active), the next to T
+        const uint32_t et = e_act ? 1u : 0u;
+        fw(id(tc ? kASetMC : kASetMF), cb, tc ? kPlain : kFetch);
+        if (fn == 2) {
+            fw(id(kAPutM), 0u, kTape);
+            fw(em.bin(kBMul, kRegSlots), 0u, kPlain);
+        } else if (fn == 3) {
+            fw(id(t_is_a ? kADInvT : kADInvM), 0u, kPlain);
+            if (t_is_a) {
+                if (tc) fw(id(kAPutU), et, kTape);
+                if (e_act) {
+                    fw(id(kADNegM), 0u, kPlain);
+                    fw(id(kAPutU), 0u, kTape);
+                }
+            } else {
+                if (e_act) fw(id(kAPutU), 0u, kTape);
+                if (tc) {
+                    fw(id(kADNegT), 0u, kPlain);
+                    fw(id(kAPutU), et, kTape);
+                }
+            }
+            fw(em.bin(t_is_a ? kBDivRev : kBDiv, kRegSlots), 0u, kPlain);
+        } else {
+            const uint32_t kind = fn == 4 ? (t_is_a ? 1u : 0u) : fn == 5 ? (t_is_a ? 3u : 2u) : (t_is_a ? 5u : 4u);
+            fw(id(kABinX + kind), 0u, kPlain);
+            if (e_act) fw(id(kAPutU), 0u, kTape);
+            if (tc) fw(id(kAPutM), et, kTape);
+        }
+        if (tc) {
+            rv(id(kAMMul), et, kTape);
+            cadd(slot_c);
+        }
+        if (e_act) rv(id(kAGMul), 0u, kTape);
+        return;
+    }
+    // both evaluated: S on top, F in slot lev; s_is_a: S is the function's first operand
+    const bool s_is_a = !sh.a_first;
+    const bool s_act = (s_is_a ? ea : eb) & kActiveEnt, f_act = (s_is_a ? eb : ea) & kActiveEnt;
+    const uint32_t plain = em.bin(bin_op(fn, !s_is_a), lev);
+    if (!act) {
+        fw(plain, 0u, kPlain);
+        return;
+    }
+    if (fn < 2) {
+        fw(plain, 0u, kPlain);
+        const bool s_neg = fn == 1 && !s_is_a, f_neg = fn == 1 && s_is_a;
+        if (s_act && f_act) {
+            if (f_neg) {
+                rv(id(kANegMT), 0u, kPlain);
+                rv(id(kASaveM + lev), 0u, kPlain);
+            } else {
+                rv(id(kOpSave + lev), 0u, kPlain);
+            }
+            if (s_neg) rv(id(kOpUnary + 0), 0u, kPlain);
+        } else if (s_act ? s_neg : f_neg) {
+            rv(id(kOpUnary + 0), 0u, kPlain);
+        }
+        return;
+    }
+    const uint32_t ef = s_act ? 1u : 0u;      // entry 0 belongs to S (if active), the next to F
+    if (fn == 2) {
+        if (f_act) fw(id(kAPutT), ef, kTape);
+        if (s_act) {
+            fw(id(kALoadM + lev), 0u, kPlain);
+            fw(id(kAPutM), 0u, kTape);
+        }
+        fw(plain, 0u, kPlain);
+    } else if (fn == 3) {
+        fw(id(kALoadM + lev), 0u, kPlain);
+        if (s_is_a) {                          // t / m
+            fw(id(kADInvM), 0u, kPlain);
+            if (s_act) fw(id(kAPutU), 0u, kTape);
+            if (f_act) {
+                fw(id(kADNegT), 0u, kPlain);
+                fw(id(kAPutU), ef, kTape);
+            }
+        } else {                               // m / t
+            fw(id(kADInvT), 0u, kPlain);
+            if (f_act) fw(id(kAPutU), ef, kTape);
+            if (s_act) {
+                fw(id(kADNegM), 0u, kPlain);
+                fw(id(kAPutU), 0u, kTape);
+            }
+        }
+        fw(plain, 0u, kPlain);
+    } else {
+        fw(id(kALoadM + lev), 0u, kPlain);
+        const uint32_t kind = fn == 4 ? (s_is_a ? 0u : 1u) : fn == 5 ? (s_is_a ? 2u : 3u) : (s_is_a ? 4u : 5u);
+        fw(id(kABinX + kind), 0u, kPlain);
+        if (s_act) fw(id(kAPutU), 0u, kTape);
+        if (f_act) fw(id(kAPutM), ef, kTape);
+    }
+    if (s_act && f_act) {
+        rv(id(kAMMul), ef, kTape);
+        rv(id(kASaveM + lev), 0u, kPlain);
+        rv(id(kAGMul), 0u, kTape);
+    } else {
+        rv(id(kAGMul), 0u, kTape);
+    }
+}
+
+// A tape instruction's register form and entry as the form its tier takes.
+__device__ __forceinline__ uint2 tape_ins(uint32_t handler, uint32_t e, int32_t R) {
+    if (e < static_cast<uint32_t>(kTapeRegs)) return make_uint2(handler + e * kOpBytes, 0u);
+    const uint32_t kind = (handler / kOpBytes - kAPutT) / kTapeRegs;     // PutT, PutM, PutU, GMul, MMul
+    const uint32_t bytes = static_cast<uint32_t>(R * kWave * 4);
+    if (e < static_cast<uint32_t>(kTapeRegs + kTapeLds))
+        return make_uint2((kAPutTL + kind) * kOpBytes, (e - kTapeRegs) * bytes);
+    return make_uint2((kAPutTG + kind) * kOpBytes, (e - kTapeRegs - kTapeLds) * bytes);
+}
+
+__global__ __launch_bounds__(kAdjCompileWaves * kWave) void k_compile_adjoint(PopView pop, uint4* __restrict__ code,
+                                                                            uint32_t* __restrict__ hdr, Emit em) {
+    __shared__ AdjNodes nodes_all[kAdjCompileWaves];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = static_cast<int>(uniform(threadIdx.x >> 6));
+    const int32_t p = static_cast<int32_t>(blockIdx.x) * kAdjCompileWaves + wid;
+    if (p >= pop.P) return;
+    const int64_t off = pop.prog_off[p];
+    // (the caller's bound on the lengths is at most kParNodes)
+    const int32_t L = min(pop.len[p], kParNodes);
+    const uint32_t* pn = pop.nodes + off;
+    const float* pc = pop.consts + pop.const_off[p];
+    uint2* out = reinterpret_cast<uint2*>(code + off * kAdjCodePerNode);
+    AdjNodes& nd = nodes_all[wid];
+    const int nb = (L + kWave - 1) / kWave;
+    // ---- heights and second operands (as k_compile_eval) ----
+    int carry = 0, lastpos = 0;
+    for (int b = nb - 1; b >= 0; --b) {
+        const int i = b * kWave + lane;
+        const bool valid = i < L;
+        const uint32_t op = valid ? (pn[i] & 0xffu) : 0u;
+        int hs = valid ? 1 - arity(op) : 0;
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int o = __shfl_down(hs, d, kWave);
+            if (lane + d < kWave) hs += o;
+        }
+        const int H = min(max(hs + carry, 0), 31);
+        uint64_t same = 0, mine = 0;
+        for (int hv = 1; hv <= GP_MAX_STACK; ++hv) {
+            const uint64_t m = __ballot(valid && H == hv);
+            if (H == hv) same = m;
+            if (lane == hv) mine = m;
+        }
+        const uint64_t right = lane < 63 ? same >> (lane + 1) : 0;
+        const int beyond = __shfl(lastpos, H, kWave);
+        const int sec = right ? i + 1 + __builtin_ctzll(right) : beyond;
+        if (mine) lastpos = b * kWave + __builtin_ctzll(mine);
+        carry = __builtin_amdgcn_readfirstlane(hs + carry);
+        if (valid) {
+            nd.op[i] = static_cast<uint8_t>(op);
+            nd.sec[i] = static_cast<uint16_t>(min(max(sec, 0), L - 1));
+            nd.start[i] = 0xffffu;
+        }
+    }
+    wave_lds_sync();
+    // ---- from the leaves up: entries, activity, counts ----
+    for (int b = nb - 1; b >= 0; --b) {
+        const int i = b * kWave + lane;
+        const bool valid = i < L;
+        const uint32_t op = valid ? nd.op[i] : 0u;
+        const int ar = arity(op);
+        const int c1 = min(i + 1, L - 1), c2 = valid && ar == 2 ? nd.sec[i] : c1;
+        bool done = !valid;
+        const uint64_t need = (ar >= 1 && c1 < (b + 1) * kWave ? 1ull << (c1 & 63) : 0ull) |
+                              (ar == 2 && c2 < (b + 1) * kWave ? 1ull << (c2 & 63) : 0ull);
+        for (int round = 0; round <= kWave; ++round) {
+            const uint64_t ready = __ballot(done);
+            if (ready == ~0ull) break;
+            if (!done && (need & ~ready) == 0) {
+                uint32_t ea = 0, eb = 0, ent = 1, fc = 0, cn = 0, rn = 0, tn = 0, act = 0;
+                bool tc = false;
+                if (ar == 0) {
+                    ent = 1u | kLeaf;
+                    act = op == GP_OP_CONST;
+                    fc = op != GP_OP_CONST;
+                } else {
+                    ea = nd.ent[c1];
+                    if (ar == 2) eb = nd.ent[c2];
+                    act = ((ea | eb) & kActiveEnt) != 0u;
+                    if (ar == 1) {
+                        ent = max(ea & kEntMask, 1u);
+                        cn = nd.cnt[c1];
+                        rn = nd.rcnt[c1];
+                        tn = nd.tcnt[c1];
+                        fc = nd.fcnt[c1];
+                    } else {
+                        const BinShape sh = bin_shape(ea, eb);
+                        const int ce = sh.a_first ? c1 : c2, co = sh.a_first ? c2 : c1;
+                        cn = nd.cnt[ce];
+                        rn = nd.rcnt[ce];
+                        tn = nd.tcnt[ce];
+                        fc = nd.fcnt[c1] + nd.fcnt[c2];
+                        if (sh.fold) {
+                            ent = (sh.a_first ? ea : eb) & kEntMask;
+                            tc = nd.op[co] == GP_OP_CONST;
+                        } else {
+                            const uint32_t na = ea & kEntMask, nb2 = eb & kEntMask;
+                            ent = na == nb2 ? na + 1u : max(na, nb2);
+                            cn += nd.cnt[co];
+                            rn += nd.rcnt[co] + ((ea & eb & kActiveEnt) ? 1u : 0u);   // the slot taken back
+                            tn += nd.tcnt[co];
+                        }
+                    }
+                }
+                // the tape entries are the highest entry a forward instruction names, plus one
+                // (the two counts in one word: as two variables the compiler keeps
+                // them in memory, chosen by address)
+                uint64_t n2 = static_cast<uint64_t>(rn) << 32 | cn;
+                uint32_t te = 0;
+                adjoint_ops(op, act, 0u, tc, 0u, 0.0f, ea, eb, em,
+                            [&](uint32_t, uint32_t e, int kind) __attribute__((always_inline)) {
+                                n2 += 1ull;
+                                if (kind == 2) te = max(te, e + 1u);
+                            },
+                            [&](uint32_t, uint32_t, int) __attribute__((always_inline)) { n2 += 1ull << 32; });
+                cn = static_cast<uint32_t>(n2);
+                rn = static_cast<uint32_t>(n2 >> 32);
+                nd.ent[i] = static_cast<uint8_t>(ent | (act ? kActiveEnt : 0u));
+                nd.cnt[i] = static_cast<uint16_t>(cn);
+                nd.rcnt[i] = static_cast<uint16_t>(rn);
+                nd.tcnt[i] = static_cast<uint16_t>(tn + te);
+                nd.fcnt[i] = static_cast<uint16_t>(fc);
+                done = true;
+            }
+            wave_lds_sync();
+        }
+    }
+    // ---- from the root down: places ----
+    const int total = nd.cnt[0], rtotal = nd.rcnt[0];
+    if (lane == 0) {
+        nd.start[0] = 0;
+        nd.rstart[0] = static_cast<uint16_t>(total + 1);
+        nd.tstart[0] = 0;
+        nd.fstart[0] = 0;
+        nd.lev[0] = 0;
+    }
+    wave_lds_sync();
+    for (int b = 0; b < nb; ++b) {
+        const int i = b * kWave + lane;
+        const bool valid = i < L;
+        const uint32_t op = valid ? nd.op[i] : 0u;
+        const int ar = arity(op);
+        const int c1 = min(i + 1, L - 1), c2 = valid && ar == 2 ? nd.sec[i] : c1;
+        const uint32_t ea = nd.ent[c1], eb = nd.ent[c2];
+        bool done = !valid;
+        for (int round = 0; round <= kWave; ++round) {
+            bool fresh = false;
+            if (!done) {
+                const uint32_t start = nd.start[i];
+                if (start != 0xffffu) {
+                    done = fresh = true;
+                    const uint32_t rs = nd.rstart[i], ts = nd.tstart[i], fs = nd.fstart[i], lev = nd.lev[i];
+                    if (ar == 1) {
+                        nd.rstart[c1] = static_cast<uint16_t>(rs + nd.rcnt[i] - nd.rcnt[c1]);
+                        nd.tstart[c1] = static_cast<uint16_t>(ts);
+                        nd.fstart[c1] = static_cast<uint16_t>(fs);
+                        nd.lev[c1] = static_cast<uint8_t>(lev);
+                        nd.start[c1] = static_cast<uint16_t>(start);
+                    } else if (ar == 2) {
+                        const BinShape sh = bin_shape(ea, eb);
+                        const int f = sh.a_first ? c1 : c2, s = sh.a_first ? c2 : c1;
+                        // the reverse part ends with the operand evaluated first
+                        nd.rstart[f] = static_cast<uint16_t>(rs + nd.rcnt[i] - nd.rcnt[f]);
+                        nd.tstart[f] = static_cast<uint16_t>(ts);
+                        nd.fstart[f] = static_cast<uint16_t>(fs);
+                        nd.lev[f] = static_cast<uint8_t>(lev);
+                        nd.start[f] = static_cast<uint16_t>(start);
+                        if (!sh.fold) {
+                            const uint32_t back = (ea & eb & kActiveEnt) ? 1u : 0u;
+                            nd.rstart[s] = static_cast<uint16_t>(rs + nd.rcnt[i] - nd.rcnt[f] - back - nd.rcnt[s]);
+                            nd.tstart[s] = static_cast<uint16_t>(ts + nd.tcnt[f]);
+                            nd.fstart[s] = static_cast<uint16_t>(fs + nd.fcnt[f]);
+                            nd.lev[s] = static_cast<uint8_t>(lev + 1);
+                            nd.start[s] = static_cast<uint16_t>(start + nd.cnt[f]);
+                        }
+                    }
+                }
+            }
+            wave_lds_sync();
+            if (__ballot(fresh) == 0) break;
+        }
+    }
+    // ---- the features in the order of their fetches ----
+    for (int b = 0; b < nb; ++b) {
+        const int i = b * kWave + lane;
+        if (i >= L || nd.start[i] == 0xffffu) continue;
+        const uint32_t op = nd.op[i];
+        if (op == GP_OP_VAR) {
+            nd.feat[nd.fstart[i]] = pn[i] >> 8;
+        } else if (arity(op) == 2) {
+            const int c1 = i + 1, c2 = nd.sec[i];
+            const BinShape sh = bin_shape(nd.ent[c1], nd.ent[c2]);
+            const int t = sh.a_first ? c2 : c1;
+            if (sh.fold && nd.op[t] == GP_OP_VAR) nd.feat[nd.fstart[i] + nd.fcnt[i] - 1] = pn[t] >> 8;
+        }
+    }
+    wave_lds_sync();
+    const int fetches = nd.fcnt[0];
+    // ---- instructions ----
+    for (int b = 0; b < nb; ++b) {
+        const int i = b * kWave + lane;
+        if (i >= L || nd.start[i] == 0xffffu) continue;
+        const uint32_t op = nd.op[i], me = nd.ent[i], lev = nd.lev[i];
+        const int ar = arity(op);
+        const int c1 = min(i + 1, L - 1), c2 = ar == 2 ? nd.sec[i] : c1;
+        const uint32_t ea = ar >= 1 ? nd.ent[c1] : 0u, eb = ar == 2 ? nd.ent[c2] : 0u;
+        uint32_t q = nd.start[i];
+        uint32_t tape = nd.tstart[i];
+        int fetch = nd.fstart[i] + nd.fcnt[i] - 1;     // this node's own, if it has one: its subtree's last
+        int term = i;
+        bool both = false;
+        int ce = c1, co = c1;
+        if (ar == 1) {
+            q += nd.cnt[c1];
+            tape += nd.tcnt[c1];
+        } else if (ar == 2) {
+            const BinShape sh = bin_shape(ea, eb);
+            ce = sh.a_first ? c1 : c2;
+            co = sh.a_first ? c2 : c1;
+            q += nd.cnt[ce];
+            tape += nd.tcnt[ce];
+            if (sh.fold) {
+                term = co;
+            } else {
+                q += nd.cnt[co];
+                tape += nd.tcnt[co];
+                both = (ea & eb & kActiveEnt) != 0u;
+            }
+        }
+        const bool is_c = nd.op[term] == GP_OP_CONST;
+        const uint32_t slot_c = is_c ? pn[term] >> 8 : 0u;
+        const float cval = is_c ? pc[slot_c] : 0.0f;
+        // the next forward instruction in the low word, the next reverse one in
+        // the high word
+        uint64_t at2 = static_cast<uint64_t>(nd.rstart[i]) << 32 | q;
+        auto put = [&](uint32_t at, uint32_t handler, uint32_t payload, int kind) __attribute__((always_inline)) {
+            uint2 ins = make_uint2(handler, payload);
+            if (kind == 1) ins.y = fetch + 1 < fetches ? nd.feat[fetch + 1] : 0xffffffffu;
+            else if (kind == 2) ins = tape_ins(handler, tape + payload, em.R);
+            out[code_pos(at)] = ins;
+        };
+        adjoint_ops(op, (me & kActiveEnt) != 0u, lev, is_c, slot_c, cval, ea, eb, em,
+                    [&](uint32_t h, uint32_t y, int kind) __attribute__((always_inline)) {
+                        put(static_cast<uint32_t>(at2), h, y, kind);
+                        at2 += 1ull;
+                    },
+                    [&](uint32_t h, uint32_t y, int kind) __attribute__((always_inline)) {
+                        put(static_cast<uint32_t>(at2 >> 32), h, y, kind);
+                        at2 += 1ull << 32;
+                    });
+        // between the two operands' reverse parts: the second's adjoint back on top
+        if (both) put(nd.rstart[i] + nd.rcnt[i] - nd.rcnt[ce] - 1u, (kOpLoadS + lev) * kOpBytes, 0u, 0);
+    }
+    const int64_t end = code_pos(total), end2 = code_pos(total + 1 + rtotal);
+    if (lane == 0) {
+        out[end] = make_uint2(em.handler(kOpEnd), 0u);
+        out[end2] = make_uint2(em.handler(kOpEnd), 0u);
+        hdr[p] = (end2 >= 64 ? kHdrBlocks : 0u) | (fetches ? kHdrFetch | (nd.feat[0] & kHdrFeature) : 0u);
+    }
+    for (int64_t x = 63 + 64 * static_cast<int64_t>(lane); x < end2; x += 64 * kWave)
+        out[x] = make_uint2(em.handler(kOpReload), 0u);
+}
+
+// ---------------------------------------------------------------------------
 // k_find_user: raises flag[0] (which the caller zeroes, k_zero_u32) if any
 // of the n nodes is a user function.
 // ---------------------------------------------------------------------------
@@ -1282,6 +1751,42 @@ __device__ __forceinline__ void ev_set(V& v, int j, T x) {
     if constexpr (std::is_arithmetic_v<V>) v = x;
     else v[j] = x;
 }
+// The interpreter's constants: scalar register groups c0 and c1, vector ones k0
+// and k1, in the generator's order.
+__device__ __forceinline__ EvVec<uint32_t, 16> interp_c0() {
+    const double c[8] = {crm::kInvPi128, crm::kPi128a, crm::kPi128b, crm::kS5, crm::kC4, crm::kL2, crm::kL3, crm::kL5};
+    EvVec<uint32_t, 16> v{};
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const uint64_t u = crm::dbits(c[q]);
+        v[2 * q] = static_cast<uint32_t>(u);
+        v[2 * q + 1] = static_cast<uint32_t>(u >> 32);
+    }
+    return v;
+}
+__device__ __forceinline__ EvVec<uint32_t, 8> interp_c1() {
+    const uint64_t ln2 = crm::dbits(crm::kLn2), c375 = crm::dbits(0.375);
+    return EvVec<uint32_t, 8>{static_cast<uint32_t>(ln2), static_cast<uint32_t>(ln2 >> 32),
+                              static_cast<uint32_t>(c375), static_cast<uint32_t>(c375 >> 32),
+                              crm::fbits(GP_PROTECT_EPS), 0x7fffffu, 0x240u, 4u};
+}
+template <typename I>
+__device__ __forceinline__ void interp_vector_constants(I& in) {
+    const double k[5] = {crm::kRound, crm::kRoundCos, crm::kS3, crm::kC2, crm::kL4};
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        const uint64_t u = crm::dbits(k[q]);
+        const float lo = crm::bitsf(static_cast<uint32_t>(u)), hi = crm::bitsf(static_cast<uint32_t>(u >> 32));
+        if (q < 4) {
+            in.k0[2 * q] = lo;
+            in.k0[2 * q + 1] = hi;
+        } else {
+            in.k1[0] = lo;
+            in.k1[1] = hi;
+        }
+    }
+}
+
 // One row of an operation the interpreter leaves to its caller (one row at a
 // time: the function library's temporaries for all the rows at once would
 // take the kernel past an occupancy step).
@@ -1328,33 +1833,9 @@ __global__ __launch_bounds__(kBlock, eval_waves(R, FREG)) void k_eval(PopView po
     stage_tabs(*reinterpret_cast<MathTabsLds*>(lds_all));
 
     Interp<R, FREG> in;
-    in.c0 = EvVec<uint32_t, 16>{};
-    {
-        const double c[8] = {crm::kInvPi128, crm::kPi128a, crm::kPi128b, crm::kS5, crm::kC4, crm::kL2, crm::kL3, crm::kL5};
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const uint64_t u = crm::dbits(c[q]);
-            in.c0[2 * q] = static_cast<uint32_t>(u);
-            in.c0[2 * q + 1] = static_cast<uint32_t>(u >> 32);
-        }
-        const uint64_t ln2 = crm::dbits(crm::kLn2), c375 = crm::dbits(0.375);
-        in.c1 = EvVec<uint32_t, 8>{static_cast<uint32_t>(ln2), static_cast<uint32_t>(ln2 >> 32),
-                                   static_cast<uint32_t>(c375), static_cast<uint32_t>(c375 >> 32),
-                                   crm::fbits(GP_PROTECT_EPS), 0x7fffffu, 0x240u, 4u};
-        const double k[5] = {crm::kRound, crm::kRoundCos, crm::kS3, crm::kC2, crm::kL4};
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-            const uint64_t u = crm::dbits(k[q]);
-            const float lo = crm::bitsf(static_cast<uint32_t>(u)), hi = crm::bitsf(static_cast<uint32_t>(u >> 32));
-            if (q < 4) {
-                in.k0[2 * q] = lo;
-                in.k0[2 * q + 1] = hi;
-            } else {
-                in.k1[0] = lo;
-                in.k1[1] = hi;
-            }
-        }
-    }
+    in.c0 = interp_c0();
+    in.c1 = interp_c1();
+    interp_vector_constants(in);
     const uint32_t wid = uniform(threadIdx.x >> 6);
     in.lds = static_cast<uint32_t>(sizeof(MathTabsLds)) + wid * static_cast<uint32_t>(s.lds_slots * R * kWave * 4);
     if constexpr (FREG == 0) in.ld4 = static_cast<uint64_t>(ld) * 4u;
@@ -1606,9 +2087,11 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const double* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// k_adjoint: derivative of every program's fitness with respect to each of
-// its constants (not in the paper), by reverse mode over the compiled
-// instructions, one wavefront per (row chunk, program) work item.
+// k_adjoint_long: derivative of every program's fitness with respect to each
+// of its constants (not in the paper), by reverse mode over the compiled
+// instructions, one wavefront per (row chunk, program) work item; for
+// populations with a program of more than kParNodes nodes (k_adjoint takes the
+// rest: its compiler holds a program's nodes in LDS).
 //
 // Per tile of 64*R rows: a forward pass runs the stack machine and records
 // on a tape the local derivatives each instruction will need (both partials
@@ -1713,8 +2196,8 @@ __device__ __forceinline__ void unary_derivative(uint32_t fn, const float (&x)[R
     }
 }
 
-template <int R, int FREG, int METRIC>
-__global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint(PopView pop, CodeView cv, DataView d, Sched s,
+template <int R, int METRIC>
+__global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint_long(PopView pop, CodeView cv, DataView d, Sched s,
                                                     const double* __restrict__ stats,
                                                     const double* __restrict__ wsum,
                                                     const float* __restrict__ gscale,
@@ -1723,7 +2206,6 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint(PopView pop, Code
                                                     double* __restrict__ gextra,
                                                     float* __restrict__ gmem,
                                                     int64_t wave_floats) {
-    constexpr int FA = FREG > 0 ? FREG : 1;
     constexpr int kTapeLds = tape_lds_bytes<R>() / (R * kWave * 4);
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -1804,18 +2286,6 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint(PopView pop, Code
                 valid[j] = r < r1;
                 row[j] = valid[j] ? r : r1 - 1;
             }
-            GP_ARRAYS(xa, FA);
-            if constexpr (FREG > 0) {
-#pragma unroll
-                for (int f = 0; f < FREG; ++f) {
-                    if (f < d.F) {
-                        xa0[f] = X[f * ld + row[0]];
-                        if constexpr (R > 1) xa1[f] = X[f * ld + row[1]];
-                        if constexpr (R > 2) xa2[f] = X[f * ld + row[2]];
-                        if constexpr (R > 3) xa3[f] = X[f * ld + row[3]];
-                    }
-                }
-            }
             // ---------------- forward pass, recording the tape ----------------
             float t[R];
 #pragma unroll
@@ -1869,12 +2339,6 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint(PopView pop, Code
                         const float cval = __uint_as_float(cur.y);
 #pragma unroll
                         for (int j = 0; j < R; ++j) v[j] = cval;
-                    } else if constexpr (FREG > 0) {
-                        const uint32_t arg = w >> 8;
-                        v[0] = xa0[arg];
-                        if constexpr (R > 1) v[1] = xa1[arg];
-                        if constexpr (R > 2) v[2] = xa2[arg];
-                        if constexpr (R > 3) v[3] = xa3[arg];
                     } else {
                         const float* __restrict__ col = X + static_cast<int64_t>(w >> 8) * ld;
 #pragma unroll
@@ -2123,6 +2587,245 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint(PopView pop, Code
             }
         }
         // ---------------- per-item results ----------------
+        wave_lds_sync();
+        if (lane < nlds) gpart[(cbase + lane) * s.n_chunks + c] = gw[lane];
+        if (part) {
+            lacc = wave_sum(lacc);
+            if (lane == 0) part[static_cast<int64_t>(p) * s.n_chunks + c] = lacc;
+        }
+        wave_lds_sync();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_adjoint: the same derivative for programs of at most kParNodes nodes, the
+// program in the interpreter of gp_eval_asm.h.  Its forward part records each
+// active operation's partial derivatives on a tape: kTapeRegs entries in
+// vector registers, kTapeLds in LDS, the rest in memory (a program of 200
+// nodes over 8 features records 22 on average, 54 at most); its reverse part
+// is straight-line instructions over the active operations alone.  Two
+// wavefronts per SIMD at four rows per lane, the registers' worth; but neither
+// the tape nor the reverse walk waits for memory.  Its bound is vector issue,
+// as the evaluation kernel's.  1,024 programs of 1 to 200 nodes on 262,144 rows
+// of 8 features: 23.9 ms by k_adjoint_long, 8.3 ms here (two rows per lane and
+// three wavefronts 9.3 ms, one row and four 12.3 ms; one tile per item to 64
+// within 7%); 100 programs of up to 120 nodes on 10,007 weighted rows,
+// forward pass, derivative and their preparation: 410 and 277 us.
+// ---------------------------------------------------------------------------
+template <int R>
+constexpr size_t adjoint_lds_wave() { return static_cast<size_t>(kTapeLds) * R * kWave * 4 + kGradLds * sizeof(double); }
+// bytes of a wavefront's memory area for at most `entries` tape entries
+template <int R>
+int64_t adjoint_area(int64_t entries) {
+    return std::max<int64_t>(entries - kTapeRegs - kTapeLds, 1) * R * kWave * 4;
+}
+
+// The caller's part of the adjoint's instructions, one row at a time.
+__device__ __forceinline__ void leave_row_adjoint(uint32_t code, float& t, float& m, float& u, const MathTabs& mt) {
+    float x[1] = {t}, y[1] = {t}, dv[1];
+    if (code < kExitAdjBinary) {
+        const uint32_t fn = code - kExitAdjUnary;
+        if (fn == 3 || fn == 4) {
+            sincos_rows_derivative<1>(fn == 4, y, dv, mt);
+        } else {
+            apply_unary<1>(fn, y, mt);
+            unary_derivative<1>(fn, x, y, dv);
+        }
+        t = y[0];
+        u = dv[0];
+        return;
+    }
+    const uint32_t kind = code - kExitAdjBinary;
+    const bool t_first = (kind & 1u) == 0u;
+    float a[1] = {t_first ? t : m}, b[1] = {t_first ? m : t};
+    float da, db;
+    if (kind < 4u) {
+        // the selected operand (the first on ties) carries it
+        const bool first = (kind < 2u ? a[0] >= b[0] : a[0] <= b[0]) || isnan(b[0]);
+        da = first ? 1.0f : 0.0f;
+        db = first ? 0.0f : 1.0f;
+        apply_binary_wide<1>(kind < 2u ? 4 : 5, a, b);
+    } else {
+        const float r2 = a[0] * a[0] + b[0] * b[0];
+        da = r2 > 0.0f ? b[0] / r2 : 0.0f;
+        db = r2 > 0.0f ? -a[0] / r2 : 0.0f;
+        apply_binary_wide<1>(6, a, b);
+    }
+    t = a[0];
+    u = t_first ? da : db;
+    m = t_first ? db : da;
+}
+
+constexpr int adjoint_waves(int R) { return R == 4 ? 2 : R == 2 ? 3 : 4; }
+
+template <int R, int METRIC>
+__global__ __launch_bounds__(kAdjWaves * kWave, adjoint_waves(R)) void k_adjoint(
+    PopView pop, CodeView cv, DataView d, Sched s, const double* __restrict__ stats, const double* __restrict__ wsum,
+    const float* __restrict__ gscale, double* __restrict__ part, double* __restrict__ gpart,
+    double* __restrict__ gextra, unsigned char* __restrict__ area, int64_t area_bytes) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t wid = uniform(threadIdx.x >> 6);
+    const int64_t N = d.N;
+    const int64_t ld = d.ld;
+    const float* __restrict__ X = d.X;
+    extern __shared__ __align__(16) unsigned char lds_all[];
+    stage_tabs(*reinterpret_cast<MathTabsLds*>(lds_all));
+    // per wavefront: the sums of constants from kAccRegs on, then the LDS tape
+    unsigned char* lds_wave = lds_all + sizeof(MathTabsLds) + wid * adjoint_lds_wave<R>();
+    double* gw = reinterpret_cast<double*>(lds_wave);
+    InterpAdjoint<R> in;
+    in.c0 = interp_c0();
+    in.c1 = interp_c1();
+    interp_vector_constants(in);
+    in.lds = static_cast<uint32_t>(sizeof(MathTabsLds) + wid * adjoint_lds_wave<R>() + kGradLds * sizeof(double));
+    in.ld4 = static_cast<uint64_t>(ld) * 4u;
+    in.area = reinterpret_cast<uint64_t>(area + (static_cast<int64_t>(blockIdx.x) * kAdjWaves + wid) * area_bytes);
+    const double W = *wsum;
+    const uint32_t P = static_cast<uint32_t>(pop.P);
+    Claims claims(s, P, wid);
+    int qx;
+    uint32_t it, it_end;
+    while (claims.next(lane, &qx, &it, &it_end)) {
+        it = uniform(it);
+        qx = static_cast<int>(uniform(static_cast<uint32_t>(qx)));
+        const uint32_t cq = it / P;
+        const int32_t k = static_cast<int32_t>(it - cq * P);
+        const int32_t c = static_cast<int32_t>(cq) * kQueues + qx;
+        const int32_t p = ldu(s.order + k);
+        const int64_t off = ldu(pop.prog_off + p);
+        const uint32_t head = static_cast<uint32_t>(ldu(cv.clen + p));
+        const int64_t cbase = ldu(pop.const_off + p);
+        const int32_t nconst = static_cast<int32_t>(ldu(pop.const_off + p + 1) - cbase);
+        const uint4* __restrict__ pcode = cv.code + off * kAdjCodePerNode;
+        in.ins = reinterpret_cast<const EvVec<uint32_t, 2>*>(pcode)[lane];
+        const int64_t r0 = static_cast<int64_t>(c) * s.chunk;
+        const int64_t r1 = min(r0 + s.chunk, N);
+        const float gsc = gscale ? ldu(gscale + p) : 1.0f;
+        if (lane < kGradLds) gw[lane] = 0.0;
+        wave_lds_sync();
+        in.acc = EvVec<float, 2 * kAccRegs>{};
+        double lacc = 0.0;
+        bool first_tile = true;
+        // a program without constants needs only its loss, and only when asked
+        const int64_t r_end = (nconst == 0 && !part) ? r0 : r1;
+        for (int64_t base = r0; base < r_end; base += kWave * R) {
+            const int left = static_cast<int>(min<int64_t>(r1 - base, kWave * R));
+            auto row_off = [left](int ln, int j) {
+                return static_cast<uint32_t>(min(j * kWave + ln, left - 1)) * 4u;
+            };
+            auto at = [](const float* col, uint32_t o) {
+                return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(col) + o);
+            };
+            in.xb = reinterpret_cast<uint64_t>(X + base);
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                ev_set(in.off, j, row_off(lane, j));
+                in.mask[j] = __ballot(j * kWave + lane < left);
+            }
+            if (head & kHdrFetch) {
+                const float* __restrict__ col = X + static_cast<int64_t>(head & kHdrFeature) * ld + base;
+#pragma unroll
+                for (int j = 0; j < R; ++j) ev_set(in.p, j, at(col, row_off(lane, j)));
+            }
+            const uint64_t blk = reinterpret_cast<uint64_t>(pcode);
+            in.blk0 = static_cast<uint32_t>(blk);
+            in.blk1 = static_cast<uint32_t>(blk >> 32);
+            if ((head & kHdrBlocks) && !first_tile) in.ins = reinterpret_cast<const EvVec<uint32_t, 2>*>(pcode)[lane];
+            first_tile = false;
+            in.idx = 0;
+            // the forward part, then (with constants) the reverse part: one walk
+            // of the caller's instructions serves both
+            for (int phase = 0;; ++phase) {
+                uint32_t code;
+                while ((code = in.run()) != kExitEnd) {
+                    if (code == kExitCAdd) {
+                        // a constant beyond the register sums
+                        double sum = 0.0;
+#pragma unroll
+                        for (int j = 0; j < R; ++j)
+                            sum += j * kWave + lane < left ? static_cast<double>(ev_get(in.m, j)) : 0.0;
+                        const double tot = wave_sum(sum);
+                        const int slot = static_cast<int>(in.payload);
+                        if (lane == 0) {
+                            if (slot < kGradLds) gw[slot] += tot;
+                            else atomicAdd(gextra + cbase + slot, tot);
+                        }
+                        continue;
+                    }
+#pragma unroll
+                    for (int j = 0; j < R; ++j) {
+                        if (code < kExitAdjUnary) {
+                            ev_set(in.t, j, leave_row(code, ev_get(in.t, j), ev_get(in.m, j), lds_all));
+                        } else {
+                            const MathTabsLds& tabs = *reinterpret_cast<const MathTabsLds*>(lds_all);
+                            float t = ev_get(in.t, j), m = ev_get(in.m, j), u = ev_get(in.u, j);
+                            leave_row_adjoint(code, t, m, u, MathTabs{tabs.sc, tabs.lg});
+                            ev_set(in.t, j, t);
+                            ev_set(in.m, j, m);
+                            ev_set(in.u, j, u);
+                        }
+                        // (one row after the other)
+                        asm volatile("" : "+v"(in.t), "+v"(in.m));
+                    }
+                }
+                if (phase == 1) break;
+                // ---------------- seeds: d fitness / d yhat per row ----------------
+                int ln = lane;
+                asm volatile("" : "+v"(ln));
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    const bool valid = j * kWave + ln < left;
+                    const float tj = ev_get(in.t, j);
+                    const float yf = at(d.y + base, row_off(ln, j));
+                    const double yh = static_cast<double>(tj);
+                    const double yv = static_cast<double>(yf);
+                    const double wv = d.w ? static_cast<double>(at(d.w + base, row_off(ln, j))) : 1.0;
+                    double sd;
+                    if constexpr (METRIC == GP_METRIC_MSE) {
+                        const double e = yh - yv;
+                        sd = 2.0 * wv * e / W;
+                        lacc += valid ? wv * (e * e) : 0.0;
+                    } else if constexpr (METRIC == GP_METRIC_RMSE) {
+                        const double sm6 = stats[static_cast<int64_t>(p) * kStats + 6];
+                        const double e = yh - yv;
+                        sd = sm6 > 0.0 ? (wv * e / W) / sm6 : 0.0;
+                    } else if constexpr (METRIC == GP_METRIC_MAE) {
+                        const double e = yh - yv;
+                        sd = wv * (e > 0.0 ? 1.0 : (e < 0.0 ? -1.0 : 0.0)) / W;
+                        lacc += valid ? wv * fabs(e) : 0.0;
+                    } else if constexpr (METRIC == GP_METRIC_LOGLOSS) {
+                        const float t1 = fmaxf(tj, 0.0f);
+                        const float t2 = yf * tj;
+                        const float t3 = t1 - t2;
+                        const float t5 = log1pf(expf(-fabsf(tj)));
+                        lacc += valid ? wv * static_cast<double>(t3 + t5) : 0.0;
+                        sd = wv * (1.0 / (1.0 + exp(-yh)) - yv) / W;
+                    } else {  // PEARSON: d|r|/dyhat
+                        const double* sp = stats + static_cast<int64_t>(p) * kStats;
+                        const double va = sp[3], vb = sp[4], rr = sp[6];
+                        if (va > 0.0 && vb > 0.0 && isfinite(va) && isfinite(vb)) {
+                            const double dr = wv * ((yv - sp[2]) / sqrt(va * vb) - rr * (yh - sp[1]) / va);
+                            sd = rr >= 0.0 ? dr : -dr;
+                        } else {
+                            sd = 0.0;
+                        }
+                    }
+                    ev_set(in.t, j, valid ? static_cast<float>(sd) * gsc : 0.0f);
+                    asm volatile("" : "+v"(in.t));     // (one row after the other)
+                }
+                if (nconst == 0) break;   // nothing to carry back
+            }
+        }
+        // ---------------- per-item results ----------------
+        const int nlds = min(nconst, kGradLds);
+#pragma unroll
+        for (int q = 0; q < kAccRegs; ++q)
+            if (q < nlds) {
+                const uint64_t u = static_cast<uint64_t>(__float_as_uint(in.acc[2 * q])) |
+                                   static_cast<uint64_t>(__float_as_uint(in.acc[2 * q + 1])) << 32;
+                const double tot = wave_sum(__longlong_as_double(static_cast<long long>(u)));
+                if (lane == 0) gw[q] = tot;
+            }
         wave_lds_sync();
         if (lane < nlds) gpart[(cbase + lane) * s.n_chunks + c] = gw[lane];
         if (part) {
@@ -3046,10 +3749,10 @@ ExpandPlan expand_plan(int mode, int metric) {
 
 // Scratch sizes one evaluation needs; grows sc's buffers to them (a fixed
 // scratch must already hold them).  Called outside any stream capture (it may
-// allocate).  The adjoint's instruction stream is reserved unless
-// `adjoint_stream` is false.
+// allocate).  adjoint_per_node: 16-byte units of the adjoint's instruction
+// stream per node (0: none).
 gp_status reserve(DeviceScratch* sc, int32_t P, int64_t total_nodes, int64_t n_chunks, int mode, int metric,
-                  bool adjoint_stream = true, int32_t ex_mul = 1, int32_t ex_add = 0) {
+                  int64_t adjoint_per_node = 0, int32_t ex_mul = 1, int32_t ex_add = 0) {
     auto need = [sc](auto** ptr, size_t* cap, size_t n, size_t elem) -> gp_status {
         if (!sc->fixed) return grow(reinterpret_cast<void**>(ptr), cap, n, elem);
         if (*ptr && *cap >= n) return GP_OK;
@@ -3057,8 +3760,8 @@ gp_status reserve(DeviceScratch* sc, int32_t P, int64_t total_nodes, int64_t n_c
     };
     gp_status rc = need(&sc->order, &sc->order_cap, P, sizeof(int32_t));
     if (rc != GP_OK) return rc;
-    if (adjoint_stream) {
-        rc = need(&sc->code, &sc->code_cap, static_cast<size_t>(total_nodes), sizeof(uint4));
+    if (adjoint_per_node > 0) {
+        rc = need(&sc->code, &sc->code_cap, static_cast<size_t>(total_nodes * adjoint_per_node + kCodePad), sizeof(uint4));
         if (rc != GP_OK) return rc;
         rc = need(&sc->clen, &sc->clen_cap, P, sizeof(int32_t));
         if (rc != GP_OK) return rc;
@@ -3099,11 +3802,12 @@ gp_status chunking(const gp_population_dev* pop, const gp_dataset_dev* data, con
 // length ordering and the instruction streams.  `force` (nullable) overrides
 // the configuration choice.  The evaluation kernel's stream (constant
 // subtrees folded) is compiled unless `adjoint` asks for the adjoint's
-// stream instead; `both` compiles the two (a backward pass that runs a
+// stream instead (for k_adjoint at adjoint_R rows per lane, or, 0, for
+// k_adjoint_long); `both` compiles the two (a backward pass that runs a
 // forward pass first).
 gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_dataset_dev* data, int mode,
                   int metric, hipStream_t st, const LaunchCfg* force, PopView* pv, CodeView* cvw, DataView* dv,
-                  Sched* sch, LaunchCfg* cfg, bool adjoint = false, bool both = false) {
+                  Sched* sch, LaunchCfg* cfg, bool adjoint = false, bool both = false, int adjoint_R = 0) {
     *pv = PopView{pop->nodes, pop->prog_off, pop->consts, pop->const_off, pop->len, pop->n_programs};
     *dv = DataView{data->X, data->ld, data->n_features, data->n_rows, data->y, data->w};
     *cfg = force ? *force
@@ -3112,7 +3816,8 @@ gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_data
     gp_status rc = chunking(pop, data, *cfg, &chunk, &n_chunks);
     if (rc != GP_OK) return rc;
     const ExpandPlan xp = expand_plan(mode, metric);
-    rc = reserve(sc, pop->n_programs, pop->total_nodes, n_chunks, mode, metric, adjoint, xp.mul, xp.add);
+    rc = reserve(sc, pop->n_programs, pop->total_nodes, n_chunks, mode, metric,
+                 adjoint ? (adjoint_R > 0 ? kAdjCodePerNode : 1) : 0, xp.mul, xp.add);
     if (rc != GP_OK) return rc;
     // items per claim: single ones up to 64 a resident wavefront (16 per CU).
     // A claim costs its queue about 25 ns, but consecutive items are programs of
@@ -3135,7 +3840,12 @@ gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_data
                            xp.loss_fn, xp.mul, xp.add, em, xp.lds_slots == kEvalLdsUser);
         GP_HIP(hipGetLastError());
     }
-    if (adjoint) {
+    if (adjoint_R > 0) {
+        const dim3 agrid((pop->n_programs + kAdjCompileWaves - 1) / kAdjCompileWaves);
+        hipLaunchKernelGGL(k_compile_adjoint, agrid, dim3(kAdjCompileWaves * kWave), 0, st, *pv, sc->code,
+                           reinterpret_cast<uint32_t*>(sc->clen), Emit{eval_ops(0), adjoint_R, 1});
+        GP_HIP(hipGetLastError());
+    } else if (adjoint) {
         hipLaunchKernelGGL(k_compile, cgrid, dim3(kBlock), 0, st, *pv, sc->code, sc->clen, 0);
         GP_HIP(hipGetLastError());
     }
@@ -4544,13 +5254,19 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
     // the adjoint's stream (no constant folding: every constant carries its
     // own derivative); RMSE and Pearson also run the evaluation kernel first
     const bool needs_forward = metric == GP_METRIC_RMSE || metric == GP_METRIC_PEARSON;
-    rc = prepare(sc, pop, data, 1, metric, st, nullptr, &pv, &cvw, &dv, &sch, &cfg, true, needs_forward);
+    // programs of at most kParNodes nodes: k_adjoint, at the rows per lane of a
+    // forced configuration, else of the heuristic (4: the fastest, or within 5%
+    // of it, from 300 rows of 20 programs to 1M rows of 100); longer ones:
+    // k_adjoint_long, at a forced configuration's, else the one (2 or 4) that
+    // keeps more rows in flight per CU (below)
+    const bool longer = pop->max_len > kParNodes;
+    const int RA = g_forced ? g_forced_cfg.R
+                            : (longer ? 0 : heuristic_cfg(data->n_features, data->n_rows, pop->n_programs, sc->n_cu).R);
+    rc = prepare(sc, pop, data, 1, metric, st, nullptr, &pv, &cvw, &dv, &sch, &cfg, true, needs_forward,
+                 longer ? 0 : RA);
     if (rc != GP_OK) return rc;
     const int32_t P = pop->n_programs;
     const int64_t nc = std::max<int64_t>(pop->total_consts, 1);
-    // rows per lane of the adjoint: a forced configuration's, else the one
-    // (2 or 4) that keeps more rows in flight per CU (below)
-    const int RA = g_forced ? g_forced_cfg.R : 0;
     const int64_t tape_max = 2 * static_cast<int64_t>(pop->max_len) + 2;   // tape entries per wavefront
     rc = grow(reinterpret_cast<void**>(&sc->stats), &sc->stats_cap, static_cast<size_t>(P) * kStats + 1,
               sizeof(double));
@@ -4590,11 +5306,6 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
     hipLaunchKernelGGL(k_zero, dim3(static_cast<unsigned>((nc + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
                        sc->gextra, nc);
     GP_HIP(hipGetLastError());
-    // features in registers when they fit -- unless a forced configuration
-    // says otherwise, or holding them would cost a wavefront of occupancy
-    // against reading them from memory (the choice below, per kernel)
-    const int freg_fit = data->n_features <= 2 ? 2 : (data->n_features <= 8 ? 8 : 0);
-    const int freg = (g_forced && g_forced_cfg.freg == 0) ? 0 : freg_fit;
     auto occ = [](const void* k) {
         int n = 0;
         (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kAdjWaves * kWave, 0);
@@ -4621,21 +5332,40 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
         GP_HIP(hipGetLastError());
         return GP_OK;
     };
-#define GP_ADJ_PICK(RR, F, M)                                                                  \
-    (g_forced || occ(reinterpret_cast<const void*>(k_adjoint<RR, F, M>)) >=                    \
-                     occ(reinterpret_cast<const void*>(k_adjoint<RR, 0, M>))                   \
-         ? go(k_adjoint<RR, F, M>, adjoint_wave_floats<RR>(tape_max))                          \
-         : go(k_adjoint<RR, 0, M>, adjoint_wave_floats<RR>(tape_max)))
-#define GP_ADJ_R(RR, M)                                                                        \
-    (freg == 2   ? GP_ADJ_PICK(RR, 2, M)                                                       \
-     : freg == 8 ? GP_ADJ_PICK(RR, 8, M)                                                       \
-                 : go(k_adjoint<RR, 0, M>, adjoint_wave_floats<RR>(tape_max)))
+    // k_adjoint: tape entries are at most one per unary function and two per
+    // binary one, of which there are fewer than half the nodes
+    const int64_t entries = static_cast<int64_t>(pop->max_len) + 2;
+    auto go_short = [&](auto kernel, size_t lds_wave, int64_t area_bytes) -> gp_status {
+        const size_t lds = sizeof(MathTabsLds) + kAdjWaves * lds_wave;
+        int per_cu = 0;
+        GP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kAdjWaves * kWave, lds));
+        per_cu = std::max(per_cu, 1);
+        int64_t blocks = std::min<int64_t>(static_cast<int64_t>(per_cu) * sc->n_cu,
+                                           (sch.n_items + kAdjWaves - 1) / kAdjWaves);
+        blocks = std::max<int64_t>(blocks, 1);
+        gp_status r2 = grow(reinterpret_cast<void**>(&sc->tape), &sc->tape_cap,
+                            static_cast<size_t>(blocks) * kAdjWaves * static_cast<size_t>(area_bytes / 4), sizeof(float));
+        if (r2 != GP_OK) return r2;
+        Sched sl = sch;
+        sl.batch = 1;
+        sl.blocks = static_cast<int32_t>(blocks);
+        sl.wpb = kAdjWaves;
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kAdjWaves * kWave), lds, st, pv, cvw, dv, sl,
+                           needs_forward ? sc->stats : nullptr, wsum, grad_fitness, lossp, sc->gpart, sc->gextra,
+                           reinterpret_cast<unsigned char*>(sc->tape), area_bytes);
+        GP_HIP(hipGetLastError());
+        return GP_OK;
+    };
+#define GP_ADJ_SHORT(RR, M) go_short(k_adjoint<RR, M>, adjoint_lds_wave<RR>(), adjoint_area<RR>(entries))
+#define GP_ADJ_LONG(RR, M) go(k_adjoint_long<RR, M>, adjoint_wave_floats<RR>(tape_max))
 #define GP_ADJ_AUTO(M)                                                                         \
-    (4 * occ(reinterpret_cast<const void*>(k_adjoint<4, 0, M>)) >                              \
-             2 * occ(reinterpret_cast<const void*>(k_adjoint<2, 0, M>))                        \
-         ? GP_ADJ_R(4, M)                                                                      \
-         : GP_ADJ_R(2, M))
-#define GP_ADJ(M) (RA == 0 ? GP_ADJ_AUTO(M) : RA == 1 ? GP_ADJ_R(1, M) : RA == 2 ? GP_ADJ_R(2, M) : GP_ADJ_R(4, M))
+    (4 * occ(reinterpret_cast<const void*>(k_adjoint_long<4, M>)) >                            \
+             2 * occ(reinterpret_cast<const void*>(k_adjoint_long<2, M>))                      \
+         ? GP_ADJ_LONG(4, M)                                                                   \
+         : GP_ADJ_LONG(2, M))
+#define GP_ADJ(M)                                                                              \
+    (!longer ? (RA == 1 ? GP_ADJ_SHORT(1, M) : RA == 2 ? GP_ADJ_SHORT(2, M) : GP_ADJ_SHORT(4, M)) \
+             : (RA == 0 ? GP_ADJ_AUTO(M) : RA == 1 ? GP_ADJ_LONG(1, M) : RA == 2 ? GP_ADJ_LONG(2, M) : GP_ADJ_LONG(4, M)))
     switch (metric) {
     case GP_METRIC_MAE: rc = GP_ADJ(GP_METRIC_MAE); break;
     case GP_METRIC_MSE: rc = GP_ADJ(GP_METRIC_MSE); break;
@@ -4645,8 +5375,8 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
     }
 #undef GP_ADJ
 #undef GP_ADJ_AUTO
-#undef GP_ADJ_R
-#undef GP_ADJ_PICK
+#undef GP_ADJ_LONG
+#undef GP_ADJ_SHORT
     if (rc != GP_OK) return rc;
     if (!needs_forward && fitness_out) {
         if (metric == GP_METRIC_MAE)

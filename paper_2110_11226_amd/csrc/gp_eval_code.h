@@ -58,3 +58,57 @@ enum : uint32_t {
     kExitAtan2TM = 34,   // atan2(t, m)
     kExitAtan2MT = 35,   // atan2(m, t)
 };
+
+// The adjoint kernel's instructions, after the table above (FREG = 0).  t is the
+// top (in the reverse part the adjoint), m the operand register, u a third.
+// kAPutT/M/U + entry: tape entry = t / m / u; kAGMul + entry: t *= entry; kAMMul +
+// entry: m = t * entry.  Entries from kTapeRegs on use the ...L forms (LDS, the
+// payload a byte offset), from kTapeRegs + kTapeLds on the ...G forms (memory).
+// kALoadM / kASaveM + slot: m = slot / slot = m.  kASetMC, kASetMF: m = constant, fetched
+// feature.  kAMovMT m = t, kANegMT m = -t, kAMovUT u = t.  kADInvM/T: u = protected
+// reciprocal of m / t; kADNegT/M: u = -t u u / -m u u; kADSqrt: u = d sqrt (u the input,
+// t the root); kASinD, kACosD: t = f(t), u = f'(t).  kACAdd + slot: the constant's adjoint
+// += m over the rows that count; kACAddX: the same by the caller (payload: slot).
+// kAUnX + unary index: t = f(t), u = f'(t) by the caller; kABinX + kind: by the caller,
+// t = f of t and m, u = its derivative by t, m = by m (kinds: max and min with t, then
+// with m as the first operand, atan2(t, m), atan2(m, t)).
+constexpr int kTapeRegs = 26, kTapeLds = 16, kAccRegs = 8;
+enum : uint32_t {
+    kAPutT = 206,
+    kAPutM = 232,
+    kAPutU = 258,
+    kAGMul = 284,
+    kAMMul = 310,
+    kAPutTL = 336,
+    kAPutML = 337,
+    kAPutUL = 338,
+    kAGMulL = 339,
+    kAMMulL = 340,
+    kAPutTG = 341,
+    kAPutMG = 342,
+    kAPutUG = 343,
+    kAGMulG = 344,
+    kAMMulG = 345,
+    kALoadM = 346,
+    kASaveM = 357,
+    kASetMC = 368,
+    kASetMF = 369,
+    kAMovMT = 370,
+    kANegMT = 371,
+    kAMovUT = 372,
+    kADInvM = 373,
+    kADInvT = 374,
+    kADNegT = 375,
+    kADNegM = 376,
+    kADSqrt = 377,
+    kASinD = 378,
+    kACosD = 379,
+    kACAddX = 380,
+    kACAdd = 381,
+    kAUnX = 389,
+    kABinX = 403,
+    kAdjointOps = 409,
+    kExitAdjUnary = 64,
+    kExitAdjBinary = 96,
+    kExitCAdd = 112,
+};

@@ -25,14 +25,14 @@ def test_headers_are_what_the_generator_writes(tmp_path, monkeypatch):
         assert (tmp_path / name).read_text() == open(os.path.join(CSRC, name)).read()
 
 
-@pytest.mark.parametrize("freg", [0, 2, 8])
+@pytest.mark.parametrize("freg", [0, 2, 8, "adjoint"])
 @pytest.mark.parametrize("rows", [1, 2, 4])
 def test_every_handler_lies_at_its_offset(tmp_path, rows, freg):
     clang = "/opt/rocm/lib/llvm/bin/clang"
     if not os.path.exists(clang) or not shutil.which("nm"):
         pytest.skip("no assembler")
     mod = generator()
-    gen = mod.Gen(rows, freg)
+    gen = mod.AdjGen(rows) if freg == "adjoint" else mod.Gen(rows, freg)
     text = "\n".join(ln.replace(".L", "L").replace("%=", "x") for ln in gen.text())
     src, obj = tmp_path / "t.s", tmp_path / "t.o"
     src.write_text('.amdgcn_target "amdgcn-amd-amdhsa--gfx950"\n.text\n.p2align 8\n' + text + "\n")
@@ -42,5 +42,5 @@ def test_every_handler_lies_at_its_offset(tmp_path, rows, freg):
         m = re.match(r"([0-9a-f]+) \w Lh(\d+)_x$", ln)
         if m:
             at[int(m.group(2))] = int(m.group(1), 16)
-    assert sorted(at) == list(range(gen.sec["count"]))
+    assert sorted(at) == list(range(gen.adj["count"] if freg == "adjoint" else gen.sec["count"]))
     assert all(at[i] == at[0] + mod.STRIDE * i for i in at)
