@@ -87,6 +87,8 @@ constexpr int kQueues = 8;
 constexpr int kQueueStride = 16;
 constexpr size_t kCounterBytes = 1024;
 constexpr int kFlagWord = 128;
+// a second such block, in scratch that grows, holds the adjoint kernel's
+constexpr int kCounterSet = kCounterBytes / sizeof(uint32_t);
 
 struct Sched {
     int64_t chunk;
@@ -452,6 +454,75 @@ __device__ __forceinline__ void apply_unary(uint32_t fn, float (&t)[R], const Ma
 }
 
 // ---------------------------------------------------------------------------
+// The evaluation order: programs by length, longest first, and the work
+// counters reset.  One block of THREADS: a counting sort over min(len,
+// kBins-1).  Block 0 of the compilers below does it while the others compile;
+// a launch of its own took 4.6 us of every call.
+// ---------------------------------------------------------------------------
+constexpr int kBins = 1024;
+struct OrderLds {
+    int32_t start[kBins];
+    int32_t wtot[kBlock / kWave];
+};
+struct OrderArgs {
+    const int32_t* len;
+    int32_t P;
+    int32_t* order;
+    uint32_t* counter;     // two sets of queues' counters, or with `sets` 1, one
+    int32_t sets;
+};
+
+template <int THREADS>
+__device__ __forceinline__ void order_programs(const OrderArgs& oa, OrderLds& sh) {
+    constexpr int kPer = kBins / THREADS, kE = 8;     // bins per thread; lengths in flight per thread
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid >> 6;
+    const int32_t* __restrict__ len = oa.len;
+    const int32_t P = oa.P;
+    for (int b = tid; b < kBins; b += THREADS) sh.start[b] = 0;
+    for (int q = tid; q < oa.sets * kQueues; q += THREADS)
+        oa.counter[(q / kQueues) * kCounterSet + (q % kQueues) * kQueueStride] = 0u;
+    __syncthreads();
+    // key: kBins-1 - min(len, kBins-1), so longer programs come first
+    auto walk = [&](auto visit) {
+        for (int64_t p0 = tid; p0 < P; p0 += THREADS * kE) {
+            int32_t key[kE];
+#pragma unroll
+            for (int e = 0; e < kE; ++e) {
+                const int64_t p = p0 + e * THREADS;
+                key[e] = p < P ? kBins - 1 - min(max(len[p], 0), kBins - 1) : -1;
+            }
+#pragma unroll
+            for (int e = 0; e < kE; ++e)
+                if (key[e] >= 0) visit(static_cast<int32_t>(p0 + e * THREADS), key[e]);
+        }
+    };
+    walk([&](int32_t, int32_t key) { atomicAdd(&sh.start[key], 1); });
+    __syncthreads();
+    int32_t c[kPer], sum = 0;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+        c[e] = sh.start[tid * kPer + e];
+        sum += c[e];
+    }
+    int32_t v = sum;
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int32_t o = __shfl_up(v, d, kWave);
+        if (lane >= d) v += o;
+    }
+    if (lane == kWave - 1) sh.wtot[wid] = v;
+    __syncthreads();
+    int32_t at = v - sum;
+    for (int q = 0; q < THREADS / kWave; ++q) at += q < wid ? sh.wtot[q] : 0;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+        sh.start[tid * kPer + e] = at;
+        at += c[e];
+    }
+    __syncthreads();
+    walk([&](int32_t p, int32_t key) { oa.order[atomicAdd(&sh.start[key], 1)] = p; });
+}
+
+// ---------------------------------------------------------------------------
 // k_compile: one lane per program.  Scans the prefix list right to left (the
 // evaluation order of Sec. III-A) and emits instructions in that order.  A
 // terminal at position i is the first operand of the function at i-1 exactly
@@ -467,11 +538,16 @@ __device__ __forceinline__ void apply_unary(uint32_t fn, float (&t)[R], const Ma
 // ---------------------------------------------------------------------------
 constexpr uint32_t kShStartMask = 0x3fffffffu;   // shadow entry: start | const-only << 30 | active << 31
 
-__global__ __launch_bounds__(kBlock) void k_compile(PopView pop, uint4* __restrict__ code,
+__global__ __launch_bounds__(kBlock) void k_compile(PopView pop, OrderArgs oa, uint4* __restrict__ code,
                                                      int32_t* __restrict__ clen, int fold) {
     __shared__ uint32_t shadow[GP_MAX_STACK][kBlock];
     __shared__ float shadow_v[GP_MAX_STACK][kBlock];   // value of a const-only entry
-    const int32_t p = static_cast<int32_t>(blockIdx.x) * kBlock + threadIdx.x;
+    static_assert(sizeof(OrderLds) <= sizeof(shadow), "");
+    if (blockIdx.x == 0) {
+        order_programs<kBlock>(oa, *reinterpret_cast<OrderLds*>(&shadow[0][0]));
+        return;
+    }
+    const int32_t p = (static_cast<int32_t>(blockIdx.x) - 1) * kBlock + threadIdx.x;
     if (p >= pop.P) return;
     const int64_t off = pop.prog_off[p];
     const int32_t L = pop.len[p];
@@ -894,7 +970,7 @@ struct ParNodes {
 };
 constexpr uint8_t kEntMask = 31, kLeaf = 64, kConst = 128;
 
-// k_compile_eval: one wavefront per program.
+// compile_eval_program: one wavefront per program.
 //   1. From the right, blocks of 64 nodes: the stack height after each node of
 //      the right-to-left scan (a suffix sum of 1 - arity).  A binary function's
 //      first operand is the node after it; its second is the nearest node to
@@ -912,22 +988,33 @@ constexpr uint8_t kEntMask = 31, kLeaf = 64, kConst = 128;
 // every step waited for memory, and 64 programs took each other's branches,
 // the functions of constant subtrees among them.  A wavefront per program
 // takes about as many steps as the program is deep.
-__global__ __launch_bounds__(kBlock) void k_compile_eval(PopView pop, uint4* __restrict__ code,
-                                                          uint32_t* __restrict__ hdr, UserDefs ud, int32_t loss_fn,
-                                                          int32_t ex_mul, int32_t ex_add, Emit em, int32_t seq_only) {
-    __shared__ ParNodes nodes_all[kBlock / kWave];
-    __shared__ uint32_t seq_sh[kBlock / kWave][kCompileDepth];
-    __shared__ float seq_shv[kBlock / kWave][kCompileDepth];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wid = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-    const int32_t p = static_cast<int32_t>(blockIdx.x) * (kBlock / kWave) + wid;
-    if (p >= pop.P) return;
+struct EvalCompileLds {
+    ParNodes nodes;
+    uint32_t seq[kCompileDepth];
+    float seqv[kCompileDepth];
+};
+struct EvalCompile {
+    uint4* code;
+    uint32_t* hdr;
+    UserDefs ud;
+    int32_t loss_fn, ex_mul, ex_add;
+    Emit em;
+    int32_t seq_only;
+};
+
+__device__ __forceinline__ void compile_eval_program(const PopView& pop, const EvalCompile& ec, EvalCompileLds& sh,
+                                                     int32_t p, int lane) {
+    uint4* __restrict__ code = ec.code;
+    uint32_t* __restrict__ hdr = ec.hdr;
+    const UserDefs& ud = ec.ud;
+    const int32_t loss_fn = ec.loss_fn, ex_mul = ec.ex_mul, ex_add = ec.ex_add, seq_only = ec.seq_only;
+    const Emit& em = ec.em;
     const int64_t off = pop.prog_off[p];
     const int32_t L = pop.len[p];
     const uint32_t* pn = pop.nodes + off;
     const float* pc = pop.consts + pop.const_off[p];
     uint2* out = reinterpret_cast<uint2*>(code + off * ex_mul + static_cast<int64_t>(p) * ex_add);
-    ParNodes& nd = nodes_all[wid];
+    ParNodes& nd = sh.nodes;
     bool sequential = seq_only || L > kParNodes;
     if (!sequential) {
         const int nb = (L + kWave - 1) / kWave;
@@ -1026,7 +1113,7 @@ __global__ __launch_bounds__(kBlock) void k_compile_eval(PopView pop, uint4* __r
     }
     if (sequential) {
         if (lane == 0)
-            compile_sequential(pn, pc, L, out, hdr + p, em, ud, loss_fn, seq_sh[wid], seq_shv[wid]);
+            compile_sequential(pn, pc, L, out, hdr + p, em, ud, loss_fn, sh.seq, sh.seqv);
         return;
     }
     // ---- 3. and 4. places and instructions ----
@@ -1162,8 +1249,8 @@ __global__ __launch_bounds__(kBlock) void k_compile_eval(PopView pop, uint4* __r
 }
 
 // ---------------------------------------------------------------------------
-// k_compile_adjoint: one wavefront per program of at most kParNodes nodes, as
-// k_compile_eval: the forward instructions of the adjoint kernel (every
+// compile_adjoint_program: one wavefront per program of at most kParNodes nodes, as
+// compile_eval_program: the forward instructions of the adjoint kernel (every
 // constant stays, active operations record their partial derivatives), kOpEnd,
 // the reverse instructions, kOpEnd.
 // ---------------------------------------------------------------------------
@@ -1377,22 +1464,28 @@ __device__ __forceinline__ uint2 tape_ins(uint32_t handler, uint32_t e, int32_t 
     return make_uint2((kAPutTG + kind) * kOpBytes, (e - kTapeRegs - kTapeLds) * bytes);
 }
 
-__global__ __launch_bounds__(kAdjCompileWaves * kWave) void k_compile_adjoint(PopView pop, uint4* __restrict__ code,
-                                                                            uint32_t* __restrict__ hdr, Emit em) {
-    __shared__ AdjNodes nodes_all[kAdjCompileWaves];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wid = static_cast<int>(uniform(threadIdx.x >> 6));
-    const int32_t p = static_cast<int32_t>(blockIdx.x) * kAdjCompileWaves + wid;
-    if (p >= pop.P) return;
+struct AdjCompile {
+    uint4* code;
+    uint32_t* hdr;
+    Emit em;
+    double* gextra;      // sums of constants beyond kGradLds (cleared here)
+};
+
+__device__ __forceinline__ void compile_adjoint_program(const PopView& pop, const AdjCompile& ac, AdjNodes& nd,
+                                                        int32_t p, int lane) {
+    uint4* __restrict__ code = ac.code;
+    uint32_t* __restrict__ hdr = ac.hdr;
+    const Emit& em = ac.em;
+    const int64_t cend = pop.const_off[p + 1];
+    for (int64_t i = pop.const_off[p] + lane; i < cend; i += kWave) ac.gextra[i] = 0.0;
     const int64_t off = pop.prog_off[p];
     // (the caller's bound on the lengths is at most kParNodes)
     const int32_t L = min(pop.len[p], kParNodes);
     const uint32_t* pn = pop.nodes + off;
     const float* pc = pop.consts + pop.const_off[p];
     uint2* out = reinterpret_cast<uint2*>(code + off * kAdjCodePerNode);
-    AdjNodes& nd = nodes_all[wid];
     const int nb = (L + kWave - 1) / kWave;
-    // ---- heights and second operands (as k_compile_eval) ----
+    // ---- heights and second operands (as compile_eval_program) ----
     int carry = 0, lastpos = 0;
     for (int b = nb - 1; b >= 0; --b) {
         const int i = b * kWave + lane;
@@ -1631,6 +1724,48 @@ __global__ __launch_bounds__(kAdjCompileWaves * kWave) void k_compile_adjoint(Po
 }
 
 // ---------------------------------------------------------------------------
+// k_compile_streams: the evaluation kernel's stream of every program, the
+// adjoint's, or both, a wavefront each; block 0 orders the programs.  A
+// backward pass that evaluates first has the two compiled side by side (100
+// programs of up to 120 nodes: 35 and 53 us one after the other; a refinement
+// step of theirs on 10,007 rows 277 us with each compiler and the order in its
+// own launch, 232 so; the fitness of 256 programs on 4,096 rows 25.6 and 22.3).
+// ---------------------------------------------------------------------------
+template <bool EVAL, bool ADJOINT>
+constexpr int compile_waves() { return ADJOINT ? kAdjCompileWaves : kBlock / kWave; }
+
+template <bool EVAL, bool ADJOINT>
+__global__ __launch_bounds__((compile_waves<EVAL, ADJOINT>()) * kWave) void k_compile_streams(PopView pop, OrderArgs oa,
+                                                                                        EvalCompile ec,
+                                                                                        AdjCompile ac) {
+    constexpr int kW = compile_waves<EVAL, ADJOINT>();
+    constexpr size_t kLds = std::max(std::max(EVAL ? sizeof(EvalCompileLds) : 0, ADJOINT ? sizeof(AdjNodes) : 0) * kW,
+                                     sizeof(OrderLds));
+    __shared__ __align__(16) unsigned char lds[kLds];
+    if (blockIdx.x == 0) {
+        order_programs<kW * kWave>(oa, *reinterpret_cast<OrderLds*>(lds));
+        return;
+    }
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = static_cast<int>(uniform(threadIdx.x >> 6));
+    const int32_t per = (pop.P + kW - 1) / kW;      // blocks to compile one of the streams
+    int32_t b = static_cast<int32_t>(blockIdx.x) - 1;
+    // (the adjoint's first: it takes longer)
+    if constexpr (ADJOINT) {
+        if (b < per) {
+            const int32_t p = b * kW + wid;
+            if (p < pop.P) compile_adjoint_program(pop, ac, reinterpret_cast<AdjNodes*>(lds)[wid], p, lane);
+            return;
+        }
+        b -= per;
+    }
+    if constexpr (EVAL) {
+        const int32_t p = b * kW + wid;
+        if (p < pop.P) compile_eval_program(pop, ec, reinterpret_cast<EvalCompileLds*>(lds)[wid], p, lane);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // k_find_user: raises flag[0] (which the caller zeroes, k_zero_u32) if any
 // of the n nodes is a user function.
 // ---------------------------------------------------------------------------
@@ -1642,46 +1777,6 @@ __global__ __launch_bounds__(kBlock) void k_find_user(const uint32_t* __restrict
 }
 
 __global__ void k_zero_u32(uint32_t* __restrict__ p) { p[0] = 0u; }
-
-// ---------------------------------------------------------------------------
-// k_prepare: order programs by length (longest first) and reset the work
-// counter.  One block; counting sort over min(len, kBins-1), one bin per
-// thread in the scan.
-// ---------------------------------------------------------------------------
-constexpr int kBins = 1024;
-
-__global__ __launch_bounds__(kBins) void k_prepare(const int32_t* __restrict__ len, int32_t P,
-                                                   int32_t* __restrict__ order,
-                                                   uint32_t* __restrict__ counter) {
-    __shared__ int32_t start[kBins];
-    __shared__ int32_t wtot[kBins / kWave];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid >> 6;
-    start[tid] = 0;
-    if (tid < kQueues) counter[tid * kQueueStride] = 0u;
-    __syncthreads();
-    // key: kBins-1 - min(len, kBins-1), so longer programs come first
-    for (int p = tid; p < P; p += kBins) {
-        const int key = kBins - 1 - min(max(len[p], 0), kBins - 1);
-        atomicAdd(&start[key], 1);
-    }
-    __syncthreads();
-    const int32_t c = start[tid];
-    int32_t v = c;
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int32_t o = __shfl_up(v, d, kWave);
-        if (lane >= d) v += o;
-    }
-    if (lane == kWave - 1) wtot[wid] = v;
-    __syncthreads();
-    int32_t before = 0;
-    for (int q = 0; q < kBins / kWave; ++q) before += q < wid ? wtot[q] : 0;
-    start[tid] = before + v - c;
-    __syncthreads();
-    for (int p = tid; p < P; p += kBins) {
-        const int key = kBins - 1 - min(max(len[p], 0), kBins - 1);
-        order[atomicAdd(&start[key], 1)] = p;
-    }
-}
 
 // ---------------------------------------------------------------------------
 // k_ystats: per chunk, float64 sums of the weights and of the shifted target
@@ -3501,8 +3596,8 @@ gp_status grow(void** ptr, size_t* cap, size_t need_elems, size_t elem) {
 
 gp_status scratch_init(DeviceScratch& s, int dev) {
     if (s.counter) return GP_OK;
-    GP_HIP(hipMalloc(&s.counter, kCounterBytes));
-    GP_HIP(hipMemset(s.counter, 0, kCounterBytes));
+    GP_HIP(hipMalloc(&s.counter, 2 * kCounterBytes));
+    GP_HIP(hipMemset(s.counter, 0, 2 * kCounterBytes));
     hipDeviceProp_t prop;
     GP_HIP(hipGetDeviceProperties(&prop, dev));
     s.n_cu = prop.multiProcessorCount;
@@ -3864,24 +3959,23 @@ gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_data
     const int32_t batch = static_cast<int32_t>(std::min<int64_t>(8, std::max<int64_t>(1, n_items / claims)));
     *sch = Sched{chunk, static_cast<int32_t>(n_chunks), n_items, sc->order, static_cast<uint32_t*>(sc->counter),
                  batch, xp.lds_slots, 0, 0};
-    hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kBins), 0, st, pop->len, pop->n_programs, sc->order,
-                       static_cast<uint32_t*>(sc->counter));
+    const bool eval = !adjoint || both;
+    const OrderArgs oa{pop->len, pop->n_programs, sc->order, static_cast<uint32_t*>(sc->counter), adjoint ? 2 : 1};
+    const EvalCompile ec{sc->ecode, sc->ehdr, xp.defs, xp.loss_fn, xp.mul, xp.add,
+                         Emit{eval_ops(cfg->freg), cfg->R, cfg->freg == 0}, xp.lds_slots == kEvalLdsUser};
+    const AdjCompile ac{sc->code, reinterpret_cast<uint32_t*>(sc->clen), Emit{eval_ops(0), adjoint_R, 1}, sc->gextra};
+    auto compile = [&](auto kernel, int waves, int streams) {
+        const int64_t per = (static_cast<int64_t>(pop->n_programs) + waves - 1) / waves;
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(1 + streams * per)), dim3(waves * kWave), 0, st, *pv, oa,
+                           ec, ac);
+    };
+    if (adjoint_R > 0 && eval) compile(k_compile_streams<true, true>, compile_waves<true, true>(), 2);
+    else if (adjoint_R > 0) compile(k_compile_streams<false, true>, compile_waves<false, true>(), 1);
+    else if (eval) compile(k_compile_streams<true, false>, compile_waves<true, false>(), 1);
     GP_HIP(hipGetLastError());
-    const dim3 cgrid((pop->n_programs + kBlock - 1) / kBlock);
-    if (!adjoint || both) {
-        const dim3 egrid((pop->n_programs + kBlock / kWave - 1) / (kBlock / kWave));
-        const Emit em{eval_ops(cfg->freg), cfg->R, cfg->freg == 0};
-        hipLaunchKernelGGL(k_compile_eval, egrid, dim3(kBlock), 0, st, *pv, sc->ecode, sc->ehdr, xp.defs,
-                           xp.loss_fn, xp.mul, xp.add, em, xp.lds_slots == kEvalLdsUser);
-        GP_HIP(hipGetLastError());
-    }
-    if (adjoint_R > 0) {
-        const dim3 agrid((pop->n_programs + kAdjCompileWaves - 1) / kAdjCompileWaves);
-        hipLaunchKernelGGL(k_compile_adjoint, agrid, dim3(kAdjCompileWaves * kWave), 0, st, *pv, sc->code,
-                           reinterpret_cast<uint32_t*>(sc->clen), Emit{eval_ops(0), adjoint_R, 1});
-        GP_HIP(hipGetLastError());
-    } else if (adjoint) {
-        hipLaunchKernelGGL(k_compile, cgrid, dim3(kBlock), 0, st, *pv, sc->code, sc->clen, 0);
+    if (adjoint && adjoint_R == 0) {
+        const unsigned blocks = 1 + (pop->n_programs + kBlock - 1) / kBlock;
+        hipLaunchKernelGGL(k_compile, dim3(blocks), dim3(kBlock), 0, st, *pv, oa, sc->code, sc->clen, 0);
         GP_HIP(hipGetLastError());
     }
     *cvw = CodeView{adjoint ? sc->code : nullptr, adjoint ? sc->clen : nullptr,
@@ -5303,19 +5397,19 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
     const bool longer = pop->max_len > kParNodes;
     const int RA = g_forced ? g_forced_cfg.R
                             : (longer ? 0 : heuristic_cfg(data->n_features, data->n_rows, pop->n_programs, sc->n_cu).R);
+    const int64_t nc = std::max<int64_t>(pop->total_consts, 1);
+    rc = grow(reinterpret_cast<void**>(&sc->gextra), &sc->gextra_cap, static_cast<size_t>(nc), sizeof(double));
+    if (rc != GP_OK) return rc;
     rc = prepare(sc, pop, data, 1, metric, st, nullptr, &pv, &cvw, &dv, &sch, &cfg, true, needs_forward,
                  longer ? 0 : RA);
     if (rc != GP_OK) return rc;
     const int32_t P = pop->n_programs;
-    const int64_t nc = std::max<int64_t>(pop->total_consts, 1);
     const int64_t tape_max = 2 * static_cast<int64_t>(pop->max_len) + 2;   // tape entries per wavefront
     rc = grow(reinterpret_cast<void**>(&sc->stats), &sc->stats_cap, static_cast<size_t>(P) * kStats + 1,
               sizeof(double));
     if (rc != GP_OK) return rc;
     rc = grow(reinterpret_cast<void**>(&sc->gpart), &sc->gpart_cap, static_cast<size_t>(nc) * sch.n_chunks,
               sizeof(double));
-    if (rc != GP_OK) return rc;
-    rc = grow(reinterpret_cast<void**>(&sc->gextra), &sc->gextra_cap, static_cast<size_t>(nc), sizeof(double));
     if (rc != GP_OK) return rc;
     rc = grow(reinterpret_cast<void**>(&sc->fit_tmp), &sc->fit_tmp_cap, static_cast<size_t>(P), sizeof(float));
     if (rc != GP_OK) return rc;
@@ -5339,14 +5433,12 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
             hipLaunchKernelGGL(k_finalize<GP_METRIC_PEARSON>, dim3(fblocks), dim3(kBlock), 0, st, sc->part,
                                sc->ystat, sch.n_chunks, P, data->n_rows, has_w, fit, sc->stats);
         GP_HIP(hipGetLastError());
-        // the forward pass consumed the work counter: reset it (and reorder)
-        hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kBins), 0, st, pop->len, P, sc->order,
-                           static_cast<uint32_t*>(sc->counter));
+    }
+    if (longer) {      // (the compiler of the shorter clears it)
+        hipLaunchKernelGGL(k_zero, dim3(static_cast<unsigned>((nc + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
+                           sc->gextra, nc);
         GP_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_zero, dim3(static_cast<unsigned>((nc + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
-                       sc->gextra, nc);
-    GP_HIP(hipGetLastError());
     auto occ = [](const void* k) {
         int n = 0;
         (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kAdjWaves * kWave, 0);
@@ -5364,6 +5456,7 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
                             static_cast<size_t>(blocks) * kAdjWaves * static_cast<size_t>(wave_floats), sizeof(float));
         if (r2 != GP_OK) return r2;
         Sched sl = sch;
+        sl.counter += kCounterSet;
         sl.batch = 1;
         sl.blocks = static_cast<int32_t>(blocks);
         sl.wpb = kAdjWaves;
@@ -5388,6 +5481,7 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
                             static_cast<size_t>(blocks) * kAdjWaves * static_cast<size_t>(area_bytes / 4), sizeof(float));
         if (r2 != GP_OK) return r2;
         Sched sl = sch;
+        sl.counter += kCounterSet;
         sl.batch = 1;
         sl.blocks = static_cast<int32_t>(blocks);
         sl.wpb = kAdjWaves;
