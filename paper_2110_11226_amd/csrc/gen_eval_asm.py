@@ -41,7 +41,7 @@ SAVE = UN + len(UNARY)
 LOADS = SAVE + SLOTS
 SET = LOADS + SLOTS
 # exit codes: 1 + unary index; these for the binary functions
-EXIT_MAX, EXIT_MIN, EXIT_AT_TB, EXIT_AT_BT = 32, 33, 34, 35
+EXIT_AT_TB, EXIT_AT_BT = 34, 35
 
 
 def sections(freg):
@@ -166,7 +166,7 @@ class Gen:
                 self.he()
             elif name == "CUBE":
                 self.br("cube")
-            elif name in ("LOG", "SQRT", "SIN", "COS"):
+            elif name in ("LOG", "SQRT", "SIN", "COS", "INV"):
                 self.br(name.lower())
             else:
                 self.o(f"s_mov_b32 s{self.XC}, {1 + u}")
@@ -384,8 +384,26 @@ class Gen:
             self.interleave(lists)
         self.he()
 
-    def div(self, name, num, den):
-        """t = |den| > eps ? num / den : 1, the compiler's IEEE division."""
+    def minmax(self, name):
+        """t = max(t, m) or min(t, m): a NaN operand is ignored, equal operands'
+        sign bits are combined (-0 below +0)."""
+        self.label(name)
+        n = self.tmp + self.R
+        qs = [f"s[{self.Q0}:{self.Q0 + 1}]", f"s[{self.Q1}:{self.Q1 + 1}]", f"s[{self.Q2}:{self.Q2 + 1}]", "vcc"]
+        for j in range(self.R):
+            self.o(f"v_cmp_eq_f32_e64 {qs[j]}, {self.T(j)}, {self.M(j)}")
+        for j in range(self.R):
+            t, m = self.T(j), self.M(j)
+            # (operands quieted first: a signalling NaN would come through)
+            self.o(f"v_max_f32 v{n}, {t}, {t}")
+            self.o(f"v_max_f32 v{n + 1}, {m}, {m}")
+            self.o(f"v_{name}_f32 v{n}, v{n}, v{n + 1}")
+            self.o(f"v_{'and' if name == 'max' else 'or'}_b32 v{n + 1}, {t}, {m}")
+            self.o(f"v_cndmask_b32_e64 {t}, v{n}, v{n + 1}, {qs[j]}")
+        self.he()
+
+    def div(self, name, num, den, other="1.0"):
+        """t = |den| > eps ? num / den : other, the compiler's IEEE division."""
         self.label(name)
         for rows in self.batches():
             lists = []
@@ -419,7 +437,7 @@ class Gen:
             for b, j in enumerate(rows):
                 q = f"v{self.tmp + self.R + 5 * b + 3}"
                 pq = (self.Q0, self.Q1)[b]
-                self.o(f"v_cndmask_b32_e64 {self.T(j)}, 1.0, {q}, s[{pq}:{pq + 1}]")
+                self.o(f"v_cndmask_b32_e64 {self.T(j)}, {other}, {q}, s[{pq}:{pq + 1}]")
         self.he()
 
     def bodies(self):
@@ -460,7 +478,13 @@ class Gen:
                 self.label("m" + name)
                 self.prefetch()
             self.div(name, num, den)
-        for name, code in (("max", EXIT_MAX), ("min", EXIT_MIN), ("attm", EXIT_AT_TB), ("atmt", EXIT_AT_BT)):
+        self.div("inv", lambda j: "1.0", self.T, "0")
+        for name in ("max", "min"):
+            if self.mem:
+                self.label("m" + name)
+                self.prefetch()
+            self.minmax(name)
+        for name, code in (("attm", EXIT_AT_TB), ("atmt", EXIT_AT_BT)):
             if self.mem:
                 self.label("m" + name)
                 self.prefetch()
@@ -910,7 +934,7 @@ def main():
     code += ["};",
              "// What the interpreter leaves to its caller: 1 + unary index (top = f(top)), or one of",
              "// these on the top t and the operand register m.",
-             "enum : uint32_t {", "    kExitEnd = 0,", f"    kExitMax = {EXIT_MAX},", f"    kExitMin = {EXIT_MIN},",
+             "enum : uint32_t {", "    kExitEnd = 0,",
              f"    kExitAtan2TM = {EXIT_AT_TB},   // atan2(t, m)", f"    kExitAtan2MT = {EXIT_AT_BT},   // atan2(m, t)",
              "};", ""]
     names = {"PUTT": "PutT", "PUTM": "PutM", "PUTU": "PutU", "GMUL": "GMul", "MMUL": "MMul", "LOADM": "LoadM",

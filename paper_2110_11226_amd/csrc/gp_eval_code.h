@@ -53,8 +53,6 @@ enum : uint32_t {
 // these on the top t and the operand register m.
 enum : uint32_t {
     kExitEnd = 0,
-    kExitMax = 32,
-    kExitMin = 33,
     kExitAtan2TM = 34,   // atan2(t, m)
     kExitAtan2MT = 35,   // atan2(m, t)
 };

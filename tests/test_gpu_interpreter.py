@@ -174,3 +174,18 @@ def test_work_claims(gp, P, n, cfg):
     fin = np.isfinite(want)
     assert np.array_equal(np.isfinite(g), fin)
     assert np.allclose(g[fin], want[fin], rtol=1e-6, atol=0)
+
+
+def test_max_min_inverse_on_special_values(gp):
+    """max, min and the protected inverse over every pair of signed zeros,
+    NaN, infinities, denormals, the protection threshold and its neighbours."""
+    eps = np.float32(0.001)
+    v = np.array([0.0, -0.0, np.nan, np.inf, -np.inf, 1e-40, -1e-40, eps, -eps, np.nextafter(eps, np.float32(1)),
+                  np.nextafter(eps, np.float32(0)), 1.0, -1.0, 3.4e38, 3e38, 2.9e38], np.float32)
+    x = np.stack([np.repeat(v, len(v)), np.tile(v, len(v))])
+    v0, v1 = N(oracle.VAR, 0), N(oracle.VAR, 1)
+    progs = [([N(op), a, b], []) for op in (oracle.MAX, oracle.MIN) for a, b in ((v0, v1), (v1, v0))]
+    # operands from a slot of the stack
+    progs += [([N(op), N(oracle.NEG), v0, N(oracle.NEG), v1], []) for op in (oracle.MAX, oracle.MIN)]
+    progs += [([N(oracle.INV), v0], []), ([N(oracle.NEG), N(oracle.INV), N(oracle.NEG), v0], [])]
+    check(gp, progs, np.ascontiguousarray(x.astype(np.float32)))
