@@ -107,11 +107,11 @@ inline uint32_t allowed_function_mask() { return kBuiltinMask | user_defined_mas
     } while (0)
 
 // Device buffers of the mutation pipeline (gp_mutate.hip): donor lengths,
-// constant counts and offsets, offspring plans, lengths and constant
-// counts ([n + 1] each), and the donors themselves.
+// offspring plans, lengths and constant counts ([n + 1] each), and the donors
+// themselves, each in a place of the largest one's size.
 struct MutateWork {
-    int64_t *dlen = nullptr, *dnc = nullptr, *doff = nullptr, *dcoff = nullptr, *clen = nullptr, *cnc = nullptr;
-    int64_t dlen_cap = 0, dnc_cap = 0, doff_cap = 0, dcoff_cap = 0, clen_cap = 0, cnc_cap = 0;
+    int64_t *dlen = nullptr, *clen = nullptr, *cnc = nullptr;
+    int64_t dlen_cap = 0, clen_cap = 0, cnc_cap = 0;
     int4* plan = nullptr;
     int64_t plan_cap = 0;
     uint32_t* dnodes = nullptr;

@@ -1,6 +1,7 @@
-// gp_mutate.hip -- the genetic operations of a generation on the device, one
-// lane per offspring, with the draws, choices and output layout of the host
-// gp_mutate (so the two agree bit for bit).
+// gp_mutate.hip -- the genetic operations of a generation on the device, a
+// wavefront per offspring (a lane per subtree-mutation donor), with the draws,
+// choices and output layout of the host gp_mutate (so the two agree bit for
+// bit).
 //
 // Sec. II-A lists the operations (crossover, subtree, hoist and point
 // mutation, reproduction) and Sec. III-C2 gives hoisted crossover; the paper
@@ -8,10 +9,8 @@
 // Here a generation's offspring come from a short pipeline on one stream:
 //   k_plan          the operation of every offspring (draw 0 of stream 2)
 //                   and where its tournaments start (a block scan);
-//   k_donor<0>      length and constant count of every subtree-mutation
-//                   donor (the initialisation method on stream 3);
-//   k_scan2         donor offsets;
-//   k_donor<1>      the donors, written;
+//   k_donor         every subtree-mutation donor (the initialisation method on
+//                   stream 3), each in a place of the largest donor's size;
 //   k_child<0>      every offspring's splice, length and constant count;
 //   k_scan2         offspring offsets (nodes and constants), totals;
 //   k_child<1>      the offspring, constants renumbered in prefix order.
@@ -31,6 +30,8 @@ namespace {
 
 constexpr int kMutBlock = 64;     // one wave per block
 constexpr int kScanBlock = 1024;
+constexpr int kChildBlock = 256;   // four offspring, a wavefront each
+constexpr int64_t kSpreadLanes = int64_t{1} << 15;   // lanes of half a wavefront per SIMD
 constexpr int kPendMax = 32;      // pending depths of a tree walk (<= max depth + 1)
 
 // Counter-based draws of one offspring: words of Philox4x32-10 with counter
@@ -82,6 +83,14 @@ struct ProgSet {
     int32_t n;
 };
 
+// The donors: offspring i's at i * bound (where it has one).
+struct DonorSet {
+    const uint32_t* nodes;
+    const float* consts;
+    const int64_t* len;
+    int64_t bound;
+};
+
 __device__ __forceinline__ uint32_t resolve_gen(uint32_t gen, const uint32_t* d_gen) {
     return d_gen ? *d_gen : gen;
 }
@@ -114,14 +123,11 @@ __device__ __forceinline__ float draw_const(const InitDev& in, DevDraws& dr) {
 
 // ---------------------------------------------------------------------------
 // Program generation by the initialisation method (Sec. II-A), as the host's
-// Gen::program.  WRITE = false only counts nodes and constants; WRITE = true
-// writes the nodes to nodes[0..) and the constants, numbered in prefix
-// order, to consts[0..); the exact-length walk needs the constant count of
-// the counting pass to number right to left.
+// Gen::program, with the nodes to nodes[0..) and the constants, numbered in the
+// order they are drawn, to consts[0..) (an offspring numbers its own afresh).
 // ---------------------------------------------------------------------------
-template <bool WRITE>
 __device__ void gen_tree(const InitDev& in, const FnLds& f, DevDraws& dr, int target, bool full, int8_t* pend,
-                         uint32_t* nodes, float* consts, int64_t* n_nodes, int64_t* n_consts) {
+                         uint32_t* nodes, float* consts, int64_t* n_nodes) {
     int np = 1;
     pend[0] = 0;
     int used = 0;
@@ -146,28 +152,23 @@ __device__ void gen_tree(const InitDev& in, const FnLds& f, DevDraws& dr, int ta
         }
         if (func) {
             const uint32_t op = f.all[pick];
-            if (WRITE) nodes[pos] = GP_NODE(op, 0);
+            nodes[pos] = GP_NODE(op, 0);
             const int a = arity(op);
             for (int k = 0; k < a && np < kPendMax; ++k) pend[np++] = static_cast<int8_t>(depth + 1);
         } else if (pick < nf) {
-            if (WRITE) nodes[pos] = GP_NODE(GP_OP_VAR, pick);
+            nodes[pos] = GP_NODE(GP_OP_VAR, pick);
         } else {
-            const float c = draw_const(in, dr);
-            if (WRITE) {
-                nodes[pos] = GP_NODE(GP_OP_CONST, used);
-                consts[used] = c;
-            }
+            nodes[pos] = GP_NODE(GP_OP_CONST, used);
+            consts[used] = draw_const(in, dr);
             ++used;
         }
         ++pos;
     }
     *n_nodes = pos;
-    *n_consts = used;
 }
 
-template <bool WRITE>
-__device__ void gen_exact(const InitDev& in, const FnLds& f, DevDraws& dr, int64_t nc_total, uint32_t* nodes,
-                          float* consts, int64_t* n_nodes, int64_t* n_consts) {
+__device__ void gen_exact(const InitDev& in, const FnLds& f, DevDraws& dr, uint32_t* nodes, float* consts,
+                          int64_t* n_nodes) {
     uint32_t L = static_cast<uint32_t>(in.min_len) +
                  below(dr.next(), static_cast<uint32_t>(in.max_len - in.min_len + 1));
     const bool no_unary = in.n_un == 0;
@@ -191,34 +192,27 @@ __device__ void gen_exact(const InitDev& in, const FnLds& f, DevDraws& dr, int64
         int pick = static_cast<int>(below(dr.next(), static_cast<uint32_t>(nt + nu + nb)));
         if (pick < nt) {
             if (pick < nf) {
-                if (WRITE) nodes[i] = GP_NODE(GP_OP_VAR, pick);
+                nodes[i] = GP_NODE(GP_OP_VAR, pick);
             } else {
-                const float c = draw_const(in, dr);
-                if (WRITE) {
-                    // generated right to left, numbered left to right
-                    const int64_t slot = nc_total - 1 - nc;
-                    nodes[i] = GP_NODE(GP_OP_CONST, static_cast<uint32_t>(slot));
-                    consts[slot] = c;
-                }
+                nodes[i] = GP_NODE(GP_OP_CONST, static_cast<uint32_t>(nc));
+                consts[nc] = draw_const(in, dr);
                 ++nc;
             }
             ++h;
         } else if ((pick -= nt) < nu) {
-            if (WRITE) nodes[i] = GP_NODE(f.un[pick], 0);
+            nodes[i] = GP_NODE(f.un[pick], 0);
         } else {
-            if (WRITE) nodes[i] = GP_NODE(f.bin[pick - nu], 0);
+            nodes[i] = GP_NODE(f.bin[pick - nu], 0);
             --h;
         }
     }
     *n_nodes = L;
-    *n_consts = nc;
 }
 
-template <bool WRITE>
-__device__ void gen_program(const InitDev& in, const FnLds& f, DevDraws& dr, int8_t* pend, int64_t nc_total,
-                            uint32_t* nodes, float* consts, int64_t* n_nodes, int64_t* n_consts) {
+__device__ void gen_program(const InitDev& in, const FnLds& f, DevDraws& dr, int8_t* pend, uint32_t* nodes,
+                            float* consts, int64_t* n_nodes) {
     if (in.method == GP_INIT_EXACT_LEN) {
-        gen_exact<WRITE>(in, f, dr, nc_total, nodes, consts, n_nodes, n_consts);
+        gen_exact(in, f, dr, nodes, consts, n_nodes);
         return;
     }
     bool full;
@@ -226,7 +220,7 @@ __device__ void gen_program(const InitDev& in, const FnLds& f, DevDraws& dr, int
     else full = in.method == GP_INIT_FULL;
     const int depth = in.min_depth +
                       static_cast<int>(below(dr.next(), static_cast<uint32_t>(in.max_depth - in.min_depth + 1)));
-    gen_tree<WRITE>(in, f, dr, depth, full, pend, nodes, consts, n_nodes, n_consts);
+    gen_tree(in, f, dr, depth, full, pend, nodes, consts, n_nodes);
 }
 
 // ---------------------------------------------------------------------------
@@ -333,131 +327,144 @@ __global__ __launch_bounds__(kScanBlock) void k_scan2(const int64_t* __restrict_
     }
 }
 
-// Clears the status word before a pipeline (a fill kernel, not a memset, so
-// that a captured graph replays it).
-__global__ void k_mut_reset(int64_t* __restrict__ info) {
-    if (threadIdx.x < 4) info[threadIdx.x] = 0;
+// Donors per wavefront: of its 64 lanes, those at multiples of 2^lg have an
+// offspring each.  A wavefront's lanes wait for its longest donor and take each
+// other's branches, so few of them do work while the offspring alone would not
+// fill the chip (spread()): donors of 1,024 offspring, trees of depth 2 to 6,
+// 25.6 us with 64 a wavefront, 20.8 with 4; exact lengths up to 120, 59 and 43.
+__device__ __forceinline__ int32_t offspring(int lg) {
+    const uint32_t at = blockIdx.x * kMutBlock + threadIdx.x;
+    return (at & ((1u << lg) - 1u)) == 0u ? static_cast<int32_t>(at >> lg) : INT32_MAX;
 }
 
 // ---------------------------------------------------------------------------
-// k_donor<WRITE>: one lane per offspring; only subtree-mutation offspring
-// have a donor.
+// k_donor: one lane per offspring; only subtree-mutation offspring have a
+// donor, of at most `bound` nodes.  Clears the pipeline's status words (a
+// kernel's store, not a memset, so that a captured graph replays it).
 // ---------------------------------------------------------------------------
-template <bool WRITE>
-__global__ __launch_bounds__(kMutBlock) void k_donor(InitDev in, EvolveDev ev, int32_t n, uint32_t gen,
+__global__ __launch_bounds__(kMutBlock) void k_donor(InitDev in, EvolveDev ev, int32_t n, int lg, uint32_t gen,
                                                      const uint32_t* d_gen, const int32_t* __restrict__ ops,
-                                                     int64_t* __restrict__ dlen, int64_t* __restrict__ dnc,
-                                                     const int64_t* __restrict__ doff,
-                                                     const int64_t* __restrict__ dcoff, uint32_t* __restrict__ dnodes,
-                                                     float* __restrict__ dconsts, int64_t donor_cap,
+                                                     int64_t* __restrict__ dlen, uint32_t* __restrict__ dnodes,
+                                                     float* __restrict__ dconsts, int64_t bound,
                                                      int64_t* __restrict__ info) {
     __shared__ FnLds f;
     __shared__ int8_t pend[kMutBlock][kPendMax];
     load_fns(f, in);
-    const int32_t i = blockIdx.x * kMutBlock + threadIdx.x;
-    if (i >= n) return;
-    const int32_t op = ops[i];
-    if (op != GP_GENOP_SUBTREE) {
-        if (!WRITE) {
-            dlen[i] = 0;
-            dnc[i] = 0;
-        }
-        return;
-    }
+    if (blockIdx.x == 0 && threadIdx.x < 4) info[threadIdx.x] = 0;
+    const int32_t i = offspring(lg);
+    if (i >= n || ops[i] != GP_GENOP_SUBTREE) return;
     const uint32_t g = resolve_gen(gen, d_gen);
     DevDraws dr(ev.seed, static_cast<uint32_t>(i), g, kStreamDonor);
-    int64_t nn = 0, nc = 0;
-    if (!WRITE) {
-        gen_program<false>(in, f, dr, pend[threadIdx.x], 0, nullptr, nullptr, &nn, &nc);
-        dlen[i] = nn;
-        dnc[i] = nc;
-        return;
-    }
-    // the donors must fit the library's buffer (their bound is exact, so
-    // this does not happen for valid settings); otherwise nothing is written
-    // and k_child treats every subtree-mutation offspring as invalid
-    if (doff[n] > donor_cap || dcoff[n] > donor_cap) {
-        atomicOr(reinterpret_cast<unsigned long long*>(info + 2), 4ull);
-        return;
-    }
-    gen_program<true>(in, f, dr, pend[threadIdx.x], dlen[i] > 0 ? dnc[i] : 0, dnodes + doff[i], dconsts + dcoff[i], &nn,
-                      &nc);
+    int64_t nn = 0;
+    gen_program(in, f, dr, pend[threadIdx.x], dnodes + i * bound, dconsts + i * bound, &nn);
+    dlen[i] = nn;
 }
 
 // ---------------------------------------------------------------------------
-// Splice arithmetic on read-only programs.
+// Splice arithmetic on read-only programs, by a whole wavefront: lane l takes
+// every 64th node, and what is summed along the prefix list (1 - arity, the
+// constants so far) is counted in the lanes' ballots.  All arguments and
+// results are the same in every lane.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ int lane_id() { return static_cast<int>(threadIdx.x & 63u); }
+__device__ __forceinline__ uint64_t lanes_below(int l) { return (uint64_t{1} << l) - 1; }
+
 // One past the last node of the subtree rooted at s (bounded by len).
 __device__ __forceinline__ int64_t subtree_end(const uint32_t* w, int64_t len, int64_t s) {
     int open = 1;
-    int64_t i = s;
-    while (open > 0 && i < len) {
-        open += arity(GP_NODE_OP(w[i])) - 1;
-        ++i;
+    for (int64_t c = s; c < len; c += 64) {
+        const int64_t i = c + lane_id();
+        const int ar = i < len ? arity(GP_NODE_OP(w[i])) : 1;
+        const uint64_t leaf = __ballot(ar == 0), bin = __ballot(ar == 2);
+        const uint64_t upto = lanes_below(lane_id()) | (uint64_t{1} << lane_id());
+        const int here = open + __popcll(bin & upto) - __popcll(leaf & upto);
+        const uint64_t done = __ballot(here == 0);
+        if (done) return min(c + __builtin_ctzll(done) + 1, len);
+        open += __popcll(bin) - __popcll(leaf);
     }
-    return i;
+    return len;
+}
+
+// A segment of the right-to-left scan: the height h after w[b-1] .. w[a], and
+// hmax, this lane's largest on the way.
+__device__ __forceinline__ void scan_heights(const uint32_t* w, int64_t a, int64_t b, int* h, int* hmax) {
+    for (int64_t c = b; c > a; c -= 64) {
+        const int64_t i = c - 1 - lane_id();
+        const int ar = i >= a ? arity(GP_NODE_OP(w[i])) : 1;
+        const uint64_t leaf = __ballot(ar == 0), bin = __ballot(ar == 2);
+        const uint64_t upto = lanes_below(lane_id()) | (uint64_t{1} << lane_id());
+        *hmax = max(*hmax, *h + __popcll(leaf & upto) - __popcll(bin & upto));
+        *h += __popcll(leaf) - __popcll(bin);
+    }
 }
 
 // Peak height of the right-to-left scan of parent[0:s) + donor[ds:de) + parent[e:L).
-__device__ int splice_peak(const uint32_t* pw, int64_t L, int64_t s, int64_t e, const uint32_t* dw, int64_t ds,
-                           int64_t de) {
+__device__ __forceinline__ int splice_peak(const uint32_t* pw, int64_t L, int64_t s, int64_t e, const uint32_t* dw,
+                                           int64_t ds, int64_t de) {
     int h = 0, hmax = 0;
-    for (int64_t i = L - 1; i >= e; --i) {
-        h += 1 - arity(GP_NODE_OP(pw[i]));
-        hmax = max(hmax, h);
-    }
-    for (int64_t i = de - 1; i >= ds; --i) {
-        h += 1 - arity(GP_NODE_OP(dw[i]));
-        hmax = max(hmax, h);
-    }
-    for (int64_t i = s - 1; i >= 0; --i) {
-        h += 1 - arity(GP_NODE_OP(pw[i]));
-        hmax = max(hmax, h);
-    }
+    scan_heights(pw, e, L, &h, &hmax);
+    scan_heights(dw, ds, de, &h, &hmax);
+    scan_heights(pw, 0, s, &h, &hmax);
+    for (int d = 32; d > 0; d >>= 1) hmax = max(hmax, __shfl_xor(hmax, d, 64));
     return hmax;
 }
 
 __device__ __forceinline__ int64_t count_consts(const uint32_t* w, int64_t a, int64_t b) {
-    int64_t c = 0;
-    for (int64_t i = a; i < b; ++i) c += GP_NODE_OP(w[i]) == GP_OP_CONST;
-    return c;
+    int64_t n = 0;
+    for (int64_t c = a; c < b; c += 64) {
+        const int64_t i = c + lane_id();
+        n += __popcll(__ballot(i < b && GP_NODE_OP(w[i]) == GP_OP_CONST));
+    }
+    return n;
 }
 
-// Copies w[a:b) to out, constants renumbered from *slot (values from cv by
+// Copies w[a:b) to out[*pos ..), constants renumbered from *slot (values from cv by
 // their old slot).
 __device__ __forceinline__ void copy_seg(const uint32_t* w, const float* cv, int64_t a, int64_t b, uint32_t* out,
                                          float* oc, int64_t* pos, uint32_t* slot) {
-    for (int64_t i = a; i < b; ++i) {
-        uint32_t x = w[i];
-        if (GP_NODE_OP(x) == GP_OP_CONST) {
-            oc[*slot] = cv[GP_NODE_ARG(x)];
-            x = GP_NODE(GP_OP_CONST, *slot);
-            ++*slot;
+    for (int64_t c = a; c < b; c += 64) {
+        const int64_t i = c + lane_id();
+        uint32_t x = i < b ? w[i] : 0u;
+        const bool is_const = i < b && GP_NODE_OP(x) == GP_OP_CONST;
+        const uint64_t consts = __ballot(is_const);
+        if (is_const) {
+            const uint32_t q = *slot + static_cast<uint32_t>(__popcll(consts & lanes_below(lane_id())));
+            oc[q] = cv[GP_NODE_ARG(x)];
+            x = GP_NODE(GP_OP_CONST, q);
         }
-        out[(*pos)++] = x;
+        if (i < b) out[*pos + (i - a)] = x;
+        *slot += static_cast<uint32_t>(__popcll(consts));
     }
+    *pos += max(b - a, int64_t{0});
 }
 
 // ---------------------------------------------------------------------------
-// k_child<WRITE>: one lane per offspring.  WRITE = false draws the splice
+// k_child<WRITE>: one wavefront per offspring.  WRITE = false draws the splice
 // (crossover / subtree: parent cut (s, e) and donor subtree (ds, de) after
 // hoisting; hoist: (s, e) and (s2, e2)), stores it in plan[i] and the child's
 // length and constant count; WRITE = true writes the child.  Point mutation
 // re-draws in both passes.  An index out of range (operation, tournament,
 // winner) sets info[2] bit 2 and yields the one-node program x0.
+//
+// A lane per offspring waited for memory at every node, and for the other
+// operations of its wavefront: with trees of depth 2 to 6, the two passes over
+// 1,024 offspring took 58 + 55 us, 11 + 12 so; over 65,536, 66 + 70 and 56 + 43.
 // ---------------------------------------------------------------------------
 template <bool WRITE>
-__global__ __launch_bounds__(kMutBlock) void k_child(
-    InitDev in, EvolveDev ev, ProgSet par, ProgSet don, int32_t n, uint32_t gen, const uint32_t* d_gen,
+__global__ __launch_bounds__(kChildBlock) void k_child(
+    InitDev in, EvolveDev ev, ProgSet par, DonorSet don, int32_t n, uint32_t gen, const uint32_t* d_gen,
     const int32_t* __restrict__ ops, const int32_t* __restrict__ first, const int32_t* __restrict__ winners,
     int32_t n_winners, int4* __restrict__ plan, int64_t* __restrict__ clen, int64_t* __restrict__ cnc,
     const int64_t* __restrict__ coff, const int64_t* __restrict__ ccoff, uint32_t* __restrict__ out_nodes,
     float* __restrict__ out_consts, int32_t* __restrict__ out_len, int64_t nodes_cap, int64_t consts_cap,
-    int64_t donor_cap, int64_t* __restrict__ info) {
+    int64_t* __restrict__ info) {
     __shared__ FnLds f;
     load_fns(f, in);
-    const int32_t i = blockIdx.x * kMutBlock + threadIdx.x;
-    if (i >= n) return;
+    const int32_t wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int64_t at = static_cast<int64_t>(blockIdx.x) * (kChildBlock / 64) + wave;
+    if (at >= n) return;
+    const int32_t i = static_cast<int32_t>(at);
+    const bool one = lane_id() == 0;      // the lane that writes what the wavefront has once
     if (WRITE) {
         if (coff[n] > nodes_cap || ccoff[n] > consts_cap) return;   // flagged by k_scan2
     }
@@ -465,19 +472,23 @@ __global__ __launch_bounds__(kMutBlock) void k_child(
     const int32_t need = op == GP_GENOP_CROSSOVER ? 2 : 1;
     const int32_t t0 = first[i];
     bool bad = op < 0 || op > GP_GENOP_REPRODUCTION || t0 < 0 || static_cast<int64_t>(t0) + need > n_winners;
-    if (op == GP_GENOP_SUBTREE && (don.off[don.n] > donor_cap || don.coff[don.n] > donor_cap)) bad = true;
     int32_t pa = 0, pb = 0;
     if (!bad) {
         pa = winners[t0];
         pb = need == 2 ? winners[t0 + 1] : 0;
         bad = pa < 0 || pa >= par.n || pb < 0 || pb >= par.n;
     }
+    auto counts = [&](int64_t len, int64_t consts) {
+        if (one) {
+            clen[i] = len;
+            cnc[i] = consts;
+        }
+    };
     if (bad) {
         if (!WRITE) {
-            atomicOr(reinterpret_cast<unsigned long long*>(info + 2), 2ull);
-            clen[i] = 1;
-            cnc[i] = 0;
-        } else {
+            if (one) atomicOr(reinterpret_cast<unsigned long long*>(info + 2), 2ull);
+            counts(1, 0);
+        } else if (one) {
             out_nodes[coff[i]] = GP_NODE(GP_OP_VAR, 0);
             out_len[i] = 1;
         }
@@ -493,6 +504,9 @@ __global__ __launch_bounds__(kMutBlock) void k_child(
     float* oc = out_consts + (WRITE ? ccoff[i] : 0);
     int64_t pos = 0;
     uint32_t slot = 0;
+    auto written = [&]() {
+        if (one) out_len[i] = static_cast<int32_t>(pos);
+    };
 
     if (op == GP_GENOP_CROSSOVER || op == GP_GENOP_SUBTREE) {
         const uint32_t* dw;
@@ -503,9 +517,9 @@ __global__ __launch_bounds__(kMutBlock) void k_child(
             dc = par.consts + par.coff[pb];
             DL = par.off[pb + 1] - par.off[pb];
         } else {
-            dw = don.nodes + don.off[i];
-            dc = don.consts + don.coff[i];
-            DL = don.off[i + 1] - don.off[i];
+            dw = don.nodes + i * don.bound;
+            dc = don.consts + i * don.bound;
+            DL = don.len[i];
         }
         int64_t s, e, ds, de;
         if (!WRITE) {
@@ -520,19 +534,15 @@ __global__ __launch_bounds__(kMutBlock) void k_child(
                 ds = ds + 1 + below(dr.next(), static_cast<uint32_t>(de - ds - 1));
                 de = subtree_end(dw, DL, ds);
             }
-            plan[i] = make_int4(static_cast<int>(s), static_cast<int>(e), static_cast<int>(ds), static_cast<int>(de));
-            clen[i] = L - (e - s) + (de - ds);
-            cnc[i] = count_consts(pw, 0, s) + count_consts(dw, ds, de) + count_consts(pw, e, L);
+            if (one)
+                plan[i] = make_int4(static_cast<int>(s), static_cast<int>(e), static_cast<int>(ds), static_cast<int>(de));
+            counts(L - (e - s) + (de - ds), count_consts(pw, 0, s) + count_consts(dw, ds, de) + count_consts(pw, e, L));
         } else {
             const int4 q = plan[i];
-            s = q.x;
-            e = q.y;
-            ds = q.z;
-            de = q.w;
-            copy_seg(pw, pc, 0, s, on, oc, &pos, &slot);
-            copy_seg(dw, dc, ds, de, on, oc, &pos, &slot);
-            copy_seg(pw, pc, e, L, on, oc, &pos, &slot);
-            out_len[i] = static_cast<int32_t>(pos);
+            copy_seg(pw, pc, 0, q.x, on, oc, &pos, &slot);
+            copy_seg(dw, dc, q.z, q.w, on, oc, &pos, &slot);
+            copy_seg(pw, pc, q.y, L, on, oc, &pos, &slot);
+            written();
         }
         return;
     }
@@ -542,27 +552,34 @@ __global__ __launch_bounds__(kMutBlock) void k_child(
             const int64_t e = subtree_end(pw, L, s);
             const int64_t s2 = s + below(dr.next(), static_cast<uint32_t>(e - s));
             const int64_t e2 = subtree_end(pw, L, s2);
-            plan[i] = make_int4(static_cast<int>(s), static_cast<int>(e), static_cast<int>(s2), static_cast<int>(e2));
-            clen[i] = L - (e - s) + (e2 - s2);
-            cnc[i] = count_consts(pw, 0, s) + count_consts(pw, s2, e2) + count_consts(pw, e, L);
+            if (one)
+                plan[i] = make_int4(static_cast<int>(s), static_cast<int>(e), static_cast<int>(s2), static_cast<int>(e2));
+            counts(L - (e - s) + (e2 - s2), count_consts(pw, 0, s) + count_consts(pw, s2, e2) + count_consts(pw, e, L));
         } else {
             const int4 q = plan[i];
             copy_seg(pw, pc, 0, q.x, on, oc, &pos, &slot);
             copy_seg(pw, pc, q.z, q.w, on, oc, &pos, &slot);
             copy_seg(pw, pc, q.y, L, on, oc, &pos, &slot);
-            out_len[i] = static_cast<int32_t>(pos);
+            written();
         }
         return;
     }
     if (op == GP_GENOP_POINT) {
+        // node by node (a node's draws depend on those before it), 64 at a time
+        // in the lanes' registers; each lane keeps its own node's result
         int n_const = static_cast<int>(count_consts(pw, 0, L));
         const int nf = in.n_features;
-        for (int64_t j = 0; j < L; ++j) {
-            uint32_t x = pw[j];
-            float v = 0.0f;
-            const uint32_t xop = GP_NODE_OP(x);
-            if (xop == GP_OP_CONST) v = pc[GP_NODE_ARG(x)];
-            if (unit(dr.next()) < ev.p_point_replace) {
+        for (int64_t c = 0; c < L; c += 64) {
+            const int64_t mine = c + lane_id();
+            uint32_t word = mine < L ? pw[mine] : 0u;
+            float value = 0.0f;
+            if (mine < L && GP_NODE_OP(word) == GP_OP_CONST) value = pc[GP_NODE_ARG(word)];
+            const int m = static_cast<int>(min(L - c, int64_t{64}));
+            for (int j = 0; j < m; ++j) {
+                if (!(unit(dr.next()) < ev.p_point_replace)) continue;
+                uint32_t x = __builtin_amdgcn_readlane(word, j);
+                float v = 0.0f;
+                const uint32_t xop = GP_NODE_OP(x);
                 const int ar = arity(xop);
                 if (ar > 0) {
                     const int ns = ar == 1 ? in.n_un : in.n_bin;
@@ -583,32 +600,34 @@ __global__ __launch_bounds__(kMutBlock) void k_child(
                         n_const = others + 1;
                     }
                 }
+                if (lane_id() == j) {
+                    word = x;
+                    value = v;
+                }
             }
             if (WRITE) {
-                if (GP_NODE_OP(x) == GP_OP_CONST) {
-                    oc[slot] = v;
-                    x = GP_NODE(GP_OP_CONST, slot);
-                    ++slot;
+                const bool is_const = mine < L && GP_NODE_OP(word) == GP_OP_CONST;
+                const uint64_t consts = __ballot(is_const);
+                if (is_const) {
+                    const uint32_t q = slot + static_cast<uint32_t>(__popcll(consts & lanes_below(lane_id())));
+                    oc[q] = value;
+                    word = GP_NODE(GP_OP_CONST, q);
                 }
-                on[pos] = x;
+                if (mine < L) on[mine] = word;
+                slot += static_cast<uint32_t>(__popcll(consts));
             }
-            ++pos;
         }
-        if (!WRITE) {
-            clen[i] = L;
-            cnc[i] = n_const;
-        } else {
-            out_len[i] = static_cast<int32_t>(pos);
-        }
+        pos = L;
+        if (!WRITE) counts(L, n_const);
+        else written();
         return;
     }
     // reproduction
     if (!WRITE) {
-        clen[i] = L;
-        cnc[i] = count_consts(pw, 0, L);
+        counts(L, count_consts(pw, 0, L));
     } else {
         copy_seg(pw, pc, 0, L, on, oc, &pos, &slot);
-        out_len[i] = static_cast<int32_t>(pos);
+        written();
     }
 }
 
@@ -620,6 +639,15 @@ int64_t donor_bound(const gp_init_params& in) {
     for (uint32_t op = GP_OP_ADD; op < GP_OP_LIMIT; ++op)
         has_binary |= arity(op) == 2 && ((in.function_mask >> op) & 1u);
     return has_binary ? (int64_t{1} << (in.max_depth + 1)) - 1 : in.max_depth + 1;
+}
+
+// The donors' spread over wavefronts (offspring()): one to a wavefront up to 511
+// offspring, all 64 from 16,384 on (there 16 to a wavefront took 35 us against
+// 37 for trees, 75 against 64 for exact lengths).
+int spread(int64_t n) {
+    int lg = 0;
+    while (lg < 6 && (n << (lg + 1)) < kSpreadLanes) ++lg;
+    return lg;
 }
 
 InitDev to_dev(const gp_init_params& p) {
@@ -716,9 +744,6 @@ gp_status mutate_work_reserve(MutateWork* w, int32_t n_offspring, const gp_init_
                                         "than 2^25 nodes; lower max_depth / max_len or mutate on the host");
     gp_status rc;
     if ((rc = grow_buf(&w->dlen, &w->dlen_cap, n1)) != GP_OK) return rc;
-    if ((rc = grow_buf(&w->dnc, &w->dnc_cap, n1)) != GP_OK) return rc;
-    if ((rc = grow_buf(&w->doff, &w->doff_cap, n1)) != GP_OK) return rc;
-    if ((rc = grow_buf(&w->dcoff, &w->dcoff_cap, n1)) != GP_OK) return rc;
     if ((rc = grow_buf(&w->clen, &w->clen_cap, n1)) != GP_OK) return rc;
     if ((rc = grow_buf(&w->cnc, &w->cnc_cap, n1)) != GP_OK) return rc;
     if ((rc = grow_buf(&w->plan, &w->plan_cap, n1)) != GP_OK) return rc;
@@ -729,8 +754,7 @@ gp_status mutate_work_reserve(MutateWork* w, int32_t n_offspring, const gp_init_
 }
 
 void mutate_work_free(MutateWork* w) {
-    for (void* p : {static_cast<void*>(w->dlen), static_cast<void*>(w->dnc), static_cast<void*>(w->doff),
-                    static_cast<void*>(w->dcoff), static_cast<void*>(w->clen), static_cast<void*>(w->cnc),
+    for (void* p : {static_cast<void*>(w->dlen), static_cast<void*>(w->clen), static_cast<void*>(w->cnc),
                     static_cast<void*>(w->plan), static_cast<void*>(w->dnodes), static_cast<void*>(w->dconsts)})
         if (p) (void)hipFree(p);
     *w = MutateWork{};
@@ -751,7 +775,12 @@ gp_status mutate_launch(MutateWork& w, const gp_evolve_params& evp, const gp_ini
     const InitDev in = to_dev(inp);
     const EvolveDev ev = to_dev(evp);
     const int32_t n = n_offspring;
-    hipLaunchKernelGGL(k_mut_reset, dim3(1), dim3(64), 0, s, info);
+    const int64_t bound = donor_bound(inp);
+    if (bound * n > w.donor_cap) return fail(GP_ERR_BUFFER_TOO_SMALL, "device mutation: the donors' buffers are too small");
+    const int lg = spread(n);
+    const dim3 grid(static_cast<unsigned>((std::max<int64_t>(static_cast<int64_t>(n) << lg, 1) + kMutBlock - 1) / kMutBlock));
+    const dim3 blk(kMutBlock);
+    hipLaunchKernelGGL(k_donor, grid, blk, 0, s, in, ev, n, lg, gen, d_gen, ops, w.dlen, w.dnodes, w.dconsts, bound, info);
     GP_HIP(hipGetLastError());
     if (n == 0) {
         hipLaunchKernelGGL(k_scan2, dim3(1), dim3(kScanBlock), 0, s, w.clen, w.cnc, 0, out.prog_off, out.const_off,
@@ -759,30 +788,21 @@ gp_status mutate_launch(MutateWork& w, const gp_evolve_params& evp, const gp_ini
         GP_HIP(hipGetLastError());
         return GP_OK;
     }
-    const dim3 grid((n + kMutBlock - 1) / kMutBlock), blk(kMutBlock);
-    hipLaunchKernelGGL(k_donor<false>, grid, blk, 0, s, in, ev, n, gen, d_gen, ops, w.dlen, w.dnc, w.doff, w.dcoff,
-                       w.dnodes, w.dconsts, w.donor_cap, info);
-    GP_HIP(hipGetLastError());
-    // donor overflow is a library bound, not the caller's capacity: bit 3
-    hipLaunchKernelGGL(k_scan2, dim3(1), dim3(kScanBlock), 0, s, w.dlen, w.dnc, n, w.doff, w.dcoff, w.donor_cap,
-                       w.donor_cap, static_cast<int64_t*>(nullptr));
-    GP_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_donor<true>, grid, blk, 0, s, in, ev, n, gen, d_gen, ops, w.dlen, w.dnc, w.doff, w.dcoff,
-                       w.dnodes, w.dconsts, w.donor_cap, info);
-    GP_HIP(hipGetLastError());
     const ProgSet p{par.nodes, par.prog_off, par.consts, par.const_off, par.n_programs};
-    const ProgSet d{w.dnodes, w.doff, w.dconsts, w.dcoff, n};
-    hipLaunchKernelGGL(k_child<false>, grid, blk, 0, s, in, ev, p, d, n, gen, d_gen, ops, first, winners, n_winners,
+    const DonorSet d{w.dnodes, w.dconsts, w.dlen, bound};
+    const dim3 cgrid(static_cast<unsigned>((static_cast<int64_t>(n) + kChildBlock / 64 - 1) / (kChildBlock / 64)));
+    const dim3 cblk(kChildBlock);
+    hipLaunchKernelGGL(k_child<false>, cgrid, cblk, 0, s, in, ev, p, d, n, gen, d_gen, ops, first, winners, n_winners,
                        w.plan, w.clen, w.cnc, static_cast<const int64_t*>(nullptr),
                        static_cast<const int64_t*>(nullptr), out.nodes, out.consts, out.len, out.node_capacity,
-                       out.const_capacity, w.donor_cap, info);
+                       out.const_capacity, info);
     GP_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_scan2, dim3(1), dim3(kScanBlock), 0, s, w.clen, w.cnc, n, out.prog_off, out.const_off,
                        out.node_capacity, out.const_capacity, info);
     GP_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_child<true>, grid, blk, 0, s, in, ev, p, d, n, gen, d_gen, ops, first, winners, n_winners,
+    hipLaunchKernelGGL(k_child<true>, cgrid, cblk, 0, s, in, ev, p, d, n, gen, d_gen, ops, first, winners, n_winners,
                        w.plan, w.clen, w.cnc, out.prog_off, out.const_off, out.nodes, out.consts, out.len,
-                       out.node_capacity, out.const_capacity, w.donor_cap, info);
+                       out.node_capacity, out.const_capacity, info);
     GP_HIP(hipGetLastError());
     return GP_OK;
 }
