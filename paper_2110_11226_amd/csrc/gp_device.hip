@@ -3307,107 +3307,113 @@ __global__ __launch_bounds__(kRsScatterBlock) void k_rs_scatter(const uint32_t* 
     }
 }
 
-// The target's ranks, from its sorted keys (one workgroup): rank2[row] is
-// twice the mean rank of the tied run holding the row, an integer.  Pass A,
-// ascending chunks of 1,024: the start of the run holding position i (an
-// inclusive max-scan: shuffles within each wavefront, the wavefronts' totals
-// through LDS, the carry of earlier chunks), kept in run_start.  Pass B,
-// descending: the end of the run (the mirror min-scan from the right), and
-// the weighted sums (w, w b, w b^2) of the centred ranks b = rank - (N+1)/2,
-// which every program's correlation shares (tsum).
-__global__ __launch_bounds__(1024) void k_spear_rank_target(const uint32_t* __restrict__ keys,
-                                                             const uint32_t* __restrict__ idx, int64_t N,
-                                                             const float* __restrict__ w,
-                                                             uint32_t* __restrict__ run_start,
-                                                             uint32_t* __restrict__ rank2_out,
-                                                             double* __restrict__ tsum) {
-    constexpr int kW = 1024 / kWave;                 // wavefronts in the block
-    __shared__ uint32_t wtot[kW];
-    __shared__ double red[3][kW];
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wid = tid >> 6;
-    const uint32_t* k = keys;
-    uint32_t* rs = run_start;
-    uint32_t carry = 0;
-    for (int64_t c0 = 0; c0 < N; c0 += 1024) {
-        const int64_t i = c0 + tid;
-        uint32_t v = 0;
-        if (i < N) v = (i == 0 || k[i] != k[i - 1]) ? static_cast<uint32_t>(i) : 0u;
-        for (int d = 1; d < kWave; d <<= 1) {
-            const uint32_t o = __shfl_up(v, d, kWave);
-            if (lane >= d) v = max(v, o);
+// First position in [lo, hi) of the sorted keys whose key is at least x (above:
+// above x), hi if there is none; by a whole wavefront, 64 probes at a time.
+__device__ __forceinline__ uint32_t run_bound(const uint32_t* __restrict__ k, uint32_t lo, uint32_t hi, uint32_t x,
+                                              bool above) {
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    while (lo < hi) {
+        const uint32_t step = (hi - lo + kWave - 1) / kWave;
+        const uint64_t at = static_cast<uint64_t>(lo) + static_cast<uint64_t>(lane) * step;
+        bool past = true;
+        if (at < hi) {
+            const uint32_t key = k[at];
+            past = above ? key > x : key >= x;
         }
-        if (lane == kWave - 1) wtot[wid] = v;
-        __syncthreads();
-        uint32_t pre = carry, all = carry;
-        for (int q = 0; q < kW; ++q) {
-            const uint32_t t = wtot[q];
-            if (q < wid) pre = max(pre, t);
-            all = max(all, t);
-        }
-        if (i < N) rs[i] = max(v, pre);
-        __syncthreads();
-        carry = all;
+        // the first lane past it: the answer lies after the probe before
+        const uint64_t m = __ballot(past);
+        const uint32_t f = m ? static_cast<uint32_t>(__builtin_ctzll(m)) : kWave;
+        const uint64_t end = static_cast<uint64_t>(lo) + static_cast<uint64_t>(f) * step;
+        hi = end < hi ? static_cast<uint32_t>(end) : hi;
+        if (step == 1) return hi;
+        if (f > 0) lo += (f - 1) * step + 1;
     }
+    return hi;
+}
+
+// Where a lane's tied run lies, from the ballot S of the run starts among 64
+// consecutive positions: the lane of its start (the highest at or below) and
+// of the next one.
+__device__ __forceinline__ int run_first(uint64_t S, int lane) {
+    return 63 - __builtin_clzll(S & (~0ull >> (63 - lane)));
+}
+__device__ __forceinline__ int run_next(uint64_t S, int lane) { return __builtin_ctzll(S & ~(~0ull >> (63 - lane))); }
+
+// The target's ranks, from its sorted keys: rank2[row] is twice the mean rank
+// of the tied run holding the row, an integer.  A wavefront takes 64
+// consecutive positions at a time: the runs that lie within them come from one
+// ballot, and the first's start and the last's end, where the neighbouring
+// keys are equal, from a search of the sorted keys.  Each block leaves its
+// weighted sums (w, w b, w b^2) of the centred ranks b = rank - (N+1)/2, which
+// every program's correlation shares.  One block that scanned all keys took
+// 160 us for 65,536 rows, 4.8 here.
+constexpr int kTargetBlocks = 512;
+
+__global__ __launch_bounds__(kBlock) void k_spear_rank_target(const uint32_t* __restrict__ keys,
+                                                               const uint32_t* __restrict__ idx, int64_t N,
+                                                               const float* __restrict__ w,
+                                                               uint32_t* __restrict__ rank2_out,
+                                                               double* __restrict__ tsum) {
+    constexpr int kW = kBlock / kWave;
+    __shared__ double red[3][kW];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = static_cast<int>(uniform(threadIdx.x >> 6));
+    const uint32_t n = static_cast<uint32_t>(N);      // below 2^31
     const double mid = 0.5 * (static_cast<double>(N) + 1.0);
-    double s_w = 0.0, s_b = 0.0, s_bb = 0.0;
-    uint32_t carry_end = static_cast<uint32_t>(N);
-    for (int64_t c1 = ((N + 1023) / 1024) * 1024; c1 > 0; c1 -= 1024) {
-        const int64_t i = c1 - 1024 + tid;
-        uint32_t v = 0xffffffffu;
-        if (i < N) v = (i == N - 1 || k[i] != k[i + 1]) ? static_cast<uint32_t>(i + 1) : 0xffffffffu;
-        for (int d = 1; d < kWave; d <<= 1) {
-            const uint32_t o = __shfl_down(v, d, kWave);
-            if (lane + d < kWave) v = min(v, o);
+    double v[3] = {0.0, 0.0, 0.0};
+    for (uint32_t c = (blockIdx.x * kW + wid) * kWave; c < n; c += gridDim.x * (kW * kWave)) {
+        const uint32_t i = c + lane, m = min(n - c, static_cast<uint32_t>(kWave));
+        const bool in = i < n;
+        const uint32_t key = in ? keys[i] : 0u;
+        const uint32_t row = in ? idx[i] : 0u;
+        uint32_t prev = __shfl_up(key, 1, kWave);
+        if (lane == 0) prev = i > 0 ? keys[i - 1] : ~key;
+        const uint64_t S = __ballot(in && key != prev);
+        uint32_t start = c, end = c + m;       // of the run before the first start, and of the last run
+        const uint32_t k0 = uniform(key), kl = static_cast<uint32_t>(__builtin_amdgcn_readlane(key, m - 1));
+        if (!(S & 1ull)) start = run_bound(keys, 0, c, k0, false);
+        if (c + m < n && keys[c + m] == kl) end = run_bound(keys, c + m, n, kl, true);
+        if (S) {
+            const int first = __builtin_ctzll(S), last = 63 - __builtin_clzll(S);
+            if (lane >= first) start = c + run_first(S, lane);
+            if (lane < last) end = c + run_next(S, lane);
         }
-        if (lane == 0) wtot[wid] = v;
-        __syncthreads();
-        uint32_t suf = carry_end, all = carry_end;
-        for (int q = 0; q < kW; ++q) {
-            const uint32_t t = wtot[q];
-            if (q > wid) suf = min(suf, t);
-            all = min(all, t);
-        }
-        if (i < N) {
-            const uint32_t row = idx[i];
-            const uint32_t r2 = rs[i] + 1u + min(v, suf);
+        if (in) {
+            const uint32_t r2 = start + 1u + end;
             rank2_out[row] = r2;
             const double wv = w ? static_cast<double>(w[row]) : 1.0;
             const double b = 0.5 * static_cast<double>(r2) - mid;
-            s_w += wv;
-            s_b += wv * b;
-            s_bb += wv * b * b;
+            v[0] += wv;
+            v[1] += wv * b;
+            v[2] += wv * b * b;
         }
-        __syncthreads();
-        carry_end = all;
     }
-    double v[3] = {s_w, s_b, s_bb};
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
         const double t = wave_sum(v[q]);
         if (lane == 0) red[q][wid] = t;
     }
     __syncthreads();
-    if (tid < 3) {
+    if (threadIdx.x < 3) {
         double acc = 0.0;
-        for (int j = 0; j < kW; ++j) acc += red[tid][j];
-        tsum[tid] = acc;
+        for (int j = 0; j < kW; ++j) acc += red[threadIdx.x][j];
+        tsum[threadIdx.x * kTargetBlocks + blockIdx.x] = acc;
     }
 }
 
 // Rank correlation of a batch of programs, one workgroup per program and one
-// pass over its sorted keys.  The tied run holding position i spans
-// [start, end) and twice its mean rank is start + 1 + end.  Each block of
-// 1,024 positions finds starts by a max-scan from the left and ends by a
-// min-scan from the right (wavefront shuffles, the wavefronts' totals in
-// double-buffered LDS: one barrier per block of positions).  A run that
-// reaches past the block is still open: each thread sums its rows' weights
-// and weighted target ranks for it, and folds those sums in with the run's
-// mean rank in the block whose first end closes the run (its start is then
-// the carry of the earlier blocks).  With a = rank - (N+1)/2 for the program
-// and b likewise for the target, the weighted sums of a, a^2 and a b and the
-// target's shared sums (tsum) give |r|: 0 for a constant rank vector, NaN if
-// the outputs or the target held a NaN.  Two blocks' loads go out together.
+// pass over its sorted keys, each wavefront a range of its own.  The tied run
+// holding position i spans [start, end) and twice its mean rank is start + 1 +
+// end.  Of 64 consecutive positions a ballot marks the run starts; the run
+// still open at their end is carried on: each lane sums its rows' weights and
+// weighted target ranks for it, and folds those sums in with the run's mean
+// rank where it ends.  A range's first start and last end, where a run crosses
+// its edge, come from a search of the sorted keys, so the wavefronts never
+// wait for each other (scans over a workgroup's 1,024 positions, a barrier
+// each: 204 us for 512 programs on 65,536 rows, 96 here).  With a = rank -
+// (N+1)/2 for the program and b likewise for the target, the weighted sums of
+// a, a^2 and a b and the target's sums (tsum, by its blocks) give |r|: 0 for a
+// constant rank vector, NaN if the outputs or the target held a NaN.
 // Unweighted, the sorted values are the target ranks themselves; weighted,
 // they are rows, whose target ranks and weights are gathered.
 template <bool WEIGHTED>
@@ -3415,105 +3421,88 @@ __global__ __launch_bounds__(1024) void k_spear_corr(const uint32_t* __restrict_
                                                       const uint32_t* __restrict__ vals, int64_t N,
                                                       const uint32_t* __restrict__ rank2_y,
                                                       const float* __restrict__ w,
-                                                      const double* __restrict__ tsum,
+                                                      const double* __restrict__ tsum, int32_t target_blocks,
                                                       const int32_t* __restrict__ nan_flag,
                                                       const int32_t* __restrict__ target_nan,
                                                       float* __restrict__ fitness, int32_t prog0) {
-    constexpr int kW = 1024 / kWave, kE = 2;
-    constexpr uint32_t kNone = 0xffffffffu;
-    __shared__ uint32_t wmax[2][kW], wmin[2][kW];
+    constexpr int kW = 1024 / kWave, kE = 4;
     __shared__ double red[3][kW];
     const int32_t seg = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wid = tid >> 6;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wid = static_cast<int>(uniform(threadIdx.x >> 6));
     const uint32_t n = static_cast<uint32_t>(N);      // below 2^31
-    const uint32_t* k = keys + static_cast<int64_t>(seg) * N;
-    const uint32_t* ix = vals + static_cast<int64_t>(seg) * N;
+    const uint32_t* __restrict__ k = keys + static_cast<int64_t>(seg) * N;
+    const uint32_t* __restrict__ ix = vals + static_cast<int64_t>(seg) * N;
     const double mid = 0.5 * (static_cast<double>(N) + 1.0);
     double s_a = 0.0, s_aa = 0.0, s_ab = 0.0;
-    double o_w = 0.0, o_wb = 0.0;     // this thread's rows of the open run
-    uint32_t carry = 0;               // start of the last run so far
-    int par = 0;
-    for (uint32_t c0 = 0; c0 < n; c0 += 1024 * kE) {
-        uint32_t kc[kE], ry[kE];
-        float wf[kE];
+    double o_w = 0.0, o_wb = 0.0;     // this lane's rows of the open run
+    auto fold = [&](uint32_t start, uint32_t end) {
+        const double a = 0.5 * (static_cast<double>(start) + 1.0 + static_cast<double>(end)) - mid;
+        s_a += a * o_w;
+        s_aa += a * a * o_w;
+        s_ab += a * o_wb;
+    };
+    // this wavefront's range, whole groups of 64
+    const uint32_t groups = (n + kWave - 1) / kWave, per = (groups + kW - 1) / kW * kWave;
+    const uint32_t r0 = min(static_cast<uint32_t>(wid) * per, n), r1 = min(r0 + per, n);
+    if (r0 < r1) {
+        uint32_t last_key = r0 > 0 ? k[r0 - 1] : 0u;      // the key before the group
+        uint32_t open = r0;                               // start of the open run
+        if (r0 > 0 && k[r0] == last_key) open = run_bound(k, 0, r0, last_key, false);
+        for (uint32_t c0 = r0; c0 < r1; c0 += kWave * kE) {
+            uint32_t key[kE], ry[kE];
+            float wf[kE];
 #pragma unroll
-        for (int e = 0; e < kE; ++e) {
-            const uint32_t i = c0 + e * 1024 + tid;
-            kc[e] = i < n ? k[i] : 0u;
-            ry[e] = i < n ? ix[i] : 0u;
-        }
+            for (int e = 0; e < kE; ++e) {
+                const uint32_t i = min(c0 + e * kWave + lane, n - 1);
+                key[e] = k[i];
+                ry[e] = ix[i];
+            }
 #pragma unroll
-        for (int e = 0; e < kE; ++e) {
-            const uint32_t i = c0 + e * 1024 + tid;
-            const uint32_t row = ry[e];
-            if constexpr (WEIGHTED) {
-                ry[e] = i < n ? rank2_y[row] : 0u;
-                wf[e] = i < n ? w[row] : 1.0f;
-            } else {
+            for (int e = 0; e < kE; ++e) {
                 wf[e] = 1.0f;
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < kE; ++e) {
-            const uint32_t i = c0 + e * 1024 + tid;
-            const bool in = i < n;
-            // neighbours by shuffles, loads at the wavefront's edges
-            uint32_t kp = __shfl_up(kc[e], 1, kWave), kn = __shfl_down(kc[e], 1, kWave);
-            if (lane == 0) kp = (in && i > 0) ? k[i - 1] : 0u;
-            if (lane == kWave - 1) kn = (i + 1 < n) ? k[i + 1] : 0u;
-            const bool start = in && (i == 0 || kc[e] != kp);
-            const bool end = in && (i == n - 1 || kc[e] != kn);
-            uint32_t vs = start ? i : 0u;
-            uint32_t ve = end ? i + 1 : kNone;
-            for (int d = 1; d < kWave; d <<= 1) {
-                const uint32_t os = __shfl_up(vs, d, kWave);
-                const uint32_t oe = __shfl_down(ve, d, kWave);
-                if (lane >= d) vs = max(vs, os);
-                if (lane + d < kWave) ve = min(ve, oe);
-            }
-            if (lane == kWave - 1) wmax[par][wid] = vs;
-            if (lane == 0) wmin[par][wid] = ve;
-            __syncthreads();
-            // the wavefronts' totals, lane q holding wavefront q's: a prefix
-            // max and a suffix min over them by shuffles
-            uint32_t tm = lane < kW ? wmax[par][lane] : 0u;
-            uint32_t te = lane < kW ? wmin[par][lane] : kNone;
-            for (int d = 1; d < kW; d <<= 1) {
-                const uint32_t om = __shfl_up(tm, d, kWave);
-                const uint32_t oe = __shfl_down(te, d, kWave);
-                if (lane >= d) tm = max(tm, om);
-                if (lane + d < kWave) te = min(te, oe);
-            }
-            const uint32_t pre = max(carry, wid > 0 ? static_cast<uint32_t>(__shfl(tm, wid - 1, kWave)) : 0u);
-            const uint32_t all = max(carry, static_cast<uint32_t>(__shfl(tm, kW - 1, kWave)));
-            const uint32_t suf = wid < kW - 1 ? static_cast<uint32_t>(__shfl(te, wid + 1, kWave)) : kNone;
-            const uint32_t first_end = __shfl(te, 0, kWave);
-            if (first_end != kNone) {       // the open run (if any) ends here
-                const double a = 0.5 * (static_cast<double>(carry) + 1.0 + static_cast<double>(first_end)) - mid;
-                s_a += a * o_w;
-                s_aa += a * a * o_w;
-                s_ab += a * o_wb;
-                o_w = 0.0;
-                o_wb = 0.0;
-            }
-            if (in) {
-                const double wv = static_cast<double>(wf[e]);
-                const double b = 0.5 * static_cast<double>(ry[e]) - mid;
-                const uint32_t en = min(ve, suf);
-                if (en != kNone) {
-                    const double a = 0.5 * (static_cast<double>(max(vs, pre)) + 1.0 + static_cast<double>(en)) - mid;
-                    s_a += wv * a;
-                    s_aa += wv * a * a;
-                    s_ab += wv * a * b;
-                } else {
-                    o_w += wv;
-                    o_wb += wv * b;
+                if constexpr (WEIGHTED) {
+                    wf[e] = w[ry[e]];
+                    ry[e] = rank2_y[ry[e]];
                 }
             }
-            carry = all;
-            par ^= 1;
+#pragma unroll
+            for (int e = 0; e < kE; ++e) {
+                const uint32_t c = c0 + e * kWave, i = c + lane;
+                if (c >= r1) break;
+                const bool in = i < r1;
+                uint32_t prev = __shfl_up(key[e], 1, kWave);
+                if (lane == 0) prev = i > 0 ? last_key : ~key[e];
+                const uint64_t S = __ballot(in && key[e] != prev);
+                last_key = static_cast<uint32_t>(__builtin_amdgcn_readlane(key[e], kWave - 1));
+                const double wv = in ? static_cast<double>(wf[e]) : 0.0;
+                const double wb = wv * (0.5 * static_cast<double>(ry[e]) - mid);
+                if (S == 0ull) {
+                    o_w += wv;
+                    o_wb += wb;
+                    continue;
+                }
+                const int first = __builtin_ctzll(S), last = 63 - __builtin_clzll(S);
+                if (lane < first) {
+                    o_w += wv;
+                    o_wb += wb;
+                }
+                fold(open, c + first);
+                o_w = lane >= last ? wv : 0.0;
+                o_wb = lane >= last ? wb : 0.0;
+                open = c + last;
+                if (lane >= first && lane < last) {
+                    const double a = 0.5 * (static_cast<double>(c + run_first(S, lane)) + 1.0 + static_cast<double>(c + run_next(S, lane))) - mid;
+                    s_a += a * wv;
+                    s_aa += a * a * wv;
+                    s_ab += a * wb;
+                }
+            }
         }
+        uint32_t end = r1;
+        const uint32_t tail = k[r1 - 1];
+        if (r1 < n && k[r1] == tail) end = run_bound(k, r1, n, tail, true);
+        fold(open, end);
     }
     double v[3] = {s_a, s_aa, s_ab};
 #pragma unroll
@@ -3522,24 +3511,29 @@ __global__ __launch_bounds__(1024) void k_spear_corr(const uint32_t* __restrict_
         if (lane == 0) red[q][wid] = t;
     }
     __syncthreads();
-    if (tid == 0) {
-        double tot[3];
+    if (wid == 0) {
+        double tot[3], ts[3];
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             double acc = 0.0;
             for (int j = 0; j < kW; ++j) acc += red[q][j];
             tot[q] = acc;
+            double t = 0.0;
+            for (int j = lane; j < target_blocks; j += kWave) t += tsum[q * kTargetBlocks + j];
+            ts[q] = wave_sum(t);
         }
-        const double W = tsum[0];
-        const double va = tot[1] - tot[0] * tot[0] / W;
-        const double vb = tsum[2] - tsum[1] * tsum[1] / W;
-        const double cab = tot[2] - tot[0] * tsum[1] / W;
-        const bool constant = k[0] == k[n - 1];    // one run of equal values
-        float f;
-        if (nan_flag[seg] || *target_nan) f = __builtin_nanf("");
-        else if (constant || !(va > 0.0) || !(vb > 0.0) || !isfinite(va) || !isfinite(vb)) f = 0.0f;
-        else f = static_cast<float>(fabs(cab / sqrt(va * vb)));
-        fitness[prog0 + seg] = f;
+        if (lane == 0) {
+            const double W = ts[0];
+            const double va = tot[1] - tot[0] * tot[0] / W;
+            const double vb = ts[2] - ts[1] * ts[1] / W;
+            const double cab = tot[2] - tot[0] * ts[1] / W;
+            const bool constant = k[0] == k[n - 1];    // one run of equal values
+            float f;
+            if (nan_flag[seg] || *target_nan) f = __builtin_nanf("");
+            else if (constant || !(va > 0.0) || !(vb > 0.0) || !isfinite(va) || !isfinite(vb)) f = 0.0f;
+            else f = static_cast<float>(fabs(cab / sqrt(va * vb)));
+            fitness[prog0 + seg] = f;
+        }
     }
 }
 
@@ -3580,7 +3574,7 @@ struct DeviceScratch {
     float* fit_tmp = nullptr;
     size_t fit_tmp_cap = 0;
     // Spearman: sort keys (the first also takes the program outputs) and
-    // carried values, double-buffered; the target's run starts, digit counts,
+    // carried values, double-buffered; digit counts,
     // the target's ranks, NaN flags
     uint32_t* sp_k0 = nullptr;
     size_t sp_k0_cap = 0;
@@ -3590,8 +3584,6 @@ struct DeviceScratch {
     size_t sp_v0_cap = 0;
     uint32_t* sp_v1 = nullptr;
     size_t sp_v1_cap = 0;
-    uint32_t* sp_rs = nullptr;
-    size_t sp_rs_cap = 0;
     uint32_t* sp_cnt = nullptr;
     size_t sp_cnt_cap = 0;
     uint32_t* sp_r2y = nullptr;
@@ -3655,7 +3647,7 @@ bool scratch_empty(const DeviceScratch& s) {
     return !s.counter && !s.order && !s.part && !s.ystat && !s.code && !s.clen && !s.ecode && !s.ehdr &&
            !s.stats && !s.gpart &&
            !s.gextra && !s.tape && !s.fit_tmp && !s.sp_k0 && !s.sp_k1 && !s.sp_v0 && !s.sp_v1 &&
-           !s.sp_rs && !s.sp_cnt && !s.sp_r2y && !s.sp_nan && !s.sp_ty;
+           !s.sp_cnt && !s.sp_r2y && !s.sp_nan && !s.sp_ty;
 }
 
 // Frees every buffer of s (the caller has made its device current and idle).
@@ -3666,7 +3658,7 @@ void scratch_free(DeviceScratch& s) {
                     static_cast<void*>(s.stats), static_cast<void*>(s.gpart), static_cast<void*>(s.gextra),
                     static_cast<void*>(s.tape), static_cast<void*>(s.fit_tmp),
                     static_cast<void*>(s.sp_k0), static_cast<void*>(s.sp_k1), static_cast<void*>(s.sp_v0),
-                    static_cast<void*>(s.sp_v1), static_cast<void*>(s.sp_rs), static_cast<void*>(s.sp_cnt),
+                    static_cast<void*>(s.sp_v1), static_cast<void*>(s.sp_cnt),
                     static_cast<void*>(s.sp_r2y), static_cast<void*>(s.sp_nan), static_cast<void*>(s.sp_ty)})
         if (q) (void)hipFree(q);
     s = DeviceScratch{};
@@ -4216,12 +4208,11 @@ gp_status spearman_impl(DeviceScratch* sc, const gp_population_dev* pop, const g
     need(reinterpret_cast<void**>(&sc->sp_k1), &sc->sp_k1_cap, BN, sizeof(uint32_t));
     need(reinterpret_cast<void**>(&sc->sp_v0), &sc->sp_v0_cap, BN, sizeof(uint32_t));
     need(reinterpret_cast<void**>(&sc->sp_v1), &sc->sp_v1_cap, BN, sizeof(uint32_t));
-    need(reinterpret_cast<void**>(&sc->sp_rs), &sc->sp_rs_cap, static_cast<size_t>(N), sizeof(uint32_t));
     need(reinterpret_cast<void**>(&sc->sp_cnt), &sc->sp_cnt_cap, static_cast<size_t>(B) * kRsRadix * T,
          sizeof(uint32_t));
     need(reinterpret_cast<void**>(&sc->sp_r2y), &sc->sp_r2y_cap, static_cast<size_t>(N), sizeof(uint32_t));
     need(reinterpret_cast<void**>(&sc->sp_nan), &sc->sp_nan_cap, static_cast<size_t>(B) + 1, sizeof(int32_t));
-    need(reinterpret_cast<void**>(&sc->sp_ty), &sc->sp_ty_cap, 3, sizeof(double));
+    need(reinterpret_cast<void**>(&sc->sp_ty), &sc->sp_ty_cap, 3 * kTargetBlocks, sizeof(double));
     if (rc != GP_OK) return rc;
     auto fill_nan_flags = [&](int32_t* flags, int32_t n) -> gp_status {
         hipLaunchKernelGGL(k_fill_i32, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, flags,
@@ -4234,8 +4225,9 @@ gp_status spearman_impl(DeviceScratch* sc, const gp_population_dev* pop, const g
     int32_t* target_nan = sc->sp_nan + B;
     if ((rc = fill_nan_flags(target_nan, 1)) != GP_OK) return rc;
     if ((rc = radix_sort_segments(sc, data->y, nullptr, N, 1, target_nan, st)) != GP_OK) return rc;
-    hipLaunchKernelGGL(k_spear_rank_target, dim3(1), dim3(1024), 0, st, sc->sp_k0, sc->sp_v0, N, data->w,
-                       sc->sp_rs, sc->sp_r2y, sc->sp_ty);
+    const int32_t target_blocks = static_cast<int32_t>(std::min<int64_t>((N + kBlock - 1) / kBlock, kTargetBlocks));
+    hipLaunchKernelGGL(k_spear_rank_target, dim3(target_blocks), dim3(kBlock), 0, st, sc->sp_k0, sc->sp_v0, N, data->w,
+                       sc->sp_r2y, sc->sp_ty);
     GP_HIP(hipGetLastError());
     for (int32_t p0 = 0; p0 < P; p0 += B) {
         const int32_t b = std::min(B, P - p0);
@@ -4261,10 +4253,10 @@ gp_status spearman_impl(DeviceScratch* sc, const gp_population_dev* pop, const g
             return rc;
         if (data->w)
             hipLaunchKernelGGL(k_spear_corr<true>, dim3(b), dim3(1024), 0, st, sc->sp_k0, sc->sp_v0, N, sc->sp_r2y,
-                               data->w, sc->sp_ty, sc->sp_nan, target_nan, fitness, p0);
+                               data->w, sc->sp_ty, target_blocks, sc->sp_nan, target_nan, fitness, p0);
         else
             hipLaunchKernelGGL(k_spear_corr<false>, dim3(b), dim3(1024), 0, st, sc->sp_k0, sc->sp_v0, N, sc->sp_r2y,
-                               nullptr, sc->sp_ty, sc->sp_nan, target_nan, fitness, p0);
+                               nullptr, sc->sp_ty, target_blocks, sc->sp_nan, target_nan, fitness, p0);
         GP_HIP(hipGetLastError());
     }
     return GP_OK;
