@@ -300,13 +300,18 @@ def _torch():
 
 
 def _tptr(t):
-    return None if t is None else _vp(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
+    """The stream's handle; the current one's is asked for as such (a
+    torch.cuda.Stream object costs more than the smallest call's kernel)."""
+    if stream is not None:
+        return stream.cuda_stream
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return _vp(s.cuda_stream)
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 class DevicePopulation:
@@ -434,7 +439,7 @@ def tournament(fit, length, metric="mse", parsimony=0.0, tournament_size=20, n_t
     _check(_tournament(_tptr(fit), _tptr(length), P, metric_id(metric), float(parsimony),
                        int(tournament_size), T, int(seed), int(generation), _tptr(out), _stream(stream)),
            "gp_tournament")
-    return out[:T]
+    return out if out.shape[0] == T else out[:T]
 
 
 def fitness_backward(pop: DevicePopulation, data: DeviceDataset, metric="mse", grad_fitness=None,
