@@ -1051,60 +1051,66 @@ __device__ __forceinline__ void compile_eval_program(const PopView& pop, const E
         }
         wave_lds_sync();
         // ---- 2. entries, instructions, constants ----
+        // (a round reads both operands' words at once and chooses: read as they
+        // were needed, one after the other, they cost a round three latencies)
+        uint64_t folds = 0;            // blocks with a function of constants
         for (int b = nb - 1; b >= 0; --b) {
             const int i = b * kWave + lane;
             const bool valid = i < L;
             const uint32_t op = valid ? nd.op[i] : 0u;
             const int ar = arity(op);
             const int c1 = min(i + 1, L - 1), c2 = valid && ar == 2 ? nd.sec[i] : c1;
-            bool done = !valid;
             // an operand outside the block is done
             const uint64_t need = (ar >= 1 && c1 < (b + 1) * kWave ? 1ull << (c1 & 63) : 0ull) |
                                   (ar == 2 && c2 < (b + 1) * kWave ? 1ull << (c2 & 63) : 0ull);
+            bool done = !valid || ar == 0, fold = false;
+            if (valid && ar == 0) {
+                nd.ent[i] = static_cast<uint8_t>(1 | (op == GP_OP_CONST ? kConst : kLeaf));
+                nd.cnt[i] = 1;
+                nd.val[i] = op == GP_OP_CONST ? pc[pn[i] >> 8] : 0.0f;
+            }
+            wave_lds_sync();
             for (int round = 0; round <= kWave; ++round) {
                 const uint64_t ready = __ballot(done);
                 if (ready == ~0ull) break;
+                const uint32_t e1 = nd.ent[c1], e2 = nd.ent[c2], n1 = nd.cnt[c1], n2 = nd.cnt[c2];
                 if (!done && (need & ~ready) == 0) {
-                    uint32_t ent = 1, cnt = 1;
-                    float v = 0.0f;
-                    if (ar == 0) {
-                        ent |= op == GP_OP_CONST ? kConst : kLeaf;
-                        if (op == GP_OP_CONST) v = pc[pn[i] >> 8];
-                    } else if (ar == 1) {
-                        const uint32_t e = nd.ent[c1];
-                        if (e & kConst) {
-                            float t[1] = {nd.val[c1]};
-                            apply_unary<1>(unary_index(op), t, global_tabs());
-                            v = t[0];
-                            ent = 1 | kConst;
-                        } else {
-                            ent = max(e & kEntMask, 1u);
-                            cnt = nd.cnt[c1] + 1u;
-                        }
-                    } else {
-                        const uint32_t ea = nd.ent[c1], eb = nd.ent[c2];
-                        if ((ea & kConst) && (eb & kConst)) {
-                            float a[1] = {nd.val[c1]};
-                            const float bb[1] = {nd.val[c2]};
-                            apply_binary<1>(binary_index(op), a, bb);
-                            v = a[0];
-                            ent = 1 | kConst;
-                        } else if (ea & (kLeaf | kConst)) {
-                            ent = eb & kEntMask;
-                            cnt = nd.cnt[c2] + 1u;
-                        } else if (eb & (kLeaf | kConst)) {
-                            ent = ea & kEntMask;
-                            cnt = nd.cnt[c1] + 1u;
-                        } else {
-                            const uint32_t na = ea & kEntMask, nb2 = eb & kEntMask;
-                            ent = na == nb2 ? na + 1u : max(na, nb2);
-                            cnt = nd.cnt[c1] + nd.cnt[c2] + 1u;
-                        }
-                    }
+                    const bool two = ar == 2, t1 = e1 & (kLeaf | kConst), t2 = e2 & (kLeaf | kConst);
+                    const uint32_t m1 = e1 & kEntMask, m2 = e2 & kEntMask;
+                    fold = (e1 & kConst) && (!two || (e2 & kConst));
+                    uint32_t ent = two ? (t1 ? m2 : t2 ? m1 : m1 == m2 ? m1 + 1u : max(m1, m2)) : max(m1, 1u);
+                    uint32_t cnt = 1u + (two ? (t1 ? n2 : t2 ? n1 : n1 + n2) : n1);
+                    ent = fold ? 1u | kConst : ent;
+                    cnt = fold ? 1u : cnt;
                     nd.ent[i] = static_cast<uint8_t>(ent);
                     nd.cnt[i] = static_cast<uint16_t>(cnt);
-                    nd.val[i] = v;
                     done = true;
+                }
+                wave_lds_sync();
+            }
+            if (__ballot(fold)) folds |= 1ull << b;
+        }
+        // the values of constant subtrees, by themselves: among the rounds above,
+        // each with such a node would wait for the functions
+        for (; folds; folds &= ~(1ull << (63 - __builtin_clzll(folds)))) {
+            const int b = 63 - __builtin_clzll(folds);
+            const int i = b * kWave + lane, ii = min(i, L - 1);
+            const uint32_t op = nd.op[ii];
+            const int ar = arity(op);
+            const int c1 = min(i + 1, L - 1), c2 = ar == 2 ? nd.sec[ii] : c1;
+            const uint64_t need = (c1 < (b + 1) * kWave ? 1ull << (c1 & 63) : 0ull) |
+                                  (c2 < (b + 1) * kWave ? 1ull << (c2 & 63) : 0ull);
+            bool todo = i < L && ar >= 1 && (nd.ent[ii] & kConst);
+            for (int round = 0; round <= kWave; ++round) {
+                const uint64_t left = __ballot(todo);
+                if (left == 0ull) break;
+                if (todo && (need & left) == 0) {
+                    float v[1] = {nd.val[c1]};
+                    const float second[1] = {nd.val[c2]};
+                    if (ar == 1) apply_unary<1>(unary_index(op), v, global_tabs());
+                    else apply_binary<1>(binary_index(op), v, second);
+                    nd.val[i] = v[0];
+                    todo = false;
                 }
                 wave_lds_sync();
             }
@@ -1254,13 +1260,15 @@ __device__ __forceinline__ void compile_eval_program(const PopView& pop, const E
 // constant stays, active operations record their partial derivatives), kOpEnd,
 // the reverse instructions, kOpEnd.
 // ---------------------------------------------------------------------------
+// Forward and reverse instructions, tape entries, feature fetches: one word,
+// read and written at once.
+struct __align__(8) AdjCounts {
+    uint16_t f, r, t, x;
+};
 struct AdjNodes {
     uint16_t sec[kParNodes];      // second operand of a binary function
-    uint16_t cnt[kParNodes], rcnt[kParNodes], tcnt[kParNodes], fcnt[kParNodes];
-                                  // forward and reverse instructions, tape entries, feature
-                                  // fetches of the subtree
-    uint16_t start[kParNodes], rstart[kParNodes], tstart[kParNodes], fstart[kParNodes];
-                                  // where they begin
+    AdjCounts cnt[kParNodes];     // of the subtree
+    AdjCounts start[kParNodes];   // where they begin (f = 0xffff: not known)
     uint8_t op[kParNodes], ent[kParNodes], lev[kParNodes];
     uint32_t feat[kParNodes / 2 + 1];   // the features in the order they are fetched
 };
@@ -1511,7 +1519,7 @@ __device__ __forceinline__ void compile_adjoint_program(const PopView& pop, cons
         if (valid) {
             nd.op[i] = static_cast<uint8_t>(op);
             nd.sec[i] = static_cast<uint16_t>(min(max(sec, 0), L - 1));
-            nd.start[i] = 0xffffu;
+            nd.start[i].f = 0xffffu;
         }
     }
     wave_lds_sync();
@@ -1522,78 +1530,61 @@ __device__ __forceinline__ void compile_adjoint_program(const PopView& pop, cons
         const uint32_t op = valid ? nd.op[i] : 0u;
         const int ar = arity(op);
         const int c1 = min(i + 1, L - 1), c2 = valid && ar == 2 ? nd.sec[i] : c1;
+        const uint32_t o1 = nd.op[c1], o2 = nd.op[c2];
         bool done = !valid;
         const uint64_t need = (ar >= 1 && c1 < (b + 1) * kWave ? 1ull << (c1 & 63) : 0ull) |
                               (ar == 2 && c2 < (b + 1) * kWave ? 1ull << (c2 & 63) : 0ull);
         for (int round = 0; round <= kWave; ++round) {
             const uint64_t ready = __ballot(done);
             if (ready == ~0ull) break;
+            // both operands' words at once, then the choice between them
+            const uint32_t e1 = nd.ent[c1], e2 = nd.ent[c2];
+            const AdjCounts n1 = nd.cnt[c1], n2 = nd.cnt[c2];
             if (!done && (need & ~ready) == 0) {
-                uint32_t ea = 0, eb = 0, ent = 1, fc = 0, cn = 0, rn = 0, tn = 0, act = 0;
+                const uint32_t ea = ar >= 1 ? e1 : 0u, eb = ar == 2 ? e2 : 0u;
+                uint32_t ent = 1u | kLeaf, fc = op != GP_OP_CONST, cn = 0, rn = 0, tn = 0;
+                const uint32_t act = ar == 0 ? op == GP_OP_CONST : ((ea | eb) & kActiveEnt) != 0u;
                 bool tc = false;
-                if (ar == 0) {
-                    ent = 1u | kLeaf;
-                    act = op == GP_OP_CONST;
-                    fc = op != GP_OP_CONST;
-                } else {
-                    ea = nd.ent[c1];
-                    if (ar == 2) eb = nd.ent[c2];
-                    act = ((ea | eb) & kActiveEnt) != 0u;
-                    if (ar == 1) {
-                        ent = max(ea & kEntMask, 1u);
-                        cn = nd.cnt[c1];
-                        rn = nd.rcnt[c1];
-                        tn = nd.tcnt[c1];
-                        fc = nd.fcnt[c1];
-                    } else {
-                        const BinShape sh = bin_shape(ea, eb);
-                        const int ce = sh.a_first ? c1 : c2, co = sh.a_first ? c2 : c1;
-                        cn = nd.cnt[ce];
-                        rn = nd.rcnt[ce];
-                        tn = nd.tcnt[ce];
-                        fc = nd.fcnt[c1] + nd.fcnt[c2];
-                        if (sh.fold) {
-                            ent = (sh.a_first ? ea : eb) & kEntMask;
-                            tc = nd.op[co] == GP_OP_CONST;
-                        } else {
-                            const uint32_t na = ea & kEntMask, nb2 = eb & kEntMask;
-                            ent = na == nb2 ? na + 1u : max(na, nb2);
-                            cn += nd.cnt[co];
-                            rn += nd.rcnt[co] + ((ea & eb & kActiveEnt) ? 1u : 0u);   // the slot taken back
-                            tn += nd.tcnt[co];
-                        }
-                    }
+                if (ar == 1) {
+                    ent = max(ea & kEntMask, 1u);
+                    cn = n1.f;
+                    rn = n1.r;
+                    tn = n1.t;
+                    fc = n1.x;
+                } else if (ar == 2) {
+                    const BinShape sh = bin_shape(ea, eb);
+                    const AdjCounts ne = sh.a_first ? n1 : n2, no = sh.a_first ? n2 : n1;
+                    const uint32_t na = ea & kEntMask, nb2 = eb & kEntMask;
+                    ent = sh.fold ? (sh.a_first ? na : nb2) : (na == nb2 ? na + 1u : max(na, nb2));
+                    tc = sh.fold && (sh.a_first ? o2 : o1) == GP_OP_CONST;
+                    cn = ne.f + (sh.fold ? 0u : no.f);
+                    rn = ne.r + (sh.fold ? 0u : no.r + ((ea & eb & kActiveEnt) ? 1u : 0u));   // the slot taken back
+                    tn = ne.t + (sh.fold ? 0u : no.t);
+                    fc = n1.x + n2.x;
                 }
                 // the tape entries are the highest entry a forward instruction names, plus one
                 // (the two counts in one word: as two variables the compiler keeps
                 // them in memory, chosen by address)
-                uint64_t n2 = static_cast<uint64_t>(rn) << 32 | cn;
+                uint64_t n64 = static_cast<uint64_t>(rn) << 32 | cn;
                 uint32_t te = 0;
                 adjoint_ops(op, act, 0u, tc, 0u, 0.0f, ea, eb, em,
                             [&](uint32_t, uint32_t e, int kind) __attribute__((always_inline)) {
-                                n2 += 1ull;
+                                n64 += 1ull;
                                 if (kind == 2) te = max(te, e + 1u);
                             },
-                            [&](uint32_t, uint32_t, int) __attribute__((always_inline)) { n2 += 1ull << 32; });
-                cn = static_cast<uint32_t>(n2);
-                rn = static_cast<uint32_t>(n2 >> 32);
+                            [&](uint32_t, uint32_t, int) __attribute__((always_inline)) { n64 += 1ull << 32; });
                 nd.ent[i] = static_cast<uint8_t>(ent | (act ? kActiveEnt : 0u));
-                nd.cnt[i] = static_cast<uint16_t>(cn);
-                nd.rcnt[i] = static_cast<uint16_t>(rn);
-                nd.tcnt[i] = static_cast<uint16_t>(tn + te);
-                nd.fcnt[i] = static_cast<uint16_t>(fc);
+                nd.cnt[i] = AdjCounts{static_cast<uint16_t>(n64), static_cast<uint16_t>(n64 >> 32),
+                                      static_cast<uint16_t>(tn + te), static_cast<uint16_t>(fc)};
                 done = true;
             }
             wave_lds_sync();
         }
     }
     // ---- from the root down: places ----
-    const int total = nd.cnt[0], rtotal = nd.rcnt[0];
+    const int total = nd.cnt[0].f, rtotal = nd.cnt[0].r;
     if (lane == 0) {
-        nd.start[0] = 0;
-        nd.rstart[0] = static_cast<uint16_t>(total + 1);
-        nd.tstart[0] = 0;
-        nd.fstart[0] = 0;
+        nd.start[0] = AdjCounts{0, static_cast<uint16_t>(total + 1), 0, 0};
         nd.lev[0] = 0;
     }
     wave_lds_sync();
@@ -1604,36 +1595,28 @@ __device__ __forceinline__ void compile_adjoint_program(const PopView& pop, cons
         const int ar = arity(op);
         const int c1 = min(i + 1, L - 1), c2 = valid && ar == 2 ? nd.sec[i] : c1;
         const uint32_t ea = nd.ent[c1], eb = nd.ent[c2];
+        // the operand evaluated first (a unary function's only one), and the other
+        const BinShape sh = bin_shape(ea, eb);
+        const int f = ar == 2 && !sh.a_first ? c2 : c1, q = f == c1 ? c2 : c1;
+        const AdjCounts own = nd.cnt[min(i, L - 1)], nf = nd.cnt[f], nq = nd.cnt[q];
+        const uint32_t back = (ea & eb & kActiveEnt) ? 1u : 0u;
         bool done = !valid;
         for (int round = 0; round <= kWave; ++round) {
             bool fresh = false;
             if (!done) {
-                const uint32_t start = nd.start[i];
-                if (start != 0xffffu) {
+                const AdjCounts at = nd.start[i];
+                const uint32_t lev = nd.lev[i];
+                if (at.f != 0xffffu) {
                     done = fresh = true;
-                    const uint32_t rs = nd.rstart[i], ts = nd.tstart[i], fs = nd.fstart[i], lev = nd.lev[i];
-                    if (ar == 1) {
-                        nd.rstart[c1] = static_cast<uint16_t>(rs + nd.rcnt[i] - nd.rcnt[c1]);
-                        nd.tstart[c1] = static_cast<uint16_t>(ts);
-                        nd.fstart[c1] = static_cast<uint16_t>(fs);
-                        nd.lev[c1] = static_cast<uint8_t>(lev);
-                        nd.start[c1] = static_cast<uint16_t>(start);
-                    } else if (ar == 2) {
-                        const BinShape sh = bin_shape(ea, eb);
-                        const int f = sh.a_first ? c1 : c2, s = sh.a_first ? c2 : c1;
+                    if (ar >= 1) {
                         // the reverse part ends with the operand evaluated first
-                        nd.rstart[f] = static_cast<uint16_t>(rs + nd.rcnt[i] - nd.rcnt[f]);
-                        nd.tstart[f] = static_cast<uint16_t>(ts);
-                        nd.fstart[f] = static_cast<uint16_t>(fs);
                         nd.lev[f] = static_cast<uint8_t>(lev);
-                        nd.start[f] = static_cast<uint16_t>(start);
-                        if (!sh.fold) {
-                            const uint32_t back = (ea & eb & kActiveEnt) ? 1u : 0u;
-                            nd.rstart[s] = static_cast<uint16_t>(rs + nd.rcnt[i] - nd.rcnt[f] - back - nd.rcnt[s]);
-                            nd.tstart[s] = static_cast<uint16_t>(ts + nd.tcnt[f]);
-                            nd.fstart[s] = static_cast<uint16_t>(fs + nd.fcnt[f]);
-                            nd.lev[s] = static_cast<uint8_t>(lev + 1);
-                            nd.start[s] = static_cast<uint16_t>(start + nd.cnt[f]);
+                        nd.start[f] = AdjCounts{at.f, static_cast<uint16_t>(at.r + own.r - nf.r), at.t, at.x};
+                        if (ar == 2 && !sh.fold) {
+                            nd.lev[q] = static_cast<uint8_t>(lev + 1);
+                            nd.start[q] = AdjCounts{static_cast<uint16_t>(at.f + nf.f),
+                                                    static_cast<uint16_t>(at.r + own.r - nf.r - back - nq.r),
+                                                    static_cast<uint16_t>(at.t + nf.t), static_cast<uint16_t>(at.x + nf.x)};
                         }
                     }
                 }
@@ -1645,47 +1628,47 @@ __device__ __forceinline__ void compile_adjoint_program(const PopView& pop, cons
     // ---- the features in the order of their fetches ----
     for (int b = 0; b < nb; ++b) {
         const int i = b * kWave + lane;
-        if (i >= L || nd.start[i] == 0xffffu) continue;
+        if (i >= L || nd.start[i].f == 0xffffu) continue;
         const uint32_t op = nd.op[i];
         if (op == GP_OP_VAR) {
-            nd.feat[nd.fstart[i]] = pn[i] >> 8;
+            nd.feat[nd.start[i].x] = pn[i] >> 8;
         } else if (arity(op) == 2) {
             const int c1 = i + 1, c2 = nd.sec[i];
             const BinShape sh = bin_shape(nd.ent[c1], nd.ent[c2]);
             const int t = sh.a_first ? c2 : c1;
-            if (sh.fold && nd.op[t] == GP_OP_VAR) nd.feat[nd.fstart[i] + nd.fcnt[i] - 1] = pn[t] >> 8;
+            if (sh.fold && nd.op[t] == GP_OP_VAR) nd.feat[nd.start[i].x + nd.cnt[i].x - 1] = pn[t] >> 8;
         }
     }
     wave_lds_sync();
-    const int fetches = nd.fcnt[0];
+    const int fetches = nd.cnt[0].x;
     // ---- instructions ----
     for (int b = 0; b < nb; ++b) {
         const int i = b * kWave + lane;
-        if (i >= L || nd.start[i] == 0xffffu) continue;
+        if (i >= L || nd.start[i].f == 0xffffu) continue;
         const uint32_t op = nd.op[i], me = nd.ent[i], lev = nd.lev[i];
         const int ar = arity(op);
         const int c1 = min(i + 1, L - 1), c2 = ar == 2 ? nd.sec[i] : c1;
         const uint32_t ea = ar >= 1 ? nd.ent[c1] : 0u, eb = ar == 2 ? nd.ent[c2] : 0u;
-        uint32_t q = nd.start[i];
-        uint32_t tape = nd.tstart[i];
-        int fetch = nd.fstart[i] + nd.fcnt[i] - 1;     // this node's own, if it has one: its subtree's last
+        uint32_t q = nd.start[i].f;
+        uint32_t tape = nd.start[i].t;
+        int fetch = nd.start[i].x + nd.cnt[i].x - 1;     // this node's own, if it has one: its subtree's last
         int term = i;
         bool both = false;
         int ce = c1, co = c1;
         if (ar == 1) {
-            q += nd.cnt[c1];
-            tape += nd.tcnt[c1];
+            q += nd.cnt[c1].f;
+            tape += nd.cnt[c1].t;
         } else if (ar == 2) {
             const BinShape sh = bin_shape(ea, eb);
             ce = sh.a_first ? c1 : c2;
             co = sh.a_first ? c2 : c1;
-            q += nd.cnt[ce];
-            tape += nd.tcnt[ce];
+            q += nd.cnt[ce].f;
+            tape += nd.cnt[ce].t;
             if (sh.fold) {
                 term = co;
             } else {
-                q += nd.cnt[co];
-                tape += nd.tcnt[co];
+                q += nd.cnt[co].f;
+                tape += nd.cnt[co].t;
                 both = (ea & eb & kActiveEnt) != 0u;
             }
         }
@@ -1694,7 +1677,7 @@ __device__ __forceinline__ void compile_adjoint_program(const PopView& pop, cons
         const float cval = is_c ? pc[slot_c] : 0.0f;
         // the next forward instruction in the low word, the next reverse one in
         // the high word
-        uint64_t at2 = static_cast<uint64_t>(nd.rstart[i]) << 32 | q;
+        uint64_t at2 = static_cast<uint64_t>(nd.start[i].r) << 32 | q;
         auto put = [&](uint32_t at, uint32_t handler, uint32_t payload, int kind) __attribute__((always_inline)) {
             uint2 ins = make_uint2(handler, payload);
             if (kind == 1) ins.y = fetch + 1 < fetches ? nd.feat[fetch + 1] : 0xffffffffu;
@@ -1711,7 +1694,7 @@ __device__ __forceinline__ void compile_adjoint_program(const PopView& pop, cons
                         at2 += 1ull << 32;
                     });
         // between the two operands' reverse parts: the second's adjoint back on top
-        if (both) put(nd.rstart[i] + nd.rcnt[i] - nd.rcnt[ce] - 1u, (kOpLoadS + lev) * kOpBytes, 0u, 0);
+        if (both) put(nd.start[i].r + nd.cnt[i].r - nd.cnt[ce].r - 1u, (kOpLoadS + lev) * kOpBytes, 0u, 0);
     }
     const int64_t end = code_pos(total), end2 = code_pos(total + 1 + rtotal);
     if (lane == 0) {
@@ -1729,7 +1712,11 @@ __device__ __forceinline__ void compile_adjoint_program(const PopView& pop, cons
 // backward pass that evaluates first has the two compiled side by side (100
 // programs of up to 120 nodes: 35 and 53 us one after the other; a refinement
 // step of theirs on 10,007 rows 277 us with each compiler and the order in its
-// own launch, 232 so; the fitness of 256 programs on 4,096 rows 25.6 and 22.3).
+// own launch, 232 so; the fitness of 256 programs on 4,096 rows 25.6 and 22.3).  Their
+// bound is the depth: each level of a tree is a round of dependent LDS reads.
+// With the operands' words read together rather than as they were needed, and
+// constant subtrees' functions in rounds of their own: evaluation streams of
+// those 100 programs 35 -> 31 us, both streams 53 -> 49, the step 229 -> 220.
 // ---------------------------------------------------------------------------
 template <bool EVAL, bool ADJOINT>
 constexpr int compile_waves() { return ADJOINT ? kAdjCompileWaves : kBlock / kWave; }
