@@ -51,14 +51,15 @@ OP_COST = (0.0, 0.0, 0.5, 0.5, 0.5, 10.0, 0.5, 5.0, 8.0, 5.0, 5.0, 14.0, 1.0, 1.
 # binary function's is twice its fold population's excess over add's plus 1
 # (a fold instruction covers two nodes).  add, sub and mul are one
 # instruction per row (no packed FP32); sin, cos and log carry the double
-# evaluation of their correctly rounded form.
-OP_COST_MEASURED = (0.0, 0.0, 1.0, 1.0, 1.0, 12.9, 1.0, 27.0, 10.9, 23.0, 21.0, 28.7, 6.0, 6.0, 38.6, 1.4,
-                    13.3, 13.3, 1.4, 2.4, 10.0, 16.3, 15.3)
+# evaluation of their correctly rounded form; tan, exp, tanh, atan, cbrt and
+# atan2 the way out of the interpreter and back.
+OP_COST_MEASURED = (0.0, 0.0, 1.0, 1.0, 1.0, 13.9, 1.0, 18.8, 9.9, 15.9, 15.9, 34.7, 6.9, 6.9, 45.3, 1.0,
+                    16.1, 12.9, 1.0, 2.0, 13.6, 20.6, 17.8)
 # what the evaluation kernel is built from: its source, the headers it
 # includes and the build flags
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2110_11226_amd", *f) for f in
-                  (("csrc", "gp_device.hip"), ("csrc", "gp_crmath.h"), ("csrc", "gp_crmath_tables.h"),
-                   ("csrc", "gp_internal.h"), ("build.py",))] + [os.path.join(ROOT, "include", "gp.h")]
+                  (("csrc", "gp_device.hip"), ("csrc", "gp_eval_asm.h"), ("csrc", "gp_eval_code.h"),
+                   ("csrc", "gp_crmath.h"), ("csrc", "gp_crmath_tables.h"), ("csrc", "gp_internal.h"), ("build.py",))] + [os.path.join(ROOT, "include", "gp.h")]
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "k_eval_pagie-16M_traffic.md")
 
 WORKLOADS = {
