@@ -344,5 +344,40 @@ GP_CRF float log_cr(float a, const LogEntry* tab, const LogK& K) {
     return a <= 0x1.fffffep+127f ? f : a;                               // +inf (and NaN) unchanged
 }
 
+// ---- log(1 + e^-a), the log-loss's ----
+// In double, rounded once: e = e^-a as 2^k p(s) with s = -a - k ln 2, |s| <=
+// ln 2 / 2 and p its series through s^8 (relative error below 2^-32), then the
+// log of x = 1 + e in [1, 2) from log's table.  d is what 1 + e rounds off, so
+// that the result keeps its relative precision down to the smallest e (the
+// table's first entry has c = 1 and L = 0).  From a = 200 on the result is 0 in
+// float.  Within 0.503 units in the last place of every float tried (one in 97
+// up to 208; the device library's log1pf(expf(-a)) 1.5), in some 45 VALU
+// instructions a row fewer: 500 programs of up to 200 nodes on 1.1M rows of 28
+// features, 9.80 ms with the library's, 9.16 with this.
+constexpr double kLog2e = 0x1.71547652b82fep+0;
+constexpr double kRound52 = 0x1.8p+52;
+constexpr double kInvFact[9] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320};
+
+GP_CRF float log1p_exp_neg(float a, const LogEntry* tab, const LogK& K) {
+    const double A = static_cast<double>(a < 200.0f ? a : 200.0f);     // (200 for NaN; the caller's own terms keep that)
+    const double kr = fma(A, -kLog2e, kRound52);
+    const double s = fma(kr - kRound52, -kLn2, -A);
+    double p = kInvFact[8];
+    for (int q = 7; q >= 0; --q) p = fma(p, s, kInvFact[q]);
+    const uint64_t pb = dbits(p) + (static_cast<uint64_t>(static_cast<uint32_t>(dbits(kr))) << 52);
+    double e;
+    __builtin_memcpy(&e, &pb, sizeof e);
+    e = e < 0x1.ffffffffffffep-1 ? e : 0x1.ffffffffffffep-1;           // x stays below 2
+    const double x = 1.0 + e;
+    const double d = e - (x - 1.0);
+    const uint32_t hi = static_cast<uint32_t>(dbits(x) >> 32);
+    const LogEntry& t = *reinterpret_cast<const LogEntry*>(reinterpret_cast<const char*>(tab) + ((hi >> 8) & 0xFF0u));
+    // (as in log_double, mantissas from 1 + 106/256 on count as halved)
+    const double base = t.hi + (hi >= 0x3FF6A000u ? kLn2 : 0.0);
+    const double r = fma(d, t.c, fma(x, t.c, -1.0));
+    const double q = fma(fma(fma(K.l5, r, K.l4), r, K.l3), r, K.l2);
+    return static_cast<float>(base + fma(r * r, q, r));
+}
+
 }  // namespace crm
 }  // namespace gp

@@ -2057,9 +2057,10 @@ __global__ __launch_bounds__(kBlock, eval_waves(R, FREG)) void k_eval(PopView po
                             const float t1 = fmaxf(z, 0.0f);
                             const float t2 = yv * z;
                             const float t3 = t1 - t2;
-                            const float t5 = log1pf(expf(-fabsf(z)));
+                            const float t5 = crm::log1p_exp_neg(fabsf(z), reinterpret_cast<const MathTabsLds*>(lds_all)->lg, crm::log_k());
                             const double term = wv * static_cast<double>(t3 + t5);
                             acc0 += valid[j] ? term : 0.0;
+                            asm volatile("" : "+v"(acc0));     // (one row after the other)
                         } else {  // PEARSON: shifted first and second moments
                             const double a = static_cast<double>(t[j]) - static_cast<double>(shift);
                             const double bb = static_cast<double>(yv) - static_cast<double>(yshift);
