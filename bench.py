@@ -59,6 +59,7 @@ OP_COST_MEASURED = (0.0, 0.0, 1.0, 1.0, 1.0, 13.9, 1.0, 18.8, 9.9, 15.9, 15.9, 3
 # includes and the build flags
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2110_11226_amd", *f) for f in
                   (("csrc", "gp_device.hip"), ("csrc", "gp_eval_asm.h"), ("csrc", "gp_eval_code.h"),
+                   ("csrc", "gp_eval_sequential.h"),
                    ("csrc", "gp_crmath.h"), ("csrc", "gp_crmath_tables.h"), ("csrc", "gp_internal.h"), ("build.py",))] + [os.path.join(ROOT, "include", "gp.h")]
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "k_eval_pagie-16M_traffic.md")
 

@@ -35,6 +35,7 @@
 #include "gp_crmath.h"
 #include "gp_eval_asm.h"
 #include "gp_eval_code.h"
+#include "gp_eval_sequential.h"
 #include "gp_internal.h"
 
 using namespace gp;
@@ -709,252 +710,10 @@ __global__ __launch_bounds__(kBlock) void k_compile(PopView pop, OrderArgs oa, u
 // These stacks reach past the program's own GP_MAX_STACK, into LDS slots
 // kEvalLds .. kEvalLdsUser-1, which launches that may meet them provide.
 // ---------------------------------------------------------------------------
-constexpr int kEvalSlots = GP_MAX_STACK - 1;   // entries below the top
-constexpr int kEvalLds = kEvalSlots - kRegSlots;
-// with user functions or a user loss: the target below the program, and a
-// definition's own GP_USER_MAX_STACK values above its arguments
-constexpr int kEvalSlotsUser = GP_MAX_STACK + GP_USER_MAX_STACK;
-constexpr int kEvalLdsUser = kEvalSlotsUser - kRegSlots;
-constexpr int kCompileDepth = kEvalSlotsUser + 1;   // entries the compiler tracks
 // instructions the evaluation kernel may fetch past a program's end (whole
 // blocks of 64), in 16-byte units
 constexpr int64_t kCodePad = 32;
 
-// A program's header word: bit 31, it has more than one block of 64
-// instructions; bit 30, it reads features from memory, the first of which is
-// the one in the low bits (kOpReload and the fetch chain of gp_eval_code.h).
-constexpr uint32_t kHdrBlocks = 1u << 31, kHdrFetch = 1u << 30, kHdrFeature = (1u << 24) - 1u;
-
-// Word pair of instruction q: every 64th is a kOpReload.
-__device__ __forceinline__ int64_t code_pos(int64_t q) { return q + q / 63; }
-
-// How the operations of a program map to handlers for one configuration of
-// the evaluation kernel.
-struct Emit {
-    EvalOps ops;
-    int32_t R;
-    int32_t mem;        // features come from memory
-    __device__ uint32_t handler(uint32_t id) const { return id * kOpBytes; }
-    __device__ uint32_t source(bool is_c, uint32_t arg) const { return is_c ? 0u : (mem ? 1u : 1u + arg); }
-    __device__ uint32_t set(uint32_t src) const { return handler(kOpSet + src); }
-    __device__ uint32_t push(uint32_t slot, uint32_t src) const { return handler(ops.push + slot * ops.n_src + src); }
-    __device__ uint32_t fold(uint32_t op, uint32_t src) const { return handler(ops.fold + op * ops.n_src + src); }
-    __device__ uint32_t bin(uint32_t op, uint32_t slot) const {
-        return handler(ops.bin + op * (kRegSlots + 1) + slot);
-    }
-    __device__ uint32_t lds(uint32_t slot) const { return (slot - kRegSlots) * static_cast<uint32_t>(R * kWave * 4); }
-};
-
-// The interpreter's operation for binary function index fn (ADD, SUB, MUL,
-// DIV, MAX, MIN, ATAN2) with its operands as given, or exchanged.
-__device__ __forceinline__ uint32_t bin_op(uint32_t fn, bool rev) {
-    switch (fn) {
-    case 0: return kBAdd;
-    case 1: return rev ? kBSubRev : kBSub;
-    case 2: return kBMul;
-    case 3: return rev ? kBDivRev : kBDiv;
-    case 4: return kBMax;
-    case 5: return kBMin;
-    default: return rev ? kBAtan2Rev : kBAtan2;
-    }
-}
-
-// One program by one lane, in the prefix list's own right-to-left order: for
-// programs with user functions or a user loss, and for those too long or too
-// deep for the wavefront-parallel path below.
-__device__ __forceinline__ void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, uint2* out,
-                                                uint32_t* hdr, const Emit& em, const UserDefs& ud, int32_t loss_fn,
-                                                uint32_t* sh, float* shv) {
-    int h = 0;                                // entries on the stack
-    int64_t k = 0;                            // instructions emitted
-    int64_t last_fetch = -1;                  // the latest feature fetch (its payload names the next)
-    uint32_t head = 0u;
-    auto clampe = [](int e) { return min(max(e, 0), kCompileDepth - 1); };
-    auto emit = [&](uint32_t handler, uint32_t payload) {
-        out[code_pos(k)] = make_uint2(handler, payload);
-        ++k;
-    };
-    // an instruction whose handler consumes the fetched feature arg
-    auto fetch = [&](uint32_t handler, uint32_t arg) {
-        if (last_fetch >= 0) out[code_pos(last_fetch)].y = arg;
-        else head |= kHdrFetch | (arg & kHdrFeature);
-        last_fetch = k;
-        emit(handler, 0xffffffffu);
-    };
-    // a terminal as entry e
-    auto push = [&](int e, bool is_c, uint32_t arg, float v) {
-        const uint32_t src = em.source(is_c, arg);
-        uint32_t handler;
-        if (e < 1) {
-            handler = em.set(src);
-        } else if (e - 1 < kRegSlots) {
-            handler = em.push(static_cast<uint32_t>(e - 1), src);
-        } else {
-            emit(em.handler(kOpSaveL), em.lds(static_cast<uint32_t>(e - 1)));
-            handler = em.set(src);
-        }
-        if (is_c) emit(handler, __float_as_uint(v));
-        else if (em.mem) fetch(handler, arg);
-        else emit(handler, 0u);
-    };
-    // a copy of entry src as entry e
-    auto push_s = [&](int e, int src) {
-        if (e >= 1) {
-            if (e - 1 < kRegSlots) emit(em.handler(kOpSave + static_cast<uint32_t>(e - 1)), 0u);
-            else emit(em.handler(kOpSaveL), em.lds(static_cast<uint32_t>(e - 1)));
-        }
-        if (src == e - 1) return;             // the entry just covered
-        const uint32_t s = static_cast<uint32_t>(clampe(src));
-        if (s < static_cast<uint32_t>(kRegSlots)) emit(em.handler(kOpLoadS + s), 0u);
-        else emit(em.handler(kOpLoadTopL), em.lds(s));
-    };
-    // The item source: the program right to left; while a user function is
-    // expanded, its definition right to left.  (i: next program position;
-    // uf: the function being expanded or -1, di its next position, call_h
-    // the stack height when it began, call_ar its arity.)
-    int32_t i = L - 1;
-    int uf = -1, di = 0, call_h = 0, call_ar = 0;
-    bool loss_pending = loss_fn >= 0;
-    if (loss_pending) {
-        // entry 0: the target, under the program's value
-        emit(em.handler(kOpLoadY), 0u);
-        sh[0] = 0u;
-        h = 1;
-    }
-    for (;;) {
-        uint32_t w;
-        bool in_def;
-        if (uf >= 0) {
-            if (di < 0) {
-                // end of the expansion: the value replaces the arguments
-                const int base = max(call_h - call_ar, 0);
-                sh[clampe(base)] = sh[clampe(base)] & 0x7fffffffu;   // the deepest argument's start
-                h = base + 1;
-                // the value is in the top's registers, as entry `base`
-                uf = -1;
-                continue;
-            }
-            w = ud.nodes[uf][di];
-            in_def = true;
-        } else {
-            if (i < 0) {
-                if (!loss_pending) break;
-                loss_pending = false;
-                uf = kUserFns / 2 + loss_fn;   // the two-argument user functions follow the one-argument ones
-                di = ud.len[uf] - 1;
-                call_h = h;
-                call_ar = 2;
-                continue;
-            }
-            w = pn[i];
-            in_def = false;
-        }
-        const uint32_t op = w & 0xffu;
-        const uint32_t arg = w >> 8;
-        if (!in_def && is_user_op(op)) {
-            uf = static_cast<int>(op - GP_OP_USER1);
-            di = ud.len[uf] - 1;
-            call_h = h;
-            call_ar = arity(op);
-            --i;
-            continue;
-        }
-        if (in_def && op == GP_OP_VAR) {
-            // argument `arg` of the function: entry call_h - 1 - arg
-            const int e = clampe(h);
-            sh[e] = static_cast<uint32_t>(k);
-            push_s(e, call_h - 1 - static_cast<int>(arg));
-            ++h;
-            --di;
-            continue;
-        }
-        // position and the item before it in the same source (a terminal
-        // fuses only with a built-in binary function of its own source)
-        const int32_t pos = in_def ? di : i;
-        const int32_t last = in_def ? ud.len[uf] - 1 : L - 1;
-        const uint32_t prev = pos >= 1 ? ((in_def ? ud.nodes[uf][pos - 1] : pn[pos - 1]) & 0xffu) : 0u;
-        const float cval = op == GP_OP_CONST ? (in_def ? ud.consts[uf][arg & (GP_USER_MAX_CONSTS - 1)] : pc[arg])
-                                             : 0.0f;
-        auto advance = [&](int n) {
-            if (in_def) di -= n;
-            else i -= n;
-        };
-        const int ar = arity(op);
-        const int top = clampe(h - 1);
-        if (ar == 1) {
-            if (h >= 1 && (sh[top] >> 31)) {
-                // a unary function of a constant: its push (the last
-                // instruction) takes the value
-                float t[1] = {shv[top]};
-                apply_unary<1>(unary_index(op), t, global_tabs());
-                shv[top] = t[0];
-                if (k >= 1) out[code_pos(k - 1)].y = __float_as_uint(t[0]);
-            } else {
-                emit(em.handler(kOpUnary + unary_index(op)), 0u);
-            }
-            advance(1);
-            continue;
-        }
-        if (ar == 0) {
-            const bool is_c = op == GP_OP_CONST;
-            if (pos >= 1 && pos != last && is_builtin_binary(prev) && h >= 1) {
-                // first operand of the binary function before it; the top is the second
-                const uint32_t fn = binary_index(prev);
-                const uint32_t e2 = sh[top];
-                if (is_c && (e2 >> 31)) {
-                    float a[1] = {cval};
-                    const float b[1] = {shv[top]};
-                    apply_binary<1>(fn, a, b);
-                    k = static_cast<int64_t>(e2 & 0x7fffffffu);   // drop the operand's instructions
-                    push(top, true, 0u, a[0]);
-                    shv[top] = a[0];
-                } else {
-                    const uint32_t handler = em.fold(bin_op(fn, false), em.source(is_c, arg));
-                    if (is_c) emit(handler, __float_as_uint(cval));
-                    else if (em.mem) fetch(handler, arg);
-                    else emit(handler, 0u);
-                    sh[top] = e2 & 0x7fffffffu;
-                }
-                advance(2);
-                continue;
-            }
-            const int e = clampe(h);
-            sh[e] = static_cast<uint32_t>(k) | (is_c ? 1u << 31 : 0u);
-            shv[e] = cval;
-            push(e, is_c, arg, cval);
-            ++h;
-            advance(1);
-            continue;
-        }
-        // binary, operands not fused: the first is the top (entry h-1), the
-        // second the entry below it (slot h-2)
-        const int e1 = clampe(h - 1), e2 = clampe(h - 2);
-        const uint32_t first = sh[e1], second = sh[e2];
-        const uint32_t fn = binary_index(op);
-        if ((first >> 31) && (second >> 31)) {
-            float a[1] = {shv[e1]};
-            const float b[1] = {shv[e2]};
-            apply_binary<1>(fn, a, b);
-            k = static_cast<int64_t>(second & 0x7fffffffu);
-            push(e2, true, 0u, a[0]);
-            shv[e2] = a[0];
-        } else {
-            uint32_t slot = static_cast<uint32_t>(e2);
-            if (slot >= static_cast<uint32_t>(kRegSlots)) {
-                emit(em.handler(kOpLoadL), em.lds(slot));
-                slot = kRegSlots;
-            }
-            emit(em.bin(bin_op(fn, false), slot), 0u);
-            sh[e2] = second & 0x7fffffffu;
-        }
-        h = max(h - 1, 0);
-        advance(1);
-    }
-    emit(em.handler(kOpEnd), 0u);
-    for (int64_t b = 63; b < code_pos(k - 1); b += 64) out[b] = make_uint2(em.handler(kOpReload), 0u);
-    if (code_pos(k - 1) >= 64) head |= kHdrBlocks;
-    *hdr = head;
-}
 
 // A wavefront's program in the parallel path, one entry per node, at most
 // kParNodes (13 KB: twelve wavefronts per CU).
@@ -992,6 +751,12 @@ struct EvalCompileLds {
     ParNodes nodes;
     uint32_t seq[kCompileDepth];
     float seqv[kCompileDepth];
+};
+// Where compile_sequential puts its word pairs.
+struct CodeOut {
+    uint2* at;
+    __device__ void put(int64_t q, uint32_t handler, uint32_t payload) { at[q] = make_uint2(handler, payload); }
+    __device__ void payload(int64_t q, uint32_t payload) { at[q].y = payload; }
 };
 struct EvalCompile {
     uint4* code;
@@ -1118,8 +883,22 @@ __device__ __forceinline__ void compile_eval_program(const PopView& pop, const E
         sequential = (nd.ent[0] & kEntMask) > kRegSlots + 1;
     }
     if (sequential) {
-        if (lane == 0)
-            compile_sequential(pn, pc, L, out, hdr + p, em, ud, loss_fn, sh.seq, sh.seqv);
+        if (lane == 0) {
+            CodeOut seq{out};
+            compile_sequential(
+                pn, pc, L, seq, hdr + p, em, ud, loss_fn, sh.seq, sh.seqv,
+                [](uint32_t fn, float x) __attribute__((always_inline)) {
+                    float t[1] = {x};
+                    apply_unary<1>(fn, t, global_tabs());
+                    return t[0];
+                },
+                [](uint32_t fn, float a, float b) __attribute__((always_inline)) {
+                    float t[1] = {a};
+                    const float u[1] = {b};
+                    apply_binary<1>(fn, t, u);
+                    return t[0];
+                });
+        }
         return;
     }
     // ---- 3. and 4. places and instructions ----

@@ -1,0 +1,62 @@
+"""User functions on a deep stack, on the GPU, bit for bit against the
+oracle: runs of calls that fill their room of the instruction stream to the
+last word, between short programs whose streams lie next to theirs, and
+definitions of a single node."""
+import os
+
+import numpy as np
+import pytest
+
+import oracle
+from _parity import check_rows_exact, to_oracle
+
+pytestmark = pytest.mark.gpu
+
+n = oracle.node
+A, B, C = n(oracle.VAR, 0), n(oracle.VAR, 1), n(oracle.CONST, 0)
+X0, X1 = n(oracle.VAR, 0), n(oracle.VAR, 1)
+U1, U2 = oracle.USER1, oracle.USER2
+DEEP = [n(oracle.ADD)] * 12
+CASES = {
+    "argument plus constant": {U1: ([n(oracle.ADD), A, C], [0.5])},
+    "single nodes": {U1: ([A], []), U1 + 1: ([C], [0.25]), U2: ([A], []), U2 + 1: ([B], [])},
+    "both orders": {U1: ([n(oracle.SUB), C, A], [0.5]), U2: ([n(oracle.SUB), B, A], []), U2 + 1: ([n(oracle.DIV), A, B], [])},
+}
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_long_runs_of_calls_between_short_programs(case):
+    import torch
+    import paper_2110_11226_amd as gp
+    defs = CASES[case]
+    for op, (d, c) in defs.items():
+        gp.register_function(op, d, c)
+        oracle.set_user_function(op, d, c)
+    try:
+        def run(op, calls, deep):
+            binary = op >= U2
+            return ((DEEP if deep else []) + sum(([n(op)] + ([X1] if binary else []) for _ in range(calls)), [])
+                    + [X0] + ([X1] * 12 if deep else []), [])
+        short = [([n(oracle.SUB), X0, X1], []), ([n(oracle.SIN), X1], []), ([X0], [])]
+        progs = []
+        for op in defs:
+            for calls in (1, 63, 1500, 4000):
+                for deep in (False, True):
+                    progs += [run(op, calls, deep)] + short
+        pop = oracle.from_programs(progs)
+        host = gp.HostPopulation(pop.nodes, pop.prog_off, pop.consts, pop.const_off, pop.length)
+        X = np.random.default_rng(8).uniform(-2, 2, size=(2, 300)).astype(np.float32)
+        dev = gp.DevicePopulation(host, n_features=2)
+        data = gp.DeviceDataset(X)
+        ref = oracle.evaluate_f32(to_oracle(host), X, n_threads=min(16, os.cpu_count() or 1))
+        for cfg in ((4, 2, 1, 4), (1, 0, 1, 4)):
+            print(f"calls: {case} {cfg}", flush=True)
+            gp.set_launch_config(cfg)
+            out = gp.evaluate(dev, data)
+            torch.cuda.synchronize()
+            check_rows_exact(out.cpu().numpy(), ref, f"{case} {cfg}")
+    finally:
+        gp.set_launch_config(None)
+        for op in defs:
+            gp.register_function(op)
+            oracle.set_user_function(op)
