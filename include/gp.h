@@ -376,7 +376,10 @@ gp_status gp_fitness(const gp_population_dev* pop, const gp_dataset_dev* data,
  * k = 4 for PEARSON else 1, m = 1 (or, while user functions are defined,
  * the longest definition's length), u = 0 (for a user loss, 1 + its
  * definition's length); above 64 MiB it returns GP_ERR_INVALID_ARG and
- * launches nothing.  Metrics: MAE, MSE, RMSE, LOGLOSS, PEARSON (SPEARMAN:
+ * launches nothing.  Where the automatic launch configuration's chunks (not a
+ * forced or tuned one's) would need more, it takes longer ones, up to 64
+ * tiles, until they fit; the fitness then differs from gp_fitness's by the
+ * order of the float64 row sums at most.  Metrics: MAE, MSE, RMSE, LOGLOSS, PEARSON (SPEARMAN:
  * GP_ERR_UNSUPPORTED).  Every call on a device shares that device's array
  * and overwrites it: calls that overlap on one device (other streams, other
  * threads' work in flight) race; a call ordered after another on the same

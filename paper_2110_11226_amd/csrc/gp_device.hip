@@ -3540,7 +3540,12 @@ struct TuneVal {
 };
 std::map<TuneKey, TuneVal> g_tuned;
 
-LaunchCfg heuristic_cfg(int F, int64_t N, int32_t P, int n_cu) {
+// doubles per partial sum of a kernel class
+int64_t class_doubles(int kclass) { return kclass == 4 ? 4 : 1; }
+constexpr int64_t kMostTiles = 64;              // tiles of the heuristic's longest chunk
+constexpr int64_t kMostPartials = int64_t{1} << 22;
+
+LaunchCfg heuristic_cfg(int F, int64_t N, int32_t P, int n_cu, int kclass) {
     LaunchCfg c;
     // four rows per lane amortise an instruction's fetch and jump best (1M rows
     // x 1,000 programs: 3.3 ms, 3.9 with two, 5.1 with one), and at 256
@@ -3575,15 +3580,23 @@ LaunchCfg heuristic_cfg(int F, int64_t N, int32_t P, int n_cu) {
         if (waste(t) < waste(best) - 0.005 ||
             (waste(t) < waste(best) + 0.005 && std::abs(t - tiles) < std::abs(best - tiles)))
             best = t;
+    // beyond 32 MiB of partial sums longer chunks: a wavefront then has a
+    // thousand items and more, so that longer ones cost next to nothing (16.8M
+    // rows x 4,096 programs of up to 60 nodes: 383.9 ms at 16 tiles, 385.1 at
+    // 64; x 2,048 of up to 200: 612, 615 at 32, 620 at 64), while scratch and
+    // the 2^30 bound on the items go by the chunks
+    const int64_t most = std::max<int64_t>(1, kMostPartials / (class_doubles(kclass) * std::max<int32_t>(P, 1)));
+    best = std::max(best, std::min(kMostTiles, (n_tiles + most - 1) / most));
     c.tiles = static_cast<int>(best);
     return c;
 }
 
-LaunchCfg pick_cfg(const DeviceScratch& sc, int F, int64_t N, int32_t P, int kclass) {
+LaunchCfg pick_cfg(const DeviceScratch& sc, int F, int64_t N, int32_t P, int kclass, bool* automatic = nullptr) {
     if (g_forced) return g_forced_cfg;
     auto it = g_tuned.find(TuneKey{sc.arch, sc.n_cu, F, N, P, kclass});
     if (it != g_tuned.end()) return it->second.cfg;
-    return heuristic_cfg(F, N, P, sc.n_cu);
+    if (automatic) *automatic = true;
+    return heuristic_cfg(F, N, P, sc.n_cu, kclass);
 }
 
 // How a launch of the evaluation kernel is timed: by the process-wide profile
@@ -3858,6 +3871,16 @@ NoAllocDevice g_noalloc[kNoAllocMaxDevices];
 
 size_t align256(size_t n) { return (n + 255) & ~size_t{255}; }
 
+// Bytes of the device's array that one fitness evaluation takes.
+size_t noalloc_bytes(int32_t P, int64_t total_nodes, int64_t n_chunks, int metric) {
+    const size_t kk = metric == GP_METRIC_PEARSON ? 4 : 1;
+    const ExpandPlan xp = expand_plan(1, metric);
+    const size_t n_code = static_cast<size_t>(total_nodes) * xp.mul + static_cast<size_t>(P) * xp.add + 1;
+    return kCounterBytes + align256(static_cast<size_t>(P) * sizeof(int32_t)) * 2 + align256(n_code * sizeof(uint4)) +
+           align256(static_cast<size_t>(P) * static_cast<size_t>(n_chunks) * kk * sizeof(double)) +
+           align256(static_cast<size_t>(n_chunks) * 4 * sizeof(double));
+}
+
 // Carves the scratch of one fitness evaluation out of the device's array into
 // sc (caps exact, fixed: reserve() checks instead of growing).  Fails if the
 // evaluation needs more than kNoAllocBytes.
@@ -3868,9 +3891,7 @@ gp_status noalloc_carve(unsigned char* base, DeviceScratch* sc, int32_t P, int64
     const size_t n_code = static_cast<size_t>(total_nodes) * xp.mul + static_cast<size_t>(P) * xp.add + 1;
     const size_t n_part = static_cast<size_t>(P) * static_cast<size_t>(n_chunks) * kk;
     const size_t n_ystat = static_cast<size_t>(n_chunks) * 4;
-    const size_t bytes = kCounterBytes + align256(static_cast<size_t>(P) * sizeof(int32_t)) * 2 +
-                         align256(n_code * sizeof(uint4)) + align256(n_part * sizeof(double)) +
-                         align256(n_ystat * sizeof(double));
+    const size_t bytes = noalloc_bytes(P, total_nodes, n_chunks, metric);
     if (bytes > kNoAllocBytes)
         return fail(GP_ERR_INVALID_ARG, "gp_fitness_noalloc: this evaluation needs " + std::to_string(bytes) +
                                             " bytes of scratch, above the limit of " +
@@ -4058,7 +4079,7 @@ gp_status autotune_impl(DeviceScratch* sc, const gp_population_dev* pop, const g
     gp_status rc = grow(reinterpret_cast<void**>(&sc->fit_tmp), &sc->fit_tmp_cap,
                         static_cast<size_t>(std::max(pop->n_programs, 1)), sizeof(float));
     if (rc != GP_OK) return rc;
-    const LaunchCfg h = heuristic_cfg(data->n_features, data->n_rows, pop->n_programs, sc->n_cu);
+    const LaunchCfg h = heuristic_cfg(data->n_features, data->n_rows, pop->n_programs, sc->n_cu, kernel_class(1, metric));
     std::vector<int> fregs;
     if (data->n_features <= 2) fregs.push_back(2);
     if (data->n_features <= 8) fregs.push_back(8);
@@ -4694,9 +4715,17 @@ gp_status gp_fitness_noalloc(const gp_population_dev* pop, const gp_dataset_dev*
     sc.n_cu = nd.n_cu;
     sc.dev = dev;
     sc.arch = nd.arch;
-    const LaunchCfg cfg = pick_cfg(sc, data->n_features, data->n_rows, pop->n_programs, kernel_class(1, metric));
+    bool automatic = false;
+    LaunchCfg cfg = pick_cfg(sc, data->n_features, data->n_rows, pop->n_programs, kernel_class(1, metric), &automatic);
     int64_t chunk = 0, n_chunks = 0;
     if ((rc = chunking(pop, data, cfg, &chunk, &n_chunks)) != GP_OK) return rc;
+    // longer chunks where the partial sums of the heuristic's, beside the
+    // instruction streams, do not fit the array
+    while (automatic && cfg.tiles < kMostTiles &&
+           noalloc_bytes(pop->n_programs, pop->total_nodes, n_chunks, metric) > kNoAllocBytes) {
+        cfg.tiles = static_cast<int>(std::min<int64_t>(kMostTiles, 2 * cfg.tiles));
+        if ((rc = chunking(pop, data, cfg, &chunk, &n_chunks)) != GP_OK) return rc;
+    }
     if ((rc = noalloc_carve(nd.ptr, &sc, pop->n_programs, pop->total_nodes, n_chunks, metric)) != GP_OK)
         return rc;
     return fitness_impl(&sc, pop, data, metric, fitness, static_cast<hipStream_t>(stream), &cfg, Timing{});
@@ -5214,7 +5243,7 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
     // keeps more rows in flight per CU (below)
     const bool longer = pop->max_len > kParNodes;
     const int RA = g_forced ? g_forced_cfg.R
-                            : (longer ? 0 : heuristic_cfg(data->n_features, data->n_rows, pop->n_programs, sc->n_cu).R);
+                            : (longer ? 0 : heuristic_cfg(data->n_features, data->n_rows, pop->n_programs, sc->n_cu, kernel_class(1, metric)).R);
     const int64_t nc = std::max<int64_t>(pop->total_consts, 1);
     rc = grow(reinterpret_cast<void**>(&sc->gextra), &sc->gextra_cap, static_cast<size_t>(nc), sizeof(double));
     if (rc != GP_OK) return rc;
