@@ -2333,7 +2333,7 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint_long(PopView pop,
                     const float t1 = fmaxf(z, 0.0f);
                     const float t2 = yf * z;
                     const float t3 = t1 - t2;
-                    const float t5 = log1pf(expf(-fabsf(z)));
+                    const float t5 = crm::log1p_exp_neg(fabsf(z), mt.lg, crm::log_k());
                     lacc += valid[j] ? wv * static_cast<double>(t3 + t5) : 0.0;
                     sd = wv * (1.0 / (1.0 + exp(-yh)) - yv) / W;
                 } else {  // PEARSON: d|r|/dyhat
@@ -2702,8 +2702,9 @@ __global__ __launch_bounds__(kAdjWaves * kWave, adjoint_waves(R)) void k_adjoint
                         const float t1 = fmaxf(tj, 0.0f);
                         const float t2 = yf * tj;
                         const float t3 = t1 - t2;
-                        const float t5 = log1pf(expf(-fabsf(tj)));
+                        const float t5 = crm::log1p_exp_neg(fabsf(tj), reinterpret_cast<const MathTabsLds*>(lds_all)->lg, crm::log_k());
                         lacc += valid ? wv * static_cast<double>(t3 + t5) : 0.0;
+                        asm volatile("" : "+v"(lacc));
                         sd = wv * (1.0 / (1.0 + exp(-yh)) - yv) / W;
                     } else {  // PEARSON: d|r|/dyhat
                         const double* sp = stats + static_cast<int64_t>(p) * kStats;
