@@ -168,8 +168,13 @@ __device__ __forceinline__ T ldu(const T* p) {
 // A wavefront's claims of work items, `batch` consecutive items each.  One
 // queue per XCD: queue x holds the chunks c with c % kQueues == x, chunk-major,
 // each chunk's programs in LPT order (longest first), so that a chunk's rows
-// are read into one L2 while every program walks them.  Blocks are dealt to
-// the XCDs in turn, so a block starts on queue blockIdx.x % kQueues.
+// are read into one L2 while every program walks them.  With fewer chunks than
+// queues, queue x holds every eighth program instead, of every chunk: the rows
+// are few then, and all claims on one counter, at some 15 ns each, bound the
+// launch (20,000 programs of up to 40 nodes on 200 rows: the call 491 us with
+// one counter, 247 with eight; 1,000 programs on 1,000 rows: 128 and 62).
+// Blocks are dealt to the XCDs in turn, so a block starts on queue blockIdx.x %
+// kQueues.
 // Every wavefront's first claim is its own by position, and the counters
 // count only the claims after those: a job of at most one claim per wavefront
 // touches no counter (with every claim an atomic, 4,096 rows x 256 programs
@@ -187,8 +192,20 @@ struct Claims {
           batch(static_cast<uint32_t>(s.batch)), blocks(static_cast<uint32_t>(s.blocks)),
           wpb(static_cast<uint32_t>(s.wpb)), index(blockIdx.x / kQueues * static_cast<uint32_t>(s.wpb) + wid), q0(static_cast<int>(blockIdx.x % kQueues)), q(q0),
           first(true) {}
+    __device__ bool striped() const { return n_chunks < static_cast<uint32_t>(kQueues); }
+    // programs of one chunk in queue x, and where place k among them of the
+    // queue's chunk cq lies
+    __device__ uint32_t per(uint32_t x) const { return striped() ? (P + kQueues - 1 - x) / kQueues : P; }
+    __device__ int32_t chunk(uint32_t cq, int x) const {
+        return static_cast<int32_t>(striped() ? cq : cq * kQueues + static_cast<uint32_t>(x));
+    }
+    __device__ int32_t program(uint32_t k, int x) const {
+        return static_cast<int32_t>(striped() ? k * kQueues + static_cast<uint32_t>(x) : k);
+    }
     // (items stay below 2^31: n_items is at most 2^30)
-    __device__ uint32_t items(uint32_t x) const { return (n_chunks - x + kQueues - 1) / kQueues * P; }
+    __device__ uint32_t items(uint32_t x) const {
+        return striped() ? n_chunks * per(x) : (n_chunks - x + kQueues - 1) / kQueues * P;
+    }
     // items covered by the first claims of queue x's wavefronts
     __device__ uint32_t given(uint32_t x) const {
         return (blocks - x + kQueues - 1) / kQueues * wpb * batch;
@@ -1735,11 +1752,12 @@ __global__ __launch_bounds__(kBlock, eval_waves(R, FREG)) void k_eval(PopView po
         it0 = uniform(it0);
         it1 = uniform(it1);
         qx = static_cast<int>(uniform(static_cast<uint32_t>(qx)));
-        uint32_t cq = it0 / P, k = it0 - cq * P;
+        const uint32_t per = claims.per(static_cast<uint32_t>(qx));
+        uint32_t cq = it0 / per, k = it0 - cq * per;
         for (uint32_t it = it0; it < it1; ++it) {
-            const int32_t c = static_cast<int32_t>(cq) * kQueues + qx;
-            const int32_t p = ldu(s.order + k);
-            if (++k == P) {
+            const int32_t c = claims.chunk(cq, qx);
+            const int32_t p = ldu(s.order + claims.program(k, qx));
+            if (++k == per) {
                 k = 0;
                 ++cq;
             }
@@ -2138,10 +2156,9 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint_long(PopView pop,
     while (claims.next(lane, &qx, &it, &it_end)) {
         it = uniform(it);
         qx = static_cast<int>(uniform(static_cast<uint32_t>(qx)));
-        const int32_t cq = static_cast<int32_t>(it / static_cast<uint32_t>(pop.P));
-        const int32_t k = static_cast<int32_t>(it) - cq * pop.P;
-        const int32_t c = cq * kQueues + qx;
-        const int32_t p = ldu(s.order + k);
+        const uint32_t per = claims.per(static_cast<uint32_t>(qx)), cq = it / per;
+        const int32_t c = claims.chunk(cq, qx);
+        const int32_t p = ldu(s.order + claims.program(it - cq * per, qx));
         const int64_t off = ldu(pop.prog_off + p);
         const int32_t CL = ldu(cv.clen + p);
         const int64_t cbase = ldu(pop.const_off + p);
@@ -2606,10 +2623,9 @@ __global__ __launch_bounds__(kAdjWaves * kWave, adjoint_waves(R)) void k_adjoint
     while (claims.next(lane, &qx, &it, &it_end)) {
         it = uniform(it);
         qx = static_cast<int>(uniform(static_cast<uint32_t>(qx)));
-        const uint32_t cq = it / P;
-        const int32_t k = static_cast<int32_t>(it - cq * P);
-        const int32_t c = static_cast<int32_t>(cq) * kQueues + qx;
-        const int32_t p = ldu(s.order + k);
+        const uint32_t per = claims.per(static_cast<uint32_t>(qx)), cq = it / per;
+        const int32_t c = claims.chunk(cq, qx);
+        const int32_t p = ldu(s.order + claims.program(it - cq * per, qx));
         const int64_t off = ldu(pop.prog_off + p);
         const uint32_t head = static_cast<uint32_t>(ldu(cv.clen + p));
         const int64_t cbase = ldu(pop.const_off + p);
