@@ -735,6 +735,7 @@ constexpr int64_t kCodePad = 32;
 // A wavefront's program in the parallel path, one entry per node, at most
 // kParNodes (13 KB: twelve wavefronts per CU).
 constexpr int kParNodes = 1024;
+constexpr int kSeqLanes = 60;     // programs side by side: their entries take no more LDS than that
 struct ParNodes {
     float val[kParNodes];        // value of a constant subtree; later, an instruction's feature
     uint16_t sec[kParNodes];     // second operand of a binary function
@@ -764,11 +765,28 @@ constexpr uint8_t kEntMask = 31, kLeaf = 64, kConst = 128;
 // every step waited for memory, and 64 programs took each other's branches,
 // the functions of constant subtrees among them.  A wavefront per program
 // takes about as many steps as the program is deep.
-struct EvalCompileLds {
-    ParNodes nodes;
-    uint32_t seq[kCompileDepth];
-    float seqv[kCompileDepth];
+//
+// Programs with user functions or a user loss, and those too long or too deep,
+// are left to compile_sequential, a lane each.  While user functions are
+// defined, a wavefront takes a group of programs, compiles those it can one
+// after the other and then the rest side by side (20,000 programs of up to 40
+// nodes with user functions on 1,000 rows: 733 us with one of 64 lanes at work
+// for each, 403 in groups of seven; 100,000 of up to 30 on 256 rows 3,151 and
+// 596, the claims' share of that included).
+struct SeqShadow {              // one lane's column
+    uint32_t* e;
+    float* v;
+    __device__ uint32_t& entry(int i) { return e[i * kSeqLanes]; }
+    __device__ float& value(int i) { return v[i * kSeqLanes]; }
 };
+union EvalCompileLds {
+    ParNodes nodes;
+    struct {
+        uint32_t e[kCompileDepth][kSeqLanes];
+        float v[kCompileDepth][kSeqLanes];
+    } seq;
+};
+static_assert(sizeof(EvalCompileLds) == sizeof(ParNodes), "twelve wavefronts per CU");
 // Where compile_sequential puts its word pairs.
 struct CodeOut {
     uint2* at;
@@ -781,145 +799,150 @@ struct EvalCompile {
     UserDefs ud;
     int32_t loss_fn, ex_mul, ex_add;
     Emit em;
-    int32_t seq_only;
+    int32_t group;       // programs per wavefront, at most kSeqLanes
 };
 
-__device__ __forceinline__ void compile_eval_program(const PopView& pop, const EvalCompile& ec, EvalCompileLds& sh,
-                                                     int32_t p, int lane) {
-    uint4* __restrict__ code = ec.code;
+__device__ __forceinline__ uint2* eval_code(const PopView& pop, const EvalCompile& ec, int32_t p) {
+    return reinterpret_cast<uint2*>(ec.code + pop.prog_off[p] * ec.ex_mul + static_cast<int64_t>(p) * ec.ex_add);
+}
+
+// The programs p0 + l, l < group, of which compile_eval_program's return marked
+// bit l.
+__device__ __forceinline__ void compile_eval_rest(const PopView& pop, const EvalCompile& ec, EvalCompileLds& sh,
+                                                  int32_t p0, uint64_t rest, int lane) {
+    if (!((rest >> lane) & 1ull)) return;
+    const int32_t p = p0 + lane;
+    CodeOut out{eval_code(pop, ec, p)};
+    compile_sequential(
+        pop.nodes + pop.prog_off[p], pop.consts + pop.const_off[p], pop.len[p], out, ec.hdr + p, ec.em, ec.ud, ec.loss_fn,
+        SeqShadow{&sh.seq.e[0][lane], &sh.seq.v[0][lane]},
+        [](uint32_t fn, float x) __attribute__((always_inline)) {
+            float t[1] = {x};
+            apply_unary<1>(fn, t, global_tabs());
+            return t[0];
+        },
+        [](uint32_t fn, float a, float b) __attribute__((always_inline)) {
+            float t[1] = {a};
+            const float u[1] = {b};
+            apply_binary<1>(fn, t, u);
+            return t[0];
+        });
+}
+
+// True if the program is left to compile_sequential.
+__device__ __forceinline__ bool compile_eval_program(const PopView& pop, const EvalCompile& ec, ParNodes& nd, int32_t p,
+                                                     int lane) {
     uint32_t* __restrict__ hdr = ec.hdr;
-    const UserDefs& ud = ec.ud;
-    const int32_t loss_fn = ec.loss_fn, ex_mul = ec.ex_mul, ex_add = ec.ex_add, seq_only = ec.seq_only;
     const Emit& em = ec.em;
     const int64_t off = pop.prog_off[p];
     const int32_t L = pop.len[p];
     const uint32_t* pn = pop.nodes + off;
     const float* pc = pop.consts + pop.const_off[p];
-    uint2* out = reinterpret_cast<uint2*>(code + off * ex_mul + static_cast<int64_t>(p) * ex_add);
-    ParNodes& nd = sh.nodes;
-    bool sequential = seq_only || L > kParNodes;
-    if (!sequential) {
-        const int nb = (L + kWave - 1) / kWave;
-        // ---- 1. heights and second operands ----
-        int carry = 0;                 // height to the right of the block
-        int lastpos = 0;               // lane h: the leftmost node so far of height h
-        for (int b = nb - 1; b >= 0; --b) {
-            const int i = b * kWave + lane;
-            const bool valid = i < L;
-            const uint32_t op = valid ? (pn[i] & 0xffu) : 0u;
-            const int ar = arity(op);
-            int hs = valid ? 1 - ar : 0;
-            for (int d = 1; d < kWave; d <<= 1) {
-                const int o = __shfl_down(hs, d, kWave);
-                if (lane + d < kWave) hs += o;
-            }
-            const int H = min(max(hs + carry, 0), 31);
-            uint64_t same = 0, mine = 0;
-            for (int hv = 1; hv <= GP_MAX_STACK; ++hv) {
-                const uint64_t m = __ballot(valid && H == hv);
-                if (H == hv) same = m;
-                if (lane == hv) mine = m;
-            }
-            const uint64_t right = lane < 63 ? same >> (lane + 1) : 0;
-            const int beyond = __shfl(lastpos, H, kWave);
-            const int sec = right ? i + 1 + __builtin_ctzll(right) : beyond;
-            if (mine) lastpos = b * kWave + __builtin_ctzll(mine);
-            carry = __builtin_amdgcn_readfirstlane(hs + carry);
-            if (valid) {
-                nd.op[i] = static_cast<uint8_t>(op);
-                nd.sec[i] = static_cast<uint16_t>(min(max(sec, 0), L - 1));   // (the clamp only guards a malformed program)
-                nd.start[i] = 0xffffu;
-            }
+    uint2* out = eval_code(pop, ec, p);
+    if (ec.loss_fn >= 0 || L > kParNodes) return true;
+    const int nb = (L + kWave - 1) / kWave;
+    // ---- 1. heights and second operands ----
+    int carry = 0;                 // height to the right of the block
+    int lastpos = 0;               // lane h: the leftmost node so far of height h
+    uint64_t user = 0;             // lanes that met a user function
+    for (int b = nb - 1; b >= 0; --b) {
+        const int i = b * kWave + lane;
+        const bool valid = i < L;
+        const uint32_t op = valid ? (pn[i] & 0xffu) : 0u;
+        const int ar = arity(op);
+        user |= __ballot(is_user_op(op));
+        int hs = valid ? 1 - ar : 0;
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int o = __shfl_down(hs, d, kWave);
+            if (lane + d < kWave) hs += o;
+        }
+        const int H = min(max(hs + carry, 0), 31);
+        uint64_t same = 0, mine = 0;
+        for (int hv = 1; hv <= GP_MAX_STACK; ++hv) {
+            const uint64_t m = __ballot(valid && H == hv);
+            if (H == hv) same = m;
+            if (lane == hv) mine = m;
+        }
+        const uint64_t right = lane < 63 ? same >> (lane + 1) : 0;
+        const int beyond = __shfl(lastpos, H, kWave);
+        const int sec = right ? i + 1 + __builtin_ctzll(right) : beyond;
+        if (mine) lastpos = b * kWave + __builtin_ctzll(mine);
+        carry = __builtin_amdgcn_readfirstlane(hs + carry);
+        if (valid) {
+            nd.op[i] = static_cast<uint8_t>(op);
+            nd.sec[i] = static_cast<uint16_t>(min(max(sec, 0), L - 1));   // (the clamp only guards a malformed program)
+            nd.start[i] = 0xffffu;
+        }
+    }
+    if (user) return true;
+    wave_lds_sync();
+    // ---- 2. entries, instructions, constants ----
+    // (a round reads both operands' words at once and chooses: read as they
+    // were needed, one after the other, they cost a round three latencies)
+    uint64_t folds = 0;            // blocks with a function of constants
+    for (int b = nb - 1; b >= 0; --b) {
+        const int i = b * kWave + lane;
+        const bool valid = i < L;
+        const uint32_t op = valid ? nd.op[i] : 0u;
+        const int ar = arity(op);
+        const int c1 = min(i + 1, L - 1), c2 = valid && ar == 2 ? nd.sec[i] : c1;
+        // an operand outside the block is done
+        const uint64_t need = (ar >= 1 && c1 < (b + 1) * kWave ? 1ull << (c1 & 63) : 0ull) |
+                              (ar == 2 && c2 < (b + 1) * kWave ? 1ull << (c2 & 63) : 0ull);
+        bool done = !valid || ar == 0, fold = false;
+        if (valid && ar == 0) {
+            nd.ent[i] = static_cast<uint8_t>(1 | (op == GP_OP_CONST ? kConst : kLeaf));
+            nd.cnt[i] = 1;
+            nd.val[i] = op == GP_OP_CONST ? pc[pn[i] >> 8] : 0.0f;
         }
         wave_lds_sync();
-        // ---- 2. entries, instructions, constants ----
-        // (a round reads both operands' words at once and chooses: read as they
-        // were needed, one after the other, they cost a round three latencies)
-        uint64_t folds = 0;            // blocks with a function of constants
-        for (int b = nb - 1; b >= 0; --b) {
-            const int i = b * kWave + lane;
-            const bool valid = i < L;
-            const uint32_t op = valid ? nd.op[i] : 0u;
-            const int ar = arity(op);
-            const int c1 = min(i + 1, L - 1), c2 = valid && ar == 2 ? nd.sec[i] : c1;
-            // an operand outside the block is done
-            const uint64_t need = (ar >= 1 && c1 < (b + 1) * kWave ? 1ull << (c1 & 63) : 0ull) |
-                                  (ar == 2 && c2 < (b + 1) * kWave ? 1ull << (c2 & 63) : 0ull);
-            bool done = !valid || ar == 0, fold = false;
-            if (valid && ar == 0) {
-                nd.ent[i] = static_cast<uint8_t>(1 | (op == GP_OP_CONST ? kConst : kLeaf));
-                nd.cnt[i] = 1;
-                nd.val[i] = op == GP_OP_CONST ? pc[pn[i] >> 8] : 0.0f;
+        for (int round = 0; round <= kWave; ++round) {
+            const uint64_t ready = __ballot(done);
+            if (ready == ~0ull) break;
+            const uint32_t e1 = nd.ent[c1], e2 = nd.ent[c2], n1 = nd.cnt[c1], n2 = nd.cnt[c2];
+            if (!done && (need & ~ready) == 0) {
+                const bool two = ar == 2, t1 = e1 & (kLeaf | kConst), t2 = e2 & (kLeaf | kConst);
+                const uint32_t m1 = e1 & kEntMask, m2 = e2 & kEntMask;
+                fold = (e1 & kConst) && (!two || (e2 & kConst));
+                uint32_t ent = two ? (t1 ? m2 : t2 ? m1 : m1 == m2 ? m1 + 1u : max(m1, m2)) : max(m1, 1u);
+                uint32_t cnt = 1u + (two ? (t1 ? n2 : t2 ? n1 : n1 + n2) : n1);
+                ent = fold ? 1u | kConst : ent;
+                cnt = fold ? 1u : cnt;
+                nd.ent[i] = static_cast<uint8_t>(ent);
+                nd.cnt[i] = static_cast<uint16_t>(cnt);
+                done = true;
             }
             wave_lds_sync();
-            for (int round = 0; round <= kWave; ++round) {
-                const uint64_t ready = __ballot(done);
-                if (ready == ~0ull) break;
-                const uint32_t e1 = nd.ent[c1], e2 = nd.ent[c2], n1 = nd.cnt[c1], n2 = nd.cnt[c2];
-                if (!done && (need & ~ready) == 0) {
-                    const bool two = ar == 2, t1 = e1 & (kLeaf | kConst), t2 = e2 & (kLeaf | kConst);
-                    const uint32_t m1 = e1 & kEntMask, m2 = e2 & kEntMask;
-                    fold = (e1 & kConst) && (!two || (e2 & kConst));
-                    uint32_t ent = two ? (t1 ? m2 : t2 ? m1 : m1 == m2 ? m1 + 1u : max(m1, m2)) : max(m1, 1u);
-                    uint32_t cnt = 1u + (two ? (t1 ? n2 : t2 ? n1 : n1 + n2) : n1);
-                    ent = fold ? 1u | kConst : ent;
-                    cnt = fold ? 1u : cnt;
-                    nd.ent[i] = static_cast<uint8_t>(ent);
-                    nd.cnt[i] = static_cast<uint16_t>(cnt);
-                    done = true;
-                }
-                wave_lds_sync();
-            }
-            if (__ballot(fold)) folds |= 1ull << b;
         }
-        // the values of constant subtrees, by themselves: among the rounds above,
-        // each with such a node would wait for the functions
-        for (; folds; folds &= ~(1ull << (63 - __builtin_clzll(folds)))) {
-            const int b = 63 - __builtin_clzll(folds);
-            const int i = b * kWave + lane, ii = min(i, L - 1);
-            const uint32_t op = nd.op[ii];
-            const int ar = arity(op);
-            const int c1 = min(i + 1, L - 1), c2 = ar == 2 ? nd.sec[ii] : c1;
-            const uint64_t need = (c1 < (b + 1) * kWave ? 1ull << (c1 & 63) : 0ull) |
-                                  (c2 < (b + 1) * kWave ? 1ull << (c2 & 63) : 0ull);
-            bool todo = i < L && ar >= 1 && (nd.ent[ii] & kConst);
-            for (int round = 0; round <= kWave; ++round) {
-                const uint64_t left = __ballot(todo);
-                if (left == 0ull) break;
-                if (todo && (need & left) == 0) {
-                    float v[1] = {nd.val[c1]};
-                    const float second[1] = {nd.val[c2]};
-                    if (ar == 1) apply_unary<1>(unary_index(op), v, global_tabs());
-                    else apply_binary<1>(binary_index(op), v, second);
-                    nd.val[i] = v[0];
-                    todo = false;
-                }
-                wave_lds_sync();
-            }
-        }
-        sequential = (nd.ent[0] & kEntMask) > kRegSlots + 1;
+        if (__ballot(fold)) folds |= 1ull << b;
     }
-    if (sequential) {
-        if (lane == 0) {
-            CodeOut seq{out};
-            compile_sequential(
-                pn, pc, L, seq, hdr + p, em, ud, loss_fn, sh.seq, sh.seqv,
-                [](uint32_t fn, float x) __attribute__((always_inline)) {
-                    float t[1] = {x};
-                    apply_unary<1>(fn, t, global_tabs());
-                    return t[0];
-                },
-                [](uint32_t fn, float a, float b) __attribute__((always_inline)) {
-                    float t[1] = {a};
-                    const float u[1] = {b};
-                    apply_binary<1>(fn, t, u);
-                    return t[0];
-                });
+    // the values of constant subtrees, by themselves: among the rounds above,
+    // each with such a node would wait for the functions
+    for (; folds; folds &= ~(1ull << (63 - __builtin_clzll(folds)))) {
+        const int b = 63 - __builtin_clzll(folds);
+        const int i = b * kWave + lane, ii = min(i, L - 1);
+        const uint32_t op = nd.op[ii];
+        const int ar = arity(op);
+        const int c1 = min(i + 1, L - 1), c2 = ar == 2 ? nd.sec[ii] : c1;
+        const uint64_t need = (c1 < (b + 1) * kWave ? 1ull << (c1 & 63) : 0ull) |
+                              (c2 < (b + 1) * kWave ? 1ull << (c2 & 63) : 0ull);
+        bool todo = i < L && ar >= 1 && (nd.ent[ii] & kConst);
+        for (int round = 0; round <= kWave; ++round) {
+            const uint64_t left = __ballot(todo);
+            if (left == 0ull) break;
+            if (todo && (need & left) == 0) {
+                float v[1] = {nd.val[c1]};
+                const float second[1] = {nd.val[c2]};
+                if (ar == 1) apply_unary<1>(unary_index(op), v, global_tabs());
+                else apply_binary<1>(binary_index(op), v, second);
+                nd.val[i] = v[0];
+                todo = false;
+            }
+            wave_lds_sync();
         }
-        return;
     }
+    if ((nd.ent[0] & kEntMask) > kRegSlots + 1) return true;
     // ---- 3. and 4. places and instructions ----
-    const int nb = (L + kWave - 1) / kWave;
     const int total = nd.cnt[0];
     if (lane == 0) {
         nd.start[0] = 0;
@@ -1048,6 +1071,7 @@ __device__ __forceinline__ void compile_eval_program(const PopView& pop, const E
         if (next != 0xffffffffu) head |= kHdrFetch | (next & kHdrFeature);
     }
     if (lane == 0) hdr[p] = head;
+    return false;
 }
 
 // ---------------------------------------------------------------------------
@@ -1543,8 +1567,14 @@ __global__ __launch_bounds__((compile_waves<EVAL, ADJOINT>()) * kWave) void k_co
         b -= per;
     }
     if constexpr (EVAL) {
-        const int32_t p = b * kW + wid;
-        if (p < pop.P) compile_eval_program(pop, ec, reinterpret_cast<EvalCompileLds*>(lds)[wid], p, lane);
+        EvalCompileLds& sh = reinterpret_cast<EvalCompileLds*>(lds)[wid];
+        const int32_t p0 = (b * kW + wid) * ec.group, n = min(ec.group, pop.P - p0);
+        uint64_t rest = 0;
+        for (int32_t g = 0; g < n; ++g) {
+            if (compile_eval_program(pop, ec, sh.nodes, p0 + g, lane)) rest |= 1ull << g;
+            wave_lds_sync();
+        }
+        if (rest) compile_eval_rest(pop, ec, sh, p0, rest, lane);
     }
 }
 
@@ -3809,17 +3839,23 @@ gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_data
                  batch, xp.lds_slots, 0, 0};
     const bool eval = !adjoint || both;
     const OrderArgs oa{pop->len, pop->n_programs, sc->order, static_cast<uint32_t*>(sc->counter), adjoint ? 2 : 1};
+    // programs per compiling wavefront: one, or while user functions are
+    // defined as many as leave each resident wavefront (12 per CU) one group
+    const int64_t resident = static_cast<int64_t>(sc->n_cu) * 12;
+    const int32_t group = xp.lds_slots == kEvalLdsUser
+                              ? static_cast<int32_t>(std::min<int64_t>(kSeqLanes, std::max<int64_t>(1, (pop->n_programs + resident - 1) / resident)))
+                              : 1;
     const EvalCompile ec{sc->ecode, sc->ehdr, xp.defs, xp.loss_fn, xp.mul, xp.add,
-                         Emit{eval_ops(cfg->freg), cfg->R, cfg->freg == 0}, xp.lds_slots == kEvalLdsUser};
+                         Emit{eval_ops(cfg->freg), cfg->R, cfg->freg == 0}, group};
     const AdjCompile ac{sc->code, reinterpret_cast<uint32_t*>(sc->clen), Emit{eval_ops(0), adjoint_R, 1}, sc->gextra};
-    auto compile = [&](auto kernel, int waves, int streams) {
-        const int64_t per = (static_cast<int64_t>(pop->n_programs) + waves - 1) / waves;
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(1 + streams * per)), dim3(waves * kWave), 0, st, *pv, oa,
-                           ec, ac);
+    auto compile = [&](auto kernel, int waves, bool with_eval, bool with_adjoint) {
+        const int64_t P = pop->n_programs, per = static_cast<int64_t>(waves) * group;
+        const int64_t blocks = 1 + (with_adjoint ? (P + waves - 1) / waves : 0) + (with_eval ? (P + per - 1) / per : 0);
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(waves * kWave), 0, st, *pv, oa, ec, ac);
     };
-    if (adjoint_R > 0 && eval) compile(k_compile_streams<true, true>, compile_waves<true, true>(), 2);
-    else if (adjoint_R > 0) compile(k_compile_streams<false, true>, compile_waves<false, true>(), 1);
-    else if (eval) compile(k_compile_streams<true, false>, compile_waves<true, false>(), 1);
+    if (adjoint_R > 0 && eval) compile(k_compile_streams<true, true>, compile_waves<true, true>(), true, true);
+    else if (adjoint_R > 0) compile(k_compile_streams<false, true>, compile_waves<false, true>(), false, true);
+    else if (eval) compile(k_compile_streams<true, false>, compile_waves<true, false>(), true, false);
     GP_HIP(hipGetLastError());
     if (adjoint && adjoint_R == 0) {
         const unsigned blocks = 1 + (pop->n_programs + kBlock - 1) / kBlock;

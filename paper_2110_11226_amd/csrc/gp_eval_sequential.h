@@ -66,8 +66,9 @@ GP_HD uint32_t float_bits(float v) {
 
 // One program by one lane.  out.put(position, handler, payload) stores a word
 // pair, out.payload(position, payload) changes its second word; unary(fn, x)
-// and binary(fn, a, b) are the float32 functions of constant subtrees; sh and
-// shv are kCompileDepth entries of the caller's.
+// and binary(fn, a, b) are the float32 functions of constant subtrees;
+// sh.entry(e) (an unsigned word) and sh.value(e) (a float) are kCompileDepth
+// entries of the caller's.
 //
 // Room: two word pairs per node, of the program (times the longest definition's
 // nodes) and of the loss's definition.  A node takes at most two instructions,
@@ -81,9 +82,9 @@ GP_HD uint32_t float_bits(float v) {
 // in 63 is spared.  Those make room for the reload after every 63rd, and the
 // nodes of the first kRegSlots entries for the end.  A definition of one node
 // takes one instruction at most, as it need not keep its arguments.
-template <typename Out, typename Unary, typename Binary>
+template <typename Out, typename Shadow, typename Unary, typename Binary>
 GP_HD void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, Out& out, uint32_t* hdr, const Emit& em,
-                              const UserDefs& ud, int32_t loss_fn, uint32_t* sh, float* shv, Unary&& unary,
+                              const UserDefs& ud, int32_t loss_fn, Shadow sh, Unary&& unary,
                               Binary&& binary) {
     int h = 0;                                // entries on the stack
     int64_t k = 0;                            // instructions emitted
@@ -150,14 +151,14 @@ GP_HD void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, Ou
     if (loss_pending) {
         // entry 0: the target, under the program's value
         emit(em.handler(kOpLoadY), 0u);
-        sh[0] = 0u;
+        sh.entry(0) = 0u;
         h = 1;
     }
     // end of an expansion: the value, in the top's registers, replaces the
     // arguments as the deepest one's entry
     auto finish = [&]() {
         const int base = clampe(call_h - call_ar);
-        sh[base] &= 0x7fffffffu;              // (that argument's start)
+        sh.entry(base) &= 0x7fffffffu;              // (that argument's start)
         h = base + 1;
         uf = -1;
     };
@@ -219,11 +220,11 @@ GP_HD void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, Ou
             if (pos >= 1 && pos != last && is_builtin_binary(prev)) {
                 // first operand of the binary function before it; the top is the second
                 bin_slot(binary_index(prev), true, src);
-                sh[top] &= 0x7fffffffu;
+                sh.entry(top) &= 0x7fffffffu;
                 di -= 2;
             } else {
                 const int e = clampe(h);
-                sh[e] = static_cast<uint32_t>(k);
+                sh.entry(e) = static_cast<uint32_t>(k);
                 push_s(e, src);
                 ++h;
                 --di;
@@ -231,11 +232,11 @@ GP_HD void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, Ou
             continue;
         }
         if (ar == 1) {
-            if (h >= 1 && (sh[top] >> 31)) {
+            if (h >= 1 && (sh.entry(top) >> 31)) {
                 // a unary function of a constant: its push (the last
                 // instruction) takes the value
-                shv[top] = unary(unary_index(op), shv[top]);
-                if (k >= 1) out.payload(code_pos(k - 1), float_bits(shv[top]));
+                sh.value(top) = unary(unary_index(op), sh.value(top));
+                if (k >= 1) out.payload(code_pos(k - 1), float_bits(sh.value(top)));
             } else {
                 emit(em.handler(kOpUnary + unary_index(op)), 0u);
             }
@@ -247,25 +248,25 @@ GP_HD void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, Ou
             if (pos >= 1 && pos != last && is_builtin_binary(prev) && h >= 1) {
                 // first operand of the binary function before it; the top is the second
                 const uint32_t fn = binary_index(prev);
-                const uint32_t e2 = sh[top];
+                const uint32_t e2 = sh.entry(top);
                 if (is_c && (e2 >> 31)) {
-                    const float v = binary(fn, cval, shv[top]);
+                    const float v = binary(fn, cval, sh.value(top));
                     k = static_cast<int64_t>(e2 & 0x7fffffffu);   // drop the operand's instructions
                     push(top, true, 0u, v);
-                    shv[top] = v;
+                    sh.value(top) = v;
                 } else {
                     const uint32_t handler = em.fold(bin_op(fn, false), em.source(is_c, arg));
                     if (is_c) emit(handler, float_bits(cval));
                     else if (em.mem) fetch(handler, arg);
                     else emit(handler, 0u);
-                    sh[top] = e2 & 0x7fffffffu;
+                    sh.entry(top) = e2 & 0x7fffffffu;
                 }
                 advance(2);
                 continue;
             }
             const int e = clampe(h);
-            sh[e] = static_cast<uint32_t>(k) | (is_c ? 1u << 31 : 0u);
-            shv[e] = cval;
+            sh.entry(e) = static_cast<uint32_t>(k) | (is_c ? 1u << 31 : 0u);
+            sh.value(e) = cval;
             push(e, is_c, arg, cval);
             ++h;
             advance(1);
@@ -274,16 +275,16 @@ GP_HD void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, Ou
         // binary, operands not fused: the first is the top (entry h-1), the
         // second the entry below it (slot h-2)
         const int e1 = clampe(h - 1), e2 = clampe(h - 2);
-        const uint32_t first = sh[e1], second = sh[e2];
+        const uint32_t first = sh.entry(e1), second = sh.entry(e2);
         const uint32_t fn = binary_index(op);
         if ((first >> 31) && (second >> 31)) {
-            const float v = binary(fn, shv[e1], shv[e2]);
+            const float v = binary(fn, sh.value(e1), sh.value(e2));
             k = static_cast<int64_t>(second & 0x7fffffffu);
             push(e2, true, 0u, v);
-            shv[e2] = v;
+            sh.value(e2) = v;
         } else {
             bin_slot(fn, false, e2);
-            sh[e2] = second & 0x7fffffffu;
+            sh.entry(e2) = second & 0x7fffffffu;
         }
         h = h > 0 ? h - 1 : 0;
         advance(1);

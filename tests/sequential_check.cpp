@@ -43,6 +43,13 @@ static float bi(uint32_t fn, float a, float b) {
     }
 }
 
+struct Shadow {
+    uint32_t e[kCompileDepth] = {};
+    float v[kCompileDepth] = {};
+    uint32_t& entry(int i) { return e[i]; }
+    float& value(int i) { return v[i]; }
+};
+
 struct Check {
     Words prog;
     std::vector<float> consts;
@@ -191,10 +198,10 @@ struct Check {
                 o.room = room();
                 o.h.assign(static_cast<size_t>(o.room), 0xdeadbeefu);
                 o.p.assign(static_cast<size_t>(o.room), 0u);
-                uint32_t head = 0, sh[kCompileDepth] = {};
-                float shv[kCompileDepth] = {};
+                uint32_t head = 0;
+                Shadow sh;
                 compile_sequential(prog.data(), consts.data(), static_cast<int32_t>(prog.size()), o, &head, em, ud, loss,
-                                   sh, shv, un, bi);
+                                   sh, un, bi);
                 if (o.worst >= o.room) {
                     std::printf("%s: %zu nodes, word pair %lld stored, room for %lld\n", what, prog.size(),
                                 static_cast<long long>(o.worst), static_cast<long long>(o.room));
