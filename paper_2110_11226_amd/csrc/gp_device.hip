@@ -787,6 +787,12 @@ union EvalCompileLds {
     } seq;
 };
 static_assert(sizeof(EvalCompileLds) == sizeof(ParNodes), "twelve wavefronts per CU");
+// Callers are not to pass programs that gp_validate_population refuses.  One all
+// the same has no operands where the parallel compilers look for them: they
+// leave it alone, so that what they write stays within its room.  h: the height
+// of the right-to-left scan after the node.
+__device__ __forceinline__ bool malformed(int arity, int h) { return arity < 0 || h < 1 || h > GP_MAX_STACK; }
+
 // Where compile_sequential puts its word pairs.
 struct CodeOut {
     uint2* at;
@@ -814,7 +820,8 @@ __device__ __forceinline__ void compile_eval_rest(const PopView& pop, const Eval
     const int32_t p = p0 + lane;
     CodeOut out{eval_code(pop, ec, p)};
     compile_sequential(
-        pop.nodes + pop.prog_off[p], pop.consts + pop.const_off[p], pop.len[p], out, ec.hdr + p, ec.em, ec.ud, ec.loss_fn,
+        pop.nodes + pop.prog_off[p], pop.consts + pop.const_off[p], pop.len[p], out,
+        2 * (static_cast<int64_t>(pop.len[p]) * ec.ex_mul + ec.ex_add), ec.hdr + p, ec.em, ec.ud, ec.loss_fn,
         SeqShadow{&sh.seq.e[0][lane], &sh.seq.v[0][lane]},
         [](uint32_t fn, float x) __attribute__((always_inline)) {
             float t[1] = {x};
@@ -844,18 +851,18 @@ __device__ __forceinline__ bool compile_eval_program(const PopView& pop, const E
     // ---- 1. heights and second operands ----
     int carry = 0;                 // height to the right of the block
     int lastpos = 0;               // lane h: the leftmost node so far of height h
-    uint64_t user = 0;             // lanes that met a user function
+    uint64_t rest = 0;             // lanes that met a user function, or a height no valid program has
     for (int b = nb - 1; b >= 0; --b) {
         const int i = b * kWave + lane;
         const bool valid = i < L;
         const uint32_t op = valid ? (pn[i] & 0xffu) : 0u;
         const int ar = arity(op);
-        user |= __ballot(is_user_op(op));
         int hs = valid ? 1 - ar : 0;
         for (int d = 1; d < kWave; d <<= 1) {
             const int o = __shfl_down(hs, d, kWave);
             if (lane + d < kWave) hs += o;
         }
+        rest |= __ballot(valid && (is_user_op(op) || malformed(ar, hs + carry)));
         const int H = min(max(hs + carry, 0), 31);
         uint64_t same = 0, mine = 0;
         for (int hv = 1; hv <= GP_MAX_STACK; ++hv) {
@@ -870,11 +877,11 @@ __device__ __forceinline__ bool compile_eval_program(const PopView& pop, const E
         carry = __builtin_amdgcn_readfirstlane(hs + carry);
         if (valid) {
             nd.op[i] = static_cast<uint8_t>(op);
-            nd.sec[i] = static_cast<uint16_t>(min(max(sec, 0), L - 1));   // (the clamp only guards a malformed program)
+            nd.sec[i] = static_cast<uint16_t>(min(max(sec, 0), L - 1));   // (a malformed program's may lie anywhere)
             nd.start[i] = 0xffffu;
         }
     }
-    if (user) return true;
+    if (rest || carry != 1) return true;
     wave_lds_sync();
     // ---- 2. entries, instructions, constants ----
     // (a round reads both operands' words at once and chooses: read as they
@@ -1315,15 +1322,18 @@ __device__ __forceinline__ void compile_adjoint_program(const PopView& pop, cons
     const int nb = (L + kWave - 1) / kWave;
     // ---- heights and second operands (as compile_eval_program) ----
     int carry = 0, lastpos = 0;
+    uint64_t bad = 0;
     for (int b = nb - 1; b >= 0; --b) {
         const int i = b * kWave + lane;
         const bool valid = i < L;
         const uint32_t op = valid ? (pn[i] & 0xffu) : 0u;
-        int hs = valid ? 1 - arity(op) : 0;
+        const int ar = arity(op);
+        int hs = valid ? 1 - ar : 0;
         for (int d = 1; d < kWave; d <<= 1) {
             const int o = __shfl_down(hs, d, kWave);
             if (lane + d < kWave) hs += o;
         }
+        bad |= __ballot(valid && malformed(ar, hs + carry));
         const int H = min(max(hs + carry, 0), 31);
         uint64_t same = 0, mine = 0;
         for (int hv = 1; hv <= GP_MAX_STACK; ++hv) {
@@ -1341,6 +1351,11 @@ __device__ __forceinline__ void compile_adjoint_program(const PopView& pop, cons
             nd.sec[i] = static_cast<uint16_t>(min(max(sec, 0), L - 1));
             nd.start[i].f = 0xffffu;
         }
+    }
+    if (bad || carry != 1) {       // nothing to do for a malformed program
+        if (lane < 2 && L > 0) out[lane] = make_uint2(em.handler(kOpEnd), 0u);
+        if (lane == 0) hdr[p] = 0u;
+        return;
     }
     wave_lds_sync();
     // ---- from the leaves up: entries, activity, counts ----

@@ -34,7 +34,10 @@ struct Emit {
     int32_t R;
     int32_t mem;        // features come from memory
     GP_HD uint32_t handler(uint32_t id) const { return id * kOpBytes; }
-    GP_HD uint32_t source(bool is_c, uint32_t arg) const { return is_c ? 0u : (mem ? 1u : 1u + arg); }
+    // (the bound only keeps a malformed program within the table)
+    GP_HD uint32_t source(bool is_c, uint32_t arg) const {
+        return is_c ? 0u : (mem ? 1u : (arg + 1u < ops.n_src ? arg + 1u : ops.n_src - 1u));
+    }
     GP_HD uint32_t set(uint32_t src) const { return handler(kOpSet + src); }
     GP_HD uint32_t push(uint32_t slot, uint32_t src) const { return handler(ops.push + slot * ops.n_src + src); }
     GP_HD uint32_t fold(uint32_t op, uint32_t src) const { return handler(ops.fold + op * ops.n_src + src); }
@@ -68,7 +71,7 @@ GP_HD uint32_t float_bits(float v) {
 // pair, out.payload(position, payload) changes its second word; unary(fn, x)
 // and binary(fn, a, b) are the float32 functions of constant subtrees;
 // sh.entry(e) (an unsigned word) and sh.value(e) (a float) are kCompileDepth
-// entries of the caller's.
+// entries of the caller's.  `room` is the program's in word pairs.
 //
 // Room: two word pairs per node, of the program (times the longest definition's
 // nodes) and of the loss's definition.  A node takes at most two instructions,
@@ -81,13 +84,17 @@ GP_HD uint32_t float_bits(float v) {
 // on (or, within a definition, its 32 nodes), so that at least one instruction
 // in 63 is spared.  Those make room for the reload after every 63rd, and the
 // nodes of the first kRegSlots entries for the end.  A definition of one node
-// takes one instruction at most, as it need not keep its arguments.
+// takes one instruction at most, as it need not keep its arguments.  (Only a
+// malformed program, which callers are not to pass, could take more: its stream
+// ends where its room does.)
 template <typename Out, typename Shadow, typename Unary, typename Binary>
-GP_HD void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, Out& out, uint32_t* hdr, const Emit& em,
-                              const UserDefs& ud, int32_t loss_fn, Shadow sh, Unary&& unary,
+GP_HD void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, Out& out, int64_t room, uint32_t* hdr,
+                              const Emit& em, const UserDefs& ud, int32_t loss_fn, Shadow sh, Unary&& unary,
                               Binary&& binary) {
     int h = 0;                                // entries on the stack
     int64_t k = 0;                            // instructions emitted
+    // those there is room for, with an end after them
+    const int64_t limit = (room - 1) - (room - 1) / 64 - (room % 64 == 0 ? 1 : 0);
     int64_t last_fetch = -1;                  // the latest feature fetch (its payload names the next)
     uint32_t head = 0u;
     auto clampe = [](int e) { return e < 0 ? 0 : e < kCompileDepth ? e : kCompileDepth - 1; };
@@ -175,6 +182,7 @@ GP_HD void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, Ou
         finish();
     };
     for (;;) {
+        if (k >= limit && (i >= 0 || uf >= 0 || loss_pending)) break;    // (an item takes two at most: the end's place may be lost)
         uint32_t w;
         bool in_def;
         if (uf >= 0) {
@@ -289,9 +297,14 @@ GP_HD void compile_sequential(const uint32_t* pn, const float* pc, int32_t L, Ou
         h = h > 0 ? h - 1 : 0;
         advance(1);
     }
-    emit(em.handler(kOpEnd), 0u);
-    for (int64_t b = 63; b < code_pos(k - 1); b += 64) out.put(b, em.handler(kOpReload), 0u);
-    if (code_pos(k - 1) >= 64) head |= kHdrBlocks;
+    if (room < 1) {                           // (no nodes)
+        *hdr = 0u;
+        return;
+    }
+    const int64_t end = k <= limit ? code_pos(k) : room - 1;
+    out.put(end, em.handler(kOpEnd), 0u);
+    for (int64_t b = 63; b < end; b += 64) out.put(b, em.handler(kOpReload), 0u);
+    if (end >= 64) head |= kHdrBlocks;
     *hdr = head;
 }
 

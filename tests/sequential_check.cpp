@@ -5,6 +5,8 @@
 //
 //   sequential_check chains     long runs of user calls on a deep stack
 //   sequential_check random N   N random programs with random definitions
+//   sequential_check malformed N   N lists that are no programs: their words
+//                               stay in their room too, and their streams end
 // Prints the number of programs checked, or the first fault and exit status 1.
 #include <algorithm>
 #include <cmath>
@@ -107,7 +109,7 @@ struct Check {
     // ---- the stream ----
     struct Out {
         std::vector<uint32_t> h, p;
-        int64_t room, worst = -1;
+        int64_t room = 0, worst = -1;
         void put(int64_t q, uint32_t handler, uint32_t pay) {
             worst = std::max(worst, q);
             if (q < 0 || q >= room) return;
@@ -188,8 +190,9 @@ struct Check {
         return t;
     }
 
-    // Compiles and runs the program for every kind of feature source.
-    bool check(const char* what) {
+    // Compiles and runs the program for every kind of feature source (a
+    // malformed one: compiles, and looks for the end).
+    bool check(const char* what, bool malformed = false) {
         for (int freg : {0, 2, 8})
             for (int R : {1, 4}) {
                 if (freg == 2 && X.size() > 2) continue;
@@ -200,12 +203,24 @@ struct Check {
                 o.p.assign(static_cast<size_t>(o.room), 0u);
                 uint32_t head = 0;
                 Shadow sh;
-                compile_sequential(prog.data(), consts.data(), static_cast<int32_t>(prog.size()), o, &head, em, ud, loss,
+                compile_sequential(prog.data(), consts.data(), static_cast<int32_t>(prog.size()), o, room(), &head, em, ud, loss,
                                    sh, un, bi);
                 if (o.worst >= o.room) {
                     std::printf("%s: %zu nodes, word pair %lld stored, room for %lld\n", what, prog.size(),
                                 static_cast<long long>(o.worst), static_cast<long long>(o.room));
                     return false;
+                }
+                if (malformed) {
+                    if (std::find(o.h.begin(), o.h.end(), kOpEnd * kOpBytes) == o.h.end()) {
+                        std::printf("%s: %zu nodes, no end\n", what, prog.size());
+                        return false;
+                    }
+                    for (size_t q = 0; o.h[q] != kOpEnd * kOpBytes; ++q)
+                        if (o.h[q] % kOpBytes || o.h[q] / kOpBytes >= em.ops.bin + 10u * (kRegSlots + 1)) {
+                            std::printf("%s: %zu nodes, word %zu is no handler\n", what, prog.size(), q);
+                            return false;
+                        }
+                    continue;
                 }
                 bool fine = true;
                 const float got = run(o, head, em, &fine), want = direct();
@@ -326,7 +341,41 @@ static int random_programs(int n) {
     return 0;
 }
 
+// Words no population may hold: too few operands, too many, unknown functions,
+// features out of range.
+static int malformed_programs(int n) {
+    std::mt19937 g(13);
+    {
+        Check c;                 // no nodes, no room: nothing stored
+        Check::Out o;
+        o.room = 0;
+        uint32_t head = 1u;
+        compile_sequential(c.prog.data(), c.consts.data(), 0, o, 0, &head, Emit{eval_ops(0), 1, 1}, c.ud, -1, Shadow{}, un, bi);
+        if (o.worst >= 0 || head != 0u) {
+            std::printf("empty: a word stored\n");
+            return 1;
+        }
+    }
+    for (int i = 0; i < n; ++i) {
+        Check c;
+        c.X.resize(2);
+        c.consts.assign(256, 0.5f);
+        c.define(GP_OP_USER1, {node(GP_OP_ADD), node(GP_OP_VAR, 0), node(GP_OP_CONST, 0)}, {0.25f});
+        const int L = 1 + static_cast<int>(g() % (i % 8 ? 40 : 3000));
+        const int kind = i % 4;
+        for (int k = 0; k < L; ++k) {
+            if (kind == 0) c.prog.push_back(node(GP_OP_VAR, g() % 2));
+            else if (kind == 1) c.prog.push_back(node(GP_OP_ADD));
+            else c.prog.push_back(node(g() % (kind == 2 ? GP_OP_LIMIT : 256u), g() % 256));
+        }
+        if (!c.check("malformed", true)) return 1;
+    }
+    std::printf("%d programs\n", n);
+    return 0;
+}
+
 int main(int argc, char** argv) {
+    if (argc > 2 && !std::strcmp(argv[1], "malformed")) return malformed_programs(std::atoi(argv[2]));
     if (argc > 1 && !std::strcmp(argv[1], "chains")) return chains();
     return random_programs(argc > 2 ? std::atoi(argv[2]) : 2000);
 }

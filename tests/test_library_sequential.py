@@ -24,7 +24,7 @@ def checker(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("args", [("chains",), ("random", "4000")])
+@pytest.mark.parametrize("args", [("chains",), ("random", "4000"), ("malformed", "4000")])
 def test_streams_stay_in_their_room_and_give_the_programs_value(checker, args):
     r = subprocess.run([checker, *args], capture_output=True, text=True)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-2000:])
