@@ -88,8 +88,12 @@ constexpr int kQueues = 8;
 constexpr int kQueueStride = 16;
 constexpr size_t kCounterBytes = 1024;
 constexpr int kFlagWord = 128;
-// a second such block, in scratch that grows, holds the adjoint kernel's
+// two more such blocks, in scratch that grows, hold the adjoint kernels', and
+// in word kLongWord the number of programs of more than kParNodes nodes, which
+// come first in the order
 constexpr int kCounterSet = kCounterBytes / sizeof(uint32_t);
+constexpr int kCounterSets = 3;
+constexpr int kLongWord = 129;
 
 struct Sched {
     int64_t chunk;
@@ -486,9 +490,12 @@ struct OrderArgs {
     const int32_t* len;
     int32_t P;
     int32_t* order;
-    uint32_t* counter;     // two sets of queues' counters, or with `sets` 1, one
+    uint32_t* counter;     // `sets` sets of queues' counters: one, or kCounterSets
     int32_t sets;
 };
+// the longest program of the wavefront-parallel compilers and of k_adjoint
+constexpr int kParNodes = 1024;
+constexpr int64_t kAdjCodePerNode = 8;  // 16-byte units of the adjoint's code per node (k_adjoint's instructions: two each)
 
 template <int THREADS>
 __device__ __forceinline__ void order_programs(const OrderArgs& oa, OrderLds& sh) {
@@ -500,14 +507,16 @@ __device__ __forceinline__ void order_programs(const OrderArgs& oa, OrderLds& sh
     for (int q = tid; q < oa.sets * kQueues; q += THREADS)
         oa.counter[(q / kQueues) * kCounterSet + (q % kQueues) * kQueueStride] = 0u;
     __syncthreads();
-    // key: kBins-1 - min(len, kBins-1), so longer programs come first
+    // key: 0 above kParNodes, else kBins-1 - min(len, kBins-2), so that longer
+    // programs come first
     auto walk = [&](auto visit) {
         for (int64_t p0 = tid; p0 < P; p0 += THREADS * kE) {
             int32_t key[kE];
 #pragma unroll
             for (int e = 0; e < kE; ++e) {
                 const int64_t p = p0 + e * THREADS;
-                key[e] = p < P ? kBins - 1 - min(max(len[p], 0), kBins - 1) : -1;
+                const int32_t n = p < P ? len[p] : 0;
+                key[e] = p >= P ? -1 : n > kParNodes ? 0 : kBins - 1 - min(max(n, 0), kBins - 2);
             }
 #pragma unroll
             for (int e = 0; e < kE; ++e)
@@ -537,43 +546,34 @@ __device__ __forceinline__ void order_programs(const OrderArgs& oa, OrderLds& sh
         at += c[e];
     }
     __syncthreads();
+    if (tid > 0 && tid < oa.sets) oa.counter[tid * kCounterSet + kLongWord] = static_cast<uint32_t>(sh.start[1]);
+    __syncthreads();
     walk([&](int32_t p, int32_t key) { oa.order[atomicAdd(&sh.start[key], 1)] = p; });
 }
 
 // ---------------------------------------------------------------------------
-// k_compile: one lane per program.  Scans the prefix list right to left (the
-// evaluation order of Sec. III-A) and emits instructions in that order.  A
-// terminal at position i is the first operand of the function at i-1 exactly
-// when that function is binary (its first operand starts right after it), so
-// such pairs become one kFold instruction; a unary function is chained onto
-// the instruction before it.  A shadow stack (in LDS, one column per lane)
-// tracks, for each value on the evaluation stack, the first instruction of
-// the subtree that produced it, whether that subtree holds a constant, and
-// whether it holds nothing but constants.  With `fold`, a subtree of
-// constants only is evaluated here, once, by the same float32 functions the
-// evaluation kernel applies per row (so every row would get these very
-// bits), and its instructions are replaced by one push of the result.
+// k_compile: the instructions of k_adjoint_long, one lane per program of more
+// than kParNodes nodes.  Scans the prefix list right to left (the evaluation
+// order of Sec. III-A) and emits instructions in that order.  A terminal at
+// position i is the first operand of the function at i-1 exactly when that
+// function is binary (its first operand starts right after it), so such pairs
+// become one kFold instruction; a unary function is chained onto the
+// instruction before it.  A shadow stack (in LDS, one column per lane) tracks,
+// for each value on the evaluation stack, the first instruction of the subtree
+// that produced it and whether that subtree holds a constant.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kShStartMask = 0x3fffffffu;   // shadow entry: start | const-only << 30 | active << 31
+constexpr uint32_t kShStartMask = 0x3fffffffu;   // shadow entry: start | active << 31
 
-__global__ __launch_bounds__(kBlock) void k_compile(PopView pop, OrderArgs oa, uint4* __restrict__ code,
-                                                     int32_t* __restrict__ clen, int fold) {
+__global__ __launch_bounds__(kBlock) void k_compile(PopView pop, uint4* __restrict__ code, int32_t* __restrict__ clen) {
     __shared__ uint32_t shadow[GP_MAX_STACK][kBlock];
-    __shared__ float shadow_v[GP_MAX_STACK][kBlock];   // value of a const-only entry
-    static_assert(sizeof(OrderLds) <= sizeof(shadow), "");
-    if (blockIdx.x == 0) {
-        order_programs<kBlock>(oa, *reinterpret_cast<OrderLds*>(&shadow[0][0]));
-        return;
-    }
-    const int32_t p = (static_cast<int32_t>(blockIdx.x) - 1) * kBlock + threadIdx.x;
-    if (p >= pop.P) return;
+    const int32_t p = static_cast<int32_t>(blockIdx.x) * kBlock + threadIdx.x;
+    if (p >= pop.P || pop.len[p] <= kParNodes) return;
     const int64_t off = pop.prog_off[p];
     const int32_t L = pop.len[p];
     const uint32_t* pn = pop.nodes + off;
     const float* pc = pop.consts + pop.const_off[p];
-    uint4* out = code + off;
+    uint4* out = code + off * kAdjCodePerNode;
     uint32_t* sh = &shadow[0][threadIdx.x];   // entry h at sh[h * kBlock]
-    float* shv = &shadow_v[0][threadIdx.x];
     int h = 0;                                // shadow stack height
     int32_t k = 0;                            // instructions emitted
     uint4 pend = make_uint4(0u, 0u, 0u, 0u);  // the last instruction, still open for a unary chain
@@ -581,17 +581,9 @@ __global__ __launch_bounds__(kBlock) void k_compile(PopView pop, OrderArgs oa, u
     for (int32_t i = L - 1; i >= 0; --i) {
         const uint32_t w = pn[i];
         const uint32_t op = w & 0xffu;
-        const uint32_t arg = w >> 8;
+        const uint32_t arg = w >> 8;          // feature index, or constant slot
         const int top_i = min(max(h - 1, 0), GP_MAX_STACK - 1);
         const int ar = arity(op);
-        if (ar == 1 && fold && h >= 1 && ((sh[top_i * kBlock] >> 30) & 1u)) {
-            // unary of a constant: the pending instruction is that constant's push
-            float t[1] = {shv[top_i * kBlock]};
-            apply_unary<1>(unary_index(op), t, global_tabs());
-            shv[top_i * kBlock] = t[0];
-            pend.y = __float_as_uint(t[0]);
-            continue;
-        }
         if (ar == 1 && chain >= 0 && chain < 8) {
             // a unary function applied to the pending instruction's result:
             // same subtree start and activity as its operand
@@ -599,64 +591,32 @@ __global__ __launch_bounds__(kBlock) void k_compile(PopView pop, OrderArgs oa, u
             ++chain;
             continue;
         }
-        uint32_t x, start, active, konst = 0u;
-        float kval = 0.0f;
-        uint2 xy;
+        uint32_t x, start, active, y;
         if (op <= GP_OP_CONST) {
             const uint32_t is_c = op == GP_OP_CONST ? 1u : 0u;
-            const uint32_t farg = arg;   // feature index, or constant slot (used by the adjoint)
             const uint32_t prev = i >= 1 ? (pn[i - 1] & 0xffu) : 0u;
             if (i >= 1 && i != L - 1 && arity(prev) == 2) {
                 const uint32_t top = sh[top_i * kBlock];    // the second operand
                 start = top & kShStartMask;
-                if (fold && is_c && ((top >> 30) & 1u)) {
-                    // constant op constant: evaluated here
-                    float a[1] = {pc[arg]};
-                    const float b[1] = {shv[top_i * kBlock]};
-                    apply_binary<1>(binary_index(prev), a, b);
-                    x = enc(kPush, 0, 1u, 0u);
-                    active = 1u;
-                    konst = 1u;
-                    kval = a[0];
-                    k = static_cast<int32_t>(start);   // drop the operand's instructions
-                    chain = -1;
-                } else {
-                    x = enc(kFold, binary_index(prev), is_c, farg);
-                    active = is_c | (top >> 31);
-                }
+                x = enc(kFold, binary_index(prev), is_c, arg);
+                active = is_c | (top >> 31);
                 --h;
                 --i;
             } else {
-                x = enc(kPush, 0, is_c, farg);
+                x = enc(kPush, 0, is_c, arg);
                 start = static_cast<uint32_t>(k);
                 active = is_c;
-                konst = is_c;
-                kval = is_c ? pc[arg] : 0.0f;
             }
-            xy = (is_c || konst) ? make_uint2(x | kActive, __float_as_uint(konst ? kval : pc[arg]))
-                                 : make_uint2(x | (active ? kActive : 0u), start);
+            y = is_c ? __float_as_uint(pc[arg]) : start;
         } else if (ar == 2) {
             const int i1 = min(max(h - 1, 0), GP_MAX_STACK - 1), i2 = min(max(h - 2, 0), GP_MAX_STACK - 1);
             const uint32_t first = sh[i1 * kBlock];      // top: the first operand
             const uint32_t second = sh[i2 * kBlock];     // evaluated before it
             start = second & kShStartMask;
             h -= 2;
-            if (fold && ((first >> 30) & 1u) && ((second >> 30) & 1u)) {
-                float a[1] = {shv[i1 * kBlock]};
-                const float b[1] = {shv[i2 * kBlock]};
-                apply_binary<1>(binary_index(op), a, b);
-                x = enc(kPush, 0, 1u, 0u);
-                active = 1u;
-                konst = 1u;
-                kval = a[0];
-                k = static_cast<int32_t>(start);
-                chain = -1;
-                xy = make_uint2(x | kActive, __float_as_uint(kval));
-            } else {
-                x = enc(kBin, binary_index(op), 0, 0);
-                active = (first >> 31) | (second >> 31);
-                xy = make_uint2(x | (active ? kActive : 0u), start);
-            }
+            x = enc(kBin, binary_index(op), 0, 0);
+            active = (first >> 31) | (second >> 31);
+            y = start;
         } else {
             // a unary function with a full chain before it: its own instruction
             const uint32_t top = sh[top_i * kBlock];
@@ -664,29 +624,25 @@ __global__ __launch_bounds__(kBlock) void k_compile(PopView pop, OrderArgs oa, u
             start = top & kShStartMask;
             active = top >> 31;
             --h;
-            xy = make_uint2(x | (active ? kActive : 0u), start);
+            y = start;
         }
         if (chain >= 0) out[k - 1] = pend;
-        pend = make_uint4(xy.x, xy.y, 0u, 0u);
+        pend = make_uint4(x | (active ? kActive : 0u), y, 0u, 0u);
         chain = 0;
         // (valid programs keep 1 <= h <= GP_MAX_STACK; the clamps only keep an
         // invalid one inside this array)
         h = max(h, 0);
-        const int hi = min(h, GP_MAX_STACK - 1);
-        sh[hi * kBlock] = start | (konst << 30) | (active << 31);
-        shv[hi * kBlock] = kval;
+        sh[min(h, GP_MAX_STACK - 1) * kBlock] = start | (active << 31);
         ++h;
         ++k;
     }
     if (chain >= 0) out[k - 1] = pend;
     clen[p] = k;
-    // the adjoint's reverse walk (its compile is the one without folding),
-    // from the last instruction down: an inactive instruction stands for its
-    // whole subtree (skipped, one stack entry); each active one is linked to
-    // the next active one and counts the skips between them.  (Indices stay
-    // below 2^26 for programs the adjoint accepts; skips never exceed the
-    // stack depth, below 2^6.)
-    if (fold) return;
+    // the reverse walk, from the last instruction down: an inactive instruction
+    // stands for its whole subtree (skipped, one stack entry); each active one
+    // is linked to the next active one and counts the skips between them.
+    // (Indices stay below 2^26 for programs the adjoint accepts; skips never
+    // exceed the stack depth, below 2^6.)
     int32_t last = -1;
     uint32_t skips = 0u;
     for (int32_t q = k - 1; q >= 0;) {
@@ -734,7 +690,6 @@ constexpr int64_t kCodePad = 32;
 
 // A wavefront's program in the parallel path, one entry per node, at most
 // kParNodes (13 KB: twelve wavefronts per CU).
-constexpr int kParNodes = 1024;
 constexpr int kSeqLanes = 60;     // programs side by side: their entries take no more LDS than that
 struct ParNodes {
     float val[kParNodes];        // value of a constant subtree; later, an instruction's feature
@@ -1101,7 +1056,6 @@ struct AdjNodes {
 };
 constexpr int kAdjCompileWaves = 2;
 constexpr uint8_t kActiveEnt = 32;      // ent bit: the subtree holds a constant
-constexpr int64_t kAdjCodePerNode = 8;  // uint4 (two instructions each) of code per node
 
 // What a binary function does with its operands: which is fused (kOpFold...)
 // or evaluated first, and in which order the function takes them.
@@ -1314,8 +1268,8 @@ __device__ __forceinline__ void compile_adjoint_program(const PopView& pop, cons
     const int64_t cend = pop.const_off[p + 1];
     for (int64_t i = pop.const_off[p] + lane; i < cend; i += kWave) ac.gextra[i] = 0.0;
     const int64_t off = pop.prog_off[p];
-    // (the caller's bound on the lengths is at most kParNodes)
-    const int32_t L = min(pop.len[p], kParNodes);
+    const int32_t L = pop.len[p];
+    if (L > kParNodes) return;         // (k_compile's)
     const uint32_t* pn = pop.nodes + off;
     const float* pc = pop.consts + pop.const_off[p];
     uint2* out = reinterpret_cast<uint2*>(code + off * kAdjCodePerNode);
@@ -2040,8 +1994,8 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const double* __restrict__ 
 // k_adjoint_long: derivative of every program's fitness with respect to each
 // of its constants (not in the paper), by reverse mode over the compiled
 // instructions, one wavefront per (row chunk, program) work item; for
-// populations with a program of more than kParNodes nodes (k_adjoint takes the
-// rest: its compiler holds a program's nodes in LDS).
+// programs of more than kParNodes nodes (k_adjoint takes the rest: its compiler
+// holds a program's nodes in LDS).
 //
 // Per tile of 64*R rows: a forward pass runs the stack machine and records
 // on a tape the local derivatives each instruction will need (both partials
@@ -2195,7 +2149,7 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint_long(PopView pop,
     };
 
     // work items: the evaluation kernel's per-XCD queues, one item per claim
-    Claims claims(s, static_cast<uint32_t>(pop.P), static_cast<uint32_t>(wid));
+    Claims claims(s, ldu(s.counter + kLongWord), static_cast<uint32_t>(wid));
     int qx;
     uint32_t it, it_end;
     while (claims.next(lane, &qx, &it, &it_end)) {
@@ -2208,7 +2162,7 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint_long(PopView pop,
         const int32_t CL = ldu(cv.clen + p);
         const int64_t cbase = ldu(pop.const_off + p);
         const int32_t nconst = static_cast<int32_t>(ldu(pop.const_off + p + 1) - cbase);
-        const uint4* __restrict__ pcode = cv.code + off;
+        const uint4* __restrict__ pcode = cv.code + off * kAdjCodePerNode;
         const int64_t r0 = static_cast<int64_t>(c) * s.chunk;
         const int64_t r1 = min(r0 + s.chunk, N);
         const float gsc = gscale ? ldu(gscale + p) : 1.0f;
@@ -2661,8 +2615,9 @@ __global__ __launch_bounds__(kAdjWaves * kWave, adjoint_waves(R)) void k_adjoint
     in.ld4 = static_cast<uint64_t>(ld) * 4u;
     in.area = reinterpret_cast<uint64_t>(area + (static_cast<int64_t>(blockIdx.x) * kAdjWaves + wid) * area_bytes);
     const double W = *wsum;
-    const uint32_t P = static_cast<uint32_t>(pop.P);
-    Claims claims(s, P, wid);
+    const uint32_t n_long = ldu(s.counter + kLongWord);      // (k_adjoint_long's, first in the order)
+    const int32_t* __restrict__ order = s.order + n_long;
+    Claims claims(s, static_cast<uint32_t>(pop.P) - n_long, wid);
     int qx;
     uint32_t it, it_end;
     while (claims.next(lane, &qx, &it, &it_end)) {
@@ -2670,7 +2625,7 @@ __global__ __launch_bounds__(kAdjWaves * kWave, adjoint_waves(R)) void k_adjoint
         qx = static_cast<int>(uniform(static_cast<uint32_t>(qx)));
         const uint32_t per = claims.per(static_cast<uint32_t>(qx)), cq = it / per;
         const int32_t c = claims.chunk(cq, qx);
-        const int32_t p = ldu(s.order + claims.program(it - cq * per, qx));
+        const int32_t p = ldu(order + claims.program(it - cq * per, qx));
         const int64_t off = ldu(pop.prog_off + p);
         const uint32_t head = static_cast<uint32_t>(ldu(cv.clen + p));
         const int64_t cbase = ldu(pop.const_off + p);
@@ -2820,11 +2775,6 @@ __global__ __launch_bounds__(kBlock) void k_finalize_grad(const double* __restri
             for (int c = 0; c < n_chunks; ++c) sum += gpart[i * n_chunks + c];
         grad[i] = static_cast<float>(sum);
     }
-}
-
-__global__ __launch_bounds__(kBlock) void k_zero(double* __restrict__ p, int64_t n) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (i < n) p[i] = 0.0;
 }
 
 // sum of weights over all rows (float64), from the per-chunk statistics
@@ -3393,7 +3343,7 @@ __global__ __launch_bounds__(kWave) void k_stamp(uint64_t* __restrict__ out) {
 // ---------------------------------------------------------------------------
 
 struct DeviceScratch {
-    void* counter = nullptr;     // 256 bytes: the work counter
+    void* counter = nullptr;     // the work counters: kCounterSets blocks of 1 KiB
     int32_t* order = nullptr;
     size_t order_cap = 0;
     double* part = nullptr;
@@ -3476,8 +3426,8 @@ gp_status grow(void** ptr, size_t* cap, size_t need_elems, size_t elem) {
 
 gp_status scratch_init(DeviceScratch& s, int dev) {
     if (s.counter) return GP_OK;
-    GP_HIP(hipMalloc(&s.counter, 2 * kCounterBytes));
-    GP_HIP(hipMemset(s.counter, 0, 2 * kCounterBytes));
+    GP_HIP(hipMalloc(&s.counter, kCounterSets * kCounterBytes));
+    GP_HIP(hipMemset(s.counter, 0, kCounterSets * kCounterBytes));
     hipDeviceProp_t prop;
     GP_HIP(hipGetDeviceProperties(&prop, dev));
     s.n_cu = prop.multiProcessorCount;
@@ -3824,13 +3774,14 @@ gp_status chunking(const gp_population_dev* pop, const gp_dataset_dev* data, con
 // Shared front half of the evaluation paths: configuration, scratch, the
 // length ordering and the instruction streams.  `force` (nullable) overrides
 // the configuration choice.  The evaluation kernel's stream (constant
-// subtrees folded) is compiled unless `adjoint` asks for the adjoint's
-// stream instead (for k_adjoint at adjoint_R rows per lane, or, 0, for
-// k_adjoint_long); `both` compiles the two (a backward pass that runs a
-// forward pass first).
+// subtrees folded) is compiled unless adjoint_R > 0 asks for the adjoint's
+// instead, for k_adjoint at that many rows per lane and, where `longer` says
+// that there may be programs of more than kParNodes nodes, for k_adjoint_long;
+// `both` compiles the two (a backward pass that runs a forward pass first).
 gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_dataset_dev* data, int mode,
                   int metric, hipStream_t st, const LaunchCfg* force, PopView* pv, CodeView* cvw, DataView* dv,
-                  Sched* sch, LaunchCfg* cfg, bool adjoint = false, bool both = false, int adjoint_R = 0) {
+                  Sched* sch, LaunchCfg* cfg, int adjoint_R = 0, bool both = false, bool longer = false) {
+    const bool adjoint = adjoint_R > 0;
     *pv = PopView{pop->nodes, pop->prog_off, pop->consts, pop->const_off, pop->len, pop->n_programs};
     *dv = DataView{data->X, data->ld, data->n_features, data->n_rows, data->y, data->w};
     *cfg = force ? *force
@@ -3840,7 +3791,7 @@ gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_data
     if (rc != GP_OK) return rc;
     const ExpandPlan xp = expand_plan(mode, metric);
     rc = reserve(sc, pop->n_programs, pop->total_nodes, n_chunks, mode, metric,
-                 adjoint ? (adjoint_R > 0 ? kAdjCodePerNode : 1) : 0, xp.mul, xp.add);
+                 adjoint ? kAdjCodePerNode : 0, xp.mul, xp.add);
     if (rc != GP_OK) return rc;
     // items per claim: single ones up to 64 a resident wavefront (16 per CU).
     // A claim costs its queue about 25 ns, but consecutive items are programs of
@@ -3853,7 +3804,7 @@ gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_data
     *sch = Sched{chunk, static_cast<int32_t>(n_chunks), n_items, sc->order, static_cast<uint32_t*>(sc->counter),
                  batch, xp.lds_slots, 0, 0};
     const bool eval = !adjoint || both;
-    const OrderArgs oa{pop->len, pop->n_programs, sc->order, static_cast<uint32_t*>(sc->counter), adjoint ? 2 : 1};
+    const OrderArgs oa{pop->len, pop->n_programs, sc->order, static_cast<uint32_t*>(sc->counter), adjoint ? kCounterSets : 1};
     // programs per compiling wavefront: one, or while user functions are
     // defined as many as leave each resident wavefront (12 per CU) one group
     const int64_t resident = static_cast<int64_t>(sc->n_cu) * 12;
@@ -3868,13 +3819,13 @@ gp_status prepare(DeviceScratch* sc, const gp_population_dev* pop, const gp_data
         const int64_t blocks = 1 + (with_adjoint ? (P + waves - 1) / waves : 0) + (with_eval ? (P + per - 1) / per : 0);
         hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(waves * kWave), 0, st, *pv, oa, ec, ac);
     };
-    if (adjoint_R > 0 && eval) compile(k_compile_streams<true, true>, compile_waves<true, true>(), true, true);
-    else if (adjoint_R > 0) compile(k_compile_streams<false, true>, compile_waves<false, true>(), false, true);
-    else if (eval) compile(k_compile_streams<true, false>, compile_waves<true, false>(), true, false);
+    if (adjoint && eval) compile(k_compile_streams<true, true>, compile_waves<true, true>(), true, true);
+    else if (adjoint) compile(k_compile_streams<false, true>, compile_waves<false, true>(), false, true);
+    else compile(k_compile_streams<true, false>, compile_waves<true, false>(), true, false);
     GP_HIP(hipGetLastError());
-    if (adjoint && adjoint_R == 0) {
-        const unsigned blocks = 1 + (pop->n_programs + kBlock - 1) / kBlock;
-        hipLaunchKernelGGL(k_compile, dim3(blocks), dim3(kBlock), 0, st, *pv, oa, sc->code, sc->clen, 0);
+    if (adjoint && longer) {
+        const unsigned blocks = (pop->n_programs + kBlock - 1) / kBlock;
+        hipLaunchKernelGGL(k_compile, dim3(blocks), dim3(kBlock), 0, st, *pv, sc->code, sc->clen);
         GP_HIP(hipGetLastError());
     }
     *cvw = CodeView{adjoint ? sc->code : nullptr, adjoint ? sc->clen : nullptr,
@@ -5306,17 +5257,18 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
     const bool needs_forward = metric == GP_METRIC_RMSE || metric == GP_METRIC_PEARSON;
     // programs of at most kParNodes nodes: k_adjoint, at the rows per lane of a
     // forced configuration, else of the heuristic (4: the fastest, or within 5%
-    // of it, from 300 rows of 20 programs to 1M rows of 100); longer ones:
-    // k_adjoint_long, at a forced configuration's, else the one (2 or 4) that
-    // keeps more rows in flight per CU (below)
+    // of it, from 300 rows of 20 programs to 1M rows of 100); longer ones, by
+    // their real lengths: k_adjoint_long, at a forced configuration's, else the
+    // one (2 or 4) that keeps more rows in flight per CU (below).  max_len only
+    // says whether there may be any.
     const bool longer = pop->max_len > kParNodes;
     const int RA = g_forced ? g_forced_cfg.R
-                            : (longer ? 0 : heuristic_cfg(data->n_features, data->n_rows, pop->n_programs, sc->n_cu, kernel_class(1, metric)).R);
+                            : heuristic_cfg(data->n_features, data->n_rows, pop->n_programs, sc->n_cu, kernel_class(1, metric)).R;
     const int64_t nc = std::max<int64_t>(pop->total_consts, 1);
     rc = grow(reinterpret_cast<void**>(&sc->gextra), &sc->gextra_cap, static_cast<size_t>(nc), sizeof(double));
     if (rc != GP_OK) return rc;
-    rc = prepare(sc, pop, data, 1, metric, st, nullptr, &pv, &cvw, &dv, &sch, &cfg, true, needs_forward,
-                 longer ? 0 : RA);
+    rc = prepare(sc, pop, data, 1, metric, st, nullptr, &pv, &cvw, &dv, &sch, &cfg, RA, needs_forward,
+                 longer);
     if (rc != GP_OK) return rc;
     const int32_t P = pop->n_programs;
     const int64_t tape_max = 2 * static_cast<int64_t>(pop->max_len) + 2;   // tape entries per wavefront
@@ -5349,43 +5301,15 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
                                sc->ystat, sch.n_chunks, P, data->n_rows, has_w, fit, sc->stats);
         GP_HIP(hipGetLastError());
     }
-    if (longer) {      // (the compiler of the shorter clears it)
-        hipLaunchKernelGGL(k_zero, dim3(static_cast<unsigned>((nc + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
-                           sc->gextra, nc);
-        GP_HIP(hipGetLastError());
-    }
     auto occ = [](const void* k) {
         int n = 0;
         (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kAdjWaves * kWave, 0);
         return n;
     };
     double* lossp = needs_forward ? nullptr : sc->part;
-    auto go = [&](auto kernel, int64_t wave_floats) -> gp_status {
-        int per_cu = 0;
-        GP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kAdjWaves * kWave, 0));
-        per_cu = std::max(per_cu, 1);
-        int64_t blocks = std::min<int64_t>(static_cast<int64_t>(per_cu) * sc->n_cu,
-                                           (sch.n_items + kAdjWaves - 1) / kAdjWaves);
-        blocks = std::max<int64_t>(blocks, 1);
-        gp_status r2 = grow(reinterpret_cast<void**>(&sc->tape), &sc->tape_cap,
-                            static_cast<size_t>(blocks) * kAdjWaves * static_cast<size_t>(wave_floats), sizeof(float));
-        if (r2 != GP_OK) return r2;
-        Sched sl = sch;
-        sl.counter += kCounterSet;
-        sl.batch = 1;
-        sl.blocks = static_cast<int32_t>(blocks);
-        sl.wpb = kAdjWaves;
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kAdjWaves * kWave), 0, st, pv, cvw, dv, sl,
-                           needs_forward ? sc->stats : nullptr, wsum, grad_fitness, lossp, sc->gpart, sc->gextra,
-                           sc->tape, wave_floats);
-        GP_HIP(hipGetLastError());
-        return GP_OK;
-    };
-    // k_adjoint: tape entries are at most one per unary function and two per
-    // binary one, of which there are fewer than half the nodes
-    const int64_t entries = static_cast<int64_t>(pop->max_len) + 2;
-    auto go_short = [&](auto kernel, size_t lds_wave, int64_t area_bytes) -> gp_status {
-        const size_t lds = sizeof(MathTabsLds) + kAdjWaves * lds_wave;
+    // `tape_floats` of the tape area per wavefront; `area` in the unit the
+    // kernel takes its size in; counter set `set`
+    auto go = [&](auto kernel, int set, size_t lds, int64_t tape_floats, auto* tape, int64_t area) -> gp_status {
         int per_cu = 0;
         GP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kAdjWaves * kWave, lds));
         per_cu = std::max(per_cu, 1);
@@ -5393,40 +5317,53 @@ gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev
                                            (sch.n_items + kAdjWaves - 1) / kAdjWaves);
         blocks = std::max<int64_t>(blocks, 1);
         gp_status r2 = grow(reinterpret_cast<void**>(&sc->tape), &sc->tape_cap,
-                            static_cast<size_t>(blocks) * kAdjWaves * static_cast<size_t>(area_bytes / 4), sizeof(float));
+                            static_cast<size_t>(blocks) * kAdjWaves * static_cast<size_t>(tape_floats), sizeof(float));
         if (r2 != GP_OK) return r2;
         Sched sl = sch;
-        sl.counter += kCounterSet;
+        sl.counter += set * kCounterSet;
         sl.batch = 1;
         sl.blocks = static_cast<int32_t>(blocks);
         sl.wpb = kAdjWaves;
+        using Tape = std::remove_pointer_t<decltype(tape)>;
         hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kAdjWaves * kWave), lds, st, pv, cvw, dv, sl,
                            needs_forward ? sc->stats : nullptr, wsum, grad_fitness, lossp, sc->gpart, sc->gextra,
-                           reinterpret_cast<unsigned char*>(sc->tape), area_bytes);
+                           reinterpret_cast<Tape*>(sc->tape), area);
         GP_HIP(hipGetLastError());
         return GP_OK;
     };
-#define GP_ADJ_SHORT(RR, M) go_short(k_adjoint<RR, M>, adjoint_lds_wave<RR>(), adjoint_area<RR>(entries))
-#define GP_ADJ_LONG(RR, M) go(k_adjoint_long<RR, M>, adjoint_wave_floats<RR>(tape_max))
-#define GP_ADJ_AUTO(M)                                                                         \
-    (4 * occ(reinterpret_cast<const void*>(k_adjoint_long<4, M>)) >                            \
-             2 * occ(reinterpret_cast<const void*>(k_adjoint_long<2, M>))                      \
-         ? GP_ADJ_LONG(4, M)                                                                   \
-         : GP_ADJ_LONG(2, M))
-#define GP_ADJ(M)                                                                              \
-    (!longer ? (RA == 1 ? GP_ADJ_SHORT(1, M) : RA == 2 ? GP_ADJ_SHORT(2, M) : GP_ADJ_SHORT(4, M)) \
-             : (RA == 0 ? GP_ADJ_AUTO(M) : RA == 1 ? GP_ADJ_LONG(1, M) : RA == 2 ? GP_ADJ_LONG(2, M) : GP_ADJ_LONG(4, M)))
-    switch (metric) {
-    case GP_METRIC_MAE: rc = GP_ADJ(GP_METRIC_MAE); break;
-    case GP_METRIC_MSE: rc = GP_ADJ(GP_METRIC_MSE); break;
-    case GP_METRIC_RMSE: rc = GP_ADJ(GP_METRIC_RMSE); break;
-    case GP_METRIC_LOGLOSS: rc = GP_ADJ(GP_METRIC_LOGLOSS); break;
-    default: rc = GP_ADJ(GP_METRIC_PEARSON); break;
-    }
-#undef GP_ADJ
-#undef GP_ADJ_AUTO
+    // k_adjoint: tape entries are at most one per unary function and two per
+    // binary one, of which there are fewer than half the nodes
+    const int64_t entries = std::min<int64_t>(pop->max_len, kParNodes) + 2;
+    auto go_short = [&](auto kernel, size_t lds_wave, int64_t bytes) {
+        return go(kernel, 1, sizeof(MathTabsLds) + kAdjWaves * lds_wave, bytes / 4, static_cast<unsigned char*>(nullptr), bytes);
+    };
+    auto go_long = [&](auto kernel, int64_t floats) {
+        return go(kernel, 2, size_t{0}, floats, static_cast<float*>(nullptr), floats);
+    };
+#define GP_ADJ_SHORT(RR) go_short(k_adjoint<RR, M>, adjoint_lds_wave<RR>(), adjoint_area<RR>(entries))
+#define GP_ADJ_LONG(RR) go_long(k_adjoint_long<RR, M>, adjoint_wave_floats<RR>(tape_max))
+    auto adjoints = [&](auto metric_c) -> gp_status {
+        constexpr int M = decltype(metric_c)::value;
+        if (longer) {
+            const int RL = g_forced ? RA
+                           : 4 * occ(reinterpret_cast<const void*>(k_adjoint_long<4, M>)) >
+                                   2 * occ(reinterpret_cast<const void*>(k_adjoint_long<2, M>))
+                               ? 4
+                               : 2;
+            const gp_status r2 = RL == 1 ? GP_ADJ_LONG(1) : RL == 2 ? GP_ADJ_LONG(2) : GP_ADJ_LONG(4);
+            if (r2 != GP_OK) return r2;
+        }
+        return RA == 1 ? GP_ADJ_SHORT(1) : RA == 2 ? GP_ADJ_SHORT(2) : GP_ADJ_SHORT(4);
+    };
 #undef GP_ADJ_LONG
 #undef GP_ADJ_SHORT
+    switch (metric) {
+    case GP_METRIC_MAE: rc = adjoints(std::integral_constant<int, GP_METRIC_MAE>{}); break;
+    case GP_METRIC_MSE: rc = adjoints(std::integral_constant<int, GP_METRIC_MSE>{}); break;
+    case GP_METRIC_RMSE: rc = adjoints(std::integral_constant<int, GP_METRIC_RMSE>{}); break;
+    case GP_METRIC_LOGLOSS: rc = adjoints(std::integral_constant<int, GP_METRIC_LOGLOSS>{}); break;
+    default: rc = adjoints(std::integral_constant<int, GP_METRIC_PEARSON>{}); break;
+    }
     if (rc != GP_OK) return rc;
     if (!needs_forward && fitness_out) {
         if (metric == GP_METRIC_MAE)
