@@ -421,7 +421,7 @@ gp_status gp_tournament(const float* fitness, const int32_t* len, int32_t n_prog
  * atomics.  Rows per lane: a forced launch configuration's, else 4; programs
  * of more than 1,024 nodes, which a kernel of their own takes where max_len
  * allows any, 2 or 4, whichever keeps more rows in flight per CU at that
- * kernel's occupancy.  Scratch: 128 bytes per node, and per wavefront 64 floats
+ * kernel's occupancy.  Scratch: 64 bytes per node, and per wavefront 64 floats
  * per row per lane for each of max_len - 40 tape entries (at most 984; where
  * max_len is above 1,024, 2 * max_len + 2). */
 gp_status gp_fitness_backward(const gp_population_dev* pop, const gp_dataset_dev* data,

@@ -495,7 +495,11 @@ struct OrderArgs {
 };
 // the longest program of the wavefront-parallel compilers and of k_adjoint
 constexpr int kParNodes = 1024;
-constexpr int64_t kAdjCodePerNode = 8;  // 16-byte units of the adjoint's code per node (k_adjoint's instructions: two each)
+// 16-byte units of the adjoint's code per node, two instructions of k_adjoint's
+// each.  A program of n nodes takes at most 6 n instructions, the reloads and
+// both ends 6.1 n (quotients of roots of constants: 10 a quotient of two
+// subtrees, 8 a root of a constant; no other nodes take more for their number).
+constexpr int64_t kAdjCodePerNode = 4;
 
 template <int THREADS>
 __device__ __forceinline__ void order_programs(const OrderArgs& oa, OrderLds& sh) {

@@ -6,6 +6,8 @@ import numpy as np
 import pytest
 
 import oracle
+from test_gpu_adjoint import check_grads, oracle_reference, run_backward
+from test_gpu_adjoint_interpreter import program
 
 pytestmark = pytest.mark.gpu
 
@@ -66,3 +68,32 @@ def test_by_length(gp, metric):
             assert np.array_equal(f, np.concatenate([alone[k][1] for k in order]))
     finally:
         gp.set_launch_config(None)
+
+
+def densest(units):
+    """Quotients of `units` roots of constants: the most instructions for the
+    nodes (6 a node)."""
+    if units == 1:
+        return [oracle.node(oracle.SQRT), "c"]
+    return [oracle.node(oracle.DIV)] + densest((units + 1) // 2) + densest(units // 2)
+
+
+def test_streams_that_fill_their_room(gp):
+    """Next to each other, so that a word past a program's room would be in
+    its neighbour's stream."""
+    lists = [densest(u) for u in (1, 2, 3, 4, 8, 21, 64, 340, 341, 1, 341, 341, 2)]
+    op = oracle.from_programs([program(w) for w in lists])
+    assert op.length.max() == 1022
+    host = gp.HostPopulation(op.nodes, op.prog_off, op.consts, op.const_off, op.length)
+    X = np.random.default_rng(5).uniform(-1, 1, size=(2, 65)).astype(np.float32)
+    y = np.random.default_rng(6).uniform(8, 12, size=65).astype(np.float32)
+    for R in (1, 4):
+        print(f"densest programs, {R} rows per lane", flush=True)
+        gp.set_launch_config((R, 0, 1))
+        try:
+            g, _, _ = run_backward(gp, host, X, y, None, "mse", 2)
+        finally:
+            gp.set_launch_config(None)
+        ref, spread, cond = oracle_reference(op, X, y, None, "mse")
+        _, escaped = check_grads(host, g, ref, spread, cond, f"densest R={R}")
+        assert escaped == 0
