@@ -4886,7 +4886,7 @@ gp_status gp_generation_run(gp_generation* g, const uint32_t* nodes, const int64
         rc = chunking(&cap_view, &g->data, g->cfg, &chunk, &n_chunks);
         if (rc != GP_OK) return rc;
         const ExpandPlan xp = expand_plan(1, p.metric);
-        rc = reserve(&g->sc, P, p.node_capacity, n_chunks, 1, p.metric, true, xp.mul, xp.add);
+        rc = reserve(&g->sc, P, p.node_capacity, n_chunks, 1, p.metric, 0, xp.mul, xp.add);
         if (rc != GP_OK) return rc;
         if (spear) {
             // grow the Spearman buffers outside the capture (on this population)
@@ -5085,7 +5085,7 @@ gp_status evo_prepare(gp_evolution_s* e) {
     gp_status rc = chunking(&v, &e->data, e->cfg, &chunk, &n_chunks);
     if (rc != GP_OK) return rc;
     const ExpandPlan xp = expand_plan(1, p.metric);
-    rc = reserve(&e->sc, P, e->node_cap, n_chunks, 1, p.metric, true, xp.mul, xp.add);
+    rc = reserve(&e->sc, P, e->node_cap, n_chunks, 1, p.metric, 0, xp.mul, xp.add);
     if (rc != GP_OK) return rc;
     if (spear) {
         // grow the Spearman buffers outside the capture (on the current population)

@@ -69,3 +69,23 @@ def test_longer_chunks_beside_many_nodes(gp):
     # that the float32 results are at most neighbours
     got, want = (x.cpu().numpy().view(np.int32).astype(np.int64) for x in (got, want))
     assert np.abs(got - want).max() <= 1
+
+
+def test_a_device_resident_run_holds_no_adjoint_stream(gp):
+    """Its memory: two populations (8 bytes a node of capacity each) and the
+    evaluation's stream (16), the rest within 128 MiB."""
+    import torch
+    P, max_len = 8192, 2048
+    cap = P * max_len
+    init = dict(n_features=2, method="rhh", min_depth=2, max_depth=4)
+    host = gp.build_population(P, 2, "rhh", min_depth=2, max_depth=4, seed=1)
+    data = gp.DeviceDataset(np.zeros((2, 64), np.float32), np.ones(64, np.float32))
+    gp.tournament(gp.fitness(gp.DevicePopulation(host, n_features=2), data), torch.ones(P, dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    evo = gp.Evolution(data, host, init, dict(max_len=max_len), max_generations=2)
+    evo.run(1)
+    held = before - torch.cuda.mem_get_info()[0]
+    evo.close()
+    print(f"held {held / cap:.2f} bytes a node of capacity", flush=True)
+    assert held <= 32 * cap + (128 << 20)
