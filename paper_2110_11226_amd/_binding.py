@@ -310,7 +310,10 @@ def _stream(stream=None):
         return stream.cuda_stream
     torch = _torch()
     if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:      # torch's own names, which another version need not have
+            pass
     return torch.cuda.current_stream().cuda_stream
 
 
