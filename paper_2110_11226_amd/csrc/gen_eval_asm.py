@@ -614,6 +614,7 @@ TAPE_LDS = 16
 ACC = 8             # constants whose adjoints are summed in registers
 ADJ_TAPE = ["PUTT", "PUTM", "PUTU", "GMUL", "MMUL"]
 ADJ_ONE = ["SETMC", "SETMF", "MOVMT", "NEGMT", "MOVUT", "DINVM", "DINVT", "DNEGT", "DNEGM", "DSQRT", "SIND", "COSD", "CADDX"]
+ADJ_UN = UNARY[UNARY.index("TAN"):]     # what the caller differentiates (the ones before have instructions of their own)
 ADJ_BIN = ["MAXT", "MAXM", "MINT", "MINM", "ATTM", "ATMT"]
 EXIT_ADJ_UN, EXIT_ADJ_BIN, EXIT_CADD = 64, 96, 112
 
@@ -624,7 +625,7 @@ def adj_sections():
     at = base
     for name, n in ([(t, TAPE) for t in ADJ_TAPE] + [(t + "L", 1) for t in ADJ_TAPE] + [(t + "G", 1) for t in ADJ_TAPE] +
                     [("LOADM", SLOTS), ("SAVEM", SLOTS)] + [(t, 1) for t in ADJ_ONE] + [("CADD", ACC)] +
-                    [("UNX", len(UNARY)), ("BINX", len(ADJ_BIN))]):
+                    [("UNX", len(ADJ_UN)), ("BINX", len(ADJ_BIN))]):
         sec[name] = at
         at += n
     sec["count"] = at
@@ -710,9 +711,9 @@ class AdjGen(Gen):
         for k in range(ACC):
             begin(a["CADD"] + k)
             self.br(f"cadd{k}")
-        for u in range(len(UNARY)):
+        for u, name in enumerate(ADJ_UN):
             begin(a["UNX"] + u)
-            self.o(f"s_mov_b32 s{self.XC}, {EXIT_ADJ_UN + u}")
+            self.o(f"s_mov_b32 s{self.XC}, {EXIT_ADJ_UN + UNARY.index(name)}")
             self.br("leave")
         for q in range(len(ADJ_BIN)):
             begin(a["BINX"] + q)
@@ -951,10 +952,11 @@ def main():
              "// reciprocal of m / t; kADNegT/M: u = -t u u / -m u u; kADSqrt: u = d sqrt (u the input,",
              "// t the root); kASinD, kACosD: t = f(t), u = f'(t).  kACAdd + slot: the constant's adjoint",
              "// += m over the rows that count; kACAddX: the same by the caller (payload: slot).",
-             "// kAUnX + unary index: t = f(t), u = f'(t) by the caller; kABinX + kind: by the caller,",
+             "// kAUnX + unary index - that of tan: t = f(t), u = f'(t) by the caller; kABinX + kind: by the caller,",
              "// t = f of t and m, u = its derivative by t, m = by m (kinds: max and min with t, then",
              "// with m as the first operand, atan2(t, m), atan2(m, t)).",
-             f"constexpr int kTapeRegs = {TAPE}, kTapeLds = {TAPE_LDS}, kAccRegs = {ACC};", "enum : uint32_t {"]
+             f"constexpr int kTapeRegs = {TAPE}, kTapeLds = {TAPE_LDS}, kAccRegs = {ACC};",
+             f"constexpr uint32_t kAUnFirst = {UNARY.index('TAN')};", "enum : uint32_t {"]
     sec = adj_sections()
     for k, v in sec.items():
         if k == "count":

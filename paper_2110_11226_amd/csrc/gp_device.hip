@@ -1114,7 +1114,7 @@ __device__ __forceinline__ void adjoint_ops(uint32_t op, bool act, uint32_t lev,
                 fw(id(kADSqrt), 0u, kPlain);
                 fw(id(kAPutU), 0u, kTape);
             } else {
-                fw(id(u == 3 ? kASinD : u == 4 ? kACosD : kAUnX + u), 0u, kPlain);
+                fw(id(u == 3 ? kASinD : u == 4 ? kACosD : kAUnX + u - kAUnFirst), 0u, kPlain);
                 fw(id(kAPutU), 0u, kTape);
             }
             rv(id(kAGMul), 0u, kTape);
@@ -1692,7 +1692,6 @@ __device__ __forceinline__ void leave_rows(uint32_t code, V& t, const V& m, cons
     case 1 + FN: rows([&](float (&x)[1], int) __attribute__((always_inline)) { apply_unary<1>(FN, x, mt); }); break
     switch (code) {
     GP_LEAVE_UNARY(1);
-    GP_LEAVE_UNARY(2);
     GP_LEAVE_UNARY(3);
     GP_LEAVE_UNARY(4);
     GP_LEAVE_UNARY(5);
@@ -2572,8 +2571,6 @@ __device__ __forceinline__ void leave_rows_adjoint(uint32_t code, V& t, V& m, V&
         }
     };
     switch (code) {
-    case kExitAdjUnary + 1: unary(1); break;
-    case kExitAdjUnary + 2: unary(2); break;
     case kExitAdjUnary + 3: unary(3); break;
     case kExitAdjUnary + 4: unary(4); break;
     case kExitAdjUnary + 5: unary(5); break;

@@ -67,10 +67,11 @@ enum : uint32_t {
 // reciprocal of m / t; kADNegT/M: u = -t u u / -m u u; kADSqrt: u = d sqrt (u the input,
 // t the root); kASinD, kACosD: t = f(t), u = f'(t).  kACAdd + slot: the constant's adjoint
 // += m over the rows that count; kACAddX: the same by the caller (payload: slot).
-// kAUnX + unary index: t = f(t), u = f'(t) by the caller; kABinX + kind: by the caller,
+// kAUnX + unary index - that of tan: t = f(t), u = f'(t) by the caller; kABinX + kind: by the caller,
 // t = f of t and m, u = its derivative by t, m = by m (kinds: max and min with t, then
 // with m as the first operand, atan2(t, m), atan2(m, t)).
 constexpr int kTapeRegs = 26, kTapeLds = 16, kAccRegs = 8;
+constexpr uint32_t kAUnFirst = 5;
 enum : uint32_t {
     kAPutT = 206,
     kAPutM = 232,
@@ -104,8 +105,8 @@ enum : uint32_t {
     kACAddX = 380,
     kACAdd = 381,
     kAUnX = 389,
-    kABinX = 403,
-    kAdjointOps = 409,
+    kABinX = 398,
+    kAdjointOps = 404,
     kExitAdjUnary = 64,
     kExitAdjBinary = 96,
     kExitCAdd = 112,
