@@ -459,9 +459,8 @@ gp_status gp_plan_generation_device(const gp_evolve_params* params, int32_t n_of
  * offspring go to `out`; info is DEVICE int64[4]: info[0], info[1] the total
  * nodes and constants; info[2] status bits -- 1: a capacity of `out` is
  * short, nothing was written; 2: an operation, tournament or winner index
- * was out of range, those offspring are the one-node program x0; 4: the
- * donors overflowed the library's bound (not reachable with settings that
- * pass the checks).  Subtree-mutation donors are bounded by 2^(max_depth+1)-1
+ * was out of range, those offspring are the one-node program x0.
+ * Subtree-mutation donors are bounded by 2^(max_depth+1)-1
  * nodes (tree methods) or max_len + 1 (exact length) each; settings whose
  * bound times n_offspring exceeds 2^25 nodes give GP_ERR_INVALID_ARG. */
 gp_status gp_mutate_device(const gp_evolve_params* params, const gp_init_params* init,

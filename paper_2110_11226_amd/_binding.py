@@ -596,8 +596,7 @@ def plan_generation_device(n_offspring, generation, stream=None, **evolve):
 
 
 MUTATE_STATUS = {1: "a capacity of the output is short; nothing was written",
-                 2: "an operation, tournament or winner index was out of range",
-                 4: "the subtree-mutation donors overflowed the library's bound"}
+                 2: "an operation, tournament or winner index was out of range"}
 
 
 class DeviceOffspring:

@@ -5132,7 +5132,7 @@ gp_status gp_evolution_run(gp_evolution* e, int32_t n) {
     if (n > 0 && e->events) GP_HIP(hipEventElapsedTime(&e->kernel_ms, e->ev_a, e->ev_b));
     if (sticky)
         return fail(GP_ERR_DEVICE, "gp_evolution_run: mutation status bits " + std::to_string(sticky) +
-                                       " (1 capacity, 2 index out of range, 4 donor bound)");
+                                       " (1 capacity, 2 index out of range)");
     return GP_OK;
 }
 
