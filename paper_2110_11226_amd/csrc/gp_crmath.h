@@ -28,7 +28,8 @@
 //   log: a = 2^e m, m in [1, 2); c = 1/(bucket centre of m) from a 256-entry
 //     table (c has 24 bits, so m c - 1 is exact); log a = E ln 2 - log c' +
 //     log1p(m c - 1) with log1p by a minimax polynomial through r^5
-//     (|m c - 1| <= 2^-8), the table's -log c' and ln 2 each rounded to double.
+//     (|m c - 1| <= 2^-8), the table's -log c' and ln 2 each rounded to double
+//     (four entries then moved, see below).
 // Table sizes: 256 entries of 16 bytes each (8 KB of LDS for the two) let the
 // polynomials stop two or three operations short of what 128 entries need; a
 // table index of eight bits is also a byte of the rounded quotient.  Where a
@@ -319,7 +320,10 @@ constexpr uint32_t kLogCarry = 150u << 15;
 // 2^-53 |L|.  Where E = 0 and L != 0, |r| <= 0.34 |L|, so the result is at
 // least 0.66 |L| and that rounding is below 2^-52.4 of it; with the rounding
 // of log1p and of the final addition the relative error stays below 2^-50
-// (E ln 2 + L is exact when E = 0).
+// (E ln 2 + L is exact when E = 0).  That bound does not hold in the four
+// buckets whose L is not -log(c) rounded but moved by 8 to 192 units
+// (gen_crmath_tables.py, NUDGE): with E near 0 they are within 2^-45 only, and
+// what carries the claim there, as for every float, is the exhaustive check.
 GP_CRF double log_double(uint32_t u, const LogEntry* tab, const LogK& K) {
 #if defined(__HIP_DEVICE_COMPILE__)
     const int E = __builtin_amdgcn_frexp_expf(bitsf(u + kLogCarry - 0x800000u));
@@ -346,7 +350,7 @@ GP_CRF float log_cr(float a, const LogEntry* tab, const LogK& K) {
 
 // ---- log(1 + e^-a), the log-loss's ----
 // In double, rounded once: e = e^-a as 2^k p(s) with s = -a - k ln 2, |s| <=
-// ln 2 / 2 and p its series through s^8 (relative error below 2^-32), then the
+// ln 2 / 2 and p its series through s^8 (relative error below 2^-31.7), then the
 // log of x = 1 + e in [1, 2) from log's table.  d is what 1 + e rounds off, so
 // that the result keeps its relative precision down to the smallest e (the
 // table's first entry has c = 1 and L = 0).  From a = 200 on the result is 0 in
