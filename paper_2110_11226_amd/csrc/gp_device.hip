@@ -188,27 +188,29 @@ __device__ __forceinline__ T ldu(const T* p) {
 struct Claims {
     uint32_t* counter;
     uint32_t P, n_chunks, batch, blocks, wpb;
+    uint32_t per;                      // places of one chunk in a queue (the last may be none, see program)
     uint32_t index;                    // this wavefront among its queue's
     int q0, q;
     bool first;
     __device__ Claims(const Sched& s, uint32_t programs, uint32_t wid)
         : counter(s.counter), P(programs), n_chunks(static_cast<uint32_t>(s.n_chunks)),
           batch(static_cast<uint32_t>(s.batch)), blocks(static_cast<uint32_t>(s.blocks)),
-          wpb(static_cast<uint32_t>(s.wpb)), index(blockIdx.x / kQueues * static_cast<uint32_t>(s.wpb) + wid), q0(static_cast<int>(blockIdx.x % kQueues)), q(q0),
+          wpb(static_cast<uint32_t>(s.wpb)), per(striped() ? (P + kQueues - 1) / kQueues : P), index(blockIdx.x / kQueues * static_cast<uint32_t>(s.wpb) + wid), q0(static_cast<int>(blockIdx.x % kQueues)), q(q0),
           first(true) {}
     __device__ bool striped() const { return n_chunks < static_cast<uint32_t>(kQueues); }
-    // programs of one chunk in queue x, and where place k among them of the
-    // queue's chunk cq lies
-    __device__ uint32_t per(uint32_t x) const { return striped() ? (P + kQueues - 1 - x) / kQueues : P; }
+    // where place k of chunk cq of queue x lies: its chunk, and its program, which
+    // may be P, none, or above.  (As many places in every queue, so that the
+    // division by their number has its reciprocal once: one for each queue cost
+    // 300 programs on 50,021 rows 1.3 us of 276.)
     __device__ int32_t chunk(uint32_t cq, int x) const {
         return static_cast<int32_t>(striped() ? cq : cq * kQueues + static_cast<uint32_t>(x));
     }
-    __device__ int32_t program(uint32_t k, int x) const {
-        return static_cast<int32_t>(striped() ? k * kQueues + static_cast<uint32_t>(x) : k);
+    __device__ uint32_t program(uint32_t k, int x) const {
+        return striped() ? k * kQueues + static_cast<uint32_t>(x) : k;
     }
     // (items stay below 2^31: n_items is at most 2^30)
     __device__ uint32_t items(uint32_t x) const {
-        return striped() ? n_chunks * per(x) : (n_chunks - x + kQueues - 1) / kQueues * P;
+        return striped() ? n_chunks * per : (n_chunks - x + kQueues - 1) / kQueues * P;
     }
     // items covered by the first claims of queue x's wavefronts
     __device__ uint32_t given(uint32_t x) const {
@@ -1754,15 +1756,16 @@ __global__ __launch_bounds__(kBlock, eval_waves(R, FREG)) void k_eval(PopView po
         it0 = uniform(it0);
         it1 = uniform(it1);
         qx = static_cast<int>(uniform(static_cast<uint32_t>(qx)));
-        const uint32_t per = claims.per(static_cast<uint32_t>(qx));
-        uint32_t cq = it0 / per, k = it0 - cq * per;
+        uint32_t cq = it0 / claims.per, k = it0 - cq * claims.per;
         for (uint32_t it = it0; it < it1; ++it) {
             const int32_t c = claims.chunk(cq, qx);
-            const int32_t p = ldu(s.order + claims.program(k, qx));
-            if (++k == per) {
+            const uint32_t place = claims.program(k, qx);
+            if (++k == claims.per) {
                 k = 0;
                 ++cq;
             }
+            if (place >= P) continue;
+            const int32_t p = ldu(s.order + place);
             const int64_t off = ldu(pop.prog_off + p);
             const uint32_t head = ldu(cv.ehdr + p);
             const uint4* __restrict__ pcode = cv.ecode + off * cv.ex_mul + static_cast<int64_t>(p) * cv.ex_add;
@@ -2158,9 +2161,10 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint_long(PopView pop,
     while (claims.next(lane, &qx, &it, &it_end)) {
         it = uniform(it);
         qx = static_cast<int>(uniform(static_cast<uint32_t>(qx)));
-        const uint32_t per = claims.per(static_cast<uint32_t>(qx)), cq = it / per;
+        const uint32_t cq = it / claims.per, place = claims.program(it - cq * claims.per, qx);
+        if (place >= claims.P) continue;
         const int32_t c = claims.chunk(cq, qx);
-        const int32_t p = ldu(s.order + claims.program(it - cq * per, qx));
+        const int32_t p = ldu(s.order + place);
         const int64_t off = ldu(pop.prog_off + p);
         const int32_t CL = ldu(cv.clen + p);
         const int64_t cbase = ldu(pop.const_off + p);
@@ -2604,6 +2608,8 @@ __global__ __launch_bounds__(kAdjWaves * kWave, adjoint_waves(R)) void k_adjoint
     const int64_t ld = d.ld;
     const float* __restrict__ X = d.X;
     extern __shared__ __align__(16) unsigned char lds_all[];
+    // k_adjoint_long's programs, first in the order (read while the tables are)
+    const uint32_t n_long = ldu(s.counter + kLongWord);
     stage_tabs(*reinterpret_cast<MathTabsLds*>(lds_all));
     // per wavefront: the sums of constants from kAccRegs on, then the LDS tape
     unsigned char* lds_wave = lds_all + sizeof(MathTabsLds) + wid * adjoint_lds_wave<R>();
@@ -2616,7 +2622,6 @@ __global__ __launch_bounds__(kAdjWaves * kWave, adjoint_waves(R)) void k_adjoint
     in.ld4 = static_cast<uint64_t>(ld) * 4u;
     in.area = reinterpret_cast<uint64_t>(area + (static_cast<int64_t>(blockIdx.x) * kAdjWaves + wid) * area_bytes);
     const double W = *wsum;
-    const uint32_t n_long = ldu(s.counter + kLongWord);      // (k_adjoint_long's, first in the order)
     const int32_t* __restrict__ order = s.order + n_long;
     Claims claims(s, static_cast<uint32_t>(pop.P) - n_long, wid);
     int qx;
@@ -2624,9 +2629,10 @@ __global__ __launch_bounds__(kAdjWaves * kWave, adjoint_waves(R)) void k_adjoint
     while (claims.next(lane, &qx, &it, &it_end)) {
         it = uniform(it);
         qx = static_cast<int>(uniform(static_cast<uint32_t>(qx)));
-        const uint32_t per = claims.per(static_cast<uint32_t>(qx)), cq = it / per;
+        const uint32_t cq = it / claims.per, place = claims.program(it - cq * claims.per, qx);
+        if (place >= claims.P) continue;
         const int32_t c = claims.chunk(cq, qx);
-        const int32_t p = ldu(order + claims.program(it - cq * per, qx));
+        const int32_t p = ldu(order + place);
         const int64_t off = ldu(pop.prog_off + p);
         const uint32_t head = static_cast<uint32_t>(ldu(cv.clen + p));
         const int64_t cbase = ldu(pop.const_off + p);
