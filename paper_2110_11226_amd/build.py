@@ -26,7 +26,9 @@ HIPCC_FLAGS = [
     # leave regions whose branches are all wave-uniform unstructured: the
     # evaluation kernel's dispatch on a scalar opcode then compiles to plain
     # compare-and-branch trees, without the exec-mask flag bookkeeping the
-    # structurizer adds (about 30% fewer scalar instructions per dispatch)
+    # structurizer adds (about 30% fewer scalar instructions per dispatch).
+    # With it the compiler once took a flag set by a divergent region's lanes
+    # as set in all of them: tests/test_lane_masks.py looks for that.
     "-mllvm", "-structurizecfg-skip-uniform-regions=true",
     # constants stay where they are used: hoisted out of the evaluation
     # kernel's loops, those of the rarely used library functions held 20

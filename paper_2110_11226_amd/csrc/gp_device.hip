@@ -6,17 +6,18 @@
 // against the target is formed in registers, and the losses are summed per
 // program.  The paper launches one thread per (program, row) and materialises
 // the (rows x programs) prediction matrix before two library reductions; here
-//   1. k_compile rewrites each prefix list once per call into its execution
-//      order as two-word instructions (the stack-schedule pre-pass): a
-//      terminal whose parent is a binary function and which is that
-//      function's first operand is fused with it, and a constant's value
-//      travels inside its instruction;
-//   2. one persistent launch of k_eval walks (row chunk, program) work items
-//      taken from an atomic counter; the 64 lanes of a wavefront run the same
-//      program on 64 different rows, so every instruction is a wave-uniform
-//      (scalar) branch, and each lane carries R rows to spread the scalar
-//      dispatch over more vector work; the row loss is formed in registers
-//      and only one float64 partial per (program, chunk) leaves the kernel;
+//   1. k_compile_streams rewrites each prefix list once per call into the
+//      instructions of an assembly interpreter (the stack-schedule pre-pass):
+//      of a binary function's operands the one that needs more stack entries
+//      comes first, a terminal is fused with the function it is an operand of,
+//      and a constant's value travels inside its instruction;
+//   2. one persistent launch of k_eval walks (row chunk, program) work items,
+//      a wavefront's first by its position and the others from a counter per
+//      XCD; the 64 lanes of a wavefront run the same program on 64 different
+//      rows, and each lane carries R rows, so that an instruction's fetch and
+//      jump are scalar work shared by 64 R rows; the row loss is formed in
+//      registers and only one float64 partial per (program, chunk) leaves the
+//      kernel;
 //   3. k_finalize merges the partials in a fixed order.
 #include <hip/hip_runtime.h>
 
@@ -176,7 +177,7 @@ __device__ __forceinline__ T ldu(const T* p) {
 // queues, queue x holds every eighth program instead, of every chunk: the rows
 // are few then, and all claims on one counter, at some 15 ns each, bound the
 // launch (20,000 programs of up to 40 nodes on 200 rows: the call 491 us with
-// one counter, 247 with eight; 1,000 programs on 1,000 rows: 128 and 62).
+// one counter, 209 with eight; 1,000 programs on 1,000 rows: 128 and 63).
 // Blocks are dealt to the XCDs in turn, so a block starts on queue blockIdx.x %
 // kQueues.
 // Every wavefront's first claim is its own by position, and the counters
@@ -210,7 +211,7 @@ struct Claims {
     }
     // (items stay below 2^31: n_items is at most 2^30)
     __device__ uint32_t items(uint32_t x) const {
-        return striped() ? n_chunks * per : (n_chunks - x + kQueues - 1) / kQueues * P;
+        return striped() ? (x < P ? n_chunks * per : 0u) : (n_chunks - x + kQueues - 1) / kQueues * P;
     }
     // items covered by the first claims of queue x's wavefronts
     __device__ uint32_t given(uint32_t x) const {
@@ -732,8 +733,8 @@ constexpr uint8_t kEntMask = 31, kLeaf = 64, kConst = 128;
 // defined, a wavefront takes a group of programs, compiles those it can one
 // after the other and then the rest side by side (20,000 programs of up to 40
 // nodes with user functions on 1,000 rows: 733 us with one of 64 lanes at work
-// for each, 403 in groups of seven; 100,000 of up to 30 on 256 rows 3,151 and
-// 596, the claims' share of that included).
+// for each, 413 in groups of seven; 4,096 of up to 120 on 4,096 rows 754 and
+// 570).
 struct SeqShadow {              // one lane's column
     uint32_t* e;
     float* v;
@@ -3637,10 +3638,15 @@ gp_status launch_eval_m(const LaunchCfg& cfg, int n_cu, const PopView& pv, const
         int per_cu = 0;
         GP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, lds));
         per_cu = std::max(per_cu, 1);
-        const int64_t waves_needed = (s.n_items + s.batch - 1) / s.batch;
-        int64_t blocks = static_cast<int64_t>(per_cu) * n_cu;
-        blocks = std::min<int64_t>(blocks, (waves_needed + cfg.wpb - 1) / cfg.wpb);
-        blocks = std::max<int64_t>(blocks, 1);
+        // as many as are resident, at most those whose first claims cover the
+        // longest queue (by the items alone, a queue with one more than its
+        // wavefronts left that one to all of them: one program on 1M rows, a
+        // kernel of 34 to 42 us, 9.6 so)
+        const int64_t longest = s.n_chunks < kQueues ? s.n_chunks * ((static_cast<int64_t>(pv.P) + kQueues - 1) / kQueues)
+                                                     : (static_cast<int64_t>(s.n_chunks) + kQueues - 1) / kQueues * pv.P;
+        const int64_t claim = static_cast<int64_t>(cfg.wpb) * s.batch;
+        const int64_t blocks = std::max<int64_t>(
+            1, std::min<int64_t>(static_cast<int64_t>(per_cu) * n_cu, kQueues * ((longest + claim - 1) / claim)));
         const bool prof = tm.profile && g_prof_on;
         ProfRec rec{nullptr, nullptr, node_rows};
         if (prof) {
