@@ -89,3 +89,18 @@ def test_a_device_resident_run_holds_no_adjoint_stream(gp):
     evo.close()
     print(f"held {held / cap:.2f} bytes a node of capacity", flush=True)
     assert held <= 32 * cap + (128 << 20)
+
+
+def test_the_autotuner_stays_within_the_longest_chunks(gp):
+    """It times a prefix of 1,048,576 rows, on which longer chunks than any the
+    heuristic takes look better than they are for the whole."""
+    import torch
+    N, P = 16_777_216, 4096
+    pop = gp.DevicePopulation(gp.build_population(P, 2, method="exact_len", min_len=1, max_len=20, seed=3), n_features=2)
+    X = torch.zeros(2, N, device="cuda")
+    data = gp.DeviceDataset(X, torch.zeros(N, device="cuda"))
+    try:
+        (R, _, tiles, _), ms = gp.autotune(pop, data, "mse", repeats=1)
+    finally:
+        gp.autotune_clear()
+    assert ms > 0.0 and R * tiles <= 4 * 64, (R, tiles)
