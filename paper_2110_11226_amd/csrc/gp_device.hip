@@ -3563,7 +3563,7 @@ std::map<TuneKey, TuneVal> g_tuned;
 // doubles per partial sum of a kernel class
 int64_t class_doubles(int kclass) { return kclass == 4 ? 4 : 1; }
 constexpr int64_t kMostTiles = 64;              // tiles of the heuristic's longest chunk
-constexpr int64_t kMostPartials = int64_t{1} << 22;
+constexpr int64_t kMostPartials = int64_t{6} << 20;
 
 LaunchCfg heuristic_cfg(int F, int64_t N, int32_t P, int n_cu, int kclass) {
     LaunchCfg c;
@@ -3600,12 +3600,16 @@ LaunchCfg heuristic_cfg(int F, int64_t N, int32_t P, int n_cu, int kclass) {
         if (waste(t) < waste(best) - 0.005 ||
             (waste(t) < waste(best) + 0.005 && std::abs(t - tiles) < std::abs(best - tiles)))
             best = t;
-    // beyond 32 MiB of partial sums longer chunks: a wavefront then has a
-    // thousand items and more, so that longer ones cost next to nothing (16.8M
-    // rows x 4,096 programs of up to 60 nodes: 383.9 ms at 16 tiles, 385.1 at
-    // 64; x 2,048 of up to 200: 612, 615 at 32, 620 at 64), while scratch and
-    // the 2^30 bound on the items go by the chunks
-    const int64_t most = std::max<int64_t>(1, kMostPartials / (class_doubles(kclass) * std::max<int32_t>(P, 1)));
+    // beyond 48 MiB of partial sums longer chunks, since scratch and the 2^30
+    // bound on the items go by the chunks: a wavefront then has hundreds of items,
+    // and longer ones cost next to nothing (16.8M rows x 4,096 programs of up to
+    // 60 nodes: 342 ms at 16 tiles, 341 at 43; of up to 200: 1,187 and 1,191; x
+    // 1,000, Pearson: 89.0, 89.6, and 91.3 at 64).  With more than eight features
+    // only beyond 192 MiB: the chunks that about a thousand programs have in
+    // flight together then exceed an L2 (20 features x 1,024 programs: 70.9 ms at
+    // 16 tiles, 81.0 at 43; eight features 80.7 and 82.0; 28 x 4,096 265 at both)
+    const int64_t doubles = F > 8 ? 4 * kMostPartials : kMostPartials;
+    const int64_t most = std::max<int64_t>(1, doubles / (class_doubles(kclass) * std::max<int32_t>(P, 1)));
     best = std::max(best, std::min(kMostTiles, (n_tiles + most - 1) / most));
     c.tiles = static_cast<int>(best);
     return c;

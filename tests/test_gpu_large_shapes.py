@@ -71,6 +71,32 @@ def test_longer_chunks_beside_many_nodes(gp):
     assert np.abs(got - want).max() <= 1
 
 
+@pytest.mark.parametrize("F,N,P,metric,tiles", [(28, 11_000_000, 2000, "logloss", 16), (28, 16_777_216, 1024, "pearson", 16),
+                                                (5, 16_777_216, 1000, "pearson", 48), (2, 16_777_216, 4096, "mse", 48)])
+def test_chunks_no_longer_than_the_partial_sums_ask_for(gp, F, N, P, metric, tiles):
+    """A chunk of many features that is longer than the programs share in an L2
+    takes up to a third more time."""
+    R, _, t, _ = gp.get_launch_config(F, N, P, metric)
+    assert R == 4 and t <= tiles
+
+
+def test_many_features_without_allocation(gp):
+    """Partial sums of 128 MiB at the launch's own chunks."""
+    import torch
+    F, N, P = 28, 4_194_304, 4096
+    assert noalloc_bytes(P, 3 * P, chunks(gp, F, N, P, "pearson"), "pearson") > 64 << 20
+    g = torch.Generator(device="cuda").manual_seed(7)
+    data = gp.DeviceDataset(torch.rand((F, N), generator=g, device="cuda"), torch.rand(N, generator=g, device="cuda"))
+    pop = gp.DevicePopulation(gp.build_population(P, F, "exact_len", min_len=1, max_len=3, seed=8), n_features=F)
+    got, want = gp.fitness_noalloc(pop, data, "pearson"), gp.fitness(pop, data, "pearson")
+    torch.cuda.synchronize()
+    got, want = got.cpu().numpy().astype(np.float64), want.cpu().numpy().astype(np.float64)
+    # moments in another order: their float64 sums within N 2^-53 of each other
+    # relative to sums of absolute terms, the correlation within 1e-9 and a rounding
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.nanmax(np.abs(got - want)) <= 1e-9 + 2.0 ** -23
+
+
 def test_a_device_resident_run_holds_no_adjoint_stream(gp):
     """Its memory: two populations (8 bytes a node of capacity each) and the
     evaluation's stream (16), the rest within 128 MiB."""
