@@ -2515,9 +2515,10 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void k_adjoint_long(PopView pop,
 // vector registers, kTapeLds in LDS, the rest in memory (a program of 200
 // nodes over 8 features records 22 on average, 54 at most); its reverse part
 // is straight-line instructions over the active operations alone.  Two
-// wavefronts per SIMD at four rows per lane, the registers' worth; but neither
-// the tape nor the reverse walk waits for memory.  Its bound is vector issue,
-// as the evaluation kernel's.  1,024 programs of 1 to 200 nodes on 262,144 rows
+// wavefronts per SIMD at four rows per lane, the registers' worth, which is too
+// few to hide every wait: the vector pipes are busy 73% of the time and a
+// wavefront waits a third of its cycles (the evaluation kernel, with four, 97%
+// busy).  1,024 programs of 1 to 200 nodes on 262,144 rows
 // of 8 features: 23.9 ms by k_adjoint_long, 8.3 ms here (two rows per lane and
 // three wavefronts 9.3 ms, one row and four 12.3 ms; one tile per item to 64
 // within 7%); 100 programs of up to 120 nodes on 10,007 weighted rows,
